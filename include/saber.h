@@ -55,9 +55,10 @@ typedef struct saber_options {
                                a chunk's sampling pass re-reads stay in the 256 MB Infinity Cache; always at least one
                                chunk per 2^30 tokens */
     int32_t block_threads;  /* threads per workgroup of the sampling kernel (multiple of 64 up to 1024);
-                               default: the size that lets a CU hold the most wavefronts given the LDS the Bhat row takes */
-    int32_t tile_tokens;    /* most tokens of one word handled by one workgroup; default 0: a 2560th of a chunk's tokens,
-                               not below 8,192 and not above 32,768 */
+                               default: the size that lets a CU hold the most wavefronts given the LDS the Bhat row takes,
+                               1,024 when the row is not kept in LDS */
+    int32_t tile_tokens;    /* most tokens of one word handled by one workgroup; default 0: a 8192th of a chunk's tokens,
+                               not below K / 16 (64 to 256) and not above 32,768 */
     int32_t stage_phi;      /* 1: keep the word's Bhat row in LDS when it fits (up to 150 KB: K <= 37,800), 0: always
                                gather from global; default 1 */
     int32_t profile;        /* 1: time every kernel group with HIP events (see saber_get_stats); default 0 */
@@ -67,7 +68,8 @@ typedef struct saber_options {
                                workgroups a CU can hold) */
     int32_t stage_min_tokens;   /* tiles with at least this many tokens are launched with block_threads threads, smaller
                                    ones with light_block_threads; default 1 (one class) */
-    int32_t light_block_threads;/* workgroup size for the smaller tiles; default: as block_threads */
+    int32_t light_block_threads;/* workgroup size for the smaller tiles and for light words' tiles; default: as block_threads,
+                               and when that is not given either, sized by the tile for light words */
     int32_t light_word_tokens;  /* words with fewer tokens than this keep their row of B sparse (rebuilt by a segmented
                                    count, like a row of A) and their Bhat row is formed in LDS from a base vector and
                                    the non-zeros; default K/2; negative: every word keeps a dense row */

@@ -89,13 +89,16 @@ static void dev_free(const Hooks &h, void *p) { hook_free(h, p); }
 // ------------------------------------------------------------------------------------------------
 // context
 // ------------------------------------------------------------------------------------------------
+// Tiles of a chunk that are launched together: `count` tiles from the chunk's tile `first` on, workgroups of `block` threads
+struct TileClass { int64_t first, count; int block; bool light; };
+
 struct Chunk {
     int64_t d0 = 0, d1 = 0;   // document range
     int64_t t0 = 0, ntok = 0; // canonical token range [t0, t0+ntok)
     int64_t tile0 = 0, ntiles = 0, words_present = 0;
-    // tiles of the chunk: [0, n_dense) belong to words with dense B rows, sorted by size, the first n_heavy of
-    // them forming the class of large tiles; [n_dense, ntiles) belong to light words (sparse B rows)
-    int64_t n_heavy = 0, n_dense = 0;
+    // tiles of the chunk: first those of words with dense B rows, then those of light words (sparse B rows), each
+    // group sorted by decreasing size and cut into classes by size
+    std::vector<TileClass> classes;
     // the chunk's documents inside the (ascending) lists of short and of long documents
     int64_t short0 = 0, nshort = 0, long0 = 0, nlong = 0;
     // the rows of A of the chunk's documents: first row and extent, in units of 32 entries (128 bytes)
@@ -118,6 +121,8 @@ struct saber_ctx {
     uint64_t seed = 0;
     uint32_t iter = 0, topic_bits = 0, topic_mask = 0;
     bool z16 = false, staged = false, b16 = false;
+    bool auto_light_block = false;    // neither workgroup size was given: those of light words' tiles follow the tile
+    int lds_per_cu = 64 * 1024;
     saber_options opt{};
     int32_t tile_tokens_asked = 0;    // the caller's tile_tokens (0: automatic), before the default was filled in
     int64_t max_doc_len = 0;
@@ -337,20 +342,11 @@ static int check_estep_lds_layout() {
     return SABER_OK;
 }
 
-// One E-step launch per tile class.  Dense-row tiles with at least stage_min_tokens tokens run with block_threads
-// threads, smaller ones with light_block_threads (so that a word with few tokens does not hold a large workgroup
-// whose wavefronts have nothing to do); tiles of light words run the variant that builds the Bhat row from the
-// base vector and the word's non-zeros.  All stage the row in LDS when it fits.
+// One E-step launch per tile class (tile_classes() below).  Tiles of light words run the variant that builds the Bhat
+// row from the base vector and the word's non-zeros.  All stage the row in LDS when it fits.
 template <int MODE>
 static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
-    struct Class { int64_t first, count; int block; bool light; };
-    const Class classes[3] = {
-        {0, ch.n_heavy, c->opt.block_threads, false},
-        {ch.n_heavy, ch.n_dense - ch.n_heavy, c->opt.light_block_threads, false},
-        {ch.n_dense, ch.ntiles - ch.n_dense, c->opt.light_block_threads, true},
-    };
-    for (const Class &cl : classes) {
-        if (cl.count == 0) continue;
+    for (const TileClass &cl : ch.classes) {
         EStepParams p = p0;
         p.tiles = p0.tiles + cl.first;
         if (p0.out_ll) p.out_ll = p0.out_ll + cl.first;
@@ -366,6 +362,44 @@ static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
         HIP_TRY(hipGetLastError());
     }
     return SABER_OK;
+}
+
+// Wavefronts a CU holds of a sampling kernel with `block` threads per workgroup, given its LDS (handed out in 512-byte
+// pieces) and the 32 wavefronts a CU can hold.
+static int estep_waves_per_cu(const saber_ctx *c, int block) {
+    const size_t need = c->staged ? ((estep_lds_bytes(c, MODE_SAMPLE) + 144 + 511) / 512) * 512 : 512;
+    const int by_lds = (int)std::min<size_t>(64, (size_t)c->lds_per_cu / need), by_waves = 32 / (block / 64);
+    return std::min(by_lds, by_waves) * (block / 64);
+}
+
+// Cuts one group of a chunk's tiles ([begin, end) of the chunk's tiles, sorted by decreasing size) into classes.  Dense
+// rows: tiles with at least stage_min_tokens tokens get block_threads threads, smaller ones light_block_threads.
+// Light words, unless the caller fixed a workgroup size: one wavefront per 64 tokens (a full batch), between the
+// smallest workgroup with which LDS still lets a CU hold 24 of its 32 wavefronts and block_threads.  A small tile dealt
+// to many wavefronts pays each one's set-up and chain of dependent loads for a few tokens: K = 1,000, T = 10 M (90,000
+// light words of 29 tokens on average), sampling pass 0.89 ms with 256 threads for all of them, 0.77 ms so; K = 2,000,
+// 5 M tokens per chunk: 2.09 and 1.89 ms per four chunks.  No difference at T = 2 M, K = 777 (0.17 ms both).
+static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64_t begin, int64_t end, bool light) {
+    int64_t at = begin;
+    auto add = [&](int64_t to, int block) {
+        if (to > at) ch.classes.push_back(TileClass{at, to - at, block, light});
+        at = std::max(at, to);
+    };
+    auto until = [&](int64_t least) {   // first tile with fewer than `least` tokens
+        return (int64_t)(std::lower_bound(tiles + at, tiles + end, least, [](const Tile &t, int64_t n) { return t.count >= n; }) - tiles);
+    };
+    if (!light) {
+        add(until(c->opt.stage_min_tokens), c->opt.block_threads);
+        add(end, c->opt.light_block_threads);
+        return;
+    }
+    int lo = c->opt.light_block_threads, hi = c->opt.light_block_threads;
+    if (c->auto_light_block) { lo = 64; while (lo < hi && estep_waves_per_cu(c, lo) < 24) lo *= 2; }
+    for (int block = hi; block > lo; block /= 2) {
+        const int64_t to = until(64 * (block / 128) + 1);   // tiles that half the workgroup would not serve in one batch each
+        if (to - at >= 128) add(to, block);                 // (a launch of its own pays from half a workgroup per CU on)
+    }
+    add(end, lo);
 }
 
 // Segmented count of one grouping of the assignments: documents over z (CountByDZ -> rows of A) or light words
@@ -826,11 +860,10 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
             return la != lb ? lb : a.count > b.count;
         });
         ch.tile0 = (int64_t)first_tile; ch.ntiles = (int64_t)(h_tiles.size() - first_tile);
-        for (size_t i = first_tile; i < h_tiles.size(); i++) {
-            if (wr[(size_t)h_tiles[i].word] < 0) continue;
-            ch.n_dense++;
-            if (h_tiles[i].count >= c->opt.stage_min_tokens) ch.n_heavy++;
-        }
+        int64_t n_dense = 0;
+        while (n_dense < ch.ntiles && wr[(size_t)h_tiles[first_tile + (size_t)n_dense].word] >= 0) n_dense++;
+        tile_classes(c, ch, h_tiles.data() + first_tile, 0, n_dense, false);
+        tile_classes(c, ch, h_tiles.data() + first_tile, n_dense, ch.ntiles, true);
         c->max_chunk_tiles = std::max(c->max_chunk_tiles, ch.ntiles);
     }
     c->total_tiles = (int64_t)h_tiles.size();
@@ -1062,13 +1095,20 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
     opt.n_chunks = (int32_t)std::max<int64_t>(opt.n_chunks, (T >> 30) + 1);
     if ((int64_t)opt.n_chunks > std::max<int64_t>(D, 1)) opt.n_chunks = (int32_t)std::max<int64_t>(D, 1);
     // automatic tile size: a heavy word's Bhat row is staged once per tile, so larger tiles stage less; but a tile is
-    // the work of one workgroup, and with about a thousand workgroups in flight a tile of chunk / 2560 tokens takes 40 %
-    // of the chunk's pass (heavy tiles are launched first; at chunk / 1500 the pass waits for them: + 5 to 20 %).
-    // Between 8,192 and 32,768 tokens.
+    // the work of one workgroup (its wavefronts take it 64 tokens at a time), and the pass waits for its largest ones.
+    // A 8192th of the chunk, at most 32,768 tokens: the sampling pass took 0.36 / 0.10 ms with tiles of 8,192 / 128
+    // tokens at T = 1 M, K = 300, 1.15 / 0.89 ms with 8,192 / 1,024 at 10 M, K = 1,000, 2.43 / 2.34 ms with 14,000 /
+    // 4,096 at 36 M, K = 5,000, and 9.14 / 9.06 ms with 32,768 / 8,192 at 100 M, K = 10,000.  A small tile has to be
+    // worth its row, though: not below K / 16 tokens, 64 to 256 (T = 300,000, K = 10,000: 0.072 ms with 64, 0.058 with 256).
     const int32_t tile_tokens_asked = opt.tile_tokens;
     if (opt.tile_tokens <= 0) {
         const int64_t per_chunk = T / std::max(1, opt.n_chunks);
-        opt.tile_tokens = (int32_t)std::min<int64_t>(32768, std::max<int64_t>(8192, (per_chunk / 2560) & ~255ll));
+        // (a vocabulary of more than 2^19 words makes a tile or more per word as it is: larger tiles keep a chunk's within
+        // the 2^20 of saber_loglik_static)
+        const bool many_words = V > (1 << 19);
+        const int64_t least = many_words ? 8192 : std::min<int64_t>(256, std::max<int64_t>(64, (K / 16) & ~63));
+        const int64_t share = many_words ? (per_chunk / 2560) & ~255ll : (per_chunk / 8192) & ~63ll;
+        opt.tile_tokens = (int32_t)std::min<int64_t>(32768, std::max<int64_t>(least, share));
     }
 
     int ndev = 0;
@@ -1090,25 +1130,21 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
     c->topic_bits = bits; c->topic_mask = (1u << bits) - 1u;
     c->z16 = K <= 65536;
     // the word's Bhat row is staged in LDS when it fits a workgroup's share: up to 150 KB of the CU's 160 KB
-    int lds_per_cu = 0;
-    if (hipDeviceGetAttribute(&lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, 0) != hipSuccess || lds_per_cu <= 0)
-        lds_per_cu = 64 * 1024;
-    const size_t stage_limit = std::min<size_t>(150 * 1024, (size_t)lds_per_cu > 10 * 1024 ? (size_t)lds_per_cu - 10 * 1024 : 0);
+    if (hipDeviceGetAttribute(&c->lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, 0) != hipSuccess || c->lds_per_cu <= 0)
+        c->lds_per_cu = 64 * 1024;
+    const size_t stage_limit = std::min<size_t>(150 * 1024, (size_t)c->lds_per_cu > 10 * 1024 ? (size_t)c->lds_per_cu - 10 * 1024 : 0);
     c->staged = opt.stage_phi && estep_row_bytes(c) <= std::max<size_t>(stage_limit, 54 * 1024);
     if (opt_in == nullptr || opt_in->block_threads <= 0) {
-        // automatic workgroup size: the one that lets a CU hold the most wavefronts given the LDS footprint
-        // (LDS is handed out in 512-byte pieces; a CU holds at most 32 wavefronts); ties go to the smaller size
-        int lds_cu = 0;
-        if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, 0) != hipSuccess || lds_cu <= 0)
-            lds_cu = 64 * 1024;
-        const size_t need = c->staged ? ((estep_lds_bytes(c, MODE_SAMPLE) + 144 + 511) / 512) * 512 : 512;
+        // automatic workgroup size: the one that lets a CU hold the most wavefronts given the LDS footprint; ties go to
+        // the smaller size.  A row that is not staged is gathered through the caches: the more of a CU's wavefronts
+        // work on the same row the better (T = 20 M, K = 45,000: 18.9, 14.5 and 10.6 ms with 256, 512 and 1,024 threads)
         int best = 256, best_waves = 0;
         for (int block : {256, 512, 1024}) {
-            const int by_lds = (int)std::min<size_t>(64, (size_t)lds_cu / need), by_waves = 32 / (block / 64);
-            const int waves = std::min(by_lds, by_waves) * (block / 64);
-            if (waves > best_waves) { best_waves = waves; best = block; }
+            const int waves = estep_waves_per_cu(c, block);
+            if (waves > best_waves || !c->staged) { best_waves = waves; best = block; }
         }
         c->opt.block_threads = best;
+        c->auto_light_block = c->opt.light_block_threads <= 0;
     }
     if (c->opt.light_block_threads <= 0) c->opt.light_block_threads = c->opt.block_threads;
     c->vbeta = (float)V * beta;
@@ -1427,6 +1463,7 @@ extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const 
         }
         saber_options opt = m->opt;
         opt.profile = 0; opt.n_chunks = 1; opt.tile_tokens = m->tile_tokens_asked;   // (0: sized for these documents)
+        if (m->auto_light_block) opt.block_threads = opt.light_block_threads = 0;
         rc = create_ctx(&obs, optr.data(), ow.data(), D, m->V, m->K, m->alpha, m->beta, seed, &opt, m, false);
         if (rc == SABER_OK && z_init) rc = saber_set_z(obs, z_init, 0);
         if (rc == SABER_OK) rc = foldin_iterate(obs, n_foldin);
