@@ -1229,23 +1229,22 @@ __global__ void __launch_bounds__(1024) count_dz_kernel(const int32_t *doc_list,
 
 // ---------------------------------------------------------------------------------------------
 // Topic totals C_k = sum_v B_vk, computed as the histogram of z (same numbers, 20x fewer bytes than
-// column sums of B at K = 10^4).  LDS histogram when K fits, else global atomics.
+// column sums of B at K = 10^4): workgroup (x, y) counts the topics [y range, (y + 1) range) of its share of z in LDS
+// and adds the non-zero bins to the totals.
 // ---------------------------------------------------------------------------------------------
 template <typename ZT>
 __global__ void __launch_bounds__(1024) topic_totals_kernel(const ZT *z, int64_t T, int64_t per_block, unsigned long long *ck, int K,
-                                                            int use_lds) {
+                                                            int range) {
     extern __shared__ uint32_t hist[];
     const int64_t b = (int64_t)blockIdx.x * per_block;
     int64_t e = b + per_block; if (e > T) e = T;
-    if (use_lds) {
-        for (int k = threadIdx.x; k < K; k += blockDim.x) hist[k] = 0u;
-        __syncthreads();
-        block_for_each_z(z + b, e - b, [&](uint32_t k) { atomicAdd(&hist[k], 1u); });
-        __syncthreads();
-        for (int k = threadIdx.x; k < K; k += blockDim.x) { const uint32_t h = hist[k]; if (h) atomicAdd(&ck[k], (unsigned long long)h); }
-    } else {
-        block_for_each_z(z + b, e - b, [&](uint32_t k) { atomicAdd(&ck[k], 1ull); });
-    }
+    const int k0 = (int)blockIdx.y * range, n = min(range, K - k0);
+    for (int k = threadIdx.x; k < n; k += blockDim.x) hist[k] = 0u;
+    __syncthreads();
+    if (gridDim.y == 1) block_for_each_z(z + b, e - b, [&](uint32_t k) { atomicAdd(&hist[k], 1u); });
+    else block_for_each_z(z + b, e - b, [&](uint32_t k) { if (k - (uint32_t)k0 < (uint32_t)n) atomicAdd(&hist[k - (uint32_t)k0], 1u); });
+    __syncthreads();
+    for (int k = threadIdx.x; k < n; k += blockDim.x) { const uint32_t h = hist[k]; if (h) atomicAdd(&ck[k0 + k], (unsigned long long)h); }
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -39,3 +39,23 @@ def test_workgroups_sized_by_the_tile(K):
     assert abs(p.loglik() - ll) <= 1e-12 * abs(ll)
     p.close()
     o.close()
+
+
+@pytest.mark.parametrize("K,T", [(15361, 16383), (36864, 16385), (36865, 40000), (73729, 300_001), (262144, 5000), (100, 1), (7, 65537)])
+def test_topic_totals_and_word_counts_at_the_edges_of_an_lds_histogram(K, T):
+    """One LDS histogram holds 36,864 topics; shares of z have at least 16,384 assignments.  The highest and the lowest
+    topic of every range occur, one topic takes a third of all tokens, and one word most of them."""
+    rng = np.random.default_rng(K)
+    V = 5
+    words = np.where(rng.random(T) < 0.9, 0, rng.integers(0, V, T)).astype(np.int32)
+    z = rng.integers(0, K, T)
+    edges = np.array([k for k in (0, K - 1, 36863, 36864, K // 2 - 1, K // 2, (K + 1) // 2, (K + 2) // 3) if 0 <= k < K])
+    z[: min(T, edges.size)] = edges[: min(T, edges.size)]
+    z[T // 2: T // 2 + T // 3] = K // 3
+    doc_ptr = np.minimum(np.arange(0, T + 300, 300), T).astype(np.int64)
+    g = saber().Saber(doc_ptr, words, V, K, 0.1, 0.01, 3)
+    g.set_z(z.astype(np.int32), 1)
+    _, _, _, cwk, ck = g.counts(want_cd=False)
+    assert np.array_equal(ck, np.bincount(z, minlength=K))
+    assert np.array_equal(cwk.reshape(-1), np.bincount(words.astype(np.int64) * K + z, minlength=V * K))
+    g.close()
