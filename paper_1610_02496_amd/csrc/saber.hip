@@ -151,8 +151,9 @@ struct saber_ctx {
     float *lw_phi = nullptr;          // Bhat of each such entry
     void *z_wm = nullptr;             // [T] word-major assignments: the light words' tokens first, then the dense rows' ones
     int64_t T_light = 0, lw_cap = 0;
-    VzItem *vz_items = nullptr;       // slabs of the dense-row words' segments of z_wm
-    int64_t n_vz_items = 0;
+    VzItem *vz_items = nullptr;       // slabs of the dense-row words' segments of z_wm, those of the longest rows first
+    int64_t n_vz_items = 0, n_vz_long = 0;   // all; those of rows that phi_tree_kernel does not count itself
+    PhiRow *phi_rows = nullptr;       // [V_dense+1] the dense rows as phi_tree_kernel takes them
     std::vector<int32_t> h_word_row;  // host: word -> dense row (>= 0) or -(light row) - 1
     // A context built on a trained model (held-out documents): it borrows the model's word classes, Bhat, tree
     // levels and sparse rows, owns only its own tokens, z and rows of A, and never rebuilds B.
@@ -236,7 +237,7 @@ extern "C" void saber_free(saber_ctx *c) {
         release(c->cwk); release(c->ck); release(c->denom); release(c->phi); release(c->l3_64); release(c->l3);
         release(c->sumphi); release(c->row_word); release(c->light_words); release(c->light_short);
         release(c->light_long); release(c->light_tok_ptr); release(c->wrec); release(c->lw_ent); release(c->lw_phi);
-        release(c->vz_items);
+        release(c->vz_items); release(c->phi_rows);
     }
     if (c->have_events) for (auto &e : c->ev) if (e) (void)hipEventDestroy(e);
     if (c->s_in) { (void)hipStreamSynchronize(c->s_in); (void)hipStreamDestroy(c->s_in); }
@@ -534,17 +535,25 @@ static int launch_row_stats(saber_ctx *c, unsigned long long *out2) {
     return SABER_OK;
 }
 
-constexpr int kHistTopics = 36 * 1024;   // topics of one LDS histogram: 144 of the CU's 160 KB
+// Topics of one workgroup's LDS histogram: at most 36,864 (144 of the CU's 160 KB); more topics are shared out evenly over
+// the grid's y.
+constexpr int kHistTopics = 36 * 1024;
+static int hist_range(const saber_ctx *c) {
+    const int ranges = (c->K + kHistTopics - 1) / kHistTopics;
+    return ((c->K + ranges - 1) / ranges + 63) / 64 * 64;
+}
+static int allow_lds(const void *kernel, size_t lds) {   // more than the default 64 KB has to be asked for
+    if (lds > 64 * 1024) HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    return SABER_OK;
+}
 
 static int launch_topic_totals(saber_ctx *c) {
     hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(2 * (int64_t)c->K, 256)), dim3(256), 0, c->stream, (uint32_t *)c->ck, 0u, (size_t)c->K * 2);
     HIP_TRY(hipGetLastError());
     if (c->T == 0) return SABER_OK;
-    // A workgroup's histogram takes up to kHistTopics topics of LDS; more topics are shared out over the grid's y.
     // Counting in LDS replaces one global atomic per token: 0.74 -> 0.04 ms at T = 15 M, K = 20,011, 0.13 -> 0.04 ms at
     // T = 1.5 M, K = 70,000.
-    const int ranges = (c->K + kHistTopics - 1) / kHistTopics;
-    const int range = ((c->K + ranges - 1) / ranges + 63) / 64 * 64;
+    const int range = hist_range(c);
     // every workgroup ends with up to K atomics into the K totals: no more than about 500 shares of z (128 where these
     // have fewer than 65,536 assignments: T = 10 M, K = 1,000 takes 17 us with 153 of them, 21 with 490), none with
     // fewer than 16 assignments per topic (at least 16,384) or more than 2^20, keep those from dominating
@@ -556,10 +565,7 @@ static int launch_topic_totals(saber_ctx *c) {
     // a histogram of all assignments: their order does not matter, and with host streaming the word-major copy is
     // the one that is resident
     const void *zsrc = c->n_slots ? c->z_wm : c->z;
-    if (lds > 64 * 1024) {
-        const void *fn = c->z16 ? (const void *)topic_totals_kernel<uint16_t> : (const void *)topic_totals_kernel<int32_t>;
-        HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    }
+    SABER_TRY(allow_lds(c->z16 ? (const void *)topic_totals_kernel<uint16_t> : (const void *)topic_totals_kernel<int32_t>, lds));
     if (c->z16)
         hipLaunchKernelGGL((topic_totals_kernel<uint16_t>), grid, dim3(1024), lds, c->stream, (const uint16_t *)zsrc, c->T,
                            per_block, c->ck, c->K, range);
@@ -573,11 +579,23 @@ static int launch_topic_totals(saber_ctx *c) {
 // LDS of one workgroup of the alias-table build: K + 1 prefix sums (binary64) and K item numbers
 static size_t alias_lds_bytes(int K) { return ((size_t)K + 1) * sizeof(double) + (size_t)K * sizeof(uint32_t); }
 
+// Threads of a phi_tree_kernel workgroup: a column for each of its four per step
+static int phi_block_threads(const saber_ctx *c) { return c->Kpad <= 1024 ? 256 : c->Kpad <= 2048 ? 512 : 1024; }
+
 static int launch_phi(saber_ctx *c) {
-    hipLaunchKernelGGL(denominators_kernel, dim3(grid_for(c->K, 256)), dim3(256), 0, c->stream, c->ck, c->denom, c->K, c->vbeta);
+    hipLaunchKernelGGL(denominators_kernel, dim3(grid_for(c->Kpad, 256)), dim3(256), 0, c->stream, c->ck, c->denom, c->K, c->Kpad, c->vbeta);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(phi_tree_kernel, dim3((unsigned)(c->V_dense + 1)), dim3(256), 0, c->stream, c->cwk, c->denom, c->phi,
-                       c->l3, c->l3_64, c->sumphi, c->row_word, c->K, c->Kpad, c->n3, c->n3pad, c->beta, 1);
+    // kPhiSteps steps of four columns per thread at a time: up to 12,288 topics (48 KB of LDS: two workgroups of 1,024
+    // threads per CU)
+    const dim3 grid((unsigned)(c->V_dense + 1)), block((unsigned)phi_block_threads(c));
+    const int range = std::min(c->Kpad, kPhiSteps * 4 * (int)block.x);
+    const size_t hist = (size_t)range * sizeof(uint32_t);
+    if (c->z16)
+        hipLaunchKernelGGL((phi_tree_kernel<uint16_t>), grid, block, hist, c->stream, c->phi_rows, (const uint16_t *)c->z_wm, c->cwk,
+                           c->denom, c->phi, c->l3, c->l3_64, c->sumphi, c->Kpad, c->n3, c->n3pad, c->beta, range);
+    else
+        hipLaunchKernelGGL((phi_tree_kernel<int32_t>), grid, block, hist, c->stream, c->phi_rows, (const int32_t *)c->z_wm, c->cwk,
+                           c->denom, c->phi, c->l3, c->l3_64, c->sumphi, c->Kpad, c->n3, c->n3pad, c->beta, range);
     HIP_TRY(hipGetLastError());
     if (c->alias_table && c->V_dense > 0) {   // measurement variant: an alias table per word on top of the tree level
         const size_t lds = alias_lds_bytes(c->K);
@@ -628,22 +646,20 @@ static int launch_estep_docmajor(saber_ctx *c, unsigned long long *n_dense) {
 
 // CountByVZ for the dense rows of B out of the word-major assignments; the rows must be all zero on entry
 // (the Bhat kernel leaves them so).
-static int launch_count_vz(saber_ctx *c) {
-    if (c->n_vz_items == 0) return SABER_OK;
-    // (in LDS up to kHistTopics topics; one global atomic per token beyond: 0.39 against 0.04 ms at T = 15 M, K = 20,011)
-    const int use_lds = c->K <= kHistTopics;
-    const size_t lds = use_lds ? (size_t)c->K * 4 : 0;
-    const dim3 grid((unsigned)c->n_vz_items), block(use_lds ? 1024u : 256u);
-    if (lds > 64 * 1024) {
-        const void *fn = c->z16 ? (const void *)count_vz_kernel<uint16_t> : (const void *)count_vz_kernel<int32_t>;
-        HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    }
+static int launch_count_vz(saber_ctx *c, int64_t n_items) {
+    if (n_items == 0) return SABER_OK;
+    // (in LDS, by ranges of topics, at any K: 0.39 -> 0.04 ms at T = 15 M, K = 20,011 against one global atomic per token,
+    // 0.24 -> 0.03 ms at T = 1.5 M, K = 70,000)
+    const int range = hist_range(c);
+    const size_t lds = (size_t)std::min(range, c->K) * 4;
+    const dim3 grid((unsigned)n_items, (unsigned)((c->K + range - 1) / range));
+    SABER_TRY(allow_lds(c->z16 ? (const void *)count_vz_kernel<uint16_t> : (const void *)count_vz_kernel<int32_t>, lds));
     if (c->z16)
-        hipLaunchKernelGGL((count_vz_kernel<uint16_t>), grid, block, lds, c->stream, c->vz_items, (const uint16_t *)c->z_wm,
-                           c->cwk, c->K, c->Kpad, use_lds);
+        hipLaunchKernelGGL((count_vz_kernel<uint16_t>), grid, dim3(1024), lds, c->stream, c->vz_items, (const uint16_t *)c->z_wm,
+                           c->cwk, c->K, c->Kpad, range);
     else
-        hipLaunchKernelGGL((count_vz_kernel<int32_t>), grid, block, lds, c->stream, c->vz_items, (const int32_t *)c->z_wm,
-                           c->cwk, c->K, c->Kpad, use_lds);
+        hipLaunchKernelGGL((count_vz_kernel<int32_t>), grid, dim3(1024), lds, c->stream, c->vz_items, (const int32_t *)c->z_wm,
+                           c->cwk, c->K, c->Kpad, range);
     HIP_TRY(hipGetLastError());
     return SABER_OK;
 }
@@ -694,7 +710,7 @@ static int full_mstep(saber_ctx *c, const int32_t *user_z = nullptr) {
         return SABER_OK;
     }
     if (!c->n_slots) SABER_TRY(launch_fill_zwm(c));
-    SABER_TRY(launch_count_vz(c));
+    SABER_TRY(launch_count_vz(c, c->n_vz_long));
     SABER_TRY(launch_topic_totals(c));
     SABER_TRY(launch_phi(c));
     SABER_TRY(launch_light_words(c));
@@ -821,6 +837,11 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     // slabs CountByVZ cuts the dense rows' segments into
     std::vector<int64_t> wm_ptr((size_t)V, 0), wm_seen((size_t)V, 0);   // wm_seen: tokens placed so far (chunk by chunk)
     std::vector<VzItem> h_vz_items;
+    std::vector<PhiRow> h_phi_rows;
+    // phi_tree_kernel counts a row itself up to 32 tokens per thread of its workgroup; longer rows are cut into slabs for
+    // count_vz_kernel (phi group of T = 2.3 M, K = 777, 256 threads: 43 us with 8,192 tokens, 49 with 32,768; of T = 100 M,
+    // K = 10,000, 1,024 threads: 343 us counting none, 323 with 8,192, 303 with 32,768, 298 with 131,072)
+    const int64_t own_tokens = 32 * phi_block_threads(c);
     {
         for (int32_t li = 0; li < c->V_light; li++) wm_ptr[(size_t)h_light_words[(size_t)li]] = h_light_tok_ptr[(size_t)li];
         int64_t pos = c->T_light;
@@ -828,10 +849,14 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         for (int32_t r = 0; r < c->V_dense; r++) {
             const int32_t v = h_row_word[(size_t)r];
             wm_ptr[(size_t)v] = pos;
+            h_phi_rows.push_back(PhiRow{v, n_v[(size_t)v] <= own_tokens ? (int32_t)n_v[(size_t)v] : -1, pos});
             for (int64_t s = 0; s < n_v[(size_t)v]; s += slab)
                 h_vz_items.push_back(VzItem{r, (int32_t)std::min<int64_t>(slab, n_v[(size_t)v] - s), pos + s});
             pos += n_v[(size_t)v];
         }
+        h_phi_rows.push_back(PhiRow{V, 0, 0});
+        c->n_vz_long = std::stable_partition(h_vz_items.begin(), h_vz_items.end(), [&](const VzItem &it) {
+                           return h_phi_rows[(size_t)it.row].count < 0; }) - h_vz_items.begin();
         c->n_vz_items = (int64_t)h_vz_items.size();
     }
     // the word-major token arrays: ordinary host memory on the way to the device, or with host streaming the
@@ -960,7 +985,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         c->phi = par->phi; c->l3 = par->l3; c->l3_64 = par->l3_64; c->sumphi = par->sumphi;
         c->wrec = par->wrec; c->lw_ent = par->lw_ent; c->lw_phi = par->lw_phi;
     } else {
-    SABER_TRY(dev_alloc(c->hooks, &c->cwk, vk)); SABER_TRY(dev_alloc(c->hooks, &c->ck, (size_t)K)); SABER_TRY(dev_alloc(c->hooks, &c->denom, (size_t)K));
+    SABER_TRY(dev_alloc(c->hooks, &c->cwk, vk)); SABER_TRY(dev_alloc(c->hooks, &c->ck, (size_t)K)); SABER_TRY(dev_alloc(c->hooks, &c->denom, (size_t)c->Kpad));
     SABER_TRY(dev_alloc(c->hooks, &c->phi, vk)); SABER_TRY(dev_alloc(c->hooks, &c->l3_64, ((size_t)V + 1) * (size_t)c->n3));
     SABER_TRY(dev_alloc(c->hooks, &c->row_word, h_row_word.size())); SABER_TRY(dev_alloc(c->hooks, &c->light_words, h_light_words.size()));
     SABER_TRY(dev_alloc(c->hooks, &c->light_short, h_light_short.size())); SABER_TRY(dev_alloc(c->hooks, &c->light_long, h_light_long.size()));
@@ -969,7 +994,8 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     }
     if (c->z16) SABER_TRY(dev_alloc(c->hooks, (uint16_t **)&c->z_wm, (size_t)T)); else SABER_TRY(dev_alloc(c->hooks, (int32_t **)&c->z_wm, (size_t)T));
     if (!par) {
-    SABER_TRY(dev_alloc(c->hooks, &c->vz_items, h_vz_items.size()));
+    SABER_TRY(dev_alloc(c->hooks, &c->vz_items, h_vz_items.size())); SABER_TRY(dev_alloc(c->hooks, &c->phi_rows, h_phi_rows.size()));
+    HIP_TRY(hipMemcpy(c->phi_rows, h_phi_rows.data(), sizeof(PhiRow) * h_phi_rows.size(), hipMemcpyHostToDevice));
     if (!h_vz_items.empty())
         HIP_TRY(hipMemcpy(c->vz_items, h_vz_items.data(), sizeof(VzItem) * h_vz_items.size(), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->row_word, h_row_word.data(), sizeof(int32_t) * h_row_word.size(), hipMemcpyHostToDevice));
@@ -1228,7 +1254,7 @@ extern "C" int saber_iterate(saber_ctx *c, int32_t n) {
             if (prof) HIP_TRY(hipEventRecord(ev[EV_DZ], c->stream));
             SABER_TRY(launch_topic_totals(c));
             if (prof) HIP_TRY(hipEventRecord(ev[EV_CK], c->stream));
-            SABER_TRY(launch_count_vz(c));
+            SABER_TRY(launch_count_vz(c, c->n_vz_long));
             SABER_TRY(launch_phi(c));
             SABER_TRY(launch_light_words(c));
             if (prof) HIP_TRY(hipEventRecord(ev[EV_PHI], c->stream));
@@ -1314,7 +1340,7 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
         }
         if (cwk) {
             // dense rows: B is consumed (and cleared) by the Bhat kernel; rebuild it from z for export
-            SABER_TRY(launch_count_vz(c));
+            SABER_TRY(launch_count_vz(c, c->n_vz_items));
             HIP_TRY(hipStreamSynchronize(c->stream));
             const int64_t slab = 2048;   // rows per host staging buffer
             std::vector<int32_t> buf((size_t)slab * (size_t)c->Kpad);

@@ -102,6 +102,14 @@ __device__ __forceinline__ int wave_vote_first(bool pred) {
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 
+// Barrier of a workgroup that exchanges data through LDS only: __syncthreads() also waits until every global store in flight
+// has been acknowledged by memory, which a kernel that streams its results out does not need between its steps.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ---------------------------------------------------------------------------------------------
 // Philox4x32-10 (Salmon et al., SC'11), written for the device; the CPU checker has its own.
 // counter = (token lo, token hi, iteration, 0), key = (seed lo, seed hi).
@@ -948,8 +956,8 @@ __global__ void prefix_export_kernel(const float *rows, const double *l3_64, con
 // CountByVZ for the words with dense rows of B.  The assignments arrive word-major (z_wm), so a word's tokens are
 // one contiguous segment; it is cut into slabs and each workgroup histograms one slab in LDS and adds the
 // non-zero bins to the word's row: at most min(slab, K) global atomics per slab instead of one per token.
-// Rows must be zero on entry (the Bhat kernel clears them after reading).  K too large for an LDS histogram:
-// one global atomic per token.
+// Workgroup (x, y) counts the topics [y range, (y + 1) range) of slab x.  Rows must be zero on entry (the Bhat kernel
+// clears them after reading).
 // ---------------------------------------------------------------------------------------------
 struct VzItem { int32_t row; int32_t count; int64_t begin; };   // slab: count tokens from z_wm[begin] on
 
@@ -986,22 +994,20 @@ __device__ __forceinline__ void block_for_each_z(const ZT *__restrict__ zs, int6
 
 template <typename ZT>
 __global__ void __launch_bounds__(1024) count_vz_kernel(const VzItem *items, const ZT *z_wm, int32_t *cwk, int K,
-                                                        int Kpad, int use_lds) {
+                                                        int Kpad, int range) {
     extern __shared__ uint32_t vz_hist[];
     const VzItem it = items[blockIdx.x];
     const ZT *__restrict__ zs = z_wm + it.begin;
-    int32_t *row = cwk + (size_t)it.row * (size_t)Kpad;
-    if (use_lds) {
-        for (int k = threadIdx.x; k < K; k += blockDim.x) vz_hist[k] = 0u;
-        __syncthreads();
-        block_for_each_z(zs, (int64_t)it.count, [&](uint32_t k) { atomicAdd(&vz_hist[k], 1u); });
-        __syncthreads();
-        for (int k = threadIdx.x; k < K; k += blockDim.x) {
-            const uint32_t h = vz_hist[k];
-            if (h) atomicAdd(&row[k], (int)h);
-        }
-    } else {
-        block_for_each_z(zs, (int64_t)it.count, [&](uint32_t k) { atomicAdd(&row[k], 1); });
+    const int k0 = (int)blockIdx.y * range, n = min(range, K - k0);
+    int32_t *row = cwk + (size_t)it.row * (size_t)Kpad + k0;
+    for (int k = threadIdx.x; k < n; k += blockDim.x) vz_hist[k] = 0u;
+    __syncthreads();
+    if (gridDim.y == 1) block_for_each_z(zs, (int64_t)it.count, [&](uint32_t k) { atomicAdd(&vz_hist[k], 1u); });
+    else block_for_each_z(zs, (int64_t)it.count, [&](uint32_t k) { if (k - (uint32_t)k0 < (uint32_t)n) atomicAdd(&vz_hist[k - (uint32_t)k0], 1u); });
+    __syncthreads();
+    for (int k = threadIdx.x; k < n; k += blockDim.x) {
+        const uint32_t h = vz_hist[k];
+        if (h) atomicAdd(&row[k], (int)h);
     }
 }
 
@@ -1254,58 +1260,114 @@ __global__ void __launch_bounds__(1024) topic_totals_kernel(const ZT *z, int64_t
 //   l3[i]    = round32(l3_64[i])                                           -- tree level above the bottom, W = 64
 // Pad columns k in [K, Kpad) get Bhat = 0, so the last block's running sum is the row total.
 // The bottom level (one prefix sum per topic) is not stored; the sampler rebuilds the 64 entries it needs.
-// The row of B is cleared after it has been read, ready for the next CountByVZ.
 // ---------------------------------------------------------------------------------------------
 // Denominators of Eq. 2, one per topic: float(C_k) + float(V) * beta (the conversion rounds to nearest even).
-__global__ void denominators_kernel(const unsigned long long *ck, float *denom, int K, float vbeta) {
+// Pad columns get an infinite one, so that their Bhat comes out as zero.
+__global__ void denominators_kernel(const unsigned long long *ck, float *denom, int K, int Kpad, float vbeta) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < K) denom[k] = (float)ck[k] + vbeta;
+    if (k < Kpad) denom[k] = k < K ? (float)ck[k] + vbeta : __builtin_inff();
 }
 
-// row_word[r] is the word of dense row r (the tree levels are indexed by word); the last row is an all-zero
-// row that yields the base vector (Bhat of a zero count) and its running sums for the light words.
-__global__ void __launch_bounds__(256) phi_tree_kernel(int32_t *cwk, const float *denom, float *phi, float *l3,
-                                                       double *l3_64, float *sumphi, const int32_t *row_word, int K,
-                                                       int Kpad, int n3, int n3pad, float beta, int clear_cwk) {
-    __shared__ double wave_tot[4];
+// One dense row: its word (the tree levels are indexed by word) and its segment of the word-major assignments.  count >= 0:
+// the workgroup histograms the segment in LDS, `range` topics at a time, and the counts never reach memory; count < 0: the
+// word has too many tokens for one workgroup, its row of B was counted by count_vz_kernel and is cleared here.
+// The last row has no tokens: it yields the base vector (Bhat of a zero count) and its running sums for the light words.
+//
+// Bound by the store of Bhat, 4 Kpad bytes per row, and by the row's chain of steps.  Counting through memory (atomics into
+// B, then read and clear it) moved three times that: K = 70,000, 4,002 rows of 375 tokens: 966 + 271 us before, 428 + 27 now
+// (2.6 TB/s); K = 10,000, 1,450 rows: 44 + 66 us before, 43 + 41 now.  Barriers that wait for LDS only, a row's few assignments
+// held in registers over the ranges and two steps per exchange of running sums (three do not leave two workgroups per CU
+// their registers) took the 70,000-topic case from 740 us to 428.
+// The running sums associate in groups of 1,024 columns whatever the workgroup's size.
+struct PhiRow { int32_t word; int32_t count; int64_t begin; };
+constexpr int kPhiSteps = 2;   // steps of 4 columns per thread that share one histogram and one exchange of running sums
+
+template <typename ZT>
+__global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, const ZT *z_wm, int32_t *cwk, const float *denom,
+                                                        float *phi, float *l3, double *l3_64, float *sumphi, int Kpad,
+                                                        int n3, int n3pad, float beta, int range) {
+    constexpr int kHeld = 4;               // assignments per thread that are read once and held
+    extern __shared__ int4 phi_hist4[];
+    uint32_t *phi_hist = reinterpret_cast<uint32_t *>(phi_hist4);
+    __shared__ double wave_tot[kPhiSteps * 16];
     __shared__ float row_total;
-    const int v = row_word[blockIdx.x];
-    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    const PhiRow pr = rows[blockIdx.x];
+    const int v = pr.word, step = 4 * (int)blockDim.x;
+    const int lane = lane_id(), wave = threadIdx.x / kWave, nwaves = blockDim.x / kWave;
     const size_t rbase = (size_t)blockIdx.x * (size_t)Kpad;
+    const bool own = pr.count >= 0, held = own && pr.count <= kHeld * (int)blockDim.x;
+    const ZT *__restrict__ zs = z_wm + pr.begin;
+    uint32_t zr[kHeld];
+#pragma unroll
+    for (int j = 0; j < kHeld; j++) {
+        const int i = (int)threadIdx.x + j * (int)blockDim.x;
+        zr[j] = held && i < pr.count ? (uint32_t)zs[i] : 0xffffffffu;
+    }
     double carry = 0.0;
-    for (int base = 0; base < Kpad; base += 1024) {
-        const int k0 = base + (int)threadIdx.x * 4;
-        float f[4] = {0.f, 0.f, 0.f, 0.f};
-        if (k0 < Kpad) {   // Kpad is a multiple of 64, so k0..k0+3 are all inside the padded row
-            const int4 c = *reinterpret_cast<const int4 *>(cwk + rbase + k0);
-            const int cc[4] = {c.x, c.y, c.z, c.w};
+    for (int r0 = 0; r0 < Kpad; r0 += range) {
+        const int n = min(range, Kpad - r0);
+        float4 den[kPhiSteps];             // requested before the counting
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const int k = k0 + q;
-                if (k < K) {
-                    const float num = (float)cc[q] + beta;
-                    f[q] = num / denom[k];
-                }
+        for (int st = 0; st < kPhiSteps; st++) {
+            const int k = st * step + (int)threadIdx.x * 4;
+            den[st] = k < n ? *reinterpret_cast<const float4 *>(denom + r0 + k) : make_float4(1.f, 1.f, 1.f, 1.f);
+        }
+        if (own) {
+            for (int k = threadIdx.x; k < n / 4; k += blockDim.x) phi_hist4[k] = make_int4(0, 0, 0, 0);
+            lds_barrier();
+            auto count = [&](uint32_t k) { if (k - (uint32_t)r0 < (uint32_t)n) atomicAdd(&phi_hist[k - (uint32_t)r0], 1u); };
+            if (held) {
+#pragma unroll
+                for (int j = 0; j < kHeld; j++) count(zr[j]);
+            } else {
+                block_for_each_z(zs, (int64_t)pr.count, count);
             }
-            *reinterpret_cast<float4 *>(phi + rbase + k0) = make_float4(f[0], f[1], f[2], f[3]);
-            if (clear_cwk) *reinterpret_cast<int4 *>(cwk + rbase + k0) = make_int4(0, 0, 0, 0);
+            lds_barrier();
         }
-        const double s3 = (((double)f[0] + (double)f[1]) + (double)f[2]) + (double)f[3];
-        const double incl = wave_incl_scan(s3);
-        if (lane == kWave - 1) wave_tot[wave] = incl;
-        __syncthreads();
-        double woff = 0.0, btot = 0.0;
+        double incl[kPhiSteps];
 #pragma unroll
-        for (int w = 0; w < 4; w++) { const double tw = wave_tot[w]; if (w < wave) woff += tw; btot += tw; }
-        if (k0 < Kpad && ((k0 + 3) & (kWave - 1)) == kWave - 1) {
-            const double run = carry + woff + incl;       // running sum through topic k0+3, the end of a block
-            const int i = (k0 + 3) / kWave;
-            l3_64[(size_t)v * (size_t)n3 + (size_t)i] = run;
-            l3[(size_t)v * (size_t)n3pad + (size_t)i] = (float)run;
-            if (i == n3 - 1) row_total = (float)run;
+        for (int st = 0; st < kPhiSteps; st++) {
+            if (st * step >= n) break;     // uniform
+            const int k = st * step + (int)threadIdx.x * 4;
+            float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (k < n) {   // n is a multiple of 64, so k..k+3 are all inside the padded row
+                int4 c;
+                if (own) c = phi_hist4[k / 4];
+                else c = *reinterpret_cast<const int4 *>(cwk + rbase + r0 + k);
+                f.x = ((float)c.x + beta) / den[st].x; f.y = ((float)c.y + beta) / den[st].y;
+                f.z = ((float)c.z + beta) / den[st].z; f.w = ((float)c.w + beta) / den[st].w;
+                *reinterpret_cast<float4 *>(phi + rbase + r0 + k) = f;
+                if (!own) *reinterpret_cast<int4 *>(cwk + rbase + r0 + k) = make_int4(0, 0, 0, 0);
+            }
+            incl[st] = wave_incl_scan((((double)f.x + (double)f.y) + (double)f.z) + (double)f.w);
+            if (lane == kWave - 1) wave_tot[st * 16 + wave] = incl[st];
         }
-        carry += btot;
-        __syncthreads();
+        lds_barrier();
+#pragma unroll
+        for (int st = 0; st < kPhiSteps; st++) {
+            if (st * step >= n) break;
+            double woff = 0.0, start = 0.0;    // `start`: running sum before the 1,024 columns of this wavefront
+            for (int g = 0; g < nwaves; g += 4) {
+                double btot = 0.0;
+                if (g == (wave & ~3)) start = carry;
+#pragma unroll
+                for (int w = 0; w < 4; w++) {
+                    const double tw = wave_tot[st * 16 + g + w];
+                    if (g + w == wave) woff = btot;
+                    btot += tw;
+                }
+                carry += btot;
+            }
+            const int k = st * step + (int)threadIdx.x * 4;
+            if (k < n && ((k + 3) & (kWave - 1)) == kWave - 1) {
+                const double run = start + woff + incl[st];       // running sum through topic r0 + k + 3, the end of a block
+                const int i = (r0 + k + 3) / kWave;
+                l3_64[(size_t)v * (size_t)n3 + (size_t)i] = run;
+                l3[(size_t)v * (size_t)n3pad + (size_t)i] = (float)run;
+                if (i == n3 - 1) row_total = (float)run;
+            }
+        }
+        lds_barrier();
     }
     const float total = row_total;   // written before the loop's last barrier
     for (int i = n3 + (int)threadIdx.x; i < n3pad; i += blockDim.x) l3[(size_t)v * (size_t)n3pad + i] = total;

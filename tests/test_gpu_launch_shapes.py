@@ -59,3 +59,28 @@ def test_topic_totals_and_word_counts_at_the_edges_of_an_lds_histogram(K, T):
     assert np.array_equal(ck, np.bincount(z, minlength=K))
     assert np.array_equal(cwk.reshape(-1), np.bincount(words.astype(np.int64) * K + z, minlength=V * K))
     g.close()
+
+
+@pytest.mark.parametrize("K", [63, 1024, 1025, 2049, 8192, 8193, 16385, 70000])
+def test_dense_rows_counted_where_they_are_normalised(K):
+    """Rows on both sides of what a workgroup holds in registers (4 assignments per thread), counts itself (32 per thread)
+    and leaves to the slab histograms, for workgroups of 256, 512 and 1,024 threads and one or several ranges of topics."""
+    block = 256 if K <= 1024 else 512 if K <= 2048 else 1024
+    counts = np.array([0, 1, 7, 4 * block - 1, 4 * block, 4 * block + 1, 32 * block, 32 * block + 1, 33 * block + 5, 3])
+    doc_ptr, words = corpus_of_word_counts(counts, 900, K)
+    V, rng = counts.size, np.random.default_rng(K)
+    z = np.where(rng.random(words.size) < 0.3, K - 1, (K * rng.random(words.size) ** 3).astype(np.int64)).astype(np.int32)
+    pk = saber()
+    for state in (0, 1):                       # rows of B are clear again after each M-step
+        z = np.roll(z, 17 * state)
+        if state == 0:
+            g = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 4, light_word_tokens=-1)
+            o = oracle.Model(doc_ptr, words, V, K, 0.1, 0.01, 4)
+        g.set_z(z, 1)
+        o.set_z(z, it=1)
+        phi, prefix = g.get_phi(np.arange(V, dtype=np.int32))
+        assert np.array_equal(phi, o.phi)
+        assert np.mean(prefix != o.c32) < 1e-5 and np.allclose(prefix, o.c32, rtol=1.2e-7, atol=0)
+        assert np.array_equal(g.counts(want_cd=False)[3], o.cwk)
+    g.close()
+    o.close()
