@@ -84,7 +84,7 @@ typedef struct saber_options {
                                    fits what is free, else host streaming with three workers (saber_stats says which;
                                    SABER_ENOMEM if that does not fit either).  -1: never stream.  Results are the
                                    same.  With profile=1 and streaming, ms_sample covers the whole chunk loop (copies
-                                   waited for, sampling, CountByDZ) and ms_count_dz is zero. */
+                                   waited for, sampling, CountByDZ) and ms_count_dz the sparse rows of B only. */
     int32_t ablation;           /* measurement aid, default 0: bit 0 samples the tokens in document order instead of
                                    word order (the layout before Sec. 3.1.3: the row of A is fetched once per document,
                                    Bhat is gathered from global memory; every word then keeps a dense row and
@@ -108,9 +108,9 @@ typedef struct saber_options {
 typedef struct saber_stats {
     int64_t iterations;       /* iterations counted */
     double ms_sample;         /* E-step sampling kernel (all chunks) */
-    double ms_count_dz;       /* CountByDZ */
-    double ms_ck;             /* topic totals C_k */
-    double ms_phi;            /* Preprocess + BuildTree */
+    double ms_count_dz;       /* CountByDZ, and the sparse rows of B (counted in the same launches) */
+    double ms_ck;             /* topic totals C_k, and the rows of B of the most frequent words (same launch) */
+    double ms_phi;            /* Preprocess + BuildTree, and the other dense rows of B */
     double ms_total;          /* whole iterations, first kernel to last */
     int64_t sample_launches;  /* sampling-kernel launches timed */
     int64_t sum_tokens;       /* tokens sampled */

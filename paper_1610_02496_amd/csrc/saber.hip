@@ -160,7 +160,7 @@ struct saber_ctx {
     const saber_ctx *parent = nullptr;
     bool no_state = false;            // no assignments of its own (tokens that are only scored)
     int32_t *cwk = nullptr;           // [V_dense+1][Kpad]
-    unsigned long long *ck = nullptr; // [K] topic totals
+    unsigned long long *ck = nullptr, *ck_acc = nullptr; // [K] topic totals; their accumulators, zero outside the M-step
     float *denom = nullptr;           // [K] denominators of Eq. 2
     float *phi = nullptr, *l3 = nullptr, *sumphi = nullptr;
     double *l3_64 = nullptr;          // [V][n3]
@@ -234,7 +234,7 @@ extern "C" void saber_free(saber_ctx *c) {
     release(c->cd_ent); release(c->doc_ptr); release(c->short_docs); release(c->long_docs);
     release(c->doc_words); release(c->counters); release(c->dense_slots); release(c->ll_partial); release(c->z_wm);
     if (!c->parent) {   // the model's arrays belong to the model
-        release(c->cwk); release(c->ck); release(c->denom); release(c->phi); release(c->l3_64); release(c->l3);
+        release(c->cwk); release(c->ck); release(c->ck_acc); release(c->denom); release(c->phi); release(c->l3_64); release(c->l3);
         release(c->sumphi); release(c->row_word); release(c->light_words); release(c->light_short);
         release(c->light_long); release(c->light_tok_ptr); release(c->wrec); release(c->lw_ent); release(c->lw_phi);
         release(c->vz_items); release(c->phi_rows);
@@ -403,17 +403,17 @@ static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64
     add(end, lo);
 }
 
-// Segmented count of one grouping of the assignments: documents over z (CountByDZ -> rows of A) or light words
+// Segmented count of up to two groupings of the assignments: documents over z (CountByDZ -> rows of A) and light words
 // over z_wm (CountByVZ -> sparse rows of B).  Two launches: short segments with one wavefront each, long ones
 // with 256 threads.
-static int launch_segmented_count(saber_ctx *c, const int32_t *short_list, int64_t n_short, const int32_t *long_list,
-                                  int64_t n_long, const int64_t *seg_ptr, const void *z, int64_t z_first, uint2 *rec,
-                                  uint32_t *ent) {
+struct SegLists { SegGroup g; const int32_t *short_list; int64_t n_short; const int32_t *long_list; int64_t n_long; };
+static int launch_segmented_count(saber_ctx *c, const SegLists &a, const SegLists &b) {
     for (int pass = 0; pass < 2; pass++) {
-        const int64_t n = pass == 0 ? n_short : n_long;
-        const int32_t *list = pass == 0 ? short_list : long_list;
+        const int64_t na = pass == 0 ? a.n_short : a.n_long, nb = pass == 0 ? b.n_short : b.n_long;
         const int block = pass == 0 ? 64 : 256;
-        if (n == 0) continue;
+        if (na + nb == 0) continue;
+        SegGroup ga = a.g, gb = b.g;
+        ga.list = pass == 0 ? a.short_list : a.long_list; gb.list = pass == 0 ? b.short_list : b.long_list;
         // LDS: bitmap + rank prefix (2 * nwords) + the row under construction; a short segment's row has at
         // most long_doc_tokens entries, so its workgroup asks for no more than that
         const int budget = std::max(0, (int)((63 * 1024 - 8 * (int64_t)c->nwords) / 4));
@@ -424,17 +424,20 @@ static int launch_segmented_count(saber_ctx *c, const int32_t *short_list, int64
             const void *fn = c->z16 ? (const void *)count_dz_kernel<uint16_t> : (const void *)count_dz_kernel<int32_t>;
             HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         }
-        const dim3 grid((unsigned)n), blk((unsigned)block);
+        const dim3 grid((unsigned)(na + nb)), blk((unsigned)block);
         if (c->z16)
-            hipLaunchKernelGGL((count_dz_kernel<uint16_t>), grid, blk, lds, c->stream, list, seg_ptr,
-                               (const uint16_t *)z, z_first, rec, ent, c->K, c->topic_bits, c->nwords, entries);
+            hipLaunchKernelGGL((count_dz_kernel<uint16_t>), grid, blk, lds, c->stream, ga, na, gb, c->topic_bits, c->nwords, entries);
         else
-            hipLaunchKernelGGL((count_dz_kernel<int32_t>), grid, blk, lds, c->stream, list, seg_ptr,
-                               (const int32_t *)z, z_first, rec, ent, c->K, c->topic_bits, c->nwords, entries);
+            hipLaunchKernelGGL((count_dz_kernel<int32_t>), grid, blk, lds, c->stream, ga, na, gb, c->topic_bits, c->nwords, entries);
         HIP_TRY(hipGetLastError());
     }
     return SABER_OK;
 }
+static SegLists light_segments(const saber_ctx *c) {
+    return SegLists{{nullptr, c->light_tok_ptr, c->z_wm, 0, c->wrec, c->lw_ent}, c->light_short, c->n_light_short, c->light_long, c->n_light_long};
+}
+// the rows of B of a model's light words; held-out documents borrow theirs and count none
+static SegLists own_light_segments(const saber_ctx *c) { return c->parent ? SegLists{} : light_segments(c); }
 
 // Ablation: A rebuilt by sorting the (document, topic) pairs of all tokens
 static int launch_sort_rebuild(saber_ctx *c) {
@@ -459,17 +462,21 @@ static int launch_sort_rebuild(saber_ctx *c) {
     return SABER_OK;
 }
 
-static int launch_count_dz(saber_ctx *c) {
-    if (c->opt.ablation & 2) return launch_sort_rebuild(c);
-    return launch_segmented_count(c, c->short_docs, c->n_short, c->long_docs, c->n_long, c->doc_ptr, c->z, 0, c->docrec,
-                                  c->cd_ent);
+// CountByDZ of all documents, and CountByVZ of the light words
+static int launch_counts(saber_ctx *c) {
+    if (c->opt.ablation & 2) {
+        SABER_TRY(launch_sort_rebuild(c));
+        return launch_segmented_count(c, SegLists{}, own_light_segments(c));
+    }
+    return launch_segmented_count(c, SegLists{{nullptr, c->doc_ptr, c->z, 0, c->docrec, c->cd_ent}, c->short_docs, c->n_short,
+                                              c->long_docs, c->n_long}, own_light_segments(c));
 }
 
 // CountByDZ for the documents of one chunk whose assignments sit in a buffer
 static int launch_count_dz_chunk(saber_ctx *c, const Chunk &ch, int slot) {
     const ZView zv = z_view(c, ch, slot);
-    return launch_segmented_count(c, c->short_docs + ch.short0, ch.nshort, c->long_docs + ch.long0, ch.nlong, c->doc_ptr,
-                                  zv.z, zv.first, c->docrec, c->cd_ent);
+    return launch_segmented_count(c, SegLists{{nullptr, c->doc_ptr, zv.z, zv.first, c->docrec, c->cd_ent}, c->short_docs + ch.short0,
+                                              ch.nshort, c->long_docs + ch.long0, ch.nlong}, SegLists{});
 }
 
 // ---- host streaming ----
@@ -505,12 +512,9 @@ static int sync_all(saber_ctx *c) {
     return SABER_OK;
 }
 
-// CountByVZ + Preprocess + BuildTree for the light words (sparse rows of B); needs the base vector, i.e. runs
-// after launch_phi
+// Preprocess + BuildTree for the light words (sparse rows of B); needs the base vector, i.e. runs after launch_phi
 static int launch_light_words(saber_ctx *c) {
     if (c->V_light == 0) return SABER_OK;
-    SABER_TRY(launch_segmented_count(c, c->light_short, c->n_light_short, c->light_long, c->n_light_long,
-                                     c->light_tok_ptr, c->z_wm, 0, c->wrec, c->lw_ent));
     const size_t lds = (size_t)c->n3 * (sizeof(double) + sizeof(int));
     hipLaunchKernelGGL(light_tree_kernel, dim3((unsigned)c->V_light), dim3(64), lds, c->stream, c->light_words, c->wrec,
                        c->lw_ent, c->lw_phi, c->denom, c->phi + (size_t)c->V_dense * (size_t)c->Kpad,
@@ -520,18 +524,12 @@ static int launch_light_words(saber_ctx *c) {
     return SABER_OK;
 }
 
-// nnz(A), sum_d K_d L_d, sum_d K_d U_d and the non-zeros of the sparse rows of B (what the next E-step will
-// read) into four device counters
-static int launch_row_stats(saber_ctx *c, unsigned long long *out2) {
-    if (c->D == 0) return SABER_OK;
-    hipLaunchKernelGGL(row_stats_kernel, dim3(grid_for(c->D, 256, 1024)), dim3(256), 0, c->stream, c->docrec,
-                       c->doc_ptr, c->doc_words, c->D, out2);
+// dense-branch tokens (slots, or null), nnz(A), sum_d K_d L_d, sum_d K_d U_d and the non-zeros of the sparse rows of B
+// (what the next E-step will read) into five device counters
+static int launch_stats(saber_ctx *c, const unsigned long long *slots, unsigned long long *out) {
+    hipLaunchKernelGGL(stats_kernel, dim3(grid_for(std::max<int64_t>(c->D, c->V_light), 256, 256)), dim3(256), 0, c->stream, slots,
+                       slots ? kDenseSlots : 0, c->docrec, c->doc_ptr, c->doc_words, c->D, c->wrec, c->V_light, out);
     HIP_TRY(hipGetLastError());
-    if (c->V_light) {
-        hipLaunchKernelGGL(light_stats_kernel, dim3(grid_for(c->V_light, 256, 256)), dim3(256), 0, c->stream, c->wrec,
-                           c->V_light, out2 + 3);
-        HIP_TRY(hipGetLastError());
-    }
     return SABER_OK;
 }
 
@@ -547,11 +545,11 @@ static int allow_lds(const void *kernel, size_t lds) {   // more than the defaul
     return SABER_OK;
 }
 
-static int launch_topic_totals(saber_ctx *c) {
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(2 * (int64_t)c->K, 256)), dim3(256), 0, c->stream, (uint32_t *)c->ck, 0u, (size_t)c->K * 2);
-    HIP_TRY(hipGetLastError());
-    if (c->T == 0) return SABER_OK;
-    // Counting in LDS replaces one global atomic per token: 0.74 -> 0.04 ms at T = 15 M, K = 20,011, 0.13 -> 0.04 ms at
+// The first n_items slabs of the dense rows' segments into B (rows all zero on entry), and with `totals` the histogram of
+// all assignments into the accumulators of the topic totals.
+static int launch_count_slabs(saber_ctx *c, int64_t n_items, bool totals) {
+    // Counting in LDS, by ranges of topics, replaces one global atomic per token where K is too large for one histogram:
+    // totals 0.74 -> 0.04 ms and rows 0.39 -> 0.04 ms at T = 15 M, K = 20,011, 0.13 -> 0.04 and 0.24 -> 0.03 ms at
     // T = 1.5 M, K = 70,000.
     const int range = hist_range(c);
     // every workgroup ends with up to K atomics into the K totals: no more than about 500 shares of z (128 where these
@@ -560,18 +558,20 @@ static int launch_topic_totals(saber_ctx *c) {
     const int64_t least = std::max<int64_t>(16384, std::min<int64_t>(16 * (int64_t)c->K, 262144));
     const int64_t share = std::max<int64_t>(c->T / 512, std::min<int64_t>(c->T / 128, 65536));
     const int64_t per_block = std::min<int64_t>(1 << 20, std::max<int64_t>(least, ((share + 4095) / 4096) * 4096));
-    const dim3 grid((unsigned)((c->T + per_block - 1) / per_block), (unsigned)((c->K + range - 1) / range));
+    const int64_t n_tot = totals ? (c->T + per_block - 1) / per_block : 0;
+    if (n_tot + n_items == 0) return SABER_OK;
+    const dim3 grid((unsigned)(n_tot + n_items), (unsigned)((c->K + range - 1) / range));
     const size_t lds = (size_t)std::min(range, c->K) * 4;
     // a histogram of all assignments: their order does not matter, and with host streaming the word-major copy is
     // the one that is resident
     const void *zsrc = c->n_slots ? c->z_wm : c->z;
-    SABER_TRY(allow_lds(c->z16 ? (const void *)topic_totals_kernel<uint16_t> : (const void *)topic_totals_kernel<int32_t>, lds));
+    SABER_TRY(allow_lds(c->z16 ? (const void *)count_slabs_kernel<uint16_t> : (const void *)count_slabs_kernel<int32_t>, lds));
     if (c->z16)
-        hipLaunchKernelGGL((topic_totals_kernel<uint16_t>), grid, dim3(1024), lds, c->stream, (const uint16_t *)zsrc, c->T,
-                           per_block, c->ck, c->K, range);
+        hipLaunchKernelGGL((count_slabs_kernel<uint16_t>), grid, dim3(1024), lds, c->stream, (const uint16_t *)zsrc, c->T, per_block,
+                           (int)n_tot, c->ck_acc, c->vz_items, (const uint16_t *)c->z_wm, c->cwk, c->K, c->Kpad, range);
     else
-        hipLaunchKernelGGL((topic_totals_kernel<int32_t>), grid, dim3(1024), lds, c->stream, (const int32_t *)zsrc, c->T,
-                           per_block, c->ck, c->K, range);
+        hipLaunchKernelGGL((count_slabs_kernel<int32_t>), grid, dim3(1024), lds, c->stream, (const int32_t *)zsrc, c->T, per_block,
+                           (int)n_tot, c->ck_acc, c->vz_items, (const int32_t *)c->z_wm, c->cwk, c->K, c->Kpad, range);
     HIP_TRY(hipGetLastError());
     return SABER_OK;
 }
@@ -583,7 +583,8 @@ static size_t alias_lds_bytes(int K) { return ((size_t)K + 1) * sizeof(double) +
 static int phi_block_threads(const saber_ctx *c) { return c->Kpad <= 1024 ? 256 : c->Kpad <= 2048 ? 512 : 1024; }
 
 static int launch_phi(saber_ctx *c) {
-    hipLaunchKernelGGL(denominators_kernel, dim3(grid_for(c->Kpad, 256)), dim3(256), 0, c->stream, c->ck, c->denom, c->K, c->Kpad, c->vbeta);
+    hipLaunchKernelGGL(denominators_kernel, dim3(grid_for(c->Kpad, 256)), dim3(256), 0, c->stream, c->ck_acc, c->ck, c->denom, c->K,
+                       c->Kpad, c->vbeta);
     HIP_TRY(hipGetLastError());
     // kPhiSteps steps of four columns per thread at a time: up to 12,288 topics (48 KB of LDS: two workgroups of 1,024
     // threads per CU)
@@ -644,26 +645,6 @@ static int launch_estep_docmajor(saber_ctx *c, unsigned long long *n_dense) {
     return launch_fill_zwm(c);
 }
 
-// CountByVZ for the dense rows of B out of the word-major assignments; the rows must be all zero on entry
-// (the Bhat kernel leaves them so).
-static int launch_count_vz(saber_ctx *c, int64_t n_items) {
-    if (n_items == 0) return SABER_OK;
-    // (in LDS, by ranges of topics, at any K: 0.39 -> 0.04 ms at T = 15 M, K = 20,011 against one global atomic per token,
-    // 0.24 -> 0.03 ms at T = 1.5 M, K = 70,000)
-    const int range = hist_range(c);
-    const size_t lds = (size_t)std::min(range, c->K) * 4;
-    const dim3 grid((unsigned)n_items, (unsigned)((c->K + range - 1) / range));
-    SABER_TRY(allow_lds(c->z16 ? (const void *)count_vz_kernel<uint16_t> : (const void *)count_vz_kernel<int32_t>, lds));
-    if (c->z16)
-        hipLaunchKernelGGL((count_vz_kernel<uint16_t>), grid, dim3(1024), lds, c->stream, c->vz_items, (const uint16_t *)c->z_wm,
-                           c->cwk, c->K, c->Kpad, range);
-    else
-        hipLaunchKernelGGL((count_vz_kernel<int32_t>), grid, dim3(1024), lds, c->stream, c->vz_items, (const int32_t *)c->z_wm,
-                           c->cwk, c->K, c->Kpad, range);
-    HIP_TRY(hipGetLastError());
-    return SABER_OK;
-}
-
 // iteration 0: the Philox draw of Alg. 1's initialisation for the canonical tokens [t0, t1), stored from z[z_rel] on
 static int launch_init_z(saber_ctx *c, void *z, int64_t z_rel, int64_t t0, int64_t t1) {
     if (t1 <= t0) return SABER_OK;
@@ -702,16 +683,16 @@ static int full_mstep(saber_ctx *c, const int32_t *user_z = nullptr) {
             SABER_TRY(launch_fill_zwm_chunk(c, ch, s));
             SABER_TRY(stream_release(c, s));
         }
+        SABER_TRY(launch_segmented_count(c, SegLists{}, own_light_segments(c)));
     } else {
-        SABER_TRY(launch_count_dz(c));
+        if (!c->parent) SABER_TRY(launch_fill_zwm(c));
+        SABER_TRY(launch_counts(c));
     }
     if (c->parent) {   // held-out documents: A only, the model stays frozen
         HIP_TRY(hipStreamSynchronize(c->stream));
         return SABER_OK;
     }
-    if (!c->n_slots) SABER_TRY(launch_fill_zwm(c));
-    SABER_TRY(launch_count_vz(c, c->n_vz_long));
-    SABER_TRY(launch_topic_totals(c));
+    SABER_TRY(launch_count_slabs(c, c->n_vz_long, true));
     SABER_TRY(launch_phi(c));
     SABER_TRY(launch_light_words(c));
     SABER_TRY(sync_all(c));
@@ -722,7 +703,7 @@ static int full_mstep(saber_ctx *c, const int32_t *user_z = nullptr) {
 static int refresh_workload_stats(saber_ctx *c) {
     hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, c->stream, (uint32_t *)c->counters, 0u, (size_t)kCtr * 2);
     HIP_TRY(hipGetLastError());
-    SABER_TRY(launch_row_stats(c, c->counters + 1));
+    SABER_TRY(launch_stats(c, nullptr, c->counters));
     HIP_TRY(hipStreamSynchronize(c->stream));
     unsigned long long h[kCtr];
     HIP_TRY(hipMemcpy(h, c->counters, sizeof(h), hipMemcpyDeviceToHost));
@@ -839,7 +820,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     std::vector<VzItem> h_vz_items;
     std::vector<PhiRow> h_phi_rows;
     // phi_tree_kernel counts a row itself up to 32 tokens per thread of its workgroup; longer rows are cut into slabs for
-    // count_vz_kernel (phi group of T = 2.3 M, K = 777, 256 threads: 43 us with 8,192 tokens, 49 with 32,768; of T = 100 M,
+    // count_slabs_kernel (phi group of T = 2.3 M, K = 777, 256 threads: 43 us with 8,192 tokens, 49 with 32,768; of T = 100 M,
     // K = 10,000, 1,024 threads: 343 us counting none, 323 with 8,192, 303 with 32,768, 298 with 131,072)
     const int64_t own_tokens = 32 * phi_block_threads(c);
     {
@@ -985,7 +966,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         c->phi = par->phi; c->l3 = par->l3; c->l3_64 = par->l3_64; c->sumphi = par->sumphi;
         c->wrec = par->wrec; c->lw_ent = par->lw_ent; c->lw_phi = par->lw_phi;
     } else {
-    SABER_TRY(dev_alloc(c->hooks, &c->cwk, vk)); SABER_TRY(dev_alloc(c->hooks, &c->ck, (size_t)K)); SABER_TRY(dev_alloc(c->hooks, &c->denom, (size_t)c->Kpad));
+    SABER_TRY(dev_alloc(c->hooks, &c->cwk, vk)); SABER_TRY(dev_alloc(c->hooks, &c->ck, (size_t)K)); SABER_TRY(dev_alloc(c->hooks, &c->ck_acc, (size_t)K)); SABER_TRY(dev_alloc(c->hooks, &c->denom, (size_t)c->Kpad));
     SABER_TRY(dev_alloc(c->hooks, &c->phi, vk)); SABER_TRY(dev_alloc(c->hooks, &c->l3_64, ((size_t)V + 1) * (size_t)c->n3));
     SABER_TRY(dev_alloc(c->hooks, &c->row_word, h_row_word.size())); SABER_TRY(dev_alloc(c->hooks, &c->light_words, h_light_words.size()));
     SABER_TRY(dev_alloc(c->hooks, &c->light_short, h_light_short.size())); SABER_TRY(dev_alloc(c->hooks, &c->light_long, h_light_long.size()));
@@ -1042,6 +1023,8 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     if (!h_long.empty()) HIP_TRY(hipMemcpy(c->long_docs, h_long.data(), sizeof(int32_t) * h_long.size(), hipMemcpyHostToDevice));
     if (!par) {
         hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for((int64_t)vk, 256, 8192)), dim3(256), 0, c->stream, (uint32_t *)c->cwk, 0u, vk);
+        HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(2 * (int64_t)K, 256)), dim3(256), 0, c->stream, (uint32_t *)c->ck_acc, 0u, (size_t)K * 2);
         HIP_TRY(hipGetLastError());
     }
     c->stats.tokens = T; c->stats.tiles = c->total_tiles; c->stats.chunks = (int64_t)c->chunks.size();
@@ -1250,18 +1233,15 @@ extern "C" int saber_iterate(saber_ctx *c, int32_t n) {
             }
             if (prof) HIP_TRY(hipEventRecord(ev[EV_SAMPLE], c->stream));
             // M-step
-            if (!c->n_slots) SABER_TRY(launch_count_dz(c));
+            if (c->n_slots) SABER_TRY(launch_segmented_count(c, SegLists{}, own_light_segments(c)));
+            else SABER_TRY(launch_counts(c));
             if (prof) HIP_TRY(hipEventRecord(ev[EV_DZ], c->stream));
-            SABER_TRY(launch_topic_totals(c));
+            SABER_TRY(launch_count_slabs(c, c->n_vz_long, true));
             if (prof) HIP_TRY(hipEventRecord(ev[EV_CK], c->stream));
-            SABER_TRY(launch_count_vz(c, c->n_vz_long));
             SABER_TRY(launch_phi(c));
             SABER_TRY(launch_light_words(c));
             if (prof) HIP_TRY(hipEventRecord(ev[EV_PHI], c->stream));
-            hipLaunchKernelGGL(sum_slots_kernel, dim3(1), dim3(256), 0, c->stream, c->dense_slots + (size_t)kDenseSlots * b,
-                               kDenseSlots, c->counters + kCtr * b);
-            HIP_TRY(hipGetLastError());
-            SABER_TRY(launch_row_stats(c, c->counters + kCtr * b + 1));
+            SABER_TRY(launch_stats(c, c->dense_slots + (size_t)kDenseSlots * b, c->counters + kCtr * b));
         }
         SABER_TRY(sync_all(c));
         unsigned long long h[kMaxTimedIters * kCtr];
@@ -1340,7 +1320,7 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
         }
         if (cwk) {
             // dense rows: B is consumed (and cleared) by the Bhat kernel; rebuild it from z for export
-            SABER_TRY(launch_count_vz(c, c->n_vz_items));
+            SABER_TRY(launch_count_slabs(c, c->n_vz_items, false));
             HIP_TRY(hipStreamSynchronize(c->stream));
             const int64_t slab = 2048;   // rows per host staging buffer
             std::vector<int32_t> buf((size_t)slab * (size_t)c->Kpad);
@@ -1477,7 +1457,7 @@ static int foldin_iterate(saber_ctx *c, int32_t n) {
             p.n_dense = c->dense_slots;
             SABER_TRY(launch_estep<MODE_SAMPLE>(c, ch, p));
         }
-        SABER_TRY(launch_count_dz(c));
+        SABER_TRY(launch_counts(c));
     }
     HIP_TRY(hipStreamSynchronize(c->stream));
     return SABER_OK;

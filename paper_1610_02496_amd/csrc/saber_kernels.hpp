@@ -953,11 +953,13 @@ __global__ void prefix_export_kernel(const float *rows, const double *l3_64, con
 }
 
 // ---------------------------------------------------------------------------------------------
-// CountByVZ for the words with dense rows of B.  The assignments arrive word-major (z_wm), so a word's tokens are
-// one contiguous segment; it is cut into slabs and each workgroup histograms one slab in LDS and adds the
-// non-zero bins to the word's row: at most min(slab, K) global atomics per slab instead of one per token.
-// Workgroup (x, y) counts the topics [y range, (y + 1) range) of slab x.  Rows must be zero on entry (the Bhat kernel
-// clears them after reading).
+// Histograms of the assignments by slabs: the topic totals C_k = sum_v B_vk, computed as the histogram of z (same numbers,
+// 20x fewer bytes than column sums of B at K = 10^4), and CountByVZ for the long dense rows of B.  The assignments
+// arrive word-major (z_wm), so a word's tokens are one contiguous segment; it is cut into slabs and each workgroup
+// histograms one slab in LDS and adds the non-zero bins to the word's row: at most min(slab, K) global atomics per slab
+// instead of one per token.  The first n_tot workgroups of a grid row take the totals' shares of z, the others the
+// slabs; grid row y counts the topics [y range, (y + 1) range).  Totals and rows must be zero on entry
+// (denominators_kernel and the Bhat kernel clear them after reading).
 // ---------------------------------------------------------------------------------------------
 struct VzItem { int32_t row; int32_t count; int64_t begin; };   // slab: count tokens from z_wm[begin] on
 
@@ -993,21 +995,32 @@ __device__ __forceinline__ void block_for_each_z(const ZT *__restrict__ zs, int6
 }
 
 template <typename ZT>
-__global__ void __launch_bounds__(1024) count_vz_kernel(const VzItem *items, const ZT *z_wm, int32_t *cwk, int K,
-                                                        int Kpad, int range) {
-    extern __shared__ uint32_t vz_hist[];
-    const VzItem it = items[blockIdx.x];
-    const ZT *__restrict__ zs = z_wm + it.begin;
+__global__ void __launch_bounds__(1024) count_slabs_kernel(const ZT *z, int64_t T, int64_t per_block, int n_tot, unsigned long long *tot,
+                                                           const VzItem *items, const ZT *z_wm, int32_t *cwk, int K, int Kpad, int range) {
+    extern __shared__ uint32_t slab_hist[];
     const int k0 = (int)blockIdx.y * range, n = min(range, K - k0);
-    int32_t *row = cwk + (size_t)it.row * (size_t)Kpad + k0;
-    for (int k = threadIdx.x; k < n; k += blockDim.x) vz_hist[k] = 0u;
+    const bool totals = (int)blockIdx.x < n_tot;
+    const ZT *__restrict__ zs;
+    int64_t len;
+    int32_t *row = nullptr;
+    if (totals) {
+        zs = z + (int64_t)blockIdx.x * per_block;
+        len = min(per_block, T - (int64_t)blockIdx.x * per_block);
+    } else {
+        const VzItem it = items[(int)blockIdx.x - n_tot];
+        zs = z_wm + it.begin; len = it.count;
+        row = cwk + (size_t)it.row * (size_t)Kpad + k0;
+    }
+    for (int k = threadIdx.x; k < n; k += blockDim.x) slab_hist[k] = 0u;
     __syncthreads();
-    if (gridDim.y == 1) block_for_each_z(zs, (int64_t)it.count, [&](uint32_t k) { atomicAdd(&vz_hist[k], 1u); });
-    else block_for_each_z(zs, (int64_t)it.count, [&](uint32_t k) { if (k - (uint32_t)k0 < (uint32_t)n) atomicAdd(&vz_hist[k - (uint32_t)k0], 1u); });
+    if (gridDim.y == 1) block_for_each_z(zs, len, [&](uint32_t k) { atomicAdd(&slab_hist[k], 1u); });
+    else block_for_each_z(zs, len, [&](uint32_t k) { if (k - (uint32_t)k0 < (uint32_t)n) atomicAdd(&slab_hist[k - (uint32_t)k0], 1u); });
     __syncthreads();
     for (int k = threadIdx.x; k < n; k += blockDim.x) {
-        const uint32_t h = vz_hist[k];
-        if (h) atomicAdd(&row[k], (int)h);
+        const uint32_t h = slab_hist[k];
+        if (!h) continue;
+        if (totals) atomicAdd(&tot[k0 + k], (unsigned long long)h);
+        else atomicAdd(&row[k], (int)h);
     }
 }
 
@@ -1161,28 +1174,37 @@ __device__ __forceinline__ void count_segment_wave(const ZT *__restrict__ zs, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// CountByDZ (Alg. 1; the "segmented count" of Sec. 3.3), one workgroup per document.
+// CountByDZ (Alg. 1; the "segmented count" of Sec. 3.3), one workgroup per document (or light word: its row of B).
 // The document's assignments are contiguous (z is kept in document order, so the "shuffle" of Sec. 3.3
 // is the E-step's scattered store).  Instead of sorting, the workgroup marks the topics present in a
 // K-bit LDS bitmap; popcount prefix sums over the bitmap give every present topic its rank, i.e. its
 // slot in the ascending row; counts are accumulated per slot with LDS atomics.
 // Rows whose K_d exceeds lds_entries are accumulated directly in the global row.
 // ---------------------------------------------------------------------------------------------
-// z[0] is the assignment at position z_first of the segment numbering (a streaming buffer holds one chunk only).
+// One grouping of the assignments: list[i] numbers the segments to count, segment s is z[ptr[s]..ptr[s+1]) with
+// z[0] at position z_first of that numbering (a streaming buffer holds one chunk only); its row goes to ent from
+// rec[s].x * 32 on, its length to rec[s].y.
+struct SegGroup { const int32_t *list; const int64_t *ptr; const void *z; int64_t z_first; uint2 *rec; uint32_t *ent; };
+
+// The first na workgroups count the segments of group a, the others those of group b: documents and light words share a
+// launch, which spares a small corpus two of them.
 template <typename ZT>
-__global__ void __launch_bounds__(1024) count_dz_kernel(const int32_t *doc_list, const int64_t *doc_ptr,
-                                                        const ZT *z, int64_t z_first, uint2 *docrec, uint32_t *cd_ent, int K,
-                                                        uint32_t topic_bits, int nwords, int lds_entries) {
+__global__ void __launch_bounds__(1024) count_dz_kernel(SegGroup a, int64_t na, SegGroup b, uint32_t topic_bits, int nwords,
+                                                        int lds_entries) {
     extern __shared__ uint32_t lds_u32[];
     __shared__ uint32_t scan_scratch[20];
     uint32_t *bitmap = lds_u32;            // [nwords]
     uint32_t *wpre = lds_u32 + nwords;     // [nwords] exclusive popcount prefix
     uint32_t *ent_lds = wpre + nwords;     // [lds_entries]
-    const int d = doc_list[blockIdx.x];
-    const int64_t begin = doc_ptr[d];
-    const int len = (int)(doc_ptr[d + 1] - begin);
+    const bool first_group = (int64_t)blockIdx.x < na;
+    const SegGroup &g = first_group ? a : b;
+    uint2 *docrec = g.rec;
+    uint32_t *cd_ent = g.ent;
+    const int d = g.list[(int64_t)blockIdx.x - (first_group ? 0 : na)];
+    const int64_t begin = g.ptr[d];
+    const int len = (int)(g.ptr[d + 1] - begin);
     if (len == 0) { if (threadIdx.x == 0) docrec[d].y = 0u; return; }
-    const ZT *__restrict__ zd = z + (begin - z_first);
+    const ZT *__restrict__ zd = reinterpret_cast<const ZT *>(g.z) + (begin - g.z_first);
     if (blockDim.x == kWave && len <= 2 * kWave) {   // a short segment and a single wavefront: sorted in registers
         uint32_t *row = cd_ent + (size_t)docrec[d].x * 32u;
         if (len <= kWave) count_segment_wave<ZT, 1>(zd, len, docrec + d, row, topic_bits);
@@ -1234,26 +1256,6 @@ __global__ void __launch_bounds__(1024) count_dz_kernel(const int32_t *doc_list,
 }
 
 // ---------------------------------------------------------------------------------------------
-// Topic totals C_k = sum_v B_vk, computed as the histogram of z (same numbers, 20x fewer bytes than
-// column sums of B at K = 10^4): workgroup (x, y) counts the topics [y range, (y + 1) range) of its share of z in LDS
-// and adds the non-zero bins to the totals.
-// ---------------------------------------------------------------------------------------------
-template <typename ZT>
-__global__ void __launch_bounds__(1024) topic_totals_kernel(const ZT *z, int64_t T, int64_t per_block, unsigned long long *ck, int K,
-                                                            int range) {
-    extern __shared__ uint32_t hist[];
-    const int64_t b = (int64_t)blockIdx.x * per_block;
-    int64_t e = b + per_block; if (e > T) e = T;
-    const int k0 = (int)blockIdx.y * range, n = min(range, K - k0);
-    for (int k = threadIdx.x; k < n; k += blockDim.x) hist[k] = 0u;
-    __syncthreads();
-    if (gridDim.y == 1) block_for_each_z(z + b, e - b, [&](uint32_t k) { atomicAdd(&hist[k], 1u); });
-    else block_for_each_z(z + b, e - b, [&](uint32_t k) { if (k - (uint32_t)k0 < (uint32_t)n) atomicAdd(&hist[k - (uint32_t)k0], 1u); });
-    __syncthreads();
-    for (int k = threadIdx.x; k < n; k += blockDim.x) { const uint32_t h = hist[k]; if (h) atomicAdd(&ck[k0 + k], (unsigned long long)h); }
-}
-
-// ---------------------------------------------------------------------------------------------
 // Preprocess + BuildTree (Alg. 1; Eq. 2; Sec. 3.2.4), one workgroup of 256 threads per word row.
 //   Bhat_vk  = (float(B_vk) + beta) / denom_k,  denom_k = float(C_k) + float(V) * beta   -- single-rounded fp32 ops
 //   l3_64[i] = running sum of Bhat_v through topic (i+1)*64 - 1, accumulated in binary64
@@ -1262,15 +1264,20 @@ __global__ void __launch_bounds__(1024) topic_totals_kernel(const ZT *z, int64_t
 // The bottom level (one prefix sum per topic) is not stored; the sampler rebuilds the 64 entries it needs.
 // ---------------------------------------------------------------------------------------------
 // Denominators of Eq. 2, one per topic: float(C_k) + float(V) * beta (the conversion rounds to nearest even).
-// Pad columns get an infinite one, so that their Bhat comes out as zero.
-__global__ void denominators_kernel(const unsigned long long *ck, float *denom, int K, int Kpad, float vbeta) {
+// Pad columns get an infinite one, so that their Bhat comes out as zero.  The totals move from the accumulators, which are
+// cleared for the next M-step, to their place of rest.
+__global__ void denominators_kernel(unsigned long long *acc, unsigned long long *ck, float *denom, int K, int Kpad, float vbeta) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < Kpad) denom[k] = k < K ? (float)ck[k] + vbeta : __builtin_inff();
+    if (k < K) {
+        const unsigned long long c = acc[k];
+        acc[k] = 0ull; ck[k] = c;
+        denom[k] = (float)c + vbeta;
+    } else if (k < Kpad) denom[k] = __builtin_inff();
 }
 
 // One dense row: its word (the tree levels are indexed by word) and its segment of the word-major assignments.  count >= 0:
 // the workgroup histograms the segment in LDS, `range` topics at a time, and the counts never reach memory; count < 0: the
-// word has too many tokens for one workgroup, its row of B was counted by count_vz_kernel and is cleared here.
+// word has too many tokens for one workgroup, its row of B was counted by count_slabs_kernel and is cleared here.
 // The last row has no tokens: it yields the base vector (Bhat of a zero count) and its running sums for the light words.
 //
 // Bound by the store of Bhat, 4 Kpad bytes per row, and by the row's chain of steps.  Counting through memory (atomics into
@@ -1455,47 +1462,35 @@ __global__ void light_rows_export_kernel(const int32_t *light_ids, int m, const 
     }
 }
 
-// Statistics for the bandwidth model (exact in binary64 below 2^53): nnz(A), sum_d K_d * L_d (row entries
-// touched if every token read its row) and sum_d K_d * U_d, U_d = distinct words of document d inside its
-// chunk (row entries the sampler has to fetch: consecutive tokens of one (word, document) pair share the row).
-__global__ void row_stats_kernel(const uint2 *docrec, const int64_t *doc_ptr, const uint32_t *doc_words, int64_t D,
-                                 unsigned long long *out3) {
-    double nnz = 0.0, reads = 0.0, fetch = 0.0;
-    for (int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; d < D; d += (int64_t)gridDim.x * blockDim.x) {
+// Statistics for the bandwidth model (exact in binary64 below 2^53), added to out[0..4]: the dense-branch counter slots
+// (n_slots of them, by workgroup 0); nnz(A); sum_d K_d * L_d (row entries touched if every token read its row);
+// sum_d K_d * U_d, U_d = distinct words of document d inside its chunk (row entries the sampler has to fetch: consecutive
+// tokens of one (word, document) pair share the row); non-zeros of the sparse rows of B (what the next E-step stages for
+// the light words).  A workgroup ends with one atomic per sum: a few hundred of them, since they are all to the same
+// addresses (1,024 took 15 us).
+__global__ void __launch_bounds__(256) stats_kernel(const unsigned long long *slots, int n_slots, const uint2 *docrec,
+                                                    const int64_t *doc_ptr, const uint32_t *doc_words, int64_t D,
+                                                    const uint2 *wrec, int n_light, unsigned long long *out) {
+    double sums[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_slots; i += blockDim.x) sums[0] += (double)slots[i];
+    for (int64_t d = first; d < D; d += stride) {
         const double kd = (double)docrec[d].y;
-        nnz += kd; reads += kd * (double)(doc_ptr[d + 1] - doc_ptr[d]); fetch += kd * (double)doc_words[d];
+        sums[1] += kd; sums[2] += kd * (double)(doc_ptr[d + 1] - doc_ptr[d]); sums[3] += kd * (double)doc_words[d];
     }
-    nnz = readlane_f64(wave_incl_scan(nnz), 63); reads = readlane_f64(wave_incl_scan(reads), 63);
-    fetch = readlane_f64(wave_incl_scan(fetch), 63);
-    __shared__ double part[3][16];
-    const int wave = threadIdx.x / kWave, nwaves = blockDim.x / kWave;
-    if (lane_id() == 0) { part[0][wave] = nnz; part[1][wave] = reads; part[2][wave] = fetch; }
-    __syncthreads();
-    if (threadIdx.x < 3) {
-        double sum = 0.0;
-        for (int w = 0; w < nwaves; w++) sum += part[threadIdx.x][w];
-        atomicAdd(&out3[threadIdx.x], (unsigned long long)sum);
+    for (int64_t i = first; i < n_light; i += stride) sums[4] += (double)wrec[i].y;
+    __shared__ double part[5][4];
+#pragma unroll
+    for (int q = 0; q < 5; q++) {
+        const double w = readlane_f64(wave_incl_scan(sums[q]), 63);
+        if (lane_id() == 0) part[q][threadIdx.x / kWave] = w;
     }
-}
-
-// Sum of the dense-branch counter slots, added to *out.
-__global__ void sum_slots_kernel(const unsigned long long *slots, int n, unsigned long long *out) {
-    unsigned long long v = 0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) v += slots[i];
-    __shared__ unsigned long long tot;
-    if (threadIdx.x == 0) tot = 0ull;
     __syncthreads();
-    if (v) atomicAdd(&tot, v);
-    __syncthreads();
-    if (threadIdx.x == 0 && tot) atomicAdd(out, tot);
-}
-
-// Non-zeros of the sparse rows of B (what the next E-step stages for the light words), added to *out.
-__global__ void light_stats_kernel(const uint2 *wrec, int n, unsigned long long *out) {
-    uint32_t nnz = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) nnz += wrec[i].y;
-    nnz = wave_sum(nnz);
-    if (lane_id() == 0 && nnz) atomicAdd(out, (unsigned long long)nnz);
+    if (threadIdx.x < 5) {
+        const double sum = ((part[threadIdx.x][0] + part[threadIdx.x][1]) + part[threadIdx.x][2]) + part[threadIdx.x][3];
+        if (sum > 0.0) atomicAdd(&out[threadIdx.x], (unsigned long long)sum);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
