@@ -216,9 +216,9 @@ class Saber:
         if want_cd:
             nnz = self.counts_nnz()
             cd_ptr = np.zeros(self.D + 1, dtype=np.int64)
-            topic = np.zeros(nnz, dtype=np.int32); count = np.zeros(nnz, dtype=np.int32)
+            topic = np.empty(nnz, dtype=np.int32); count = np.empty(nnz, dtype=np.int32)
         if want_cwk:
-            cwk = np.zeros((self.V, self.K), dtype=np.int32)
+            cwk = np.empty((self.V, self.K), dtype=np.int32)
         if want_ck:
             ck = np.zeros(self.K, dtype=np.int64)
         _check(load_library().saber_counts(self._h, _ptr(cd_ptr), _ptr(topic), _ptr(count), _ptr(cwk), _ptr(ck)))
@@ -277,7 +277,7 @@ class Saber:
         return prob, alias
 
     def get_z(self):
-        z = np.zeros(self.T, dtype=np.int32)
+        z = np.empty(self.T, dtype=np.int32)
         _check(load_library().saber_get_z(self._h, _ptr(z)))
         return z
 

@@ -7,12 +7,14 @@
 #include "../../include/saber_measure.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include <rocprim/rocprim.hpp>
@@ -106,6 +108,8 @@ struct Chunk {
 };
 
 constexpr int kMaxSlots = 8;
+constexpr int kPullSlots = 12, kPullThreads = 8;      // see pull()
+constexpr int64_t kPullPiece = 1 << 20;               // bytes
 
 constexpr int kMaxTimedIters = 32;
 constexpr int kCtr = 8;   // device counters per timed iteration
@@ -176,6 +180,11 @@ struct saber_ctx {
     hipEvent_t ev[kMaxTimedIters * EV_PER_ITER] = {};
     bool have_events = false;
     saber_stats stats{};
+    // device -> host results: pinned staging and its events, made by the first call that needs them
+    char *pull_buf = nullptr;
+    size_t pull_bytes = 0;
+    bool pull_pinned = false;
+    hipEvent_t pull_ev[kPullSlots] = {};
     std::vector<int64_t> doc_len;     // host copy of the document lengths (statistics only)
     // Host streaming (Sec. 3.1.2), n_slots > 0: tok_t lives in pinned host memory; a chunk's part of it is copied
     // into one of n_slots device buffers for the chunk's pass (4 bytes per token and iteration over the host link).
@@ -250,6 +259,8 @@ extern "C" void saber_free(saber_ctx *c) {
     release(c->word_ids_d); release(c->word_row_d); release(c->sort_keys); release(c->sort_keys_out);
     release(c->sort_rank); release(c->sort_tmp); release(c->alias_table);
     if (c->h_tok_t) (void)hipHostFree(c->h_tok_t);
+    if (c->pull_buf) { if (c->pull_pinned) (void)hipHostFree(c->pull_buf); else free(c->pull_buf); }
+    for (auto &e : c->pull_ev) if (e) (void)hipEventDestroy(e);
     if (c->stream && c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }
@@ -1276,6 +1287,102 @@ extern "C" int saber_iterate(saber_ctx *c, int32_t n) {
 // ------------------------------------------------------------------------------------------------
 // outputs
 // ------------------------------------------------------------------------------------------------
+// Results on their way to the caller's memory: piece i, the elements [cuts[i], cuts[i + 1]) of the device array, is copied
+// into pinned staging on the context's stream and handed to consume(i, host pointer), which puts it where it belongs; up to
+// kPullThreads threads consume while the next pieces are in flight.  A caller's fresh pages cost far more than the link:
+// into ordinary memory a copy of 100 M assignments as int32 took 44 ms, as 16 bits through this path 8.
+// The threads end before the call returns; consume must not throw.  No piece may exceed kPullPiece bytes.
+template <typename F>
+static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<int64_t> &cuts, F consume) {
+    const int64_t np = (int64_t)cuts.size() - 1;
+    if (np <= 0) return SABER_OK;
+    size_t largest = 1;
+    for (int64_t i = 0; i < np; i++) largest = std::max(largest, (size_t)(cuts[(size_t)i + 1] - cuts[(size_t)i]) * elem);
+    largest = (largest + 255) & ~(size_t)255;
+    const int slots = (int)std::min<int64_t>(np, kPullSlots);
+    if (c->pull_bytes < largest * (size_t)slots) {
+        if (c->pull_buf) { if (c->pull_pinned) (void)hipHostFree(c->pull_buf); else free(c->pull_buf); }
+        c->pull_buf = nullptr; c->pull_bytes = 0; c->pull_pinned = true;
+        if (hipHostMalloc((void **)&c->pull_buf, largest * (size_t)slots, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            c->pull_pinned = false;
+            c->pull_buf = (char *)malloc(largest * (size_t)slots);
+            if (!c->pull_buf) return fail(SABER_ENOMEM, "out of host memory");
+        }
+        c->pull_bytes = largest * (size_t)slots;
+    }
+    for (int i = 0; i < slots; i++)
+        if (!c->pull_ev[i]) HIP_TRY(hipEventCreateWithFlags(&c->pull_ev[i], hipEventDisableTiming));
+    auto request = [&](int64_t k) {
+        const size_t bytes = (size_t)(cuts[(size_t)k + 1] - cuts[(size_t)k]) * elem;
+        hipError_t e = hipSuccess;
+        if (bytes) e = hipMemcpyAsync(c->pull_buf + (size_t)(k % slots) * largest, (const char *)dev + (size_t)cuts[(size_t)k] * elem,
+                                      bytes, hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess) e = hipEventRecord(c->pull_ev[k % slots], c->stream);
+        return e;
+    };
+    std::vector<std::atomic<char>> done((size_t)np);
+    for (auto &d : done) d.store(0, std::memory_order_relaxed);
+    std::atomic<int64_t> issued{0}, next{0};
+    std::atomic<int> error{(int)hipSuccess};
+    auto work = [&]() {
+        (void)hipSetDevice(c->device);
+        for (;;) {
+            const int64_t k = next.fetch_add(1);
+            if (k >= np) return;
+            while (issued.load(std::memory_order_acquire) <= k) {
+                if (error.load() != (int)hipSuccess) return;
+                std::this_thread::yield();
+            }
+            const hipError_t e = hipEventSynchronize(c->pull_ev[k % slots]);
+            if (e != hipSuccess) { error.store((int)e); return; }
+            consume(k, (const void *)(c->pull_buf + (size_t)(k % slots) * largest));
+            done[(size_t)k].store(1, std::memory_order_release);
+        }
+    };
+    std::vector<std::thread> threads;
+    if (np > 2) {
+        try {
+            threads.reserve(kPullThreads);
+            for (int64_t i = 0; i < std::min<int64_t>(np, kPullThreads); i++) threads.emplace_back(work);
+        } catch (...) {}   // with fewer threads, or none, it only takes longer
+    }
+    hipError_t e = hipSuccess;
+    for (int64_t k = 0; k < np && e == hipSuccess; k++) {
+        if (threads.empty()) {
+            e = request(k);
+            if (e == hipSuccess) e = hipEventSynchronize(c->pull_ev[k % slots]);
+            if (e == hipSuccess) consume(k, (const void *)(c->pull_buf + (size_t)(k % slots) * largest));
+            continue;
+        }
+        while (k >= slots && !done[(size_t)(k - slots)].load(std::memory_order_acquire) && error.load() == (int)hipSuccess)
+            std::this_thread::yield();
+        if (error.load() != (int)hipSuccess) break;
+        e = request(k);
+        if (e == hipSuccess) issued.store(k + 1, std::memory_order_release);
+    }
+    if (e != hipSuccess) error.store((int)e);
+    for (auto &t : threads) t.join();
+    e = (hipError_t)error.load();
+    if (e != hipSuccess) return fail(SABER_EDEVICE, "copying results from the device failed: %s", hipGetErrorString(e));
+    return SABER_OK;
+}
+
+// n assignments from the device array z (of the context's assignment type) to the caller's int32
+static int pull_z(saber_ctx *c, const void *z, int64_t n, int32_t *out) {
+    const int64_t elem = c->z16 ? 2 : 4;
+    // (pieces of a sixteenth of the array, 128 K to 512 K assignments: a small one is shared by the threads as well)
+    const int64_t piece = std::min<int64_t>(kPullPiece / elem, std::max<int64_t>(131072, (n / 16 + 4095) & ~4095ll));
+    std::vector<int64_t> cuts(1, 0);
+    while (cuts.back() < n) cuts.push_back(std::min<int64_t>(n, cuts.back() + piece));
+    return pull(c, z, (size_t)elem, cuts, [&](int64_t i, const void *host) {
+        const int64_t a = cuts[(size_t)i], m = cuts[(size_t)i + 1] - a;
+        if (elem == 4) { memcpy(out + a, host, (size_t)m * 4); return; }
+        const uint16_t *src = (const uint16_t *)host;
+        for (int64_t j = 0; j < m; j++) out[a + j] = (int32_t)src[j];
+    });
+}
+
 extern "C" int saber_counts_nnz(saber_ctx *c, int64_t *nnz) {
     if (!c || !nnz) return fail(SABER_EINVAL, "saber_counts_nnz: null argument");
     try {
@@ -1298,61 +1405,70 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
             cd_row_ptr[0] = 0;
             for (int64_t d = 0; d < c->D; d++) cd_row_ptr[d + 1] = cd_row_ptr[d] + rec[(size_t)d].y;
             if (cd_topic || cd_count) {
-                // unpack the device rows slab by slab (format conversion only)
-                const int64_t slab_docs = 65536;
-                std::vector<uint32_t> buf;
-                for (int64_t d0 = 0; d0 < c->D; d0 += slab_docs) {
-                    const int64_t d1 = std::min(c->D, d0 + slab_docs);
-                    const int64_t e0 = (int64_t)rec[(size_t)d0].x * 32;
-                    const int64_t e1 = d1 < c->D ? (int64_t)rec[(size_t)d1].x * 32 : c->cd_cap;
-                    buf.resize((size_t)std::max<int64_t>(e1 - e0, 1));
-                    if (e1 > e0) HIP_TRY(hipMemcpy(buf.data(), c->cd_ent + e0, sizeof(uint32_t) * (size_t)(e1 - e0), hipMemcpyDeviceToHost));
-                    for (int64_t d = d0; d < d1; d++) {
-                        const uint32_t *row = buf.data() + ((int64_t)rec[(size_t)d].x * 32 - e0);
+                // unpack the device rows by pieces of whole documents (format conversion only)
+                std::vector<int64_t> cuts(1, 0), piece_doc(1, 0);
+                for (int64_t d = 0; d < c->D; d++) {
+                    const int64_t end = d + 1 < c->D ? (int64_t)rec[(size_t)d + 1].x * 32 : c->cd_cap;
+                    if ((end - cuts.back()) * 4 > kPullPiece) { cuts.push_back((int64_t)rec[(size_t)d].x * 32); piece_doc.push_back(d); }
+                }
+                cuts.push_back(c->cd_cap); piece_doc.push_back(c->D);
+                SABER_TRY(pull(c, c->cd_ent, sizeof(uint32_t), cuts, [&](int64_t i, const void *host) {
+                    for (int64_t d = piece_doc[(size_t)i]; d < piece_doc[(size_t)i + 1]; d++) {
+                        const uint32_t *row = (const uint32_t *)host + ((int64_t)rec[(size_t)d].x * 32 - cuts[(size_t)i]);
                         int64_t o = cd_row_ptr[d];
                         for (uint32_t j = 0; j < rec[(size_t)d].y; j++, o++) {
                             if (cd_topic) cd_topic[o] = (int32_t)(row[j] & c->topic_mask);
                             if (cd_count) cd_count[o] = (int32_t)(row[j] >> c->topic_bits);
                         }
                     }
-                }
+                }));
             }
         }
         if (cwk) {
             // dense rows: B is consumed (and cleared) by the Bhat kernel; rebuild it from z for export
-            SABER_TRY(launch_count_slabs(c, c->n_vz_items, false));
-            HIP_TRY(hipStreamSynchronize(c->stream));
-            const int64_t slab = 2048;   // rows per host staging buffer
-            std::vector<int32_t> buf((size_t)slab * (size_t)c->Kpad);
-            std::vector<int32_t> row_word((size_t)c->V_dense + 1);
-            HIP_TRY(hipMemcpy(row_word.data(), c->row_word, sizeof(int32_t) * row_word.size(), hipMemcpyDeviceToHost));
-            for (int64_t r0 = 0; r0 < c->V_dense; r0 += slab) {
-                const int64_t r1 = std::min<int64_t>(c->V_dense, r0 + slab);
-                HIP_TRY(hipMemcpy(buf.data(), c->cwk + (size_t)r0 * (size_t)c->Kpad,
-                                  sizeof(int32_t) * (size_t)(r1 - r0) * (size_t)c->Kpad, hipMemcpyDeviceToHost));
-                for (int64_t r = r0; r < r1; r++)
-                    memcpy(cwk + (size_t)row_word[(size_t)r] * (size_t)c->K, buf.data() + (size_t)(r - r0) * (size_t)c->Kpad,
-                           sizeof(int32_t) * (size_t)c->K);
+            if (c->V_dense) {
+                SABER_TRY(launch_count_slabs(c, c->n_vz_items, false));
+                std::vector<int32_t> row_word((size_t)c->V_dense + 1);
+                HIP_TRY(hipMemcpy(row_word.data(), c->row_word, sizeof(int32_t) * row_word.size(), hipMemcpyDeviceToHost));
+                const int64_t rows = std::max<int64_t>(1, kPullPiece / ((int64_t)c->Kpad * 4));   // (Kpad * 4 is at most 1 MB)
+                std::vector<int64_t> cuts(1, 0);
+                while (cuts.back() < (int64_t)c->V_dense * c->Kpad)
+                    cuts.push_back(std::min<int64_t>((int64_t)c->V_dense * c->Kpad, cuts.back() + rows * c->Kpad));
+                SABER_TRY(pull(c, c->cwk, sizeof(int32_t), cuts, [&](int64_t i, const void *host) {
+                    for (int64_t e = cuts[(size_t)i]; e < cuts[(size_t)i + 1]; e += c->Kpad)
+                        memcpy(cwk + (size_t)row_word[(size_t)(e / c->Kpad)] * (size_t)c->K, (const int32_t *)host + (e - cuts[(size_t)i]),
+                               sizeof(int32_t) * (size_t)c->K);
+                }));
+                const size_t vk = (size_t)c->V_dense * (size_t)c->Kpad;
+                hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for((int64_t)vk, 256, 8192)), dim3(256), 0, c->stream,
+                                   (uint32_t *)c->cwk, 0u, vk);
+                HIP_TRY(hipGetLastError());
+                HIP_TRY(hipStreamSynchronize(c->stream));
             }
-            const size_t vk = (size_t)c->V_dense * (size_t)c->Kpad;
-            hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for((int64_t)vk, 256, 8192)), dim3(256), 0, c->stream,
-                               (uint32_t *)c->cwk, 0u, vk);
-            HIP_TRY(hipGetLastError());
-            HIP_TRY(hipStreamSynchronize(c->stream));
-            // light words: unpack the sparse rows (format conversion only)
+            // light words: unpack the sparse rows by pieces of whole words (format conversion only)
             if (c->V_light) {
                 std::vector<uint2> wrec((size_t)c->V_light);
                 std::vector<int32_t> lwords((size_t)c->V_light);
                 HIP_TRY(hipMemcpy(wrec.data(), c->wrec, sizeof(uint2) * wrec.size(), hipMemcpyDeviceToHost));
                 HIP_TRY(hipMemcpy(lwords.data(), c->light_words, sizeof(int32_t) * lwords.size(), hipMemcpyDeviceToHost));
-                std::vector<uint32_t> ent((size_t)std::max<int64_t>(c->lw_cap, 1));
-                if (c->lw_cap) HIP_TRY(hipMemcpy(ent.data(), c->lw_ent, sizeof(uint32_t) * (size_t)c->lw_cap, hipMemcpyDeviceToHost));
-                for (int32_t li = 0; li < c->V_light; li++) {
-                    int32_t *row = cwk + (size_t)lwords[(size_t)li] * (size_t)c->K;
-                    memset(row, 0, sizeof(int32_t) * (size_t)c->K);
-                    const uint32_t *e = ent.data() + (size_t)wrec[(size_t)li].x * 32u;
-                    for (uint32_t j = 0; j < wrec[(size_t)li].y; j++) row[e[j] & c->topic_mask] = (int32_t)(e[j] >> c->topic_bits);
+                std::vector<int64_t> cuts(1, 0), piece_word(1, 0);
+                // (a word's row of K counts has to be cleared as well: at most 1 MB of those per piece too)
+                const int64_t most = std::max<int64_t>(1, kPullPiece / (4 * (int64_t)c->K));
+                for (int64_t li = 0; li < c->V_light; li++) {
+                    const int64_t end = li + 1 < c->V_light ? (int64_t)wrec[(size_t)li + 1].x * 32 : c->lw_cap;
+                    if ((end - cuts.back()) * 4 > kPullPiece || li - piece_word.back() >= most) {
+                        cuts.push_back((int64_t)wrec[(size_t)li].x * 32); piece_word.push_back(li);
+                    }
                 }
+                cuts.push_back(c->lw_cap); piece_word.push_back(c->V_light);
+                SABER_TRY(pull(c, c->lw_ent, sizeof(uint32_t), cuts, [&](int64_t i, const void *host) {
+                    for (int64_t li = piece_word[(size_t)i]; li < piece_word[(size_t)i + 1]; li++) {
+                        int32_t *row = cwk + (size_t)lwords[(size_t)li] * (size_t)c->K;
+                        memset(row, 0, sizeof(int32_t) * (size_t)c->K);
+                        const uint32_t *e = (const uint32_t *)host + ((int64_t)wrec[(size_t)li].x * 32 - cuts[(size_t)i]);
+                        for (uint32_t j = 0; j < wrec[(size_t)li].y; j++) row[e[j] & c->topic_mask] = (int32_t)(e[j] >> c->topic_bits);
+                    }
+                }));
             }
         }
         if (ck) {
@@ -1516,9 +1632,8 @@ extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const 
 extern "C" int saber_get_z(saber_ctx *c, int32_t *z) {
     if (!c || !z) return fail(SABER_EINVAL, "saber_get_z: null argument");
     if (c->T == 0) return SABER_OK;
-    if (c->n_slots) {   // document order is re-created chunk by chunk from the word-major copy
-        try {
-            std::vector<uint16_t> stage;
+    try {
+        if (c->n_slots) {   // document order is re-created chunk by chunk from the word-major copy
             for (const Chunk &ch : c->chunks) {
                 if (ch.ntok == 0) continue;
                 int s;
@@ -1530,30 +1645,13 @@ extern "C" int saber_get_z(saber_ctx *c, int32_t *z) {
                     hipLaunchKernelGGL((scatter_zwm_kernel<int32_t>), dim3((unsigned)ch.ntiles), dim3(256), 0, c->stream,
                                        c->tiles + ch.tile0, c->slot_tok_t[s], (const int32_t *)c->z_wm, (int32_t *)c->slot_z[s]);
                 HIP_TRY(hipGetLastError());
+                SABER_TRY(pull_z(c, c->slot_z[s], ch.ntok, z + ch.t0));
                 SABER_TRY(stream_release(c, s));
-                HIP_TRY(hipStreamSynchronize(c->stream));
-                if (c->z16) {
-                    stage.resize((size_t)ch.ntok);
-                    HIP_TRY(hipMemcpy(stage.data(), c->slot_z[s], (size_t)ch.ntok * 2, hipMemcpyDeviceToHost));
-                    for (int64_t i = 0; i < ch.ntok; i++) z[ch.t0 + i] = (int32_t)stage[(size_t)i];
-                } else {
-                    HIP_TRY(hipMemcpy(z + ch.t0, c->slot_z[s], (size_t)ch.ntok * 4, hipMemcpyDeviceToHost));
-                }
             }
-        } catch (const std::bad_alloc &) { return fail(SABER_ENOMEM, "saber_get_z: out of host memory"); }
-        return SABER_OK;
-    }
-    if (!c->z16) { HIP_TRY(hipMemcpy(z, c->z, sizeof(int32_t) * (size_t)c->T, hipMemcpyDeviceToHost)); return SABER_OK; }
-    int32_t *tmp = nullptr;
-    SABER_TRY(dev_alloc(c->hooks, &tmp, (size_t)c->T));
-    hipLaunchKernelGGL((z_to_i32_kernel<uint16_t>), dim3(grid_for(c->T, 256, 8192)), dim3(256), 0, c->stream,
-                       (const uint16_t *)c->z, tmp, c->T);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e == hipSuccess) e = hipMemcpy(z, tmp, sizeof(int32_t) * (size_t)c->T, hipMemcpyDeviceToHost);
-    dev_free(c->hooks, tmp);
-    if (e != hipSuccess) return fail(SABER_EDEVICE, "saber_get_z: %s", hipGetErrorString(e));
-    return SABER_OK;
+            return SABER_OK;
+        }
+        return pull_z(c, c->z, c->T, z);
+    } catch (const std::bad_alloc &) { return fail(SABER_ENOMEM, "saber_get_z: out of host memory"); }
 }
 
 extern "C" int saber_set_z(saber_ctx *c, const int32_t *z, uint32_t iter) {

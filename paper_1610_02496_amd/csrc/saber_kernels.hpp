@@ -154,11 +154,6 @@ __global__ void z_from_i32_kernel(ZT *z, const int32_t *src, int64_t T) {
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
     for (; t < T; t += stride) z[t] = (ZT)src[t];
 }
-template <typename ZT>
-__global__ void z_to_i32_kernel(const ZT *z, int32_t *dst, int64_t T) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-    for (; t < T; t += stride) dst[t] = (int32_t)z[t];
-}
 
 // Normalisers of Alg. 2 for the requested tokens that lie in the chunk [t0, t0 + n): S and Q as the sampling
 // kernel's inspection mode left them (indexed by the token's position in the chunk) and the probability of the

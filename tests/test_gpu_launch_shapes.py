@@ -84,3 +84,34 @@ def test_dense_rows_counted_where_they_are_normalised(K):
         assert np.array_equal(g.counts(want_cd=False)[3], o.cwk)
     g.close()
     o.close()
+
+
+@pytest.mark.parametrize("T,K,opts", [(1, 5, {}), (131072, 50, {}), (131073, 300, {}), (2_500_000, 40, {}), (300_001, 70000, {}),
+                                      (1_000_003, 2000, {"light_word_tokens": 1 << 16}), (700_000, 9000, {"light_word_tokens": -1}),
+                                      (900_000, 100, {"stream_workers": 3, "n_chunks": 4})])
+def test_results_that_leave_in_pieces(T, K, opts):
+    """Assignments and counts go to the caller by pieces, several at a time: one piece, two, many, more than the staging
+    holds; documents longer than the others' average piece; repeated calls on one context."""
+    rng = np.random.default_rng(T)
+    V = 37
+    most = (1 << (32 - max(1, (K - 1).bit_length()))) - 1        # tokens of the longest document that K leaves count bits for
+    lens = np.r_[7, min(T // 3, most), rng.integers(0, 900, 2 + T // 440)]
+    doc_ptr = np.r_[0, np.minimum(np.cumsum(lens), T)].astype(np.int64)
+    T = int(doc_ptr[-1])
+    words = np.minimum(rng.geometric(0.2, T), V).astype(np.int32) - 1
+    z = np.minimum(rng.geometric(20.0 / K, T) % K, K - 1).astype(np.int32) if K > 20 else rng.integers(0, K, T).astype(np.int32)
+    g = saber().Saber(doc_ptr, words, V, K, 0.1, 0.01, 3, **opts)
+    z0 = g.get_z()
+    g.set_z(z, 2)
+    for _ in range(2):
+        assert np.array_equal(g.get_z(), z)
+        cd_ptr, topic, count, cwk, ck = g.counts()
+        doc = np.repeat(np.arange(doc_ptr.size - 1), np.diff(doc_ptr))
+        key, n = np.unique(doc * K + z, return_counts=True)
+        assert np.array_equal(cd_ptr, np.searchsorted(key, np.arange(doc_ptr.size) * K))
+        assert np.array_equal(topic, key % K) and np.array_equal(count, n)
+        assert np.array_equal(cwk.reshape(-1), np.bincount(words.astype(np.int64) * K + z, minlength=V * K))
+        assert np.array_equal(ck, np.bincount(z, minlength=K))
+    g.set_z(z0, 0)
+    assert np.array_equal(g.get_z(), z0)
+    g.close()
