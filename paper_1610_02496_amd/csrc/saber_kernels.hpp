@@ -529,16 +529,20 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     }
     uint2 rec = make_uint2(p.row_unit0, 0u);
     if (d >= 0) rec = p.docrec[d];
-    __syncthreads();
     if (LIGHT) {
-        // the staged row is the base vector so far; overwrite the topics this word has counts for
+        // the staged row is the base vector so far; overwrite the topics this word has counts for.  The word's first
+        // entries, one per thread, are requested before the barrier as well.
         const uint2 wr = p.wrec[tile.row];
         const uint32_t *__restrict__ ent = p.lw_ent + (size_t)wr.x * 32u;
         const float *__restrict__ val = p.lw_phi + (size_t)wr.x * 32u;
         const uint32_t tm = B16 ? 0xffffu : p.topic_mask;
-        for (int j = threadIdx.x; j < (int)wr.y; j += blockDim.x) lds_phi[ent[j] & tm] = val[j];
+        uint32_t e0 = 0u; float v0 = 0.f;
+        if ((int)threadIdx.x < (int)wr.y) { e0 = ent[threadIdx.x]; v0 = val[threadIdx.x]; }
         __syncthreads();
+        if ((int)threadIdx.x < (int)wr.y) lds_phi[e0 & tm] = v0;
+        for (int j = threadIdx.x + blockDim.x; j < (int)wr.y; j += blockDim.x) lds_phi[ent[j] & tm] = val[j];
     }
+    __syncthreads();
     const float sum_w = p.sumphi[tile.word];
     const float Q = p.alpha * sum_w;
     int l3_top_shift = 0;                      // the dense branch's descent over l3 starts with stride 16^(l3_top_shift / 4)
