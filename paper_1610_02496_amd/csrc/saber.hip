@@ -414,6 +414,38 @@ static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64
     add(end, lo);
 }
 
+// Every row of A is fetched once per word of its document, by the frequent words' tiles about a hundred times in a pass, and
+// in a large chunk from beyond L2 (14 % hits at T = 100 M).  So the tiles of frequent words are cut at the ends of
+// kDocRanges ranges of documents and launched range by range, each XCD (workgroups go to them round robin) at a range of
+// its own at a time, whose rows its 4 MB L2 holds in part.  Sampling pass, iterations 11..20: T = 100 M, K = 10,000 7.92 ->
+// 7.21 ms, K = 1,000 7.46 -> 6.48; T = 246 M in three chunks, K = 5,000, short documents 15.6 -> 14.4, 240 M of long ones,
+// K = 10,000 26.5 -> 23.8; T = 36 M, K = 5,000 2.27 -> 2.14; T = 5 M, K = 3,000 0.43 -> 0.41.  8 or 32 ranges gain half to all of
+// that.  A word is cut if its pieces have 64 tokens on average (32 to 512 differ by 1 to 3 %).  Words that are not cut come
+// first: at the end of the launch their larger tiles cost 3 to 5 %.  Where it stops:
+//   * chunks below 4 M tokens (K = 777, T = 2.3 M: 0.159 -> 0.164 ms), or 16 M where rows are short and few words are cut
+//     (K = 300: 0.558 -> 0.563 ms at 10 M);
+//   * above K = 16,384 the rows are too long (K = 20,011, T = 15 M: first iterations 4.75 -> 5.02 ms, later ones 1.82 -> 1.79), and
+//     rows that are not staged (K = 45,000, T = 20 M) lose the sharing of a row between tiles: 8.9 -> 9.9 ms;
+//   * classes by size (stage_min_tokens) need the tiles in order of size.
+constexpr int kXcds = 8, kDocRanges = 16;
+constexpr int64_t kRangeTokens = 4ll << 20, kRangePiece = 64;
+
+// tiles[0, n) sorted by decreasing size -> the order of the launch: tile i
+// is the next one of XCD i mod 8, which takes the ranges congruent to its number one after the other; uncut tiles first.
+static void order_tiles_by_range(Tile *tiles, int64_t n) {
+    std::vector<Tile> list[kXcds], out;
+    out.reserve((size_t)n);
+    for (int64_t i = 0; i < n; i++) (tiles[i].range ? list[(tiles[i].range - 1) % kXcds] : out).push_back(tiles[i]);
+    for (auto &l : list) std::stable_sort(l.begin(), l.end(), [](const Tile &a, const Tile &b) { return a.range < b.range; });
+    size_t at[kXcds] = {};
+    while ((int64_t)out.size() < n) {
+        int x = (int)(out.size() % kXcds);
+        if (at[x] == list[x].size()) for (x = 0; at[x] == list[x].size(); x++) {}   // its ranges are done: what another has left
+        out.push_back(list[x][at[x]++]);
+    }
+    std::copy(out.begin(), out.end(), tiles);
+}
+
 // Segmented count of up to two groupings of the assignments: documents over z (CountByDZ -> rows of A) and light words
 // over z_wm (CountByVZ -> sparse rows of B).  Two launches: short segments with one wavefront each, long ones
 // with 256 threads.
@@ -871,22 +903,39 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         for (int64_t t = ch.t0; t < ch.t0 + ch.ntok; t++) wcount[(size_t)word_ids[t] + 1]++;
         for (int32_t v = 0; v < V; v++) wcount[(size_t)v + 1] += wcount[(size_t)v];
         const size_t first_tile = h_tiles.size();
-        for (int32_t v = 0; v < V; v++) {
-            const int64_t b = wcount[(size_t)v], e = wcount[(size_t)v + 1];
-            const int32_t row = c->h_word_row[(size_t)v];
-            if (e > b) { ch.words_present++; if (row < 0) c->stats.light_words_present++; }
-            for (int64_t s = b; s < e; s += tile_tokens) {
-                const int32_t cnt = (int32_t)std::min<int64_t>(tile_tokens, e - s);
-                h_tiles.push_back(Tile{v, (int32_t)s, cnt, row >= 0 ? row : -row - 1, wm_ptr[(size_t)v] + wm_seen[(size_t)v], 0});
-                wm_seen[(size_t)v] += cnt;
-            }
-        }
         for (int64_t d = ch.d0; d < ch.d1; d++)
             for (int64_t t = doc_ptr[d]; t < doc_ptr[d + 1]; t++) {
                 const int64_t pos = ch.t0 + wcount[(size_t)word_ids[t]]++;
                 if (h_tok_doc) h_tok_doc[(size_t)pos] = (int32_t)d;
                 h_tok_t[(size_t)pos] = (uint32_t)(t - ch.t0);
             }
+        // ranges of documents: see order_tiles_by_range()
+        const bool ranges = c->staged && K <= 16384 && c->opt.stage_min_tokens <= 1 && ch.ntok >= (K >= 1000 ? kRangeTokens : 4 * kRangeTokens);
+        const int n_ranges = ranges ? kDocRanges : 1;
+        std::vector<uint32_t> range_end((size_t)n_ranges, 0u);   // tokens of the chunk up to the end of each range
+        int64_t rd = ch.d0;
+        for (int r = 0; r < n_ranges; r++) {
+            const int64_t target = ch.t0 + ch.ntok * (r + 1) / n_ranges;
+            while (rd < ch.d1 && (r == n_ranges - 1 || doc_ptr[rd + 1] <= target)) rd++;
+            range_end[(size_t)r] = (uint32_t)(doc_ptr[rd] - ch.t0);
+        }
+        for (int32_t v = 0; v < V; v++) {
+            const int64_t b = v ? wcount[(size_t)v - 1] : 0, e = wcount[(size_t)v];   // (the starts have moved to the ends)
+            const int32_t row = c->h_word_row[(size_t)v];
+            if (e > b) { ch.words_present++; if (row < 0) c->stats.light_words_present++; }
+            const bool split = n_ranges > 1 && row >= 0 && e - b >= n_ranges * kRangePiece;
+            int64_t s = b;
+            for (int r = 0; r < (split ? n_ranges : 1); r++) {
+                const uint32_t *seg = h_tok_t + ch.t0;   // (ascending inside a word's segment)
+                const int64_t end = split ? std::lower_bound(seg + s, seg + e, range_end[(size_t)r]) - seg : e;
+                while (s < end) {
+                    const int32_t cnt = (int32_t)std::min<int64_t>(tile_tokens, end - s);
+                    h_tiles.push_back(Tile{v, (int32_t)s, cnt, row >= 0 ? row : -row - 1, wm_ptr[(size_t)v] + wm_seen[(size_t)v], split ? r + 1 : 0});
+                    wm_seen[(size_t)v] += cnt;
+                    s += cnt;
+                }
+            }
+        }
         // tiles of dense-row words first, then those of light words; inside each group heavy tiles first so the
         // tail of a launch is made of small ones (Sec. 3.4)
         const std::vector<int32_t> &wr = c->h_word_row;
@@ -894,9 +943,10 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
             const bool la = wr[(size_t)a.word] < 0, lb = wr[(size_t)b.word] < 0;
             return la != lb ? lb : a.count > b.count;
         });
-        ch.tile0 = (int64_t)first_tile; ch.ntiles = (int64_t)(h_tiles.size() - first_tile);
         int64_t n_dense = 0;
-        while (n_dense < ch.ntiles && wr[(size_t)h_tiles[first_tile + (size_t)n_dense].word] >= 0) n_dense++;
+        while (first_tile + (size_t)n_dense < h_tiles.size() && wr[(size_t)h_tiles[first_tile + (size_t)n_dense].word] >= 0) n_dense++;
+        if (n_ranges > 1) order_tiles_by_range(h_tiles.data() + first_tile, n_dense);
+        ch.tile0 = (int64_t)first_tile; ch.ntiles = (int64_t)(h_tiles.size() - first_tile);
         tile_classes(c, ch, h_tiles.data() + first_tile, 0, n_dense, false);
         tile_classes(c, ch, h_tiles.data() + first_tile, n_dense, ch.ntiles, true);
         c->max_chunk_tiles = std::max(c->max_chunk_tiles, ch.ntiles);

@@ -174,7 +174,8 @@ __global__ void gather_probs_kernel(const float *S, const float *Q, const int64_
 // ---------------------------------------------------------------------------------------------
 // row: the word's row in the dense B / Bhat arrays, or its index among the light words (see below)
 // wm_begin: position of the tile's first token in the corpus-wide word-major order
-struct Tile { int32_t word; int32_t begin; int32_t count; int32_t row; int64_t wm_begin; int64_t pad; };
+// range: host only, 1 + range of documents the tile was cut to (0: whole)
+struct Tile { int32_t word; int32_t begin; int32_t count; int32_t row; int64_t wm_begin; int64_t range; };
 
 struct EStepParams {
     const Tile *tiles;

@@ -115,3 +115,28 @@ def test_results_that_leave_in_pieces(T, K, opts):
     g.set_z(z0, 0)
     assert np.array_equal(g.get_z(), z0)
     g.close()
+
+
+@pytest.mark.parametrize("T,K,opts", [(4_400_000, 1000, {}), (4_400_000, 16384, {}), (17_300_000, 300, {}),
+                                      (9_000_000, 2500, {"n_chunks": 2, "stream_workers": 2})])
+def test_frequent_words_cut_by_ranges_of_documents(T, K, opts):
+    """Tiles cut at the ends of sixteen ranges of documents, against the plain order of tiles (classes by size switch the
+    ranges off).  Empty documents on both ends, one document longer than several ranges (some ranges are empty), words that
+    occur in one range only, words with too few tokens to be cut."""
+    rng = np.random.default_rng(K)
+    lens = np.r_[0, 0, rng.integers(0, 700, T // 900), min(T // 5, (1 << (32 - (K - 1).bit_length())) - 1), rng.integers(0, 700, T // 600), 0]
+    doc_ptr = np.r_[0, np.minimum(np.cumsum(lens), T)].astype(np.int64)
+    T, V = int(doc_ptr[-1]), 900
+    words = np.minimum(rng.geometric(0.01, T) - 1, V - 2).astype(np.int32)
+    words[T // 3: T // 3 + 40000] = V - 1
+    pk = saber()
+    g = pk.Saber(doc_ptr, words, V, K, 50.0 / K, 0.01, 8, **opts)
+    p = pk.Saber(doc_ptr, words, V, K, 50.0 / K, 0.01, 8, stage_min_tokens=2, light_block_threads=256, n_chunks=opts.get("n_chunks", 0))
+    assert g.get_stats()["tiles"] > p.get_stats()["tiles"]
+    for _ in range(2):
+        g.iterate(1)
+        p.iterate(1)
+        assert np.array_equal(g.get_z(), p.get_z())
+    assert abs(g.loglik() - p.loglik()) <= 1e-11 * abs(p.loglik())
+    g.close()
+    p.close()
