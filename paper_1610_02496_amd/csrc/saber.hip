@@ -1778,31 +1778,21 @@ extern "C" int saber_get_phi(saber_ctx *c, const int32_t *words, int32_t m, floa
     for (int32_t i = 0; i < m; i++)
         if (words[i] < 0 || words[i] >= c->V) return fail(SABER_EINVAL, "saber_get_phi: word %d is outside [0,%d)", words[i], c->V);
     if (m == 0) return SABER_OK;
-    // assemble the requested Bhat rows on the device: dense rows are copied, light rows are the base vector
-    // overwritten at the word's non-zeros; the prefix rows are then rebuilt the way the dense branch does
-    float *drows = nullptr, *dout = nullptr; int32_t *dw = nullptr, *dlight = nullptr;
-    auto cleanup = [&]() { dev_free(c->hooks, drows); dev_free(c->hooks, dout); dev_free(c->hooks, dw); dev_free(c->hooks, dlight); };
+    std::vector<int32_t> rows;
+    try { rows.resize((size_t)m); } catch (const std::bad_alloc &) { return fail(SABER_ENOMEM, "saber_get_phi: out of host memory"); }
+    for (int32_t i = 0; i < m; i++) rows[(size_t)i] = c->h_word_row[(size_t)words[i]];
+    // assemble the requested Bhat rows on the device; the prefix rows are then rebuilt the way the dense branch does
+    float *drows = nullptr, *dout = nullptr; int32_t *dw = nullptr, *drow = nullptr;
+    auto cleanup = [&]() { dev_free(c->hooks, drows); dev_free(c->hooks, dout); dev_free(c->hooks, dw); dev_free(c->hooks, drow); };
     int rc;
     if ((rc = dev_alloc(c->hooks, &drows, (size_t)m * (size_t)c->K)) || (rc = dev_alloc(c->hooks, &dout, (size_t)m * (size_t)c->K)) ||
-        (rc = dev_alloc(c->hooks, &dw, (size_t)m)) || (rc = dev_alloc(c->hooks, &dlight, (size_t)m))) { cleanup(); return rc; }
+        (rc = dev_alloc(c->hooks, &dw, (size_t)m)) || (rc = dev_alloc(c->hooks, &drow, (size_t)m))) { cleanup(); return rc; }
     hipError_t e = hipMemcpy(dw, words, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice);
-    for (int32_t i = 0; i < m && e == hipSuccess; i++) {
-        const int32_t row = c->h_word_row[(size_t)words[i]];
-        if (row >= 0) {
-            e = hipMemcpyAsync(drows + (size_t)i * (size_t)c->K, c->phi + (size_t)row * (size_t)c->Kpad,
-                               sizeof(float) * (size_t)c->K, hipMemcpyDeviceToDevice, c->stream);
-        } else {
-            const int32_t li = -row - 1;
-            e = hipMemcpyAsync(dlight, &li, sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-            if (e == hipSuccess) {
-                hipLaunchKernelGGL(light_rows_export_kernel, dim3(1), dim3(256), 0, c->stream, dlight, 1, c->wrec, c->lw_ent,
-                                   c->lw_phi, c->phi + (size_t)c->V_dense * (size_t)c->Kpad, c->K, c->topic_bits,
-                                   drows + (size_t)i * (size_t)c->K, (int32_t *)nullptr);
-                e = hipGetLastError();
-            }
-            if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        }
+    if (e == hipSuccess) e = hipMemcpy(drow, rows.data(), sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(phi_export_kernel, dim3((unsigned)m), dim3(256), 0, c->stream, drow, c->phi,
+                           c->phi + (size_t)c->V_dense * (size_t)c->Kpad, c->wrec, c->lw_ent, c->lw_phi, c->K, c->Kpad, c->topic_bits, drows);
+        e = hipGetLastError();
     }
     if (e == hipSuccess && prefix) {
         const int64_t items = (int64_t)m * ((c->K + 63) / 64);

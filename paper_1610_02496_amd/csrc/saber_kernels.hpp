@@ -1442,24 +1442,21 @@ __global__ void __launch_bounds__(64) light_tree_kernel(const int32_t *light_wor
     if (lane == 0) sumphi[v] = total;
 }
 
-// Dense image of light words' rows for export: out[i][k] = base[k] (Bhat) or 0 (counts), then the non-zeros.
-__global__ void light_rows_export_kernel(const int32_t *light_ids, int m, const uint2 *wrec, const uint32_t *lw_ent,
-                                         const float *lw_phi, const float *base, int K, uint32_t topic_bits,
-                                         float *out_phi, int32_t *out_cnt) {
-    const int i = blockIdx.x;
-    if (i >= m) return;
-    const uint2 wr = wrec[light_ids[i]];
-    const uint32_t tmask = (1u << topic_bits) - 1u;
-    for (int k = threadIdx.x; k < K; k += blockDim.x) {
-        if (out_phi) out_phi[(size_t)i * (size_t)K + k] = base[k];
-        if (out_cnt) out_cnt[(size_t)i * (size_t)K + k] = 0;
-    }
+// Bhat rows of the words asked for, out[i][k], one workgroup each: a dense row is copied, a light word's is the base vector
+// overwritten at its non-zeros.  rows[i] is the word's dense row, or -1 - its index among the light words.
+// (One launch and one wait for all words: a copy or a launch, and two waits, per word took 6.4 ms for 400 words at K = 1,500.)
+__global__ void __launch_bounds__(256) phi_export_kernel(const int32_t *rows, const float *phi, const float *base, const uint2 *wrec,
+                                                         const uint32_t *lw_ent, const float *lw_phi, int K, int Kpad,
+                                                         uint32_t topic_bits, float *out) {
+    const int row = rows[blockIdx.x];
+    const float *__restrict__ src = row >= 0 ? phi + (size_t)row * (size_t)Kpad : base;
+    float *__restrict__ dst = out + (size_t)blockIdx.x * (size_t)K;
+    for (int k = threadIdx.x; k < K; k += blockDim.x) dst[k] = src[k];
+    if (row >= 0) return;
     __syncthreads();
-    for (int j = threadIdx.x; j < (int)wr.y; j += blockDim.x) {
-        const uint32_t e = lw_ent[(size_t)wr.x * 32u + j];
-        if (out_phi) out_phi[(size_t)i * (size_t)K + (e & tmask)] = lw_phi[(size_t)wr.x * 32u + j];
-        if (out_cnt) out_cnt[(size_t)i * (size_t)K + (e & tmask)] = (int32_t)(e >> topic_bits);
-    }
+    const uint2 wr = wrec[-row - 1];
+    const uint32_t tmask = (1u << topic_bits) - 1u;
+    for (int j = threadIdx.x; j < (int)wr.y; j += blockDim.x) dst[lw_ent[(size_t)wr.x * 32u + j] & tmask] = lw_phi[(size_t)wr.x * 32u + j];
 }
 
 // Statistics for the bandwidth model (exact in binary64 below 2^53), added to out[0..4]: the dense-branch counter slots
