@@ -91,8 +91,9 @@ static void dev_free(const Hooks &h, void *p) { hook_free(h, p); }
 // ------------------------------------------------------------------------------------------------
 // context
 // ------------------------------------------------------------------------------------------------
-// Tiles of a chunk that are launched together: `count` tiles from the chunk's tile `first` on, workgroups of `block` threads
-struct TileClass { int64_t first, count; int block; bool light; };
+// Tiles of a chunk that are launched together: `count` tiles from the chunk's tile `first` on, the first `n_dense` of them of
+// words with dense rows, workgroups of `block` threads
+struct TileClass { int64_t first, count, n_dense; int block; };
 
 struct Chunk {
     int64_t d0 = 0, d1 = 0;   // document range
@@ -322,14 +323,9 @@ static void launch_with_lds(Kern kern, dim3 grid, dim3 block, size_t lds, hipStr
 }
 
 template <int MODE, bool STAGED, typename ZT>
-static void launch_estep_b16(saber_ctx *c, dim3 grid, dim3 block, size_t lds, const EStepParams &p, bool light) {
-    if (light) {   // light words exist only in the staged, 16-bit-z configuration
-        if (c->b16) launch_with_lds(estep_kernel<MODE, true, uint16_t, true, true>, grid, block, lds, c->stream, p);
-        else launch_with_lds(estep_kernel<MODE, true, uint16_t, false, true>, grid, block, lds, c->stream, p);
-        return;
-    }
-    if (c->b16) launch_with_lds(estep_kernel<MODE, STAGED, ZT, true, false>, grid, block, lds, c->stream, p);
-    else launch_with_lds(estep_kernel<MODE, STAGED, ZT, false, false>, grid, block, lds, c->stream, p);
+static void launch_estep_b16(saber_ctx *c, dim3 grid, dim3 block, size_t lds, const EStepParams &p) {
+    if (c->b16) launch_with_lds(estep_kernel<MODE, STAGED, ZT, true>, grid, block, lds, c->stream, p);
+    else launch_with_lds(estep_kernel<MODE, STAGED, ZT, false>, grid, block, lds, c->stream, p);
 }
 
 // The staged 16/16 sampler addresses its Bhat row from LDS address 0: its kernels must have no static LDS in
@@ -342,34 +338,31 @@ static int static_lds_is_zero(F kernel) {
     return SABER_OK;
 }
 static int check_estep_lds_layout() {
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, uint16_t, true, false>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, uint16_t, true, true>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_PROBS, true, uint16_t, true, false>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_PROBS, true, uint16_t, true, true>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_LOGLIK, true, uint16_t, true, false>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_LOGLIK, true, uint16_t, true, true>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, int32_t, true, false>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_PROBS, true, int32_t, true, false>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_LOGLIK, true, int32_t, true, false>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, uint16_t, true>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_PROBS, true, uint16_t, true>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_LOGLIK, true, uint16_t, true>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, int32_t, true>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_PROBS, true, int32_t, true>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_LOGLIK, true, int32_t, true>));
     return SABER_OK;
 }
 
-// One E-step launch per tile class (tile_classes() below).  Tiles of light words run the variant that builds the Bhat
-// row from the base vector and the word's non-zeros.  All stage the row in LDS when it fits.
+// One E-step launch per tile class (tile_classes() below).  All stage the row in LDS when it fits.
 template <int MODE>
 static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
     for (const TileClass &cl : ch.classes) {
         EStepParams p = p0;
         p.tiles = p0.tiles + cl.first;
         if (p0.out_ll) p.out_ll = p0.out_ll + cl.first;
+        p.first_light = (int32_t)cl.n_dense;
         const dim3 grid((unsigned)cl.count), block((unsigned)cl.block);
         const size_t lds = estep_lds_bytes(c, MODE);
         if (c->staged) {
-            if (c->z16) launch_estep_b16<MODE, true, uint16_t>(c, grid, block, lds, p, cl.light);
-            else launch_estep_b16<MODE, true, int32_t>(c, grid, block, lds, p, false);
+            if (c->z16) launch_estep_b16<MODE, true, uint16_t>(c, grid, block, lds, p);
+            else launch_estep_b16<MODE, true, int32_t>(c, grid, block, lds, p);
         } else {
-            if (c->z16) launch_estep_b16<MODE, false, uint16_t>(c, grid, block, lds, p, false);
-            else launch_estep_b16<MODE, false, int32_t>(c, grid, block, lds, p, false);
+            if (c->z16) launch_estep_b16<MODE, false, uint16_t>(c, grid, block, lds, p);
+            else launch_estep_b16<MODE, false, int32_t>(c, grid, block, lds, p);
         }
         HIP_TRY(hipGetLastError());
     }
@@ -384,34 +377,37 @@ static int estep_waves_per_cu(const saber_ctx *c, int block) {
     return std::min(by_lds, by_waves) * (block / 64);
 }
 
-// Cuts one group of a chunk's tiles ([begin, end) of the chunk's tiles, sorted by decreasing size) into classes.  Dense
-// rows: tiles with at least stage_min_tokens tokens get block_threads threads, smaller ones light_block_threads.
-// Light words, unless the caller fixed a workgroup size: one wavefront per 64 tokens (a full batch), between the
-// smallest workgroup with which LDS still lets a CU hold 24 of its 32 wavefronts and block_threads.  A small tile dealt
-// to many wavefronts pays each one's set-up and chain of dependent loads for a few tokens: K = 1,000, T = 10 M (90,000
-// light words of 29 tokens on average), sampling pass 0.89 ms with 256 threads for all of them, 0.77 ms so; K = 2,000,
-// 5 M tokens per chunk: 2.09 and 1.89 ms per four chunks.  No difference at T = 2 M, K = 777 (0.17 ms both).
-static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64_t begin, int64_t end, bool light) {
-    int64_t at = begin;
+// Cuts a chunk's tiles - n_dense of words with dense rows, then those of light words, each group sorted by decreasing size -
+// into classes.  Dense rows: tiles with at least stage_min_tokens tokens get block_threads threads, smaller ones
+// light_block_threads.  Light words, unless the caller fixed a workgroup size: one wavefront per 64 tokens (a full batch),
+// between the smallest workgroup with which LDS still lets a CU hold 24 of its 32 wavefronts and block_threads.  A small
+// tile dealt to many wavefronts pays each one's set-up and chain of dependent loads for a few tokens: K = 1,000, T = 10 M
+// (90,000 light words of 29 tokens on average), sampling pass 0.89 ms with 256 threads for all of them, 0.77 ms so; K = 2,000,
+// 5 M tokens per chunk: 2.09 and 1.89 ms per four chunks.  Up to two rounds of the chip's 8,192 wavefronts it makes no
+// difference (T = 2 M, K = 777: 0.17 ms both), and the light words' tiles then go with the dense rows' launch.
+static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64_t n_dense) {
+    int64_t at = 0;
     auto add = [&](int64_t to, int block) {
-        if (to > at) ch.classes.push_back(TileClass{at, to - at, block, light});
-        at = std::max(at, to);
+        if (to <= at) return;
+        const int64_t dense = std::max<int64_t>(0, std::min(to, n_dense) - at);
+        TileClass *last = ch.classes.empty() ? nullptr : &ch.classes.back();
+        if (last && last->block == block) { last->count += to - at; last->n_dense += dense; }
+        else ch.classes.push_back(TileClass{at, to - at, dense, block});
+        at = to;
     };
-    auto until = [&](int64_t least) {   // first tile with fewer than `least` tokens
+    auto until = [&](int64_t end, int64_t least) {   // first tile from `at` to `end` with fewer than `least` tokens
         return (int64_t)(std::lower_bound(tiles + at, tiles + end, least, [](const Tile &t, int64_t n) { return t.count >= n; }) - tiles);
     };
-    if (!light) {
-        add(until(c->opt.stage_min_tokens), c->opt.block_threads);
-        add(end, c->opt.light_block_threads);
-        return;
-    }
+    if (c->opt.stage_min_tokens > 1) add(until(n_dense, c->opt.stage_min_tokens), c->opt.block_threads);
+    else add(n_dense, c->opt.block_threads);
+    add(n_dense, c->opt.light_block_threads);
     int lo = c->opt.light_block_threads, hi = c->opt.light_block_threads;
-    if (c->auto_light_block) { lo = 64; while (lo < hi && estep_waves_per_cu(c, lo) < 24) lo *= 2; }
+    if (c->auto_light_block && ch.ntiles - n_dense > 16384) { lo = 64; while (lo < hi && estep_waves_per_cu(c, lo) < 24) lo *= 2; }
     for (int block = hi; block > lo; block /= 2) {
-        const int64_t to = until(64 * (block / 128) + 1);   // tiles that half the workgroup would not serve in one batch each
-        if (to - at >= 128) add(to, block);                 // (a launch of its own pays from half a workgroup per CU on)
+        const int64_t to = until(ch.ntiles, 64 * (block / 128) + 1);   // tiles that half the workgroup would not serve in one batch each
+        if (to - at >= 128 || (block == hi && !ch.classes.empty() && ch.classes.back().block == hi)) add(to, block);   // (a launch of its own pays from half a workgroup per CU on)
     }
-    add(end, lo);
+    add(ch.ntiles, lo);
 }
 
 // Every row of A is fetched once per word of its document, by the frequent words' tiles about a hundred times in a pass, and
@@ -947,8 +943,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         while (first_tile + (size_t)n_dense < h_tiles.size() && wr[(size_t)h_tiles[first_tile + (size_t)n_dense].word] >= 0) n_dense++;
         if (n_ranges > 1) order_tiles_by_range(h_tiles.data() + first_tile, n_dense);
         ch.tile0 = (int64_t)first_tile; ch.ntiles = (int64_t)(h_tiles.size() - first_tile);
-        tile_classes(c, ch, h_tiles.data() + first_tile, 0, n_dense, false);
-        tile_classes(c, ch, h_tiles.data() + first_tile, n_dense, ch.ntiles, true);
+        tile_classes(c, ch, h_tiles.data() + first_tile, n_dense);
         c->max_chunk_tiles = std::max(c->max_chunk_tiles, ch.ntiles);
     }
     c->total_tiles = (int64_t)h_tiles.size();

@@ -209,6 +209,7 @@ struct EStepParams {
     double *out_ll;             // loglik mode: one partial sum per tile
     unsigned long long *n_dense;// sample mode: kDenseSlots dense-branch token counters (workgroup b adds to slot b mod
                                 // kDenseSlots: one hot address would serialise the atomics of the whole launch)
+    int32_t first_light;        // tiles of the launch from this one on belong to light words
     int64_t t_base;             // canonical index of the chunk's first token
     int64_t z_rel;              // position of that token in z
     int32_t K, Kpad, n3, n3pad;
@@ -467,9 +468,10 @@ __device__ __forceinline__ uint32_t search_block(const uint4 e, const RowBlock &
 
 // New assignments are written twice: to z (canonical order) and to z_wm (word-major, coalesced), from which the
 // M-step counts B; the sampler itself adds nothing to B.
-// LIGHT: the tile's word keeps B sparse.  Its Bhat row is built in LDS from the base vector and the word's
-// non-zeros.
-template <int MODE, bool STAGED, typename ZT, bool B16, bool LIGHT>
+// A light word keeps B sparse: its Bhat row is built in LDS from the base vector and the word's non-zeros (staged rows and
+// 16-bit assignments only).  Tiles of both kinds share a launch: a launch of its own for the light words cost a small
+// corpus 10 of its 47 us per iteration (T = 100 K, K = 100), a large one the tail of the other.
+template <int MODE, bool STAGED, typename ZT, bool B16>
 __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     extern __shared__ float4 lds_f4[];
     // LDS, all of it dynamic so that the Bhat row starts at address 0 and a gather needs no base added:
@@ -487,8 +489,9 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     unsigned int &wg_dense = reinterpret_cast<unsigned int *>(ctrl)[1];   // dense-branch tokens of this workgroup
     double *ll_wave = reinterpret_cast<double *>(lds_l3 + (STAGED ? (p.n3 + 3) & ~3 : 0));
     const Tile tile = p.tiles[blockIdx.x];
+    const bool light = STAGED && sizeof(ZT) == 2 && (int)blockIdx.x >= p.first_light;
     const int K = p.K;
-    const float *__restrict__ phi_row = LIGHT ? p.base : p.phi + (size_t)tile.row * (size_t)p.Kpad;
+    const float *__restrict__ phi_row = light ? p.base : p.phi + (size_t)tile.row * (size_t)p.Kpad;
     const float *__restrict__ l3_row = p.l3 + (size_t)tile.word * (size_t)p.n3pad;
     const double *__restrict__ l3_64_row = p.l3_64 + (size_t)tile.word * (size_t)p.n3;
     const int lane = lane_id(), nwaves = blockDim.x / kWave;
@@ -530,7 +533,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     }
     uint2 rec = make_uint2(p.row_unit0, 0u);
     if (d >= 0) rec = p.docrec[d];
-    if (LIGHT) {
+    if (light) {
         // the staged row is the base vector so far; overwrite the topics this word has counts for.  The word's first
         // entries, one per thread, are requested before the barrier as well.
         const uint2 wr = p.wrec[tile.row];
@@ -838,7 +841,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         if (MODE == MODE_SAMPLE && dense_mask) {
             // problem 2 for the tokens whose coin chose it: DPP row g (16 lanes) serves the g-th of up to four tokens
             if (lane == 0) atomicAdd(&wg_dense, (unsigned int)__builtin_popcountll(dense_mask));   // statistic only
-            if (!LIGHT && p.alias_table != nullptr) {
+            if (p.alias_table != nullptr) {   // (every word then keeps a dense row)
                 // Walker's alias method for all these tokens at once: the bucket is floor(u1 K), taken in integers from
                 // the 24 random bits behind u1; the bucket's own topic if the fraction of u1 K lies below its
                 // probability, its alias otherwise
