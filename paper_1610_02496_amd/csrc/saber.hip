@@ -111,6 +111,8 @@ struct Chunk {
 constexpr int kMaxSlots = 8;
 constexpr int kPullSlots = 12, kPullThreads = 8;      // see pull()
 constexpr int64_t kPullPiece = 1 << 20;               // bytes
+// Pinned staging of results and the events of its slots, made by the first call that needs them.
+struct Staging { char *buf = nullptr; size_t bytes = 0; bool pinned = false; hipEvent_t ev[kPullSlots] = {}; };
 
 constexpr int kMaxTimedIters = 32;
 constexpr int kCtr = 8;   // device counters per timed iteration
@@ -181,11 +183,7 @@ struct saber_ctx {
     hipEvent_t ev[kMaxTimedIters * EV_PER_ITER] = {};
     bool have_events = false;
     saber_stats stats{};
-    // device -> host results: pinned staging and its events, made by the first call that needs them
-    char *pull_buf = nullptr;
-    size_t pull_bytes = 0;
-    bool pull_pinned = false;
-    hipEvent_t pull_ev[kPullSlots] = {};
+    Staging staging;                  // device -> host results, see pull()
     std::vector<int64_t> doc_len;     // host copy of the document lengths (statistics only)
     // Host streaming (Sec. 3.1.2), n_slots > 0: tok_t lives in pinned host memory; a chunk's part of it is copied
     // into one of n_slots device buffers for the chunk's pass (4 bytes per token and iteration over the host link).
@@ -260,8 +258,8 @@ extern "C" void saber_free(saber_ctx *c) {
     release(c->word_ids_d); release(c->word_row_d); release(c->sort_keys); release(c->sort_keys_out);
     release(c->sort_rank); release(c->sort_tmp); release(c->alias_table);
     if (c->h_tok_t) (void)hipHostFree(c->h_tok_t);
-    if (c->pull_buf) { if (c->pull_pinned) (void)hipHostFree(c->pull_buf); else free(c->pull_buf); }
-    for (auto &e : c->pull_ev) if (e) (void)hipEventDestroy(e);
+    if (c->staging.buf) { if (c->staging.pinned) (void)hipHostFree(c->staging.buf); else free(c->staging.buf); }
+    for (auto &e : c->staging.ev) if (e) (void)hipEventDestroy(e);
     if (c->stream && c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }
@@ -422,9 +420,15 @@ static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64
 //     (K = 300: 0.558 -> 0.563 ms at 10 M);
 //   * above K = 16,384 the rows are too long (K = 20,011, T = 15 M: first iterations 4.75 -> 5.02 ms, later ones 1.82 -> 1.79), and
 //     rows that are not staged (K = 45,000, T = 20 M) lose the sharing of a row between tiles: 8.9 -> 9.9 ms;
-//   * classes by size (stage_min_tokens) need the tiles in order of size.
+//   * classes by size (stage_min_tokens) need the tiles in order of size;
+//   * a chunk's tiles have to stay within the 2^20 of saber_loglik_static whatever the words' sizes are.
 constexpr int kXcds = 8, kDocRanges = 16;
 constexpr int64_t kRangeTokens = 4ll << 20, kRangePiece = 64;
+
+static bool may_cut_by_range(const saber_ctx *c, const Chunk &ch) {
+    return c->staged && c->K <= 16384 && c->opt.stage_min_tokens <= 1 && ch.ntok >= (c->K >= 1000 ? kRangeTokens : 4 * kRangeTokens) &&
+           (int64_t)c->V + (int64_t)kDocRanges * c->V_dense <= (1 << 20) - (1 << 16);
+}
 
 // tiles[0, n) sorted by decreasing size -> the order of the launch: tile i
 // is the next one of XCD i mod 8, which takes the ranges congruent to its number one after the other; uncut tiles first.
@@ -829,6 +833,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         for (const Chunk &ch : c->chunks) {
             slot_tokens = std::max(slot_tokens, (size_t)ch.ntok);
             tiles_bound += (size_t)std::min<int64_t>(V, ch.ntok);
+            if (may_cut_by_range(c, ch)) tiles_bound += (size_t)std::min<int64_t>((int64_t)kDocRanges * c->V_dense, ch.ntok / kRangePiece);
         }
         const size_t common = row_units * 128 + (size_t)D * 32 + tiles_bound * sizeof(Tile) +
                               ((size_t)c->V_dense + 1) * (size_t)c->Kpad * 8 +
@@ -906,7 +911,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
                 h_tok_t[(size_t)pos] = (uint32_t)(t - ch.t0);
             }
         // ranges of documents: see order_tiles_by_range()
-        const bool ranges = c->staged && K <= 16384 && c->opt.stage_min_tokens <= 1 && ch.ntok >= (K >= 1000 ? kRangeTokens : 4 * kRangeTokens);
+        const bool ranges = may_cut_by_range(c, ch);
         const int n_ranges = ranges ? kDocRanges : 1;
         std::vector<uint32_t> range_end((size_t)n_ranges, 0u);   // tokens of the chunk up to the end of each range
         int64_t rd = ch.d0;
@@ -952,11 +957,14 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     std::vector<int32_t> h_short, h_long;
     std::vector<uint32_t> h_doc_words((size_t)std::max<int64_t>(D, 1));
     {   // distinct words per document (layout statistic for the bandwidth model)
-        std::vector<int64_t> last_doc((size_t)V, -1);
+        std::vector<int32_t> last_doc((size_t)V, -1);
         for (int64_t d = 0; d < D; d++) {
             uint32_t u = 0;
-            for (int64_t t = doc_ptr[d]; t < doc_ptr[d + 1]; t++)
-                if (last_doc[(size_t)word_ids[t]] != d) { last_doc[(size_t)word_ids[t]] = d; u++; }
+            for (int64_t t = doc_ptr[d]; t < doc_ptr[d + 1]; t++) {   // (no branch: repeats are irregular)
+                int32_t &last = last_doc[(size_t)word_ids[t]];
+                u += last != (int32_t)d;
+                last = (int32_t)d;
+            }
             h_doc_words[(size_t)d] = u;
         }
     }
@@ -1345,25 +1353,25 @@ static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<in
     for (int64_t i = 0; i < np; i++) largest = std::max(largest, (size_t)(cuts[(size_t)i + 1] - cuts[(size_t)i]) * elem);
     largest = (largest + 255) & ~(size_t)255;
     const int slots = (int)std::min<int64_t>(np, kPullSlots);
-    if (c->pull_bytes < largest * (size_t)slots) {
-        if (c->pull_buf) { if (c->pull_pinned) (void)hipHostFree(c->pull_buf); else free(c->pull_buf); }
-        c->pull_buf = nullptr; c->pull_bytes = 0; c->pull_pinned = true;
-        if (hipHostMalloc((void **)&c->pull_buf, largest * (size_t)slots, hipHostMallocDefault) != hipSuccess) {
+    if (c->staging.bytes < largest * (size_t)slots) {
+        if (c->staging.buf) { if (c->staging.pinned) (void)hipHostFree(c->staging.buf); else free(c->staging.buf); }
+        c->staging.buf = nullptr; c->staging.bytes = 0; c->staging.pinned = true;
+        if (hipHostMalloc((void **)&c->staging.buf, largest * (size_t)slots, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
-            c->pull_pinned = false;
-            c->pull_buf = (char *)malloc(largest * (size_t)slots);
-            if (!c->pull_buf) return fail(SABER_ENOMEM, "out of host memory");
+            c->staging.pinned = false;
+            c->staging.buf = (char *)malloc(largest * (size_t)slots);
+            if (!c->staging.buf) return fail(SABER_ENOMEM, "out of host memory");
         }
-        c->pull_bytes = largest * (size_t)slots;
+        c->staging.bytes = largest * (size_t)slots;
     }
     for (int i = 0; i < slots; i++)
-        if (!c->pull_ev[i]) HIP_TRY(hipEventCreateWithFlags(&c->pull_ev[i], hipEventDisableTiming));
+        if (!c->staging.ev[i]) HIP_TRY(hipEventCreateWithFlags(&c->staging.ev[i], hipEventDisableTiming));
     auto request = [&](int64_t k) {
         const size_t bytes = (size_t)(cuts[(size_t)k + 1] - cuts[(size_t)k]) * elem;
         hipError_t e = hipSuccess;
-        if (bytes) e = hipMemcpyAsync(c->pull_buf + (size_t)(k % slots) * largest, (const char *)dev + (size_t)cuts[(size_t)k] * elem,
+        if (bytes) e = hipMemcpyAsync(c->staging.buf + (size_t)(k % slots) * largest, (const char *)dev + (size_t)cuts[(size_t)k] * elem,
                                       bytes, hipMemcpyDeviceToHost, c->stream);
-        if (e == hipSuccess) e = hipEventRecord(c->pull_ev[k % slots], c->stream);
+        if (e == hipSuccess) e = hipEventRecord(c->staging.ev[k % slots], c->stream);
         return e;
     };
     std::vector<std::atomic<char>> done((size_t)np);
@@ -1379,9 +1387,9 @@ static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<in
                 if (error.load() != (int)hipSuccess) return;
                 std::this_thread::yield();
             }
-            const hipError_t e = hipEventSynchronize(c->pull_ev[k % slots]);
+            const hipError_t e = hipEventSynchronize(c->staging.ev[k % slots]);
             if (e != hipSuccess) { error.store((int)e); return; }
-            consume(k, (const void *)(c->pull_buf + (size_t)(k % slots) * largest));
+            consume(k, (const void *)(c->staging.buf + (size_t)(k % slots) * largest));
             done[(size_t)k].store(1, std::memory_order_release);
         }
     };
@@ -1396,8 +1404,8 @@ static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<in
     for (int64_t k = 0; k < np && e == hipSuccess; k++) {
         if (threads.empty()) {
             e = request(k);
-            if (e == hipSuccess) e = hipEventSynchronize(c->pull_ev[k % slots]);
-            if (e == hipSuccess) consume(k, (const void *)(c->pull_buf + (size_t)(k % slots) * largest));
+            if (e == hipSuccess) e = hipEventSynchronize(c->staging.ev[k % slots]);
+            if (e == hipSuccess) consume(k, (const void *)(c->staging.buf + (size_t)(k % slots) * largest));
             continue;
         }
         while (k >= slots && !done[(size_t)(k - slots)].load(std::memory_order_acquire) && error.load() == (int)hipSuccess)
@@ -1652,7 +1660,11 @@ extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const 
         rc = create_ctx(&obs, optr.data(), ow.data(), D, m->V, m->K, m->alpha, m->beta, seed, &opt, m, false);
         if (rc == SABER_OK && z_init) rc = saber_set_z(obs, z_init, 0);
         if (rc == SABER_OK) rc = foldin_iterate(obs, n_foldin);
-        if (rc == SABER_OK && z_out) rc = saber_get_z(obs, z_out);
+        if (rc == SABER_OK && z_out) {
+            std::swap(obs->staging, m->staging);   // the model's, which outlives the call
+            rc = saber_get_z(obs, z_out);
+            std::swap(obs->staging, m->staging);
+        }
         if (rc == SABER_OK) rc = create_ctx(&scr, sptr.data(), sw.data(), D, m->V, m->K, m->alpha, m->beta, seed, &opt, m, true);
         double ll = 0.0;
         if (rc == SABER_OK && scr->T > 0) {
