@@ -26,6 +26,8 @@ using namespace saber;
 // ------------------------------------------------------------------------------------------------
 static thread_local char g_err[512] = "";
 static int fail(int code, const char *fmt, ...) {
+    // the runtime keeps the thread's last error until it is asked for: left there, it would be taken for the next launch's
+    if (code == SABER_ENOMEM || code == SABER_EDEVICE) (void)hipGetLastError();
     va_list ap; va_start(ap, fmt); vsnprintf(g_err, sizeof(g_err), fmt, ap); va_end(ap);
     return code;
 }

@@ -1,0 +1,169 @@
+// A HIP runtime without a GPU, for tests of the library's host code: the library is loaded with these symbols in front
+// of the real ones.  Memory is host memory (reserved, touched on use), copies are memcpy, kernels do not run - their
+// launches are checked against the documented limits and logged.  A few kernels of the M-step can be imitated, and a
+// call can be made to fail.  Two devices; objects belong to the one that was current when they were made.
+#include <sys/mman.h>
+
+#include <algorithm>
+#include <cstdint>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <mutex>
+#include <string>
+#include <vector>
+
+namespace {
+enum { kOk = 0, kInvalidValue = 1, kOutOfMemory = 2, kInvalidConfiguration = 9, kInvalidDevice = 101, kInvalidHandle = 400 };
+struct Dim { uint32_t x, y, z; };
+struct Object { int device; };
+struct Launch { std::string name; Dim grid, block; };
+struct Config { Dim grid, block; size_t lds; Object *stream; };
+
+std::mutex mu;
+std::map<void *, size_t> blocks;
+std::map<const void *, std::string> kernels;
+std::map<const void *, size_t> vars;
+std::map<const void *, void *> var_mem;
+std::vector<Launch> launches;
+std::string fail_name;
+int fail_at = 0, imitate = 0;
+thread_local int device = 0, last_error = 0;
+thread_local std::vector<Config> configs;
+
+// the call that fake_fail() chose fails
+bool fails(const std::string &name) {
+    std::lock_guard<std::mutex> lock(mu);
+    return fail_at > 0 && name.find(fail_name) != std::string::npos && --fail_at == 0;
+}
+int result(int e) { if (e) last_error = e; return e; }
+void *reserve(size_t bytes) {
+    void *p = mmap(nullptr, bytes ? bytes : 1, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    if (p == MAP_FAILED) return nullptr;
+    std::lock_guard<std::mutex> lock(mu);
+    blocks[p] = bytes ? bytes : 1;
+    return p;
+}
+int release(void *p) {
+    if (!p) return kOk;
+    std::lock_guard<std::mutex> lock(mu);
+    auto it = blocks.find(p);
+    if (it == blocks.end()) return kInvalidValue;
+    munmap(p, it->second);
+    blocks.erase(it);
+    return kOk;
+}
+template <typename T> T arg(void **args, int i) { T v; memcpy(&v, args[i], sizeof(v)); return v; }
+
+// what the M-step's accumulators hold: B, the topic totals
+struct VzItem { int32_t row, count; int64_t begin; };
+struct PhiRow { int32_t word, count; int64_t begin; };
+template <typename Z> void count_slabs(Dim grid, void **a) {
+    const Z *z = arg<const Z *>(a, 0), *z_wm = arg<const Z *>(a, 6);
+    const int64_t T = arg<int64_t>(a, 1), per_block = arg<int64_t>(a, 2);
+    const int n_tot = arg<int>(a, 3), Kpad = arg<int>(a, 9);
+    for (int b = 0; b < (int)grid.x; b++) {
+        if (b < n_tot) {
+            for (int64_t t = b * per_block; t < std::min(T, (b + 1) * per_block); t++) arg<unsigned long long *>(a, 4)[z[t]]++;
+        } else {
+            const VzItem it = arg<const VzItem *>(a, 5)[b - n_tot];
+            for (int64_t t = it.begin; t < it.begin + it.count; t++) arg<int32_t *>(a, 7)[(size_t)it.row * Kpad + z_wm[t]]++;
+        }
+    }
+}
+void run(const std::string &name, Dim grid, void **a) {
+    auto is = [&](const char *s) { return name.find(s) != std::string::npos; };
+    if (is("fill_u32_kernel")) std::fill_n(arg<uint32_t *>(a, 0), arg<size_t>(a, 2), arg<uint32_t>(a, 1));
+    else if (is("count_slabs_kernelIt")) count_slabs<uint16_t>(grid, a);
+    else if (is("count_slabs_kernelIi")) count_slabs<int32_t>(grid, a);
+    else if (is("denominators_kernel")) {
+        unsigned long long *acc = arg<unsigned long long *>(a, 0), *ck = arg<unsigned long long *>(a, 1);
+        for (int k = 0; k < arg<int>(a, 3); k++) { ck[k] = acc[k]; acc[k] = 0; }
+    } else if (is("phi_tree_kernel")) {
+        const int Kpad = arg<int>(a, 8);
+        for (uint32_t r = 0; r < grid.x; r++)
+            if (arg<const PhiRow *>(a, 0)[r].count < 0) memset(arg<int32_t *>(a, 2) + (size_t)r * Kpad, 0, sizeof(int32_t) * Kpad);
+    }
+}
+}  // namespace
+
+extern "C" {
+// ---- for the tests ----
+void fake_fail(const char *name, int nth) { std::lock_guard<std::mutex> lock(mu); fail_name = name; fail_at = nth; }   // the nth call (launch) whose name contains `name`
+int fake_fail_pending() { std::lock_guard<std::mutex> lock(mu); return fail_at; }
+void fake_imitate(int on) { imitate = on; }
+void fake_clear() { std::lock_guard<std::mutex> lock(mu); launches.clear(); }
+int64_t fake_launches(const char *name, uint64_t *most_threads) {   // launches of kernels whose name contains `name`
+    std::lock_guard<std::mutex> lock(mu);
+    int64_t n = 0;
+    *most_threads = 0;
+    for (const Launch &l : launches)
+        if (l.name.find(name) != std::string::npos) { n++; *most_threads = std::max(*most_threads, (uint64_t)l.grid.x * l.block.x); }
+    return n;
+}
+uint64_t fake_blocks(const char *name) {   // workgroups of all of them
+    std::lock_guard<std::mutex> lock(mu);
+    uint64_t n = 0;
+    for (const Launch &l : launches) if (l.name.find(name) != std::string::npos) n += (uint64_t)l.grid.x * l.grid.y;
+    return n;
+}
+
+// ---- the runtime ----
+void **__hipRegisterFatBinary(const void *) { static void *handle; return &handle; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterFunction(void **, const void *host, char *, const char *name, unsigned, void *, void *, void *, void *, int *) { kernels[host] = name; }
+void __hipRegisterVar(void **, void *var, char *, char *, int, size_t size, int, int) { vars[var] = size; }
+int __hipPushCallConfiguration(Dim grid, Dim block, size_t lds, Object *stream) { configs.push_back({grid, block, lds, stream}); return kOk; }
+int __hipPopCallConfiguration(Dim *grid, Dim *block, size_t *lds, Object **stream) {
+    const Config c = configs.back();
+    configs.pop_back();
+    *grid = c.grid; *block = c.block; *lds = c.lds; *stream = c.stream;
+    return kOk;
+}
+int hipLaunchKernel(const void *fn, Dim grid, Dim block, void **args, size_t lds, Object *) {
+    const std::string name = kernels[fn];
+    if (fails(name)) return result(kOutOfMemory);
+    // threads per grid dimension below 2^32, at most 1,024 per workgroup, at least one
+    if (!grid.x || !grid.y || !grid.z || !block.x || (uint64_t)block.x * block.y * block.z > 1024 || lds > 160 * 1024 ||
+        (uint64_t)grid.x * block.x >> 32 || (uint64_t)grid.y * block.y >> 32) return result(kInvalidConfiguration);
+    { std::lock_guard<std::mutex> lock(mu); launches.push_back({name, grid, block}); }
+    if (imitate) run(name, grid, args);
+    return kOk;
+}
+int hipGetLastError() { const int e = last_error; last_error = kOk; return e; }
+const char *hipGetErrorString(int) { return "error of the stand-in runtime"; }
+int hipGetDeviceCount(int *n) { *n = 2; return kOk; }
+int hipGetDevice(int *d) { *d = device; return kOk; }
+int hipSetDevice(int d) { if (d < 0 || d > 1) return result(kInvalidDevice); device = d; return kOk; }
+int hipDeviceGetAttribute(int *v, int, int) { *v = 160 * 1024; return kOk; }
+int hipFuncGetAttributes(void *attr, const void *) { memset(attr, 0, 56); return kOk; }
+int hipFuncSetAttribute(const void *, int, int) { return kOk; }
+int hipGetSymbolAddress(void **p, const void *var) {
+    if (!vars.count(var)) return result(kInvalidValue);
+    if (!var_mem[var]) var_mem[var] = reserve(vars[var]);
+    *p = var_mem[var];
+    return kOk;
+}
+int hipMemGetInfo(size_t *f, size_t *t) { *f = *t = (size_t)288 << 30; return kOk; }
+int hipMalloc(void **p, size_t n) { if (fails("hipMalloc")) return result(kOutOfMemory); *p = reserve(n); return *p ? kOk : result(kOutOfMemory); }
+int hipFree(void *p) { return result(release(p)); }
+int hipHostMalloc(void **p, size_t n, unsigned) { if (fails("hipHostMalloc")) return result(kOutOfMemory); *p = reserve(n); return *p ? kOk : result(kOutOfMemory); }
+int hipHostFree(void *p) { return result(release(p)); }
+int hipMemcpy(void *d, const void *s, size_t n, int) { if (fails("hipMemcpy:")) return result(kInvalidValue); memcpy(d, s, n); return kOk; }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int, Object *) { if (fails("hipMemcpyAsync")) return result(kInvalidValue); memcpy(d, s, n); return kOk; }
+int hipMemsetAsync(void *d, int v, size_t n, Object *) { memset(d, v, n); return kOk; }
+int hipStreamCreate(Object **s) { *s = new Object{device}; return kOk; }
+int hipStreamCreateWithFlags(Object **s, unsigned) { return hipStreamCreate(s); }
+int hipStreamDestroy(Object *s) { delete s; return kOk; }
+int hipStreamSynchronize(Object *) { return kOk; }
+int hipStreamWaitEvent(Object *, Object *, unsigned) { return kOk; }
+int hipEventCreate(Object **e) { if (fails("hipEventCreate")) return result(kOutOfMemory); *e = new Object{device}; return kOk; }
+int hipEventCreateWithFlags(Object **e, unsigned) { return hipEventCreate(e); }
+int hipEventDestroy(Object *e) { delete e; return kOk; }
+int hipEventRecord(Object *e, Object *s) {   // both have to belong to one device
+    if (fails("hipEventRecord")) return result(kInvalidValue);
+    return e->device == (s ? s->device : device) ? kOk : result(kInvalidHandle);
+}
+int hipEventSynchronize(Object *) { return kOk; }
+int hipEventElapsedTime(float *ms, Object *, Object *) { *ms = 1.f; return kOk; }
+}
