@@ -170,6 +170,7 @@ struct saber_ctx {
     bool no_state = false;            // no assignments of its own (tokens that are only scored)
     int32_t *cwk = nullptr;           // [V_dense+1][Kpad]
     unsigned long long *ck = nullptr, *ck_acc = nullptr; // [K] topic totals; their accumulators, zero outside the M-step
+    bool acc_used = true;             // cwk or ck_acc may hold counts: set before any are added, cleared once what empties them is queued
     float *denom = nullptr;           // [K] denominators of Eq. 2
     float *phi = nullptr, *l3 = nullptr, *sumphi = nullptr;
     double *l3_64 = nullptr;          // [V][n3]
@@ -590,9 +591,24 @@ static int allow_lds(const void *kernel, size_t lds) {   // more than the defaul
     return SABER_OK;
 }
 
+// B and the accumulators of the topic totals, all zero.  An M-step finds them so, as the one before left them; a new
+// context, or one in which a call broke off in between, clears them first.
+static int launch_clear_accumulators(saber_ctx *c, bool totals) {
+    const size_t vk = ((size_t)c->V_dense + 1) * (size_t)c->Kpad;
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for((int64_t)vk, 256, 8192)), dim3(256), 0, c->stream, (uint32_t *)c->cwk, 0u, vk);
+    HIP_TRY(hipGetLastError());
+    if (totals) {
+        hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(2 * (int64_t)c->K, 256)), dim3(256), 0, c->stream, (uint32_t *)c->ck_acc, 0u, (size_t)c->K * 2);
+        HIP_TRY(hipGetLastError());
+    }
+    c->acc_used = false;
+    return SABER_OK;
+}
+
 // The first n_items slabs of the dense rows' segments into B (rows all zero on entry), and with `totals` the histogram of
 // all assignments into the accumulators of the topic totals.
 static int launch_count_slabs(saber_ctx *c, int64_t n_items, bool totals) {
+    if (c->acc_used) SABER_TRY(launch_clear_accumulators(c, true));
     // Counting in LDS, by ranges of topics, replaces one global atomic per token where K is too large for one histogram:
     // totals 0.74 -> 0.04 ms and rows 0.39 -> 0.04 ms at T = 15 M, K = 20,011, 0.13 -> 0.04 and 0.24 -> 0.03 ms at
     // T = 1.5 M, K = 70,000.
@@ -611,6 +627,7 @@ static int launch_count_slabs(saber_ctx *c, int64_t n_items, bool totals) {
     // the one that is resident
     const void *zsrc = c->n_slots ? c->z_wm : c->z;
     SABER_TRY(allow_lds(c->z16 ? (const void *)count_slabs_kernel<uint16_t> : (const void *)count_slabs_kernel<int32_t>, lds));
+    c->acc_used = true;
     if (c->z16)
         hipLaunchKernelGGL((count_slabs_kernel<uint16_t>), grid, dim3(1024), lds, c->stream, (const uint16_t *)zsrc, c->T, per_block,
                            (int)n_tot, c->ck_acc, c->vz_items, (const uint16_t *)c->z_wm, c->cwk, c->K, c->Kpad, range);
@@ -643,6 +660,7 @@ static int launch_phi(saber_ctx *c) {
         hipLaunchKernelGGL((phi_tree_kernel<int32_t>), grid, block, hist, c->stream, c->phi_rows, (const int32_t *)c->z_wm, c->cwk,
                            c->denom, c->phi, c->l3, c->l3_64, c->sumphi, c->Kpad, c->n3, c->n3pad, c->beta, range);
     HIP_TRY(hipGetLastError());
+    c->acc_used = false;
     if (c->alias_table && c->V_dense > 0) {   // measurement variant: an alias table per word on top of the tree level
         const size_t lds = alias_lds_bytes(c->K);
         if (lds > 64 * 1024)
@@ -1087,12 +1105,6 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     HIP_TRY(hipMemcpy(c->doc_ptr, doc_ptr, sizeof(int64_t) * ((size_t)D + 1), hipMemcpyHostToDevice));
     if (!h_short.empty()) HIP_TRY(hipMemcpy(c->short_docs, h_short.data(), sizeof(int32_t) * h_short.size(), hipMemcpyHostToDevice));
     if (!h_long.empty()) HIP_TRY(hipMemcpy(c->long_docs, h_long.data(), sizeof(int32_t) * h_long.size(), hipMemcpyHostToDevice));
-    if (!par) {
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for((int64_t)vk, 256, 8192)), dim3(256), 0, c->stream, (uint32_t *)c->cwk, 0u, vk);
-        HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(2 * (int64_t)K, 256)), dim3(256), 0, c->stream, (uint32_t *)c->ck_acc, 0u, (size_t)K * 2);
-        HIP_TRY(hipGetLastError());
-    }
     c->stats.tokens = T; c->stats.tiles = c->total_tiles; c->stats.chunks = (int64_t)c->chunks.size();
     if (c->no_state) { HIP_TRY(hipStreamSynchronize(c->stream)); return SABER_OK; }
 
@@ -1482,22 +1494,19 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
         if (cwk) {
             // dense rows: B is consumed (and cleared) by the Bhat kernel; rebuild it from z for export
             if (c->V_dense) {
-                SABER_TRY(launch_count_slabs(c, c->n_vz_items, false));
                 std::vector<int32_t> row_word((size_t)c->V_dense + 1);
                 HIP_TRY(hipMemcpy(row_word.data(), c->row_word, sizeof(int32_t) * row_word.size(), hipMemcpyDeviceToHost));
                 const int64_t rows = std::max<int64_t>(1, kPullPiece / ((int64_t)c->Kpad * 4));   // (Kpad * 4 is at most 1 MB)
                 std::vector<int64_t> cuts(1, 0);
                 while (cuts.back() < (int64_t)c->V_dense * c->Kpad)
                     cuts.push_back(std::min<int64_t>((int64_t)c->V_dense * c->Kpad, cuts.back() + rows * c->Kpad));
+                SABER_TRY(launch_count_slabs(c, c->n_vz_items, false));
                 SABER_TRY(pull(c, c->cwk, sizeof(int32_t), cuts, [&](int64_t i, const void *host) {
                     for (int64_t e = cuts[(size_t)i]; e < cuts[(size_t)i + 1]; e += c->Kpad)
                         memcpy(cwk + (size_t)row_word[(size_t)(e / c->Kpad)] * (size_t)c->K, (const int32_t *)host + (e - cuts[(size_t)i]),
                                sizeof(int32_t) * (size_t)c->K);
                 }));
-                const size_t vk = (size_t)c->V_dense * (size_t)c->Kpad;
-                hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for((int64_t)vk, 256, 8192)), dim3(256), 0, c->stream,
-                                   (uint32_t *)c->cwk, 0u, vk);
-                HIP_TRY(hipGetLastError());
+                SABER_TRY(launch_clear_accumulators(c, false));   // (an export that broke off leaves that to the next count)
                 HIP_TRY(hipStreamSynchronize(c->stream));
             }
             // light words: unpack the sparse rows by pieces of whole words (format conversion only)

@@ -22,3 +22,44 @@ def test_a_failed_call_does_not_fail_the_next_one(host):
             g.iterate(1)
             assert g.loglik() == 0.0                # (no kernel has run)
     """)
+
+
+@pytest.mark.parametrize("call", ["hipHostMalloc", "hipEventCreate", "hipMemcpyAsync", "hipMemcpy:", "hipEventRecord"])
+def test_counts_after_an_export_that_failed(host, call):
+    """saber_counts rebuilds B for the export; whatever fails on the way, later counts do not contain it."""
+    host("""
+        call = %r
+        counts = [3, 40000, 900, 0, 9000]
+        words = np.repeat(np.arange(5, dtype=np.int32), counts)
+        fake.fake_imitate(1)                        # (no sampling: every token keeps topic 0)
+        g = pk.Saber(np.r_[0, 500, words.size], words, 5, 100, 0.1, 0.01, 3, light_word_tokens=-1)
+        nth = 0
+        while True:
+            nth += 1
+            fake.fake_fail(call.encode(), nth)
+            code = code_of(lambda: g.counts(want_cd=False, want_ck=False))
+            if fake.fake_fail_pending() > 0: break  # fewer calls than that
+            assert code in (0, -2, -3)              # (memory refused: another kind is used)
+            fake.fake_fail(b"", 0)
+            if nth %% 2:
+                g.iterate(1)
+            cwk, ck = g.counts(want_cd=False)[3:]
+            assert np.array_equal(cwk[:, 0], counts) and not cwk[:, 1:].any(), (nth, cwk)
+            if nth == 1: g.set_z(np.zeros(words.size, np.int32), 0)
+        assert nth > 1
+    """ % call)
+
+
+def test_topic_totals_after_an_iteration_that_failed(host):
+    """The accumulators of the M-step are clear at its start, also where the one before broke off."""
+    host("""
+        words = np.zeros(50000, np.int32)
+        fake.fake_imitate(1)
+        g = pk.Saber(np.r_[0, 500, words.size], words, 1, 100, 0.1, 0.01, 3, light_word_tokens=-1)
+        for kernel in (b"denominators_kernel", b"phi_tree_kernel"):
+            fake.fake_fail(kernel, 1)
+            assert code_of(lambda: g.iterate(1)) == -2
+            g.set_z(np.zeros(words.size, np.int32), 0)
+            cwk, ck = g.counts(want_cd=False)[3:]
+            assert ck[0] == 50000 and cwk[0, 0] == 50000, (kernel, ck[0], cwk[0, 0])
+    """)
