@@ -1354,15 +1354,28 @@ extern "C" int saber_iterate(saber_ctx *c, int32_t n) {
 // ------------------------------------------------------------------------------------------------
 // outputs
 // ------------------------------------------------------------------------------------------------
+// Makes a device current for a scope; the one that was current before comes back at its end.
+struct DeviceScope {
+    int before = -1;
+    explicit DeviceScope(int device) {
+        int now = device;
+        if (hipGetDevice(&now) == hipSuccess && now != device && hipSetDevice(device) == hipSuccess) before = now;
+    }
+    ~DeviceScope() { if (before >= 0) (void)hipSetDevice(before); }
+};
+
 // Results on their way to the caller's memory: piece i, the elements [cuts[i], cuts[i + 1]) of the device array, is copied
 // into pinned staging on the context's stream and handed to consume(i, host pointer), which puts it where it belongs; up to
 // kPullThreads threads consume while the next pieces are in flight.  A caller's fresh pages cost far more than the link:
 // into ordinary memory a copy of 100 M assignments as int32 took 44 ms, as 16 bits through this path 8.
 // The threads end before the call returns; consume must not throw.  No piece may exceed kPullPiece bytes.
+// Events belong to the device that is current when they are made, and only its streams record them; the caller may have
+// another one current.
 template <typename F>
 static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<int64_t> &cuts, F consume) {
     const int64_t np = (int64_t)cuts.size() - 1;
     if (np <= 0) return SABER_OK;
+    const DeviceScope scope(c->device);
     size_t largest = 1;
     for (int64_t i = 0; i < np; i++) largest = std::max(largest, (size_t)(cuts[(size_t)i + 1] - cuts[(size_t)i]) * elem);
     largest = (largest + 255) & ~(size_t)255;
@@ -1672,9 +1685,11 @@ extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const 
         if (rc == SABER_OK && z_init) rc = saber_set_z(obs, z_init, 0);
         if (rc == SABER_OK) rc = foldin_iterate(obs, n_foldin);
         if (rc == SABER_OK && z_out) {
-            std::swap(obs->staging, m->staging);   // the model's, which outlives the call
+            // the model's, which outlives the call (its events are of the model's device)
+            const bool borrow = obs->device == m->device;
+            if (borrow) std::swap(obs->staging, m->staging);
             rc = saber_get_z(obs, z_out);
-            std::swap(obs->staging, m->staging);
+            if (borrow) std::swap(obs->staging, m->staging);
         }
         if (rc == SABER_OK) rc = create_ctx(&scr, sptr.data(), sw.data(), D, m->V, m->K, m->alpha, m->beta, seed, &opt, m, true);
         double ll = 0.0;

@@ -63,3 +63,22 @@ def test_topic_totals_after_an_iteration_that_failed(host):
             cwk, ck = g.counts(want_cd=False)[3:]
             assert ck[0] == 50000 and cwk[0, 0] == 50000, (kernel, ck[0], cwk[0, 0])
     """)
+
+
+@pytest.mark.parametrize("K", [100, 70000])
+def test_results_with_another_device_current(host, K):
+    """Results are copied out on the context's own device, whichever the caller has current."""
+    host("""
+        words = np.arange(400000, dtype=np.int32) %% 50
+        doc_ptr = np.r_[0, np.arange(999, words.size, 1000), words.size]
+        g = pk.Saber(doc_ptr, words, 50, %d, 0.1, 0.01, 3)
+        first = pk.Saber(doc_ptr, words, 50, %d, 0.1, 0.01, 3)
+        first.get_z()
+        fake.hipSetDevice(1)
+        now = ctypes.c_int()
+        for use in (g.get_z, lambda: g.counts(want_cwk=False), g.counts, first.get_z,
+                    lambda: first.holdout_loglik(np.array([0, 5000]), words[:5000], words[:5000] %% 2 == 0, 1, 5)):
+            use()
+            fake.hipGetDevice(ctypes.byref(now))
+            assert now.value == 1
+    """ % (K, K))
