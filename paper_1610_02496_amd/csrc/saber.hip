@@ -221,6 +221,10 @@ static inline int grid_for(int64_t n, int block, int cap = 65535 * 16) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(g, cap));
 }
 
+// A grid has at most 2^32 - 1 threads in a dimension: what a launch of workgroups of `block` threads can take.  A longer
+// list of work is launched by pieces.
+static inline int64_t most_blocks(int block) { return 0xffffffffll / block; }
+
 extern "C" int saber_set_hooks(void *(*alloc)(size_t), void (*dealloc)(void *), void *hip_stream) {
     if ((alloc == nullptr) != (dealloc == nullptr))
         return fail(SABER_EINVAL, "saber_set_hooks: alloc and dealloc must be given together");
@@ -1822,9 +1826,11 @@ extern "C" int saber_get_phi(saber_ctx *c, const int32_t *words, int32_t m, floa
         (rc = dev_alloc(c->hooks, &dw, (size_t)m)) || (rc = dev_alloc(c->hooks, &drow, (size_t)m))) { cleanup(); return rc; }
     hipError_t e = hipMemcpy(dw, words, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(drow, rows.data(), sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(phi_export_kernel, dim3((unsigned)m), dim3(256), 0, c->stream, drow, c->phi,
-                           c->phi + (size_t)c->V_dense * (size_t)c->Kpad, c->wrec, c->lw_ent, c->lw_phi, c->K, c->Kpad, c->topic_bits, drows);
+    for (int64_t i = 0, n; i < m && e == hipSuccess; i += n) {
+        n = std::min<int64_t>(m - i, most_blocks(256));
+        hipLaunchKernelGGL(phi_export_kernel, dim3((unsigned)n), dim3(256), 0, c->stream, drow + i, c->phi,
+                           c->phi + (size_t)c->V_dense * (size_t)c->Kpad, c->wrec, c->lw_ent, c->lw_phi, c->K, c->Kpad, c->topic_bits,
+                           drows + (size_t)i * (size_t)c->K);
         e = hipGetLastError();
     }
     if (e == hipSuccess && prefix) {

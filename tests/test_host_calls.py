@@ -82,3 +82,15 @@ def test_results_with_another_device_current(host, K):
             fake.hipGetDevice(ctypes.byref(now))
             assert now.value == 1
     """ % (K, K))
+
+
+def test_rows_of_more_words_than_a_launch_takes(host):
+    """saber_get_phi: one workgroup per word asked for, words in any number (repeats count)."""
+    host("""
+        words = np.zeros(100, np.int32)
+        g = pk.Saber(np.r_[0, 50, 100], words, 3, 2, 0.1, 0.01, 3)
+        m = (1 << 24) + 1
+        g.get_phi(np.zeros(m, np.int32))
+        n, blocks, most = launches("phi_export")
+        assert blocks == m and most < 1 << 32
+    """)
