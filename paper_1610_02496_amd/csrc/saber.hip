@@ -654,16 +654,22 @@ static int launch_phi(saber_ctx *c) {
     HIP_TRY(hipGetLastError());
     // kPhiSteps steps of four columns per thread at a time: up to 12,288 topics (48 KB of LDS: two workgroups of 1,024
     // threads per CU)
-    const dim3 grid((unsigned)(c->V_dense + 1)), block((unsigned)phi_block_threads(c));
+    const dim3 block((unsigned)phi_block_threads(c));
     const int range = std::min(c->Kpad, kPhiSteps * 4 * (int)block.x);
     const size_t hist = (size_t)range * sizeof(uint32_t);
-    if (c->z16)
-        hipLaunchKernelGGL((phi_tree_kernel<uint16_t>), grid, block, hist, c->stream, c->phi_rows, (const uint16_t *)c->z_wm, c->cwk,
-                           c->denom, c->phi, c->l3, c->l3_64, c->sumphi, c->Kpad, c->n3, c->n3pad, c->beta, range);
-    else
-        hipLaunchKernelGGL((phi_tree_kernel<int32_t>), grid, block, hist, c->stream, c->phi_rows, (const int32_t *)c->z_wm, c->cwk,
-                           c->denom, c->phi, c->l3, c->l3_64, c->sumphi, c->Kpad, c->n3, c->n3pad, c->beta, range);
-    HIP_TRY(hipGetLastError());
+    const int64_t rows = (int64_t)c->V_dense + 1;
+    for (int64_t r = 0, n; r < rows; r += n) {
+        n = std::min(rows - r, most_blocks((int)block.x));
+        const dim3 grid((unsigned)n);
+        const size_t at = (size_t)r * (size_t)c->Kpad;
+        if (c->z16)
+            hipLaunchKernelGGL((phi_tree_kernel<uint16_t>), grid, block, hist, c->stream, c->phi_rows + r, (const uint16_t *)c->z_wm, c->cwk + at,
+                               c->denom, c->phi + at, c->l3, c->l3_64, c->sumphi, c->Kpad, c->n3, c->n3pad, c->beta, range);
+        else
+            hipLaunchKernelGGL((phi_tree_kernel<int32_t>), grid, block, hist, c->stream, c->phi_rows + r, (const int32_t *)c->z_wm, c->cwk + at,
+                               c->denom, c->phi + at, c->l3, c->l3_64, c->sumphi, c->Kpad, c->n3, c->n3pad, c->beta, range);
+        HIP_TRY(hipGetLastError());
+    }
     c->acc_used = false;
     if (c->alias_table && c->V_dense > 0) {   // measurement variant: an alias table per word on top of the tree level
         const size_t lds = alias_lds_bytes(c->K);

@@ -94,3 +94,15 @@ def test_rows_of_more_words_than_a_launch_takes(host):
         n, blocks, most = launches("phi_export")
         assert blocks == m and most < 1 << 32
     """)
+
+
+@pytest.mark.parametrize("V,K,threads", [(1 << 23, 1025, 512), (1 << 22, 2049, 1024)])
+def test_dense_rows_of_more_words_than_a_launch_takes(host, V, K, threads):
+    """One workgroup per dense row, of more threads the longer the row."""
+    host("""
+        V, K, threads = %d, %d, %d
+        words = np.array([0, V - 1, 5], np.int32)
+        g = pk.Saber(np.array([0, 1, 3]), words, V, K, 0.1, 0.01, 3, light_word_tokens=-1)
+        n, blocks, most = launches("phi_tree")
+        assert n == 2 and blocks == V + 1 and most < 1 << 32 and most %% threads == 0
+    """ % (V, K, threads))
