@@ -474,12 +474,18 @@ static int launch_segmented_count(saber_ctx *c, const SegLists &a, const SegList
             const void *fn = c->z16 ? (const void *)count_dz_kernel<uint16_t> : (const void *)count_dz_kernel<int32_t>;
             HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         }
-        const dim3 grid((unsigned)(na + nb)), blk((unsigned)block);
-        if (c->z16)
-            hipLaunchKernelGGL((count_dz_kernel<uint16_t>), grid, blk, lds, c->stream, ga, na, gb, c->topic_bits, c->nwords, entries);
-        else
-            hipLaunchKernelGGL((count_dz_kernel<int32_t>), grid, blk, lds, c->stream, ga, na, gb, c->topic_bits, c->nwords, entries);
-        HIP_TRY(hipGetLastError());
+        for (int64_t i = 0, n; i < na + nb; i += n) {   // segments [i, i + n) of both lists: one launch unless there are more than a grid takes
+            n = std::min(na + nb - i, most_blocks(block));
+            const int64_t left = std::max<int64_t>(0, std::min(i + n, na) - i);   // of the first list
+            SegGroup pa = ga, pb = gb;
+            if (left) pa.list += i; else pb.list += i - na;
+            const dim3 grid((unsigned)n), blk((unsigned)block);
+            if (c->z16)
+                hipLaunchKernelGGL((count_dz_kernel<uint16_t>), grid, blk, lds, c->stream, pa, left, pb, c->topic_bits, c->nwords, entries);
+            else
+                hipLaunchKernelGGL((count_dz_kernel<int32_t>), grid, blk, lds, c->stream, pa, left, pb, c->topic_bits, c->nwords, entries);
+            HIP_TRY(hipGetLastError());
+        }
     }
     return SABER_OK;
 }

@@ -106,3 +106,15 @@ def test_dense_rows_of_more_words_than_a_launch_takes(host, V, K, threads):
         n, blocks, most = launches("phi_tree")
         assert n == 2 and blocks == V + 1 and most < 1 << 32 and most %% threads == 0
     """ % (V, K, threads))
+
+
+def test_more_documents_and_light_words_than_a_launch_takes(host):
+    """Documents and light words share the launches of the segmented count, one wavefront each."""
+    host("""
+        D = (1 << 26) - 4
+        doc_ptr = np.zeros(D + 1, np.int64)
+        doc_ptr[D:] = 5
+        g = pk.Saber(doc_ptr, np.arange(5, dtype=np.int32), 10, 40, 0.1, 0.01, 3)
+        n, blocks, most = launches("count_dz")
+        assert n == 2 and blocks == D + 10 and most < 1 << 32, (n, blocks, most)
+    """)
