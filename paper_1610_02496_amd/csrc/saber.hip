@@ -356,20 +356,23 @@ static int check_estep_lds_layout() {
 template <int MODE>
 static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
     for (const TileClass &cl : ch.classes) {
-        EStepParams p = p0;
-        p.tiles = p0.tiles + cl.first;
-        if (p0.out_ll) p.out_ll = p0.out_ll + cl.first;
-        p.first_light = (int32_t)cl.n_dense;
-        const dim3 grid((unsigned)cl.count), block((unsigned)cl.block);
-        const size_t lds = estep_lds_bytes(c, MODE);
-        if (c->staged) {
-            if (c->z16) launch_estep_b16<MODE, true, uint16_t>(c, grid, block, lds, p);
-            else launch_estep_b16<MODE, true, int32_t>(c, grid, block, lds, p);
-        } else {
-            if (c->z16) launch_estep_b16<MODE, false, uint16_t>(c, grid, block, lds, p);
-            else launch_estep_b16<MODE, false, int32_t>(c, grid, block, lds, p);
+        for (int64_t i = 0, n; i < cl.count; i += n) {
+            n = std::min(cl.count - i, most_blocks(cl.block));
+            EStepParams p = p0;
+            p.tiles = p0.tiles + cl.first + i;
+            if (p0.out_ll) p.out_ll = p0.out_ll + cl.first + i;
+            p.first_light = (int32_t)std::max<int64_t>(0, std::min(cl.n_dense - i, n));
+            const dim3 grid((unsigned)n), block((unsigned)cl.block);
+            const size_t lds = estep_lds_bytes(c, MODE);
+            if (c->staged) {
+                if (c->z16) launch_estep_b16<MODE, true, uint16_t>(c, grid, block, lds, p);
+                else launch_estep_b16<MODE, true, int32_t>(c, grid, block, lds, p);
+            } else {
+                if (c->z16) launch_estep_b16<MODE, false, uint16_t>(c, grid, block, lds, p);
+                else launch_estep_b16<MODE, false, int32_t>(c, grid, block, lds, p);
+            }
+            HIP_TRY(hipGetLastError());
         }
-        HIP_TRY(hipGetLastError());
     }
     return SABER_OK;
 }

@@ -118,3 +118,20 @@ def test_more_documents_and_light_words_than_a_launch_takes(host):
         n, blocks, most = launches("count_dz")
         assert n == 2 and blocks == D + 10 and most < 1 << 32, (n, blocks, most)
     """)
+
+
+def test_more_tiles_than_a_launch_takes(host):
+    """One workgroup per tile; a word that occurs has at least one."""
+    host("""
+        V = (1 << 22) + 3
+        words = np.arange(V, dtype=np.int32)
+        doc_ptr = np.r_[np.arange(0, V, 1000), V]
+        for opts in ({"stage_phi": 0, "block_threads": 1024}, {"block_threads": 1024}):
+            g = pk.Saber(doc_ptr, words, V, 20, 0.1, 0.01, 3, **opts)
+            for use in (lambda: g.iterate(1), g.loglik, lambda: g.token_probs([0, V - 1])):
+                fake.fake_clear()
+                use()
+                n, blocks, most = launches("estep_kernel")
+                assert blocks == V and most < 1 << 32, (n, blocks, most)
+            g.close()
+    """)
