@@ -55,8 +55,8 @@ typedef struct saber_options {
                                a chunk's sampling pass re-reads stay in the 256 MB Infinity Cache; always at least one
                                chunk per 2^30 tokens */
     int32_t block_threads;  /* threads per workgroup of the sampling kernel (multiple of 64 up to 1024);
-                               default: the size that lets a CU hold the most wavefronts given the LDS the Bhat row takes,
-                               1,024 when the row is not kept in LDS */
+                               default: the size that lets a CU hold the most wavefronts given the LDS the Bhat row takes;
+                               when the row is not kept in LDS, 256 up to K = 2,048 and 1,024 beyond */
     int32_t tile_tokens;    /* most tokens of one word handled by one workgroup; default 0: a 8192th of a chunk's tokens,
                                not below K / 16 (64 to 256) and not above 32,768 */
     int32_t stage_phi;      /* 1: keep the word's Bhat row in LDS when it fits (up to 150 KB: K <= 37,800), 0: always

@@ -1261,11 +1261,15 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
     if (opt_in == nullptr || opt_in->block_threads <= 0) {
         // automatic workgroup size: the one that lets a CU hold the most wavefronts given the LDS footprint; ties go to
         // the smaller size.  A row that is not staged is gathered through the caches: the more of a CU's wavefronts
-        // work on the same row the better (T = 20 M, K = 45,000: 18.9, 14.5 and 10.6 ms with 256, 512 and 1,024 threads)
+        // work on the same row the better, once it is too long for the 32 KB of a CU's L1 to hold several.  An iteration
+        // with 256, 512 and 1,024 threads at V = 50,000, T = 20 M: K = 300 2.03, 2.09 and 2.25 ms, K = 1,000 2.76, 2.69 and
+        // 2.81, K = 3,000 4.74, 4.00 and 3.47, K = 10,000 9.16, 7.00 and 6.01, K = 45,000 15.6, 12.9 and 10.6; at V = 100,000,
+        // T = 3 M, where most words have few tokens: K = 1,000 0.66, 0.77 and 0.98, K = 3,000 2.16, 2.07 and 2.26 in the
+        // first iterations and 1.41, 1.43 and 1.62 in later ones, K = 45,000 15.8, 13.8 and 12.7, and 6.98, 6.96 and 7.21.
         int best = 256, best_waves = 0;
         for (int block : {256, 512, 1024}) {
             const int waves = estep_waves_per_cu(c, block);
-            if (waves > best_waves || !c->staged) { best_waves = waves; best = block; }
+            if (waves > best_waves || (!c->staged && K > 2048)) { best_waves = waves; best = block; }
         }
         c->opt.block_threads = best;
         c->auto_light_block = c->opt.light_block_threads <= 0;

@@ -107,6 +107,12 @@ uint64_t fake_blocks(const char *name) {   // workgroups of all of them
     for (const Launch &l : launches) if (l.name.find(name) != std::string::npos) n += (uint64_t)l.grid.x * l.grid.y;
     return n;
 }
+int fake_block(const char *name) {   // threads per workgroup of the last of them
+    std::lock_guard<std::mutex> lock(mu);
+    int n = 0;
+    for (const Launch &l : launches) if (l.name.find(name) != std::string::npos) n = (int)l.block.x;
+    return n;
+}
 
 // ---- the runtime ----
 void **__hipRegisterFatBinary(const void *) { static void *handle; return &handle; }

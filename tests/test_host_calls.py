@@ -135,3 +135,14 @@ def test_more_tiles_than_a_launch_takes(host):
                 assert blocks == V and most < 1 << 32, (n, blocks, most)
             g.close()
     """)
+
+
+@pytest.mark.parametrize("K,threads", [(100, 256), (2048, 256), (2049, 1024), (60000, 1024), (70000, 1024)])
+def test_threads_of_a_workgroup_whose_row_is_not_staged(host, K, threads):
+    """Large workgroups are for rows too long for the first-level cache; with short ones they lose."""
+    host("""
+        words = np.arange(5000, dtype=np.int32) %% 40
+        g = pk.Saber(np.r_[0, 2000, 5000], words, 40, %d, 0.1, 0.01, 3, stage_phi=0)
+        g.iterate(1)
+        assert fake.fake_block(b"estep_kernel") == %d
+    """ % (K, threads))
