@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <thread>
 #include <vector>
@@ -113,6 +114,7 @@ struct Chunk {
 constexpr int kMaxSlots = 8;
 constexpr int kPullSlots = 12, kPullThreads = 8;      // see pull()
 constexpr int64_t kPullPiece = 1 << 20;               // bytes
+constexpr int64_t kPullFew = 4 << 20, kPullMany = 8 << 20;   // bytes written for the caller
 // Pinned staging of results and the events of its slots, made by the first call that needs them.
 struct Staging { char *buf = nullptr; size_t bytes = 0; bool pinned = false; hipEvent_t ev[kPullSlots] = {}; };
 
@@ -1387,22 +1389,48 @@ struct DeviceScope {
     ~DeviceScope() { if (before >= 0) (void)hipSetDevice(before); }
 };
 
-// Results on their way to the caller's memory: piece i, the elements [cuts[i], cuts[i + 1]) of the device array, is copied
-// into pinned staging on the context's stream and handed to consume(i, host pointer), which puts it where it belongs; up to
-// kPullThreads threads consume while the next pieces are in flight.  A caller's fresh pages cost far more than the link:
-// into ordinary memory a copy of 100 M assignments as int32 took 44 ms, as 16 bits through this path 8.
+// Bytes of the pieces that so many bytes for the caller are cut into; a longer row is a piece of its own.
+static int64_t pull_piece(int64_t out_bytes) { return out_bytes > kPullMany ? kPullPiece : kPullPiece / 4; }
+
+// Results on their way to the caller's memory: piece i, the elements [cuts[i], cuts[i + 1]) of the device array, is handed
+// to consume(i, host pointer), which puts it where it belongs.  How that is done depends on the bytes written for the caller
+// (out_bytes):
+//   * above kPullMany by way of pinned staging of kPullSlots slots, which up to kPullThreads threads consume while the next
+//     pieces are in flight.  A caller's fresh pages cost far more than the link: into ordinary memory a copy of 100 M
+//     assignments as int32 took 44 ms, as 16 bits through this path 8;
+//   * below, the calling thread alone, out of two small slots: threads, and the first touch of pinned memory, cost a
+//     context's first call a millisecond (A in CSR of T = 1 M, K = 100, first and later calls: 1.62 and 0.25 ms with them,
+//     0.36 and 0.34 this way, 0.45 and 0.41 by a plain copy);
+//   * up to `few` bytes by plain copies into ordinary memory (the assignments of T = 300,000: 0.07 and 0.05 ms, 0.24 and 0.06
+//     through two slots).  consume() hides under no copy then, so `few` is 4 MB where it only moves data (B of 2,000 words,
+//     K = 500: 0.23 ms, two slots 0.36) and 1 MB where it takes entries apart.
 // The threads end before the call returns; consume must not throw.  No piece may exceed kPullPiece bytes.
 // Events belong to the device that is current when they are made, and only its streams record them; the caller may have
 // another one current.
 template <typename F>
-static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<int64_t> &cuts, F consume) {
+static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<int64_t> &cuts, int64_t out_bytes, int64_t few, F consume) {
     const int64_t np = (int64_t)cuts.size() - 1;
     if (np <= 0) return SABER_OK;
-    const DeviceScope scope(c->device);
+    auto piece_bytes = [&](int64_t k) { return (size_t)(cuts[(size_t)k + 1] - cuts[(size_t)k]) * elem; };
+    auto source = [&](int64_t k) { return (const char *)dev + (size_t)cuts[(size_t)k] * elem; };
     size_t largest = 1;
-    for (int64_t i = 0; i < np; i++) largest = std::max(largest, (size_t)(cuts[(size_t)i + 1] - cuts[(size_t)i]) * elem);
-    largest = (largest + 255) & ~(size_t)255;
-    const int slots = (int)std::min<int64_t>(np, kPullSlots);
+    for (int64_t i = 0; i < np; i++) largest = std::max(largest, piece_bytes(i));
+    if (out_bytes <= few) {
+        const int64_t group = kPullPiece / (int64_t)elem;   // as many pieces at a time as that
+        const std::unique_ptr<char[]> host(new char[std::max(largest, (size_t)std::min(cuts.back(), group) * elem)]);
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        for (int64_t k = 0, end; k < np; k = end) {
+            for (end = k + 1; end < np && cuts[(size_t)end + 1] - cuts[(size_t)k] <= group;) end++;
+            const size_t bytes = (size_t)(cuts[(size_t)end] - cuts[(size_t)k]) * elem;
+            if (bytes) HIP_TRY(hipMemcpy(host.get(), source(k), bytes, hipMemcpyDeviceToHost));
+            for (int64_t i = k; i < end; i++) consume(i, (const void *)(host.get() + (size_t)(cuts[(size_t)i] - cuts[(size_t)k]) * elem));
+        }
+        return SABER_OK;
+    }
+    const DeviceScope scope(c->device);
+    const bool many = out_bytes > kPullMany;
+    largest = (std::max(largest, (size_t)pull_piece(out_bytes)) + 255) & ~(size_t)255;   // (so that the slots serve later calls as well)
+    const int slots = many ? (int)std::min<int64_t>(np, kPullSlots) : 2;
     if (c->staging.bytes < largest * (size_t)slots) {
         if (c->staging.buf) { if (c->staging.pinned) (void)hipHostFree(c->staging.buf); else free(c->staging.buf); }
         c->staging.buf = nullptr; c->staging.bytes = 0; c->staging.pinned = true;
@@ -1416,15 +1444,14 @@ static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<in
     }
     for (int i = 0; i < slots; i++)
         if (!c->staging.ev[i]) HIP_TRY(hipEventCreateWithFlags(&c->staging.ev[i], hipEventDisableTiming));
+    auto slot = [&](int64_t k) { return c->staging.buf + (size_t)(k % slots) * largest; };
     auto request = [&](int64_t k) {
-        const size_t bytes = (size_t)(cuts[(size_t)k + 1] - cuts[(size_t)k]) * elem;
         hipError_t e = hipSuccess;
-        if (bytes) e = hipMemcpyAsync(c->staging.buf + (size_t)(k % slots) * largest, (const char *)dev + (size_t)cuts[(size_t)k] * elem,
-                                      bytes, hipMemcpyDeviceToHost, c->stream);
+        if (piece_bytes(k)) e = hipMemcpyAsync(slot(k), source(k), piece_bytes(k), hipMemcpyDeviceToHost, c->stream);
         if (e == hipSuccess) e = hipEventRecord(c->staging.ev[k % slots], c->stream);
         return e;
     };
-    std::vector<std::atomic<char>> done((size_t)np);
+    std::vector<std::atomic<char>> done(many ? (size_t)np : 0);
     for (auto &d : done) d.store(0, std::memory_order_relaxed);
     std::atomic<int64_t> issued{0}, next{0};
     std::atomic<int> error{(int)hipSuccess};
@@ -1439,30 +1466,34 @@ static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<in
             }
             const hipError_t e = hipEventSynchronize(c->staging.ev[k % slots]);
             if (e != hipSuccess) { error.store((int)e); return; }
-            consume(k, (const void *)(c->staging.buf + (size_t)(k % slots) * largest));
+            consume(k, (const void *)slot(k));
             done[(size_t)k].store(1, std::memory_order_release);
         }
     };
     std::vector<std::thread> threads;
-    if (np > 2) {
+    if (many && np > 2) {
         try {
             threads.reserve(kPullThreads);
             for (int64_t i = 0; i < std::min<int64_t>(np, kPullThreads); i++) threads.emplace_back(work);
         } catch (...) {}   // with fewer threads, or none, it only takes longer
     }
     hipError_t e = hipSuccess;
-    for (int64_t k = 0; k < np && e == hipSuccess; k++) {
-        if (threads.empty()) {
-            e = request(k);
+    if (threads.empty()) {
+        if (slots > 1) e = request(0);
+        for (int64_t k = 0; k < np && e == hipSuccess; k++) {   // piece k + 1 goes to the other slot, free since piece k - 1
+            if (slots == 1) e = request(k);
+            else if (k + 1 < np) e = request(k + 1);
             if (e == hipSuccess) e = hipEventSynchronize(c->staging.ev[k % slots]);
-            if (e == hipSuccess) consume(k, (const void *)(c->staging.buf + (size_t)(k % slots) * largest));
-            continue;
+            if (e == hipSuccess) consume(k, (const void *)slot(k));
         }
+    }
+    for (int64_t k = 0; k < np && !threads.empty(); k++) {
         while (k >= slots && !done[(size_t)(k - slots)].load(std::memory_order_acquire) && error.load() == (int)hipSuccess)
             std::this_thread::yield();
         if (error.load() != (int)hipSuccess) break;
         e = request(k);
-        if (e == hipSuccess) issued.store(k + 1, std::memory_order_release);
+        if (e != hipSuccess) break;
+        issued.store(k + 1, std::memory_order_release);
     }
     if (e != hipSuccess) error.store((int)e);
     for (auto &t : threads) t.join();
@@ -1474,11 +1505,16 @@ static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<in
 // n assignments from the device array z (of the context's assignment type) to the caller's int32
 static int pull_z(saber_ctx *c, const void *z, int64_t n, int32_t *out) {
     const int64_t elem = c->z16 ? 2 : 4;
+    if (!c->z16 && n * elem <= kPullMany) {   // nothing to convert: straight to the caller's memory
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        HIP_TRY(hipMemcpy(out, z, (size_t)n * 4, hipMemcpyDeviceToHost));
+        return SABER_OK;
+    }
     // (pieces of a sixteenth of the array, 128 K to 512 K assignments: a small one is shared by the threads as well)
     const int64_t piece = std::min<int64_t>(kPullPiece / elem, std::max<int64_t>(131072, (n / 16 + 4095) & ~4095ll));
     std::vector<int64_t> cuts(1, 0);
     while (cuts.back() < n) cuts.push_back(std::min<int64_t>(n, cuts.back() + piece));
-    return pull(c, z, (size_t)elem, cuts, [&](int64_t i, const void *host) {
+    return pull(c, z, (size_t)elem, cuts, n * 4, kPullFew, [&](int64_t i, const void *host) {
         const int64_t a = cuts[(size_t)i], m = cuts[(size_t)i + 1] - a;
         if (elem == 4) { memcpy(out + a, host, (size_t)m * 4); return; }
         const uint16_t *src = (const uint16_t *)host;
@@ -1510,12 +1546,13 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
             if (cd_topic || cd_count) {
                 // unpack the device rows by pieces of whole documents (format conversion only)
                 std::vector<int64_t> cuts(1, 0), piece_doc(1, 0);
+                const int64_t out_bytes = 4 * std::max(2 * cd_row_ptr[c->D], c->cd_cap), piece = pull_piece(out_bytes);
                 for (int64_t d = 0; d < c->D; d++) {
                     const int64_t end = d + 1 < c->D ? (int64_t)rec[(size_t)d + 1].x * 32 : c->cd_cap;
-                    if ((end - cuts.back()) * 4 > kPullPiece) { cuts.push_back((int64_t)rec[(size_t)d].x * 32); piece_doc.push_back(d); }
+                    if ((end - cuts.back()) * 4 > piece) { cuts.push_back((int64_t)rec[(size_t)d].x * 32); piece_doc.push_back(d); }
                 }
                 cuts.push_back(c->cd_cap); piece_doc.push_back(c->D);
-                SABER_TRY(pull(c, c->cd_ent, sizeof(uint32_t), cuts, [&](int64_t i, const void *host) {
+                SABER_TRY(pull(c, c->cd_ent, sizeof(uint32_t), cuts, out_bytes, kPullFew / 4, [&](int64_t i, const void *host) {
                     for (int64_t d = piece_doc[(size_t)i]; d < piece_doc[(size_t)i + 1]; d++) {
                         const uint32_t *row = (const uint32_t *)host + ((int64_t)rec[(size_t)d].x * 32 - cuts[(size_t)i]);
                         int64_t o = cd_row_ptr[d];
@@ -1532,12 +1569,13 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
             if (c->V_dense) {
                 std::vector<int32_t> row_word((size_t)c->V_dense + 1);
                 HIP_TRY(hipMemcpy(row_word.data(), c->row_word, sizeof(int32_t) * row_word.size(), hipMemcpyDeviceToHost));
-                const int64_t rows = std::max<int64_t>(1, kPullPiece / ((int64_t)c->Kpad * 4));   // (Kpad * 4 is at most 1 MB)
+                const int64_t out_bytes = 4 * (int64_t)c->V_dense * c->Kpad;
+                const int64_t rows = std::max<int64_t>(1, pull_piece(out_bytes) / ((int64_t)c->Kpad * 4));   // (Kpad * 4 is at most 1 MB)
                 std::vector<int64_t> cuts(1, 0);
                 while (cuts.back() < (int64_t)c->V_dense * c->Kpad)
                     cuts.push_back(std::min<int64_t>((int64_t)c->V_dense * c->Kpad, cuts.back() + rows * c->Kpad));
                 SABER_TRY(launch_count_slabs(c, c->n_vz_items, false));
-                SABER_TRY(pull(c, c->cwk, sizeof(int32_t), cuts, [&](int64_t i, const void *host) {
+                SABER_TRY(pull(c, c->cwk, sizeof(int32_t), cuts, out_bytes, kPullFew, [&](int64_t i, const void *host) {
                     for (int64_t e = cuts[(size_t)i]; e < cuts[(size_t)i + 1]; e += c->Kpad)
                         memcpy(cwk + (size_t)row_word[(size_t)(e / c->Kpad)] * (size_t)c->K, (const int32_t *)host + (e - cuts[(size_t)i]),
                                sizeof(int32_t) * (size_t)c->K);
@@ -1552,16 +1590,17 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
                 HIP_TRY(hipMemcpy(wrec.data(), c->wrec, sizeof(uint2) * wrec.size(), hipMemcpyDeviceToHost));
                 HIP_TRY(hipMemcpy(lwords.data(), c->light_words, sizeof(int32_t) * lwords.size(), hipMemcpyDeviceToHost));
                 std::vector<int64_t> cuts(1, 0), piece_word(1, 0);
-                // (a word's row of K counts has to be cleared as well: at most 1 MB of those per piece too)
-                const int64_t most = std::max<int64_t>(1, kPullPiece / (4 * (int64_t)c->K));
+                // (a word's row of K counts has to be cleared as well: threads share those out by at most 1 MB per piece)
+                const int64_t out_bytes = 4 * std::max((int64_t)c->V_light * c->K, c->lw_cap), piece = pull_piece(out_bytes);
+                const int64_t most = out_bytes > kPullMany ? std::max<int64_t>(1, kPullPiece / (4 * (int64_t)c->K)) : c->V_light;
                 for (int64_t li = 0; li < c->V_light; li++) {
                     const int64_t end = li + 1 < c->V_light ? (int64_t)wrec[(size_t)li + 1].x * 32 : c->lw_cap;
-                    if ((end - cuts.back()) * 4 > kPullPiece || li - piece_word.back() >= most) {
+                    if ((end - cuts.back()) * 4 > piece || li - piece_word.back() >= most) {
                         cuts.push_back((int64_t)wrec[(size_t)li].x * 32); piece_word.push_back(li);
                     }
                 }
                 cuts.push_back(c->lw_cap); piece_word.push_back(c->V_light);
-                SABER_TRY(pull(c, c->lw_ent, sizeof(uint32_t), cuts, [&](int64_t i, const void *host) {
+                SABER_TRY(pull(c, c->lw_ent, sizeof(uint32_t), cuts, out_bytes, kPullFew, [&](int64_t i, const void *host) {
                     for (int64_t li = piece_word[(size_t)i]; li < piece_word[(size_t)i + 1]; li++) {
                         int32_t *row = cwk + (size_t)lwords[(size_t)li] * (size_t)c->K;
                         memset(row, 0, sizeof(int32_t) * (size_t)c->K);

@@ -26,14 +26,17 @@ std::map<const void *, std::string> kernels;
 std::map<const void *, size_t> vars;
 std::map<const void *, void *> var_mem;
 std::vector<Launch> launches;
+std::map<std::string, int64_t> calls;
 std::string fail_name;
 int fail_at = 0, imitate = 0;
+int64_t host_bytes = 0;
 thread_local int device = 0, last_error = 0;
 thread_local std::vector<Config> configs;
 
 // the call that fake_fail() chose fails
 bool fails(const std::string &name) {
     std::lock_guard<std::mutex> lock(mu);
+    calls[name]++;
     return fail_at > 0 && name.find(fail_name) != std::string::npos && --fail_at == 0;
 }
 int result(int e) { if (e) last_error = e; return e; }
@@ -92,7 +95,9 @@ extern "C" {
 void fake_fail(const char *name, int nth) { std::lock_guard<std::mutex> lock(mu); fail_name = name; fail_at = nth; }   // the nth call (launch) whose name contains `name`
 int fake_fail_pending() { std::lock_guard<std::mutex> lock(mu); return fail_at; }
 void fake_imitate(int on) { imitate = on; }
-void fake_clear() { std::lock_guard<std::mutex> lock(mu); launches.clear(); }
+void fake_clear() { std::lock_guard<std::mutex> lock(mu); launches.clear(); calls.clear(); host_bytes = 0; }
+int64_t fake_host_bytes() { return host_bytes; }   // of pinned memory asked for
+int64_t fake_calls(const char *name) { std::lock_guard<std::mutex> lock(mu); return calls[name]; }   // of those that can be made to fail
 int64_t fake_launches(const char *name, uint64_t *most_threads) {   // launches of kernels whose name contains `name`
     std::lock_guard<std::mutex> lock(mu);
     int64_t n = 0;
@@ -153,7 +158,7 @@ int hipGetSymbolAddress(void **p, const void *var) {
 int hipMemGetInfo(size_t *f, size_t *t) { *f = *t = (size_t)288 << 30; return kOk; }
 int hipMalloc(void **p, size_t n) { if (fails("hipMalloc")) return result(kOutOfMemory); *p = reserve(n); return *p ? kOk : result(kOutOfMemory); }
 int hipFree(void *p) { return result(release(p)); }
-int hipHostMalloc(void **p, size_t n, unsigned) { if (fails("hipHostMalloc")) return result(kOutOfMemory); *p = reserve(n); return *p ? kOk : result(kOutOfMemory); }
+int hipHostMalloc(void **p, size_t n, unsigned) { if (fails("hipHostMalloc")) return result(kOutOfMemory); host_bytes += (int64_t)n; *p = reserve(n); return *p ? kOk : result(kOutOfMemory); }
 int hipHostFree(void *p) { return result(release(p)); }
 int hipMemcpy(void *d, const void *s, size_t n, int) { if (fails("hipMemcpy:")) return result(kInvalidValue); memcpy(d, s, n); return kOk; }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int, Object *) { if (fails("hipMemcpyAsync")) return result(kInvalidValue); memcpy(d, s, n); return kOk; }

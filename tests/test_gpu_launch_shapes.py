@@ -88,10 +88,14 @@ def test_dense_rows_counted_where_they_are_normalised(K):
 
 @pytest.mark.parametrize("T,K,opts", [(1, 5, {}), (131072, 50, {}), (131073, 300, {}), (2_500_000, 40, {}), (300_001, 70000, {}),
                                       (1_000_003, 2000, {"light_word_tokens": 1 << 16}), (700_000, 9000, {"light_word_tokens": -1}),
-                                      (900_000, 100, {"stream_workers": 3, "n_chunks": 4})])
+                                      (900_000, 100, {"stream_workers": 3, "n_chunks": 4}), (2 << 20, 50, {}), ((2 << 20) + 1, 50, {}),
+                                      (2_300_000, 70000, {}), (2_500_000, 60000, {"light_word_tokens": -1}),
+                                      (2_500_000, 60000, {"light_word_tokens": 1 << 16}),
+                                      (9_000_000, 100, {"stream_workers": 3, "n_chunks": 4})])
 def test_results_that_leave_in_pieces(T, K, opts):
-    """Assignments and counts go to the caller by pieces, several at a time: one piece, two, many, more than the staging
-    holds; documents longer than the others' average piece; repeated calls on one context."""
+    """Assignments and counts go to the caller by plain copies, or above 8 MB by pieces through staging, several
+    at a time: some, many, more than the staging holds; documents longer than the others' average piece; repeated calls on
+    one context."""
     rng = np.random.default_rng(T)
     V = 37
     most = (1 << (32 - max(1, (K - 1).bit_length()))) - 1        # tokens of the longest document that K leaves count bits for

@@ -24,15 +24,17 @@ def test_a_failed_call_does_not_fail_the_next_one(host):
     """)
 
 
-@pytest.mark.parametrize("call", ["hipHostMalloc", "hipEventCreate", "hipMemcpyAsync", "hipMemcpy:", "hipEventRecord"])
-def test_counts_after_an_export_that_failed(host, call):
+@pytest.mark.parametrize("call,K", [("hipHostMalloc", 60000), ("hipEventCreate", 60000), ("hipMemcpyAsync", 60000),
+                                    ("hipMemcpy:", 60000), ("hipEventRecord", 60000), ("hipMemcpy:", 100)])
+def test_counts_after_an_export_that_failed(host, call, K):
     """saber_counts rebuilds B for the export; whatever fails on the way, later counts do not contain it."""
     host("""
         call = %r
-        counts = [3, 40000, 900, 0, 9000]
-        words = np.repeat(np.arange(5, dtype=np.int32), counts)
+        counts = [3, 40000, 900, 0, 9000] + 35 * [2]
+        words = np.repeat(np.arange(40, dtype=np.int32), counts)
         fake.fake_imitate(1)                        # (no sampling: every token keeps topic 0)
-        g = pk.Saber(np.r_[0, 500, words.size], words, 5, 100, 0.1, 0.01, 3, light_word_tokens=-1)
+        K = %d                                      # (rows of 40 words for one copy, and for several through staging)
+        g = pk.Saber(np.r_[0, 500, words.size], words, 40, K, 0.1, 0.01, 3, light_word_tokens=-1)
         nth = 0
         while True:
             nth += 1
@@ -47,7 +49,7 @@ def test_counts_after_an_export_that_failed(host, call):
             assert np.array_equal(cwk[:, 0], counts) and not cwk[:, 1:].any(), (nth, cwk)
             if nth == 1: g.set_z(np.zeros(words.size, np.int32), 0)
         assert nth > 1
-    """ % call)
+    """ % (call, K))
 
 
 def test_topic_totals_after_an_iteration_that_failed(host):
@@ -69,7 +71,7 @@ def test_topic_totals_after_an_iteration_that_failed(host):
 def test_results_with_another_device_current(host, K):
     """Results are copied out on the context's own device, whichever the caller has current."""
     host("""
-        words = np.arange(400000, dtype=np.int32) %% 50
+        words = np.arange(5_000_000, dtype=np.int32) %% 50
         doc_ptr = np.r_[0, np.arange(999, words.size, 1000), words.size]
         g = pk.Saber(doc_ptr, words, 50, %d, 0.1, 0.01, 3)
         first = pk.Saber(doc_ptr, words, 50, %d, 0.1, 0.01, 3)
@@ -77,7 +79,7 @@ def test_results_with_another_device_current(host, K):
         fake.hipSetDevice(1)
         now = ctypes.c_int()
         for use in (g.get_z, lambda: g.counts(want_cwk=False), g.counts, first.get_z,
-                    lambda: first.holdout_loglik(np.array([0, 5000]), words[:5000], words[:5000] %% 2 == 0, 1, 5)):
+                    lambda: first.holdout_loglik(np.arange(0, 5_000_001, 1000), words, words %% 4 > 0, 1, 5)):
             use()
             fake.hipGetDevice(ctypes.byref(now))
             assert now.value == 1
@@ -146,3 +148,18 @@ def test_threads_of_a_workgroup_whose_row_is_not_staged(host, K, threads):
         g.iterate(1)
         assert fake.fake_block(b"estep_kernel") == %d
     """ % (K, threads))
+
+
+@pytest.mark.parametrize("K,T,least,most", [(100, 1 << 20, 0, 0), (100, (1 << 20) + 1, 1, 1 << 19), (100, 2 << 20, 1, 1 << 19),
+                                            (100, (2 << 20) + 1, 3 << 20, 13 << 20), (70000, 2 << 20, 0, 0),
+                                            (70000, (2 << 20) + 1, 3 << 20, 13 << 20)])
+def test_staging_grows_with_the_results(host, K, T, least, most):
+    """Threads and a large pinned staging are for results that are worth them; those of a small model take little or none."""
+    host("""
+        words = np.zeros(%d, np.int32)
+        g = pk.Saber(np.r_[np.arange(0, words.size, 1000), words.size], words, 1, %d, 0.1, 0.01, 3)
+        fake.fake_clear()
+        for i in range(3):
+            g.get_z()
+            assert %d <= fake.fake_host_bytes() <= %d
+    """ % (T, K, least, most))
