@@ -433,13 +433,14 @@ static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64
 //   * above K = 16,384 the rows are too long (K = 20,011, T = 15 M: first iterations 4.75 -> 5.02 ms, later ones 1.82 -> 1.79), and
 //     rows that are not staged (K = 45,000, T = 20 M) lose the sharing of a row between tiles: 8.9 -> 9.9 ms;
 //   * classes by size (stage_min_tokens) need the tiles in order of size;
-//   * a chunk's tiles have to stay within the 2^20 of saber_loglik_static whatever the words' sizes are.
+//   * a chunk's tiles have to stay within the 2^20 of saber_loglik_static whatever the words' sizes are: one per word or piece
+//     of a word, and one more per tile_tokens tokens.
 constexpr int kXcds = 8, kDocRanges = 16;
 constexpr int64_t kRangeTokens = 4ll << 20, kRangePiece = 64;
 
 static bool may_cut_by_range(const saber_ctx *c, const Chunk &ch) {
     return c->staged && c->K <= 16384 && c->opt.stage_min_tokens <= 1 && ch.ntok >= (c->K >= 1000 ? kRangeTokens : 4 * kRangeTokens) &&
-           (int64_t)c->V + (int64_t)kDocRanges * c->V_dense <= (1 << 20) - (1 << 16);
+           (int64_t)c->V + (int64_t)kDocRanges * c->V_dense + std::max<int64_t>(1 << 16, ch.ntok / c->opt.tile_tokens) <= 1 << 20;
 }
 
 // tiles[0, n) sorted by decreasing size -> the order of the launch: tile i
@@ -1232,7 +1233,9 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
         // (a vocabulary of more than 2^19 words makes a tile or more per word as it is: larger tiles keep a chunk's within
         // the 2^20 of saber_loglik_static)
         const bool many_words = V > (1 << 19);
-        const int64_t least = many_words ? 8192 : std::min<int64_t>(256, std::max<int64_t>(64, (K / 16) & ~63));
+        // (likewise where documents are longer than the share of a chunk: it then has as many tokens as the longest more)
+        const int64_t longest = (((per_chunk + maxlen) >> 19) + 64) & ~63ll;
+        const int64_t least = many_words ? 8192 : std::max<int64_t>(longest, std::min<int64_t>(256, std::max<int64_t>(64, (K / 16) & ~63)));
         const int64_t share = many_words ? (per_chunk / 2560) & ~255ll : (per_chunk / 8192) & ~63ll;
         opt.tile_tokens = (int32_t)std::min<int64_t>(32768, std::max<int64_t>(least, share));
     }

@@ -163,3 +163,39 @@ def test_staging_grows_with_the_results(host, K, T, least, most):
             g.get_z()
             assert %d <= fake.fake_host_bytes() <= %d
     """ % (T, K, least, most))
+
+
+@pytest.mark.parametrize("what", ["small tiles", "one long document", "many words", "words within the limit of the cut"])
+def test_tiles_of_a_chunk_stay_within_the_static_work_space(host, what):
+    """saber_loglik_static takes 2^20 tiles per chunk: neither the cut by ranges of documents nor the automatic size of a tile
+    goes beyond, for a corpus that plain tiles of 8,192 tokens, or the caller's size, keep within."""
+    host("""
+        import paper_1610_02496_amd.binding as binding
+        what, opts, K = %r, {}, 1000
+        if what == "small tiles":                    # as many as there may be, unless words are cut into pieces on top
+            V, tile = 40, 9
+            T = tile * ((1 << 20) - 200)
+            words = np.arange(T, dtype=np.int32) %% V
+            words[:T // 2] = words[:T // 2] * 7 %% 11 # (uneven counts)
+            doc_ptr, opts = np.r_[np.arange(0, T, 32), T], {"tile_tokens": tile}
+        elif what == "one long document":            # a chunk of 70 M tokens where a hundredth of the corpus is 0.7 M
+            V, K, T = 3, 2, 70_000_000
+            words = np.zeros(T, np.int32)
+            doc_ptr, opts = np.r_[np.arange(200), T], {"n_chunks": 100}
+        elif what == "many words":
+            V, K, T = (1 << 19) + 1, 20, 3_000_000
+            words = (np.arange(T) * 7919 %% V).astype(np.int32)
+            doc_ptr = np.r_[np.arange(0, T, 100), T]
+        else:                                        # 17 V + 2^16 = 2^20 - 15
+            V, T = 57825, 9_000_000
+            words = (np.random.default_rng(1).random(T) ** 3 * V).astype(np.int32)
+            doc_ptr, opts = np.r_[np.arange(0, T, 32), T], {"light_word_tokens": -1}
+        g = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 3, **opts)
+        out = ctypes.c_double()
+        assert binding.load_library().saber_loglik_static(g._h, ctypes.addressof(out)) == 0
+        tiles = g.get_stats()["tiles"]
+        if what == "many words": assert tiles == V   # (8,192 tokens at least: none of these words has more)
+        if what == "words within the limit of the cut":
+            n = np.bincount(words, minlength=V)
+            assert tiles >= np.count_nonzero(n) + 15 * np.count_nonzero(n >= 2048)
+    """ % what)
