@@ -425,21 +425,24 @@ static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64
 // kDocRanges ranges of documents and launched range by range, each XCD (workgroups go to them round robin) at a range of
 // its own at a time, whose rows its 4 MB L2 holds in part.  Sampling pass, iterations 11..20: T = 100 M, K = 10,000 7.92 ->
 // 7.21 ms, K = 1,000 7.46 -> 6.48; T = 246 M in three chunks, K = 5,000, short documents 15.6 -> 14.4, 240 M of long ones,
-// K = 10,000 26.5 -> 23.8; T = 36 M, K = 5,000 2.27 -> 2.14; T = 5 M, K = 3,000 0.43 -> 0.41.  8 or 32 ranges gain half to all of
-// that.  A word is cut if its pieces have 64 tokens on average (32 to 512 differ by 1 to 3 %).  Words that are not cut come
+// K = 10,000 26.5 -> 23.8; T = 36 M, K = 5,000 2.27 -> 2.14.  8 or 32 ranges gain half to all of that.  A word is cut if its pieces have 64 tokens on average (32 to 512 differ by 1 to 3 %).  Words that are not cut come
 // first: at the end of the launch their larger tiles cost 3 to 5 %.  Where it stops:
-//   * chunks below 4 M tokens (K = 777, T = 2.3 M: 0.159 -> 0.164 ms), or 16 M where rows are short and few words are cut
-//     (K = 300: 0.558 -> 0.563 ms at 10 M);
+//   * chunks whose rows of A the eight L2s hold together (32 MB, taken from the rows' capacities), and chunks below 8 M
+//     tokens, where the pieces are small and 16 times the tiles weigh more than the traffic they save.  Change of the pass by
+//     the cut, per cent, iterations 1..5 / 18..37: T = 4.5 M, rows of 13 to 18 MB (K = 300 to 1,000) +2..+4 / +1..+5, of
+//     28 MB (short documents) +3..+5 / +1..+4; 8 M tokens, 33 MB -4..-1 / +1..+3, 37 MB -2..+3 / -2..+1, 50 MB (short
+//     documents) +2..+5 / -3..0; 12 M, 18 MB +1 / +1, 55 MB -3..+1 / -5..-2; 24 M, 68 to 110 MB -8..-2 / -7..-3.  The
+//     number of topics alone does not tell: K = 300, 1,000 and 2,500 differ by 1 to 3 where the rows are alike;
 //   * above K = 16,384 the rows are too long (K = 20,011, T = 15 M: first iterations 4.75 -> 5.02 ms, later ones 1.82 -> 1.79), and
 //     rows that are not staged (K = 45,000, T = 20 M) lose the sharing of a row between tiles: 8.9 -> 9.9 ms;
 //   * classes by size (stage_min_tokens) need the tiles in order of size;
 //   * a chunk's tiles have to stay within the 2^20 of saber_loglik_static whatever the words' sizes are: one per word or piece
 //     of a word, and one more per tile_tokens tokens.
 constexpr int kXcds = 8, kDocRanges = 16;
-constexpr int64_t kRangeTokens = 4ll << 20, kRangePiece = 64;
+constexpr int64_t kRangeTokens = 8ll << 20, kRangeRowUnits = (32ll << 20) / 128, kRangePiece = 64;
 
 static bool may_cut_by_range(const saber_ctx *c, const Chunk &ch) {
-    return c->staged && c->K <= 16384 && c->opt.stage_min_tokens <= 1 && ch.ntok >= (c->K >= 1000 ? kRangeTokens : 4 * kRangeTokens) &&
+    return c->staged && c->K <= 16384 && c->opt.stage_min_tokens <= 1 && ch.ntok >= kRangeTokens && ch.row_units >= kRangeRowUnits &&
            (int64_t)c->V + (int64_t)kDocRanges * c->V_dense + std::max<int64_t>(1 << 16, ch.ntok / c->opt.tile_tokens) <= 1 << 20;
 }
 
@@ -825,7 +828,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
                 if (units + u > unit_limit) break;
                 units += u; d++;
             }
-            ch.d1 = d; ch.ntok = doc_ptr[d] - ch.t0;
+            ch.d1 = d; ch.ntok = doc_ptr[d] - ch.t0; ch.row_units = units;
             if (ch.ntok >= (1ll << 31)) return fail(SABER_ERANGE, "saber_init: a document chunk holds %lld tokens (limit 2^31)", (long long)ch.ntok);
             if (ch.d1 > ch.d0) c->chunks.push_back(ch);
         }
@@ -1024,7 +1027,6 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     c->n_short = (int64_t)h_short.size(); c->n_long = (int64_t)h_long.size();
     for (Chunk &ch : c->chunks) {   // both lists ascend by document: a chunk's documents are a contiguous part of each
         ch.row_unit0 = (int64_t)h_rec[(size_t)ch.d0].x;
-        ch.row_units = (ch.d1 < D ? (int64_t)h_rec[(size_t)ch.d1].x : units) - ch.row_unit0;
         ch.short0 = std::lower_bound(h_short.begin(), h_short.end(), (int32_t)ch.d0) - h_short.begin();
         ch.nshort = (std::lower_bound(h_short.begin(), h_short.end(), (int32_t)std::min<int64_t>(ch.d1, 0x7fffffff)) - h_short.begin()) - ch.short0;
         ch.long0 = std::lower_bound(h_long.begin(), h_long.end(), (int32_t)ch.d0) - h_long.begin();

@@ -121,8 +121,8 @@ def test_results_that_leave_in_pieces(T, K, opts):
     g.close()
 
 
-@pytest.mark.parametrize("T,K,opts", [(4_400_000, 1000, {}), (4_400_000, 16384, {}), (17_300_000, 300, {}),
-                                      (9_000_000, 2500, {"n_chunks": 2, "stream_workers": 2})])
+@pytest.mark.parametrize("T,K,opts", [(11_000_000, 1000, {}), (11_000_000, 16384, {}), (17_300_000, 300, {}),
+                                      (24_000_000, 2500, {"n_chunks": 2, "stream_workers": 2})])
 def test_frequent_words_cut_by_ranges_of_documents(T, K, opts):
     """Tiles cut at the ends of sixteen ranges of documents, against the plain order of tiles (classes by size switch the
     ranges off).  Empty documents on both ends, one document longer than several ranges (some ranges are empty), words that

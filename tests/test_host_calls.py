@@ -199,3 +199,22 @@ def test_tiles_of_a_chunk_stay_within_the_static_work_space(host, what):
             n = np.bincount(words, minlength=V)
             assert tiles >= np.count_nonzero(n) + 15 * np.count_nonzero(n >= 2048)
     """ % what)
+
+
+@pytest.mark.parametrize("T,length,K,cut", [(9_000_000, 32, 999, True), (9_000_000, 32, 1000, True), (9_000_000, 32, 60, True),
+                                            (8_300_000, 32, 1000, False), (9_000_000, 250, 100, False),
+                                            (9_000_000, 250, 999, True), (9_000_000, 250, 16384, True),
+                                            (9_000_000, 250, 16385, False)])
+def test_which_chunks_are_cut_by_ranges_of_documents(host, T, length, K, cut):
+    """Those with enough tokens and with more rows of A than the caches hold, whatever the number of topics below the limit."""
+    host("""
+        T, length, K, cut = %d, %d, %d, %r
+        words = np.arange(T, dtype=np.int32) %% 50
+        doc_ptr = np.r_[np.arange(0, T, length), T]
+        tiles = []
+        for opts in ({}, {"stage_min_tokens": 2, "light_block_threads": 256}):   # (the second: never cut)
+            g = pk.Saber(doc_ptr, words, 50, K, 0.1, 0.01, 3, tile_tokens=1 << 20, **opts)
+            tiles.append(g.get_stats()["tiles"])
+            g.close()
+        assert tiles == [800 if cut else 50, 50]
+    """ % (T, length, K, cut))
