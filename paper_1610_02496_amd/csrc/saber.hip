@@ -114,7 +114,11 @@ struct Chunk {
 constexpr int kMaxSlots = 8;
 constexpr int kPullSlots = 12, kPullThreads = 8;      // see pull()
 constexpr int64_t kPullPiece = 1 << 20;               // bytes
-constexpr int64_t kPullFew = 4 << 20, kPullMany = 8 << 20;   // bytes written for the caller
+// Bytes written for the caller up to which plain copies do, and from which on threads are worth their start and the large
+// staging, or if that is there already (`next`) their start: for assignments, which are only widened; entries of A, which
+// are taken apart; rows of B, copied or filled in.
+struct PullBy { int64_t few, many, next; };
+constexpr PullBy kPullZ = {4 << 20, 8 << 20, 8 << 20}, kPullEntries = {1 << 20, 8 << 20, 1 << 20}, kPullRows = {4 << 20, 8 << 20, 1 << 20};
 // Pinned staging of results and the events of its slots, made by the first call that needs them.
 struct Staging { char *buf = nullptr; size_t bytes = 0; bool pinned = false; hipEvent_t ev[kPullSlots] = {}; };
 
@@ -1394,33 +1398,38 @@ struct DeviceScope {
     ~DeviceScope() { if (before >= 0) (void)hipSetDevice(before); }
 };
 
-// Bytes of the pieces that so many bytes for the caller are cut into; a longer row is a piece of its own.
-static int64_t pull_piece(int64_t out_bytes) { return out_bytes > kPullMany ? kPullPiece : kPullPiece / 4; }
+// Whether so many bytes for the caller are worth threads, and the bytes of the pieces they are cut into (a longer row is a
+// piece of its own).
+static bool pull_many(const saber_ctx *c, int64_t out_bytes, PullBy by) {
+    return out_bytes > (c->staging.bytes >= (size_t)(kPullSlots / 2 * kPullPiece) ? by.next : by.many);
+}
+static int64_t pull_piece(bool many) { return many ? kPullPiece : kPullPiece / 4; }
 
 // Results on their way to the caller's memory: piece i, the elements [cuts[i], cuts[i + 1]) of the device array, is handed
 // to consume(i, host pointer), which puts it where it belongs.  How that is done depends on the bytes written for the caller
 // (out_bytes):
-//   * above kPullMany by way of pinned staging of kPullSlots slots, which up to kPullThreads threads consume while the next
+//   * above by.many, or by.next, by way of pinned staging of kPullSlots slots, which up to kPullThreads threads consume while the next
 //     pieces are in flight.  A caller's fresh pages cost far more than the link: into ordinary memory a copy of 100 M
 //     assignments as int32 took 44 ms, as 16 bits through this path 8;
 //   * below, the calling thread alone, out of two small slots: threads, and the first touch of pinned memory, cost a
 //     context's first call a millisecond (A in CSR of T = 1 M, K = 100, first and later calls: 1.62 and 0.25 ms with them,
 //     0.36 and 0.34 this way, 0.45 and 0.41 by a plain copy);
-//   * up to `few` bytes by plain copies into ordinary memory (the assignments of T = 300,000: 0.07 and 0.05 ms, 0.24 and 0.06
-//     through two slots).  consume() hides under no copy then, so `few` is 4 MB where it only moves data (B of 2,000 words,
-//     K = 500: 0.23 ms, two slots 0.36) and 1 MB where it takes entries apart.
+//   * up to by.few by plain copies into ordinary memory (the assignments of T = 300,000: 0.07 and 0.05 ms, 0.24 and 0.06
+//     through two slots; 4 MB of rows of B: 0.23 ms, 0.36 through two slots, 0.29 with threads - which are the faster ones by
+//     0.2 ms for 3.5 MB after 20 MB of A).  consume() hides under no copy then, so that is less where it takes entries apart.
 // The threads end before the call returns; consume must not throw.  No piece may exceed kPullPiece bytes.
 // Events belong to the device that is current when they are made, and only its streams record them; the caller may have
 // another one current.
 template <typename F>
-static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<int64_t> &cuts, int64_t out_bytes, int64_t few, F consume) {
+static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<int64_t> &cuts, int64_t out_bytes, PullBy by, F consume) {
     const int64_t np = (int64_t)cuts.size() - 1;
     if (np <= 0) return SABER_OK;
     auto piece_bytes = [&](int64_t k) { return (size_t)(cuts[(size_t)k + 1] - cuts[(size_t)k]) * elem; };
     auto source = [&](int64_t k) { return (const char *)dev + (size_t)cuts[(size_t)k] * elem; };
     size_t largest = 1;
     for (int64_t i = 0; i < np; i++) largest = std::max(largest, piece_bytes(i));
-    if (out_bytes <= few) {
+    const bool many = pull_many(c, out_bytes, by);
+    if (out_bytes <= by.few && !many) {
         const int64_t group = kPullPiece / (int64_t)elem;   // as many pieces at a time as that
         const std::unique_ptr<char[]> host(new char[std::max(largest, (size_t)std::min(cuts.back(), group) * elem)]);
         HIP_TRY(hipStreamSynchronize(c->stream));
@@ -1433,8 +1442,8 @@ static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<in
         return SABER_OK;
     }
     const DeviceScope scope(c->device);
-    const bool many = out_bytes > kPullMany;
-    largest = (std::max(largest, (size_t)pull_piece(out_bytes)) + 255) & ~(size_t)255;   // (so that the slots serve later calls as well)
+    if (!many) largest = std::max(largest, (size_t)pull_piece(many));   // (so that the slots serve later calls as well)
+    largest = (largest + 255) & ~(size_t)255;
     const int slots = many ? (int)std::min<int64_t>(np, kPullSlots) : 2;
     if (c->staging.bytes < largest * (size_t)slots) {
         if (c->staging.buf) { if (c->staging.pinned) (void)hipHostFree(c->staging.buf); else free(c->staging.buf); }
@@ -1510,7 +1519,7 @@ static int pull(saber_ctx *c, const void *dev, size_t elem, const std::vector<in
 // n assignments from the device array z (of the context's assignment type) to the caller's int32
 static int pull_z(saber_ctx *c, const void *z, int64_t n, int32_t *out) {
     const int64_t elem = c->z16 ? 2 : 4;
-    if (!c->z16 && n * elem <= kPullMany) {   // nothing to convert: straight to the caller's memory
+    if (!c->z16 && n * elem <= kPullZ.many) {   // nothing to convert: straight to the caller's memory
         HIP_TRY(hipStreamSynchronize(c->stream));
         HIP_TRY(hipMemcpy(out, z, (size_t)n * 4, hipMemcpyDeviceToHost));
         return SABER_OK;
@@ -1519,7 +1528,7 @@ static int pull_z(saber_ctx *c, const void *z, int64_t n, int32_t *out) {
     const int64_t piece = std::min<int64_t>(kPullPiece / elem, std::max<int64_t>(131072, (n / 16 + 4095) & ~4095ll));
     std::vector<int64_t> cuts(1, 0);
     while (cuts.back() < n) cuts.push_back(std::min<int64_t>(n, cuts.back() + piece));
-    return pull(c, z, (size_t)elem, cuts, n * 4, kPullFew, [&](int64_t i, const void *host) {
+    return pull(c, z, (size_t)elem, cuts, n * 4, kPullZ, [&](int64_t i, const void *host) {
         const int64_t a = cuts[(size_t)i], m = cuts[(size_t)i + 1] - a;
         if (elem == 4) { memcpy(out + a, host, (size_t)m * 4); return; }
         const uint16_t *src = (const uint16_t *)host;
@@ -1551,13 +1560,13 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
             if (cd_topic || cd_count) {
                 // unpack the device rows by pieces of whole documents (format conversion only)
                 std::vector<int64_t> cuts(1, 0), piece_doc(1, 0);
-                const int64_t out_bytes = 4 * std::max(2 * cd_row_ptr[c->D], c->cd_cap), piece = pull_piece(out_bytes);
+                const int64_t out_bytes = 4 * std::max(2 * cd_row_ptr[c->D], c->cd_cap), piece = pull_piece(pull_many(c, out_bytes, kPullEntries));
                 for (int64_t d = 0; d < c->D; d++) {
                     const int64_t end = d + 1 < c->D ? (int64_t)rec[(size_t)d + 1].x * 32 : c->cd_cap;
                     if ((end - cuts.back()) * 4 > piece) { cuts.push_back((int64_t)rec[(size_t)d].x * 32); piece_doc.push_back(d); }
                 }
                 cuts.push_back(c->cd_cap); piece_doc.push_back(c->D);
-                SABER_TRY(pull(c, c->cd_ent, sizeof(uint32_t), cuts, out_bytes, kPullFew / 4, [&](int64_t i, const void *host) {
+                SABER_TRY(pull(c, c->cd_ent, sizeof(uint32_t), cuts, out_bytes, kPullEntries, [&](int64_t i, const void *host) {
                     for (int64_t d = piece_doc[(size_t)i]; d < piece_doc[(size_t)i + 1]; d++) {
                         const uint32_t *row = (const uint32_t *)host + ((int64_t)rec[(size_t)d].x * 32 - cuts[(size_t)i]);
                         int64_t o = cd_row_ptr[d];
@@ -1575,12 +1584,12 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
                 std::vector<int32_t> row_word((size_t)c->V_dense + 1);
                 HIP_TRY(hipMemcpy(row_word.data(), c->row_word, sizeof(int32_t) * row_word.size(), hipMemcpyDeviceToHost));
                 const int64_t out_bytes = 4 * (int64_t)c->V_dense * c->Kpad;
-                const int64_t rows = std::max<int64_t>(1, pull_piece(out_bytes) / ((int64_t)c->Kpad * 4));   // (Kpad * 4 is at most 1 MB)
+                const int64_t rows = std::max<int64_t>(1, pull_piece(pull_many(c, out_bytes, kPullRows)) / ((int64_t)c->Kpad * 4));   // (Kpad * 4 is at most 1 MB)
                 std::vector<int64_t> cuts(1, 0);
                 while (cuts.back() < (int64_t)c->V_dense * c->Kpad)
                     cuts.push_back(std::min<int64_t>((int64_t)c->V_dense * c->Kpad, cuts.back() + rows * c->Kpad));
                 SABER_TRY(launch_count_slabs(c, c->n_vz_items, false));
-                SABER_TRY(pull(c, c->cwk, sizeof(int32_t), cuts, out_bytes, kPullFew, [&](int64_t i, const void *host) {
+                SABER_TRY(pull(c, c->cwk, sizeof(int32_t), cuts, out_bytes, kPullRows, [&](int64_t i, const void *host) {
                     for (int64_t e = cuts[(size_t)i]; e < cuts[(size_t)i + 1]; e += c->Kpad)
                         memcpy(cwk + (size_t)row_word[(size_t)(e / c->Kpad)] * (size_t)c->K, (const int32_t *)host + (e - cuts[(size_t)i]),
                                sizeof(int32_t) * (size_t)c->K);
@@ -1596,8 +1605,9 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
                 HIP_TRY(hipMemcpy(lwords.data(), c->light_words, sizeof(int32_t) * lwords.size(), hipMemcpyDeviceToHost));
                 std::vector<int64_t> cuts(1, 0), piece_word(1, 0);
                 // (a word's row of K counts has to be cleared as well: threads share those out by at most 1 MB per piece)
-                const int64_t out_bytes = 4 * std::max((int64_t)c->V_light * c->K, c->lw_cap), piece = pull_piece(out_bytes);
-                const int64_t most = out_bytes > kPullMany ? std::max<int64_t>(1, kPullPiece / (4 * (int64_t)c->K)) : c->V_light;
+                const int64_t out_bytes = 4 * std::max((int64_t)c->V_light * c->K, c->lw_cap);
+                const bool many = pull_many(c, out_bytes, kPullRows);
+                const int64_t piece = pull_piece(many), most = many ? std::max<int64_t>(1, kPullPiece / (4 * (int64_t)c->K)) : c->V_light;
                 for (int64_t li = 0; li < c->V_light; li++) {
                     const int64_t end = li + 1 < c->V_light ? (int64_t)wrec[(size_t)li + 1].x * 32 : c->lw_cap;
                     if ((end - cuts.back()) * 4 > piece || li - piece_word.back() >= most) {
@@ -1605,7 +1615,7 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
                     }
                 }
                 cuts.push_back(c->lw_cap); piece_word.push_back(c->V_light);
-                SABER_TRY(pull(c, c->lw_ent, sizeof(uint32_t), cuts, out_bytes, kPullFew, [&](int64_t i, const void *host) {
+                SABER_TRY(pull(c, c->lw_ent, sizeof(uint32_t), cuts, out_bytes, kPullRows, [&](int64_t i, const void *host) {
                     for (int64_t li = piece_word[(size_t)i]; li < piece_word[(size_t)i + 1]; li++) {
                         int32_t *row = cwk + (size_t)lwords[(size_t)li] * (size_t)c->K;
                         memset(row, 0, sizeof(int32_t) * (size_t)c->K);
