@@ -20,8 +20,8 @@ def corpus_of_word_counts(counts, D, seed):
 
 @pytest.mark.parametrize("K", [60, 1000, 2000, 9000])
 def test_workgroups_sized_by_the_tile(K):
-    """Light words on both sides of every class boundary (64, 128, 256, 512 tokens), enough of each for launches of their
-    own, and a few frequent words cut into tiles."""
+    """Light words of 1 to 513 tokens and a few frequent words cut into tiles: too few tiles for classes by size, so all of a
+    chunk's share one launch and one size of workgroup."""
     edges = [1, 2, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513]
     counts = np.r_[np.repeat(edges, 60), [3000, 9000]]
     doc_ptr, words = corpus_of_word_counts(counts, 700, K)
@@ -39,6 +39,47 @@ def test_workgroups_sized_by_the_tile(K):
     assert abs(p.loglik() - ll) <= 1e-12 * abs(ll)
     p.close()
     o.close()
+
+
+def corpus_of_three_classes():
+    """17,500 light words and two frequent ones.  With whole words as tiles the classes of light words are, where a wavefront is
+    the least workgroup, more than 128 tokens, 65 to 128 and fewer; 200 words on every side of each line."""
+    edges = [63, 64, 65, 127, 128, 129, 255, 256, 257, 400]
+    counts = np.r_[np.repeat(edges, 200), 3000, 9000, np.resize([1, 2, 3, 17], 15500)]
+    return counts, *corpus_of_word_counts(counts, 900, 5)
+
+
+# topics -> sampling launches per chunk: at K = 1,000 a CU holds 32 workgroups of one wavefront, at K = 2,000 two wavefronts
+# are the least, at K = 9,000 LDS takes four workgroups, all of 512 threads then
+CLASSES = {1000: 3, 2000: 2, 9000: 1}
+
+
+@pytest.mark.parametrize("K", sorted(CLASSES))
+def test_classes_of_light_words(K):
+    """Tiles of light words in several launches: the classes' offsets into tiles and partial sums, and the first launch, which
+    takes the frequent words too."""
+    counts, doc_ptr, words = corpus_of_three_classes()
+    pk, V, alpha = saber(), counts.size, 50.0 / K
+    tok = np.random.default_rng(K).integers(0, words.size, 50000)
+    results = []
+    for opts in ({"tile_tokens": 1024}, {"block_threads": 256, "light_block_threads": 256, "tile_tokens": 8192}):
+        g = pk.Saber(doc_ptr, words, V, K, alpha, 0.01, 11, **opts)
+        if not results:
+            o = oracle.Model(doc_ptr, words, V, K, alpha, 0.01, 11)
+            z_ref, _, _, _, margin = o.estep_detail(nthreads=4)
+        g.iterate(1)
+        if not results:
+            bad = np.nonzero(g.get_z() != z_ref)[0]
+            assert bad.size <= 1e-3 * words.size and np.all(margin[bad] < 1e-5)
+            o.close()
+        g.iterate(1)
+        results.append((g.get_z(), g.loglik(), *g.token_probs(tok)))
+        g.close()
+    for a, b in zip(*results):
+        if isinstance(a, float):                    # partial sums of other tiles, 64 bits
+            assert abs(a - b) <= 1e-12 * abs(b)
+        else:
+            assert np.array_equal(a, b)
 
 
 @pytest.mark.parametrize("K,T", [(15361, 16383), (36864, 16385), (36865, 40000), (73729, 300_001), (262144, 5000), (100, 1), (7, 65537)])

@@ -218,3 +218,21 @@ def test_which_chunks_are_cut_by_ranges_of_documents(host, T, length, K, cut):
             g.close()
         assert tiles == [800 if cut else 50, 50]
     """ % (T, length, K, cut))
+
+
+def test_classes_of_light_words_have_launches_of_their_own(host):
+    """Of the corpora that the GPU tests compare: one launch for each class, tiles and workgroups as they should be."""
+    host("""
+        sys.path.insert(0, "tests")
+        from test_gpu_launch_shapes import CLASSES, corpus_of_three_classes, corpus_of_word_counts
+        counts, doc_ptr, words = corpus_of_three_classes()
+        for K, n in CLASSES.items():
+            g = pk.Saber(doc_ptr, words, counts.size, K, 50 / K, 0.01, 11, tile_tokens=1024)
+            for use in (lambda: g.iterate(1), g.loglik, lambda: g.token_probs([0])):
+                fake.fake_clear()
+                use()
+                got, blocks, most = launches("estep_kernel")
+                assert got == n and blocks == g.get_stats()["tiles"], (K, got, blocks)
+            assert fake.fake_block(b"estep_kernel") == {1000: 64, 2000: 128, 9000: 512}[K]
+            g.close()
+    """)
