@@ -644,20 +644,25 @@ static int launch_count_slabs(saber_ctx *c, int64_t n_items, bool totals) {
     const int64_t per_block = std::min<int64_t>(1 << 20, std::max<int64_t>(least, ((share + 4095) / 4096) * 4096));
     const int64_t n_tot = totals ? (c->T + per_block - 1) / per_block : 0;
     if (n_tot + n_items == 0) return SABER_OK;
-    const dim3 grid((unsigned)(n_tot + n_items), (unsigned)((c->K + range - 1) / range));
     const size_t lds = (size_t)std::min(range, c->K) * 4;
     // a histogram of all assignments: their order does not matter, and with host streaming the word-major copy is
     // the one that is resident
     const void *zsrc = c->n_slots ? c->z_wm : c->z;
     SABER_TRY(allow_lds(c->z16 ? (const void *)count_slabs_kernel<uint16_t> : (const void *)count_slabs_kernel<int32_t>, lds));
     c->acc_used = true;
-    if (c->z16)
-        hipLaunchKernelGGL((count_slabs_kernel<uint16_t>), grid, dim3(1024), lds, c->stream, (const uint16_t *)zsrc, c->T, per_block,
-                           (int)n_tot, c->ck_acc, c->vz_items, (const uint16_t *)c->z_wm, c->cwk, c->K, c->Kpad, range);
-    else
-        hipLaunchKernelGGL((count_slabs_kernel<int32_t>), grid, dim3(1024), lds, c->stream, (const int32_t *)zsrc, c->T, per_block,
-                           (int)n_tot, c->ck_acc, c->vz_items, (const int32_t *)c->z_wm, c->cwk, c->K, c->Kpad, range);
-    HIP_TRY(hipGetLastError());
+    for (int64_t i = 0, n; i < n_tot + n_items; i += n) {
+        n = std::min(n_tot + n_items - i, most_blocks(1024));
+        const int tot = i == 0 ? (int)n_tot : 0;   // (far fewer than a launch takes: all in the first one)
+        const VzItem *items = c->vz_items + (i == 0 ? 0 : i - n_tot);
+        const dim3 grid((unsigned)n, (unsigned)((c->K + range - 1) / range));
+        if (c->z16)
+            hipLaunchKernelGGL((count_slabs_kernel<uint16_t>), grid, dim3(1024), lds, c->stream, (const uint16_t *)zsrc, c->T, per_block,
+                               tot, c->ck_acc, items, (const uint16_t *)c->z_wm, c->cwk, c->K, c->Kpad, range);
+        else
+            hipLaunchKernelGGL((count_slabs_kernel<int32_t>), grid, dim3(1024), lds, c->stream, (const int32_t *)zsrc, c->T, per_block,
+                               tot, c->ck_acc, items, (const int32_t *)c->z_wm, c->cwk, c->K, c->Kpad, range);
+        HIP_TRY(hipGetLastError());
+    }
     return SABER_OK;
 }
 

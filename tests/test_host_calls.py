@@ -136,6 +136,12 @@ def test_more_tiles_than_a_launch_takes(host):
                 n, blocks, most = launches("estep_kernel")
                 assert blocks == V and most < 1 << 32, (n, blocks, most)
             g.close()
+        fake.fake_imitate(1)                        # B of as many dense rows: a slab each, and the totals beside them
+        g = pk.Saber(doc_ptr, words, V, 2, 0.1, 0.01, 3, light_word_tokens=-1)
+        cwk, ck = g.counts(want_cd=False)[3:]
+        assert (cwk[:, 0] == 1).all() and not cwk[:, 1].any() and ck[0] == V
+        n, blocks, most = launches("count_slabs")
+        assert most < 1 << 32
     """)
 
 
