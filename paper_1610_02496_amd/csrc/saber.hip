@@ -638,7 +638,8 @@ static int launch_count_slabs(saber_ctx *c, int64_t n_items, bool totals) {
     const int range = hist_range(c);
     // every workgroup ends with up to K atomics into the K totals: no more than about 500 shares of z (128 where these
     // have fewer than 65,536 assignments: T = 10 M, K = 1,000 takes 17 us with 153 of them, 21 with 490), none with
-    // fewer than 16 assignments per topic (at least 16,384) or more than 2^20, keep those from dominating
+    // fewer than 16 assignments per topic (but 16,384 at least, and 262,144 are enough at any K) or more than 2^20, keep
+    // those from dominating
     const int64_t least = std::max<int64_t>(16384, std::min<int64_t>(16 * (int64_t)c->K, 262144));
     const int64_t share = std::max<int64_t>(c->T / 512, std::min<int64_t>(c->T / 128, 65536));
     const int64_t per_block = std::min<int64_t>(1 << 20, std::max<int64_t>(least, ((share + 4095) / 4096) * 4096));
@@ -676,8 +677,8 @@ static int launch_phi(saber_ctx *c) {
     hipLaunchKernelGGL(denominators_kernel, dim3(grid_for(c->Kpad, 256)), dim3(256), 0, c->stream, c->ck_acc, c->ck, c->denom, c->K,
                        c->Kpad, c->vbeta);
     HIP_TRY(hipGetLastError());
-    // kPhiSteps steps of four columns per thread at a time: up to 12,288 topics (48 KB of LDS: two workgroups of 1,024
-    // threads per CU)
+    // kPhiSteps steps of four columns per thread at a time: up to 8,192 topics (32 KB of LDS; a CU holds two workgroups of
+    // 1,024 threads, by its 32 wavefronts)
     const dim3 block((unsigned)phi_block_threads(c));
     const int range = std::min(c->Kpad, kPhiSteps * 4 * (int)block.x);
     const size_t hist = (size_t)range * sizeof(uint32_t);
@@ -1413,9 +1414,9 @@ static int64_t pull_piece(bool many) { return many ? kPullPiece : kPullPiece / 4
 // Results on their way to the caller's memory: piece i, the elements [cuts[i], cuts[i + 1]) of the device array, is handed
 // to consume(i, host pointer), which puts it where it belongs.  How that is done depends on the bytes written for the caller
 // (out_bytes):
-//   * above by.many, or by.next, by way of pinned staging of kPullSlots slots, which up to kPullThreads threads consume while the next
-//     pieces are in flight.  A caller's fresh pages cost far more than the link: into ordinary memory a copy of 100 M
-//     assignments as int32 took 44 ms, as 16 bits through this path 8;
+//   * above by.many, or by.next, by way of pinned staging of kPullSlots slots, which up to kPullThreads threads consume while
+//     the next pieces are in flight.  A caller's fresh pages cost far more than the link: into ordinary memory a copy of
+//     100 M assignments as int32 took 44 ms, as 16 bits through this path 8;
 //   * below, the calling thread alone, out of two small slots: threads, and the first touch of pinned memory, cost a
 //     context's first call a millisecond (A in CSR of T = 1 M, K = 100, first and later calls: 1.62 and 0.25 ms with them,
 //     0.36 and 0.34 this way, 0.45 and 0.41 by a plain copy);

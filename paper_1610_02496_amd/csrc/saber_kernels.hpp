@@ -1262,7 +1262,7 @@ __global__ void __launch_bounds__(1024) count_dz_kernel(SegGroup a, int64_t na, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Preprocess + BuildTree (Alg. 1; Eq. 2; Sec. 3.2.4), one workgroup of 256 threads per word row.
+// Preprocess + BuildTree (Alg. 1; Eq. 2; Sec. 3.2.4), one workgroup of 256, 512 or 1,024 threads per dense row.
 //   Bhat_vk  = (float(B_vk) + beta) / denom_k,  denom_k = float(C_k) + float(V) * beta   -- single-rounded fp32 ops
 //   l3_64[i] = running sum of Bhat_v through topic (i+1)*64 - 1, accumulated in binary64
 //   l3[i]    = round32(l3_64[i])                                           -- tree level above the bottom, W = 64
