@@ -429,13 +429,14 @@ static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64
 // kDocRanges ranges of documents and launched range by range, each XCD (workgroups go to them round robin) at a range of
 // its own at a time, whose rows its 4 MB L2 holds in part.  Sampling pass, iterations 11..20: T = 100 M, K = 10,000 7.92 ->
 // 7.21 ms, K = 1,000 7.46 -> 6.48; T = 246 M in three chunks, K = 5,000, short documents 15.6 -> 14.4, 240 M of long ones,
-// K = 10,000 26.5 -> 23.8; T = 36 M, K = 5,000 2.27 -> 2.14.  8 or 32 ranges gain half to all of that.  A word is cut if its pieces have 64 tokens on average (32 to 512 differ by 1 to 3 %).  Words that are not cut come
-// first: at the end of the launch their larger tiles cost 3 to 5 %.  Where it stops:
+// K = 10,000 26.5 -> 23.8; T = 36 M, K = 5,000 2.27 -> 2.14.  8 or 32 ranges gain half to all of that.  A word is cut if
+// its pieces have 64 tokens on average (32 to 512 differ by 1 to 3 %).  Words that are not cut come first: at the end of the
+// launch their larger tiles cost 3 to 5 %.  Where it stops:
 //   * chunks whose rows of A the eight L2s hold together (32 MB, taken from the rows' capacities), and chunks below 8 M
 //     tokens, where the pieces are small and 16 times the tiles weigh more than the traffic they save.  Change of the pass by
 //     the cut, per cent, iterations 1..5 / 18..37: T = 4.5 M, rows of 13 to 18 MB (K = 300 to 1,000) +2..+4 / +1..+5, of
 //     28 MB (short documents) +3..+5 / +1..+4; 8 M tokens, 33 MB -4..-1 / +1..+3, 37 MB -2..+3 / -2..+1, 50 MB (short
-//     documents) +2..+5 / -3..0; 12 M, 18 MB +1 / +1, 55 MB -3..+1 / -5..-2; 24 M, 68 to 110 MB -8..-2 / -7..-3.  The
+//     documents) +2..+5 / -3..0; 12 M, 18 MB +1 / +1, 55 MB -3..+1 / -6..0; 24 M, 68 to 110 MB -8..-2 / -7..-3.  The
 //     number of topics alone does not tell: K = 300, 1,000 and 2,500 differ by 1 to 3 where the rows are alike;
 //   * above K = 16,384 the rows are too long (K = 20,011, T = 15 M: first iterations 4.75 -> 5.02 ms, later ones 1.82 -> 1.79), and
 //     rows that are not staged (K = 45,000, T = 20 M) lose the sharing of a row between tiles: 8.9 -> 9.9 ms;
@@ -487,7 +488,7 @@ static int launch_segmented_count(saber_ctx *c, const SegLists &a, const SegList
             const void *fn = c->z16 ? (const void *)count_dz_kernel<uint16_t> : (const void *)count_dz_kernel<int32_t>;
             HIP_TRY(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         }
-        for (int64_t i = 0, n; i < na + nb; i += n) {   // segments [i, i + n) of both lists: one launch unless there are more than a grid takes
+        for (int64_t i = 0, n; i < na + nb; i += n) {   // segments [i, i + n) of the two lists in a row
             n = std::min(na + nb - i, most_blocks(block));
             const int64_t left = std::max<int64_t>(0, std::min(i + n, na) - i);   // of the first list
             SegGroup pa = ga, pb = gb;
@@ -1566,7 +1567,8 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
             if (cd_topic || cd_count) {
                 // unpack the device rows by pieces of whole documents (format conversion only)
                 std::vector<int64_t> cuts(1, 0), piece_doc(1, 0);
-                const int64_t out_bytes = 4 * std::max(2 * cd_row_ptr[c->D], c->cd_cap), piece = pull_piece(pull_many(c, out_bytes, kPullEntries));
+                const int64_t out_bytes = 4 * std::max(2 * cd_row_ptr[c->D], c->cd_cap);
+                const int64_t piece = pull_piece(pull_many(c, out_bytes, kPullEntries));
                 for (int64_t d = 0; d < c->D; d++) {
                     const int64_t end = d + 1 < c->D ? (int64_t)rec[(size_t)d + 1].x * 32 : c->cd_cap;
                     if ((end - cuts.back()) * 4 > piece) { cuts.push_back((int64_t)rec[(size_t)d].x * 32); piece_doc.push_back(d); }
@@ -1590,7 +1592,8 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
                 std::vector<int32_t> row_word((size_t)c->V_dense + 1);
                 HIP_TRY(hipMemcpy(row_word.data(), c->row_word, sizeof(int32_t) * row_word.size(), hipMemcpyDeviceToHost));
                 const int64_t out_bytes = 4 * (int64_t)c->V_dense * c->Kpad;
-                const int64_t rows = std::max<int64_t>(1, pull_piece(pull_many(c, out_bytes, kPullRows)) / ((int64_t)c->Kpad * 4));   // (Kpad * 4 is at most 1 MB)
+                const int64_t piece = pull_piece(pull_many(c, out_bytes, kPullRows));
+                const int64_t rows = std::max<int64_t>(1, piece / ((int64_t)c->Kpad * 4));   // (Kpad * 4 is at most 1 MB)
                 std::vector<int64_t> cuts(1, 0);
                 while (cuts.back() < (int64_t)c->V_dense * c->Kpad)
                     cuts.push_back(std::min<int64_t>((int64_t)c->V_dense * c->Kpad, cuts.back() + rows * c->Kpad));
@@ -1934,7 +1937,8 @@ extern "C" int saber_alias_build_probe(saber_ctx *c, const int32_t *words, int32
     if (!c || m < 0 || (m > 0 && (!words || !prob || !alias)) || !ms_build)
         return fail(SABER_EINVAL, "saber_alias_build_probe: bad argument");
     if (c->parent) return fail(SABER_EINVAL, "saber_alias_build_probe: needs a context made by saber_init");
-    std::vector<int32_t> rows((size_t)std::max(m, 1));
+    std::vector<int32_t> rows;
+    try { rows.resize((size_t)std::max(m, 1)); } catch (const std::bad_alloc &) { return fail(SABER_ENOMEM, "saber_alias_build_probe: out of host memory"); }
     for (int32_t i = 0; i < m; i++) {
         if (words[i] < 0 || words[i] >= c->V) return fail(SABER_EINVAL, "saber_alias_build_probe: word %d is outside [0,%d)", words[i], c->V);
         rows[(size_t)i] = c->h_word_row[(size_t)words[i]];

@@ -242,3 +242,18 @@ def test_classes_of_light_words_have_launches_of_their_own(host):
             assert fake.fake_block(b"estep_kernel") == {1000: 64, 2000: 128, 9000: 512}[K]
             g.close()
     """)
+
+
+def test_host_memory_that_runs_out_is_a_status(host):
+    """No exception leaves the library: also where the list of rows of an inspection call does not fit."""
+    host("""
+        import resource
+        import paper_1610_02496_amd.binding as binding
+        words = np.zeros(1000, np.int32)
+        g = pk.Saber(np.array([0, 1000]), words, 1, 10, 0.1, 0.01, 3, light_word_tokens=-1)
+        out = np.zeros(10)
+        size = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+        resource.setrlimit(resource.RLIMIT_AS, (size + (1 << 30), -1))
+        L, m = binding.load_library(), 1 << 30
+        assert L.saber_alias_build_probe(g._h, words.ctypes.data, m, out.ctypes.data, out.ctypes.data, out.ctypes.data, None) == -2
+    """)
