@@ -60,10 +60,12 @@ typedef struct saber_options {
                                a chunk's sampling pass re-reads stay in the 256 MB Infinity Cache; always at least one
                                chunk per 2^30 tokens */
     int32_t block_threads;  /* threads per workgroup of the sampling kernel (multiple of 64 up to 1024);
-                               default: the size that lets a CU hold the most wavefronts given the LDS the Bhat row takes;
+                               default: the smallest size with which a CU still holds most of its 32 wavefronts given the
+                               LDS the Bhat row takes (with tile_tokens given: the one with the most wavefronts);
                                when the row is not kept in LDS, 256 up to K = 2,048 and 1,024 beyond */
-    int32_t tile_tokens;    /* most tokens of one word handled by one workgroup; default 0: a 8192th of a chunk's tokens,
-                               not below K / 16 (64 to 256) and not above 32,768; with more than 2^19 words a 2560th, not
+    int32_t tile_tokens;    /* most tokens of one word handled by one workgroup; default 0: a 32,768th of a chunk's tokens per
+                               wavefront of the workgroup (at most four), not below K / 16 (64 to 256) and not above
+                               32,768; with more than 2^19 words a 2560th, not
                                below 8,192.  Larger where a document is far longer than a chunk's share, so that a chunk
                                of up to 2^19 words has at most 2^20 tiles (saber_loglik_static) */
     int32_t stage_phi;      /* 1: keep the word's Bhat row in LDS when it fits (up to 150 KB: K <= 37,800), 0: always
@@ -76,7 +78,7 @@ typedef struct saber_options {
     int32_t stage_min_tokens;   /* tiles with at least this many tokens are launched with block_threads threads, smaller
                                    ones with light_block_threads; default 1 (one class) */
     int32_t light_block_threads;/* workgroup size for the smaller tiles and for light words' tiles; default: as block_threads,
-                               and when that is not given either, sized by the tile for light words */
+                               and when that is not given either but tile_tokens is, sized by the tile for light words */
     int32_t light_word_tokens;  /* words with fewer tokens than this keep their row of B sparse (rebuilt by a segmented
                                    count, like a row of A) and their Bhat row is formed in LDS from a base vector and
                                    the non-zeros; default K/2; negative: every word keeps a dense row */

@@ -391,14 +391,70 @@ static int estep_waves_per_cu(const saber_ctx *c, int block) {
     return std::min(by_lds, by_waves) * (block / 64);
 }
 
+// Threads of a sampling workgroup where the caller leaves them open.
+//
+// A staged row: the smallest workgroup with which LDS still lets a CU hold most of its 32 wavefronts.  A word's tile is dealt to
+// the workgroup's wavefronts, and each pays its set-up (Philox for a few lanes, run boundaries, the chain of dependent loads)
+// for its share: sampling pass at T = 20 M, 60,000 words, K from 1,200 to 9,500, always 32 wavefronts per CU: 1.17 ms with 64
+// threads, 1.21 with 128, 1.30 with 256, 1.51 with 512, 1.93 with 1,024.  Fewer wavefronts cost: 28 of them 6 %, 24 11 %, 20
+// 43 %, 16 45 %.  So a size is taken from 31, 28, 24, 20 wavefronts on, the more the larger the next size's loss.  In chunks
+// below 4 M tokens the shares are small and the sizes further apart (T = 1.5 M, 15,000 words: 0.09, 0.11, 0.13, 0.17 and 0.27
+// ms), and 22, 22, 20 and 16 wavefronts do.  T = 10 M, K = 1,000 0.68 -> 0.62 ms, T = 2.3 M, K = 777 0.15 -> 0.13, T = 20 M in
+// four chunks, K = 2,000 2.3 -> 1.6, T = 100 M, K = 1,000 6.45 -> 6.29, all against 256 threads and launches by size of tile.
+//
+// With the caller's tile_tokens the tiles are not matched to the workgroup (below), and one wavefront may be left with the
+// whole of a large one (T = 10 M, K = 73, tiles of 1,280 tokens: 0.53 ms with 64 threads, 0.44 with 128 or with tiles of
+// 320): the size is then the one with the most wavefronts, ties to the smaller, and light words' tiles get launches by size.
+//
+// A row that is not staged is gathered through the caches: the more of a CU's wavefronts
+// work on the same row the better, once it is too long for the 32 KB of a CU's L1 to hold several.  An iteration
+// with 256, 512 and 1,024 threads at V = 50,000, T = 20 M: K = 300 2.03, 2.09 and 2.25 ms, K = 1,000 2.76, 2.69 and
+// 2.81, K = 3,000 4.74, 4.00 and 3.47, K = 10,000 9.16, 7.00 and 6.01, K = 45,000 15.6, 12.9 and 10.6; at V = 100,000,
+// T = 3 M, where most words have few tokens: K = 1,000 0.66, 0.77 and 0.98, K = 3,000 2.16, 2.07 and 2.26 in the
+// first iterations and 1.41, 1.43 and 1.62 in later ones, K = 45,000 15.8, 13.8 and 12.7, and 6.98, 6.96 and 7.21.
+static int estep_auto_block(const saber_ctx *c, int64_t per_chunk) {
+    if (!c->staged) return c->K <= 2048 ? 256 : 1024;
+    if (c->tile_tokens_asked > 0) {
+        int best = 256;
+        for (int block : {512, 1024}) if (estep_waves_per_cu(c, block) > estep_waves_per_cu(c, best)) best = block;
+        return best;
+    }
+    const bool small = per_chunk < (4ll << 20);
+    const int least[4] = {small ? 22 : 31, small ? 22 : 28, small ? 20 : 24, small ? 16 : 20};
+    for (int i = 0; i < 4; i++)
+        if (estep_waves_per_cu(c, 64 << i) >= least[i]) return 64 << i;
+    return 1024;
+}
+
+// Automatic tile size: a heavy word's Bhat row is staged once per tile, so larger tiles stage less; but a tile is
+// the work of one workgroup (its wavefronts take it 64 tokens at a time), and the pass waits for its largest ones.
+// A 32,768th of the chunk per wavefront of the workgroup, at most an 8192th and at most 32,768 tokens.  With 256 threads the
+// sampling pass took 0.36 / 0.10 ms with tiles of 8,192 / 128
+// tokens at T = 1 M, K = 300, 1.15 / 0.89 ms with 8,192 / 1,024 at 10 M, K = 1,000, 2.43 / 2.34 ms with 14,000 /
+// 4,096 at 36 M, K = 5,000, and 9.14 / 9.06 ms with 32,768 / 8,192 at 100 M, K = 10,000 (512 threads); with 64 threads 0.53 /
+// 0.43 ms with 1,280 / 320 at 10 M, K = 73, and 7.31 / 6.30 / 6.29 with 12,160 / 3,008 / 1,472 at 100 M, K = 1,000.
+// A small tile has to be worth its row, though: not below K / 16 tokens, 64 to 256 (T = 300,000, K = 10,000: 0.072 ms with
+// 64, 0.058 with 256).
+static int32_t auto_tile_tokens(const saber_ctx *c, int64_t per_chunk) {
+    // (a vocabulary of more than 2^19 words makes a tile or more per word as it is: larger tiles keep a chunk's within
+    // the 2^20 of saber_loglik_static)
+    const bool many_words = c->V > (1 << 19);
+    // (likewise where documents are longer than the share of a chunk: it then has as many tokens as the longest more)
+    const int64_t longest = (((per_chunk + c->max_doc_len) >> 19) + 64) & ~63ll;
+    const int64_t least = many_words ? 8192 : std::max<int64_t>(longest, std::min<int64_t>(256, std::max<int64_t>(64, (c->K / 16) & ~63)));
+    const int waves = c->staged ? std::min(4, c->opt.block_threads / 64) : 4;
+    const int64_t share = many_words ? (per_chunk / 2560) & ~255ll : (per_chunk * waves / 32768) & ~63ll;
+    return (int32_t)std::min<int64_t>(32768, std::max<int64_t>(least, share));
+}
+
 // Cuts a chunk's tiles - n_dense of words with dense rows, then those of light words, each group sorted by decreasing size -
 // into classes.  Dense rows: tiles with at least stage_min_tokens tokens get block_threads threads, smaller ones
-// light_block_threads.  Light words, unless the caller fixed a workgroup size: one wavefront per 64 tokens (a full batch),
-// between the smallest workgroup with which LDS still lets a CU hold 24 of its 32 wavefronts and block_threads.  A small
-// tile dealt to many wavefronts pays each one's set-up and chain of dependent loads for a few tokens: K = 1,000, T = 10 M
-// (90,000 light words of 29 tokens on average), sampling pass 0.89 ms with 256 threads for all of them, 0.77 ms so; K = 2,000,
-// 5 M tokens per chunk: 2.09 and 1.89 ms per four chunks.  Up to two rounds of the chip's 8,192 wavefronts it makes no
-// difference (T = 2 M, K = 777: 0.17 ms both), and the light words' tiles then go with the dense rows' launch.
+// light_block_threads.  Light words get light_block_threads as well, and one launch takes all tiles where the two are equal, as
+// they are by default.  With the caller's tile_tokens, unless the caller fixed a workgroup size: one wavefront per 64 tokens
+// (a full batch), between the smallest workgroup with which LDS still lets a CU hold 24 of its 32 wavefronts and block_threads
+// (K = 1,000, T = 10 M, 90,000 light words of 29 tokens on average: 0.89 ms with 256 threads for all of them, 0.77 ms so).  Up
+// to two rounds of the chip's 8,192 wavefronts that makes no difference (T = 2 M, K = 777: 0.17 ms both), and the light
+// words' tiles then go with the dense rows' launch.
 static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64_t n_dense) {
     int64_t at = 0;
     auto add = [&](int64_t to, int block) {
@@ -416,7 +472,7 @@ static void tile_classes(const saber_ctx *c, Chunk &ch, const Tile *tiles, int64
     else add(n_dense, c->opt.block_threads);
     add(n_dense, c->opt.light_block_threads);
     int lo = c->opt.light_block_threads, hi = c->opt.light_block_threads;
-    if (c->auto_light_block && ch.ntiles - n_dense > 16384) { lo = 64; while (lo < hi && estep_waves_per_cu(c, lo) < 24) lo *= 2; }
+    if (c->auto_light_block && c->tile_tokens_asked > 0 && ch.ntiles - n_dense > 16384) { lo = 64; while (lo < hi && estep_waves_per_cu(c, lo) < 24) lo *= 2; }
     for (int block = hi; block > lo; block /= 2) {
         const int64_t to = until(ch.ntiles, 64 * (block / 128) + 1);   // tiles that half the workgroup would not serve in one batch each
         if (to - at >= 128 || (block == hi && !ch.classes.empty() && ch.classes.back().block == hi)) add(to, block);   // (a launch of its own pays from half a workgroup per CU on)
@@ -1234,24 +1290,7 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
     // token positions inside a chunk are 32-bit: keep every chunk below 2^30 tokens (documents are far shorter)
     opt.n_chunks = (int32_t)std::max<int64_t>(opt.n_chunks, (T >> 30) + 1);
     if ((int64_t)opt.n_chunks > std::max<int64_t>(D, 1)) opt.n_chunks = (int32_t)std::max<int64_t>(D, 1);
-    // automatic tile size: a heavy word's Bhat row is staged once per tile, so larger tiles stage less; but a tile is
-    // the work of one workgroup (its wavefronts take it 64 tokens at a time), and the pass waits for its largest ones.
-    // A 8192th of the chunk, at most 32,768 tokens: the sampling pass took 0.36 / 0.10 ms with tiles of 8,192 / 128
-    // tokens at T = 1 M, K = 300, 1.15 / 0.89 ms with 8,192 / 1,024 at 10 M, K = 1,000, 2.43 / 2.34 ms with 14,000 /
-    // 4,096 at 36 M, K = 5,000, and 9.14 / 9.06 ms with 32,768 / 8,192 at 100 M, K = 10,000.  A small tile has to be
-    // worth its row, though: not below K / 16 tokens, 64 to 256 (T = 300,000, K = 10,000: 0.072 ms with 64, 0.058 with 256).
     const int32_t tile_tokens_asked = opt.tile_tokens;
-    if (opt.tile_tokens <= 0) {
-        const int64_t per_chunk = T / std::max(1, opt.n_chunks);
-        // (a vocabulary of more than 2^19 words makes a tile or more per word as it is: larger tiles keep a chunk's within
-        // the 2^20 of saber_loglik_static)
-        const bool many_words = V > (1 << 19);
-        // (likewise where documents are longer than the share of a chunk: it then has as many tokens as the longest more)
-        const int64_t longest = (((per_chunk + maxlen) >> 19) + 64) & ~63ll;
-        const int64_t least = many_words ? 8192 : std::max<int64_t>(longest, std::min<int64_t>(256, std::max<int64_t>(64, (K / 16) & ~63)));
-        const int64_t share = many_words ? (per_chunk / 2560) & ~255ll : (per_chunk / 8192) & ~63ll;
-        opt.tile_tokens = (int32_t)std::min<int64_t>(32768, std::max<int64_t>(least, share));
-    }
 
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return fail(SABER_EDEVICE, "saber_init: no HIP device available");
@@ -1262,7 +1301,7 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
     if (hipGetDevice(&c->device) != hipSuccess) { delete c; return fail(SABER_EDEVICE, "saber_init: hipGetDevice failed"); }
     { const int rc0 = static_scratch_init(c->device); if (rc0 != SABER_OK) { delete c; return rc0; } }
     c->D = D; c->T = T; c->V = V; c->K = K; c->alpha = alpha; c->beta = beta; c->seed = seed; c->opt = opt; c->tile_tokens_asked = tile_tokens_asked;
-    c->parent = parent; c->no_state = no_state;
+    c->parent = parent; c->no_state = no_state; c->max_doc_len = maxlen;
     c->n_slots = std::max(0, opt.stream_workers);
     c->Kpad = (K + 63) / 64 * 64;
     c->n3 = c->Kpad / 64;
@@ -1276,25 +1315,14 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
         c->lds_per_cu = 64 * 1024;
     const size_t stage_limit = std::min<size_t>(150 * 1024, (size_t)c->lds_per_cu > 10 * 1024 ? (size_t)c->lds_per_cu - 10 * 1024 : 0);
     c->staged = opt.stage_phi && estep_row_bytes(c) <= std::max<size_t>(stage_limit, 54 * 1024);
+    const int64_t per_chunk = T / std::max(1, c->opt.n_chunks);
     if (opt_in == nullptr || opt_in->block_threads <= 0) {
-        // automatic workgroup size: the one that lets a CU hold the most wavefronts given the LDS footprint; ties go to
-        // the smaller size.  A row that is not staged is gathered through the caches: the more of a CU's wavefronts
-        // work on the same row the better, once it is too long for the 32 KB of a CU's L1 to hold several.  An iteration
-        // with 256, 512 and 1,024 threads at V = 50,000, T = 20 M: K = 300 2.03, 2.09 and 2.25 ms, K = 1,000 2.76, 2.69 and
-        // 2.81, K = 3,000 4.74, 4.00 and 3.47, K = 10,000 9.16, 7.00 and 6.01, K = 45,000 15.6, 12.9 and 10.6; at V = 100,000,
-        // T = 3 M, where most words have few tokens: K = 1,000 0.66, 0.77 and 0.98, K = 3,000 2.16, 2.07 and 2.26 in the
-        // first iterations and 1.41, 1.43 and 1.62 in later ones, K = 45,000 15.8, 13.8 and 12.7, and 6.98, 6.96 and 7.21.
-        int best = 256, best_waves = 0;
-        for (int block : {256, 512, 1024}) {
-            const int waves = estep_waves_per_cu(c, block);
-            if (waves > best_waves || (!c->staged && K > 2048)) { best_waves = waves; best = block; }
-        }
-        c->opt.block_threads = best;
+        c->opt.block_threads = estep_auto_block(c, per_chunk);
         c->auto_light_block = c->opt.light_block_threads <= 0;
     }
     if (c->opt.light_block_threads <= 0) c->opt.light_block_threads = c->opt.block_threads;
+    if (c->opt.tile_tokens <= 0) c->opt.tile_tokens = auto_tile_tokens(c, per_chunk);
     c->vbeta = (float)V * beta;
-    c->max_doc_len = maxlen;
     int rc;
     if ((rc = check_estep_lds_layout()) != SABER_OK) { delete c; return rc; }
     try { rc = build(c, doc_ptr, word_ids); }

@@ -156,6 +156,30 @@ def test_threads_of_a_workgroup_whose_row_is_not_staged(host, K, threads):
     """ % (K, threads))
 
 
+@pytest.mark.parametrize("T,edges", [(5000, {64: 1724, 128: 3612, 256: 8024, 512: 20124}),
+                                     (4_300_000, {64: 1220, 128: 2732, 256: 6640, 512: 13316})])
+def test_threads_and_tiles_of_a_workgroup_whose_row_is_staged(host, T, edges):
+    """The smallest workgroup with which LDS leaves a CU enough wavefronts, more of them in large chunks; a tile is a 32,768th of
+    the chunk per wavefront.  Both sides of every line; a caller's tile_tokens keeps the size with the most wavefronts."""
+    host("""
+        T, edges = %d, %r
+        words = np.zeros(T, np.int32)
+        doc_ptr = np.r_[np.arange(0, T, 1000), T]
+        for block, K in edges.items():
+            for k, b in ((K, block), (K + 4, 2 * block)):
+                tile = min(256, max(64, k // 16 & ~63), 1 << 15)
+                tile = max(tile, (T * min(b // 64, 4) // 32768) & ~63)
+                g = pk.Saber(doc_ptr, words, 1, k, 0.1, 0.01, 3)
+                g.iterate(1)
+                assert fake.fake_block(b"estep_kernel") == b, (k, b, fake.fake_block(b"estep_kernel"))
+                assert g.get_stats()["tiles"] == -(-T // tile), (k, b, g.get_stats()["tiles"], tile)
+                g.close()
+        g = pk.Saber(doc_ptr, words, 1, 100, 0.1, 0.01, 3, tile_tokens=1024)
+        g.iterate(1)
+        assert fake.fake_block(b"estep_kernel") == 256
+    """ % (T, edges))
+
+
 @pytest.mark.parametrize("K,T,least,most", [(100, 1 << 20, 0, 0), (100, (1 << 20) + 1, 1, 1 << 19), (100, 2 << 20, 1, 1 << 19),
                                             (100, (2 << 20) + 1, 3 << 20, 13 << 20), (70000, 2 << 20, 0, 0),
                                             (70000, (2 << 20) + 1, 3 << 20, 13 << 20)])
