@@ -65,8 +65,7 @@ typedef struct saber_options {
                                when the row is not kept in LDS, 256 up to K = 2,048 and 1,024 beyond */
     int32_t tile_tokens;    /* most tokens of one word handled by one workgroup; default 0: a 32,768th of a chunk's tokens per
                                wavefront of the workgroup (at most four), not below K / 16 (64 to 256) and not above
-                               32,768; with more than 2^19 words a 2560th, not
-                               below 8,192.  Larger where a document is far longer than a chunk's share, so that a chunk
+                               32,768; with more than 2^19 words a 2560th, not below 8,192.  Larger where a document is far longer than a chunk's share, so that a chunk
                                of up to 2^19 words has at most 2^20 tiles (saber_loglik_static) */
     int32_t stage_phi;      /* 1: keep the word's Bhat row in LDS when it fits (up to 150 KB: K <= 37,800), 0: always
                                gather from global; default 1 */
@@ -120,6 +119,8 @@ typedef struct saber_stats {
     double ms_count_dz;       /* CountByDZ, and the sparse rows of B (counted in the same launches) */
     double ms_ck;             /* topic totals C_k, and the rows of B of the most frequent words (same launch) */
     double ms_phi;            /* Preprocess + BuildTree, and the other dense rows of B */
+                              /* (a small corpus' M-step takes two launches: all counts, totals included, are in
+                                 ms_count_dz then, the rest in ms_phi, and ms_ck is 0) */
     double ms_total;          /* whole iterations, first kernel to last */
     int64_t sample_launches;  /* sampling-kernel launches timed */
     int64_t sum_tokens;       /* tokens sampled */

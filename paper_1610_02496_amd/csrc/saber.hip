@@ -167,15 +167,17 @@ struct saber_ctx {
     void *z_wm = nullptr;             // [T] word-major assignments: the light words' tokens first, then the dense rows' ones
     int64_t T_light = 0, lw_cap = 0;
     VzItem *vz_items = nullptr;       // slabs of the dense-row words' segments of z_wm, those of the longest rows first
-    int64_t n_vz_items = 0, n_vz_long = 0;   // all; those of rows that phi_tree_kernel does not count itself
-    PhiRow *phi_rows = nullptr;       // [V_dense+1] the dense rows as phi_tree_kernel takes them
+    int64_t n_vz_items = 0, n_vz_long = 0;   // all; those of rows that are not counted where they are normalised
+    PhiRow *phi_rows = nullptr;       // [V_dense+1] the dense rows as phi_row() takes them
+    bool joined = false;              // the M-step takes two launches (see launch_joined_mstep)
     std::vector<int32_t> h_word_row;  // host: word -> dense row (>= 0) or -(light row) - 1
     // A context built on a trained model (held-out documents): it borrows the model's word classes, Bhat, tree
     // levels and sparse rows, owns only its own tokens, z and rows of A, and never rebuilds B.
     const saber_ctx *parent = nullptr;
     bool no_state = false;            // no assignments of its own (tokens that are only scored)
     int32_t *cwk = nullptr;           // [V_dense+1][Kpad]
-    unsigned long long *ck = nullptr, *ck_acc = nullptr; // [K] topic totals; their accumulators, zero outside the M-step
+    unsigned long long *ck = nullptr, *ck_acc = nullptr; // [K] topic totals; their accumulators, zero outside the M-step, and a
+                                                         // ticket counter behind them, likewise
     bool acc_used = true;             // cwk or ck_acc may hold counts: set before any are added, cleared once what empties them is queued
     float *denom = nullptr;           // [K] denominators of Eq. 2
     float *phi = nullptr, *l3 = nullptr, *sumphi = nullptr;
@@ -639,22 +641,25 @@ static int sync_all(saber_ctx *c) {
 }
 
 // Preprocess + BuildTree for the light words (sparse rows of B); needs the base vector, i.e. runs after launch_phi
+static LightParams light_params(const saber_ctx *c) {
+    return LightParams{c->light_words, c->wrec, c->lw_ent, c->lw_phi, c->denom, c->phi + (size_t)c->V_dense * (size_t)c->Kpad,
+                       c->l3_64 + (size_t)c->V * (size_t)c->n3, c->l3, c->l3_64, c->sumphi, c->n3, c->n3pad, c->topic_bits, c->beta};
+}
 static int launch_light_words(saber_ctx *c) {
     if (c->V_light == 0) return SABER_OK;
-    const size_t lds = (size_t)c->n3 * (sizeof(double) + sizeof(int));
-    hipLaunchKernelGGL(light_tree_kernel, dim3((unsigned)c->V_light), dim3(64), lds, c->stream, c->light_words, c->wrec,
-                       c->lw_ent, c->lw_phi, c->denom, c->phi + (size_t)c->V_dense * (size_t)c->Kpad,
-                       c->l3_64 + (size_t)c->V * (size_t)c->n3, c->l3, c->l3_64, c->sumphi, c->n3, c->n3pad,
-                       c->topic_bits, c->beta);
+    hipLaunchKernelGGL(light_tree_kernel, dim3((unsigned)c->V_light), dim3(64), light_lds_bytes(c->n3), c->stream, light_params(c));
     HIP_TRY(hipGetLastError());
     return SABER_OK;
 }
 
 // dense-branch tokens (slots, or null), nnz(A), sum_d K_d L_d, sum_d K_d U_d and the non-zeros of the sparse rows of B
 // (what the next E-step will read) into five device counters
+static StatsParams stats_params(const saber_ctx *c, const unsigned long long *slots, unsigned long long *out) {
+    return StatsParams{slots, slots ? kDenseSlots : 0, c->docrec, c->doc_ptr, c->doc_words, c->D, c->wrec, c->V_light, out};
+}
+static int stats_blocks(const saber_ctx *c, int block) { return grid_for(std::max<int64_t>(c->D, c->V_light), block, 256); }
 static int launch_stats(saber_ctx *c, const unsigned long long *slots, unsigned long long *out) {
-    hipLaunchKernelGGL(stats_kernel, dim3(grid_for(std::max<int64_t>(c->D, c->V_light), 256, 256)), dim3(256), 0, c->stream, slots,
-                       slots ? kDenseSlots : 0, c->docrec, c->doc_ptr, c->doc_words, c->D, c->wrec, c->V_light, out);
+    hipLaunchKernelGGL(stats_kernel, dim3(stats_blocks(c, 256)), dim3(256), 0, c->stream, stats_params(c, slots, out));
     HIP_TRY(hipGetLastError());
     return SABER_OK;
 }
@@ -678,7 +683,7 @@ static int launch_clear_accumulators(saber_ctx *c, bool totals) {
     hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for((int64_t)vk, 256, 8192)), dim3(256), 0, c->stream, (uint32_t *)c->cwk, 0u, vk);
     HIP_TRY(hipGetLastError());
     if (totals) {
-        hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(2 * (int64_t)c->K, 256)), dim3(256), 0, c->stream, (uint32_t *)c->ck_acc, 0u, (size_t)c->K * 2);
+        hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(2 * (int64_t)c->K + 1, 256)), dim3(256), 0, c->stream, (uint32_t *)c->ck_acc, 0u, (size_t)c->K * 2 + 1);
         HIP_TRY(hipGetLastError());
     }
     c->acc_used = false;
@@ -730,6 +735,19 @@ static size_t alias_lds_bytes(int K) { return ((size_t)K + 1) * sizeof(double) +
 // Threads of a phi_tree_kernel workgroup: a column for each of its four per step
 static int phi_block_threads(const saber_ctx *c) { return c->Kpad <= 1024 ? 256 : c->Kpad <= 2048 ? 512 : 1024; }
 
+// Which contexts' M-steps take two launches instead of seven or eight: those with light words, resident, and small.  An iteration
+// that way and the other: T = 100 K, K = 100 30 and 38 us; 1 M, K = 21 75 and 103; 1.9 M, K = 44 98 and 120; 2.3 M, K = 777 162 and
+// 181; 10 M, K = 1,000 649 and 671; 10.8 M in 207,000 documents, K = 73 519 and 544.  Not with more topics than 4,096, where the last
+// workgroup of the totals takes longer than the launches saved (T = 725 K, K = 3,000 84 and 92 us, 5,612 99 and 96, 14,000 174 and
+// 156), nor with more segments (T = 36 M, 535,000 documents and light words: 2,604 and 2,577): wavefronts that share a workgroup
+// hold their places until the last is done.
+constexpr int kJoinedTopics = 4096;
+constexpr int64_t kJoinedSegments = 384 * 1024, kJoinedTokens = 16ll << 20;
+// Assignments of one share of the totals, or of one slab, in a joined M-step (its workgroups have 256 threads, and every share
+// ends with K atomics, a fence and a ticket): T = 2.3 M, K = 777 182, 177, 169, 161 us per iteration with 4, 8, 17, 48 thousand;
+// T = 10 M, K = 1,000 649 with T / 48, 653 with T / 32, 686 with T / 20.
+static int64_t joined_share(const saber_ctx *c) { return std::max<int64_t>(std::max<int64_t>(16384, std::min(16 * c->K, 65536)), (c->T / 48 + 4095) & ~4095ll); }
+
 static int launch_phi(saber_ctx *c) {
     hipLaunchKernelGGL(denominators_kernel, dim3(grid_for(c->Kpad, 256)), dim3(256), 0, c->stream, c->ck_acc, c->ck, c->denom, c->K,
                        c->Kpad, c->vbeta);
@@ -760,6 +778,42 @@ static int launch_phi(saber_ctx *c) {
         hipLaunchKernelGGL(alias_sweep_kernel, dim3((unsigned)c->V_dense), dim3(kAliasThreads), lds, c->stream, c->phi, c->K, c->Kpad, c->alias_table);
         HIP_TRY(hipGetLastError());
     }
+    return SABER_OK;
+}
+
+// The M-step of a small corpus: all counts in one launch, all that follows from them in another (see MCounts).
+static int launch_joined_mstep(saber_ctx *c, const unsigned long long *slots, unsigned long long *stats_out, hipEvent_t counted) {
+    if (c->acc_used) SABER_TRY(launch_clear_accumulators(c, true));
+    MCounts p{};
+    p.docs = SegGroup{c->long_docs, c->doc_ptr, c->z, 0, c->docrec, c->cd_ent}; p.short_docs = c->short_docs;
+    p.words = SegGroup{c->light_long, c->light_tok_ptr, c->z_wm, 0, c->wrec, c->lw_ent}; p.short_words = c->light_short;
+    p.n_long_docs = (int)c->n_long; p.n_short_docs = (int)c->n_short;
+    p.n_long_words = (int)c->n_light_long; p.n_short_words = (int)c->n_light_short;
+    p.T = c->T; p.per_block = joined_share(c); p.n_tot = (int)((c->T + p.per_block - 1) / p.per_block); p.n_items = (int)c->n_vz_long;
+    p.acc = c->ck_acc; p.ck = c->ck; p.ticket = (unsigned *)(c->ck_acc + c->K);
+    p.items = c->vz_items; p.cwk = c->cwk;
+    p.topic_bits = c->topic_bits; p.nwords = c->nwords; p.lds_entries = std::min(c->opt.dz_lds_entries, c->K); p.wave_entries = std::min(c->opt.long_doc_tokens, c->K);
+    p.vbeta = c->vbeta; p.beta = c->beta; p.denom = c->denom; p.phi = c->phi; p.l3 = c->l3; p.sumphi = c->sumphi; p.l3_64 = c->l3_64;
+    p.K = c->K; p.Kpad = c->Kpad; p.n3 = c->n3; p.n3pad = c->n3pad; p.range = std::min(c->Kpad, kPhiSteps * 4 * 256);
+    p.base_row = c->V_dense; p.base_word = c->V;
+    const int64_t n_short = (int64_t)p.n_short_docs + p.n_short_words;
+    const int64_t grid = (int64_t)p.n_tot + p.n_items + p.n_long_docs + p.n_long_words + (n_short + 3) / 4;
+    const size_t lds = 4 * std::max({(size_t)c->Kpad, (size_t)2 * c->nwords + (size_t)p.lds_entries, 4 * ((size_t)2 * c->nwords + (size_t)p.wave_entries)});
+    SABER_TRY(allow_lds((const void *)mstep_counts_kernel, lds));
+    c->acc_used = true;
+    hipLaunchKernelGGL(mstep_counts_kernel, dim3((unsigned)grid), dim3(256), lds, c->stream, p);
+    HIP_TRY(hipGetLastError());
+    if (counted) HIP_TRY(hipEventRecord(counted, c->stream));
+    const int block = phi_block_threads(c), nw = block / 64, range = std::min(c->Kpad, kPhiSteps * 4 * block);
+    const LightParams lp = light_params(c);
+    const StatsParams st = stats_params(c, slots, stats_out);
+    const int n_stats = stats_blocks(c, block);
+    const unsigned grid2 = (unsigned)(n_stats + c->V_dense + (c->V_light + nw - 1) / nw);
+    const size_t lds2 = std::max((size_t)range * 4, (size_t)nw * light_lds_bytes(c->n3));
+    hipLaunchKernelGGL(mstep_rows_kernel, dim3(grid2), dim3((unsigned)block), lds2, c->stream, c->phi_rows, c->V_dense,
+                       (const uint16_t *)c->z_wm, c->cwk, c->phi, c->Kpad, range, st, n_stats, lp, c->V_light);
+    HIP_TRY(hipGetLastError());
+    c->acc_used = false;
     return SABER_OK;
 }
 
@@ -841,25 +895,24 @@ static int full_mstep(saber_ctx *c, const int32_t *user_z = nullptr) {
         SABER_TRY(launch_segmented_count(c, SegLists{}, own_light_segments(c)));
     } else {
         if (!c->parent) SABER_TRY(launch_fill_zwm(c));
-        SABER_TRY(launch_counts(c));
+        if (!c->joined) SABER_TRY(launch_counts(c));
     }
     if (c->parent) {   // held-out documents: A only, the model stays frozen
         HIP_TRY(hipStreamSynchronize(c->stream));
         return SABER_OK;
     }
-    SABER_TRY(launch_count_slabs(c, c->n_vz_long, true));
-    SABER_TRY(launch_phi(c));
-    SABER_TRY(launch_light_words(c));
-    SABER_TRY(sync_all(c));
-    return SABER_OK;
-}
-
-// Workload numbers of the E-step that will read the current A: nnz(A) and sum_d K_d * L_d.
-static int refresh_workload_stats(saber_ctx *c) {
+    // with the workload numbers of the E-step that will read the new A: nnz(A), sum_d K_d * L_d, ...
     hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, c->stream, (uint32_t *)c->counters, 0u, (size_t)kCtr * 2);
     HIP_TRY(hipGetLastError());
-    SABER_TRY(launch_stats(c, nullptr, c->counters));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    if (c->joined) {
+        SABER_TRY(launch_joined_mstep(c, nullptr, c->counters, nullptr));
+    } else {
+        SABER_TRY(launch_count_slabs(c, c->n_vz_long, true));
+        SABER_TRY(launch_phi(c));
+        SABER_TRY(launch_light_words(c));
+        SABER_TRY(launch_stats(c, nullptr, c->counters));
+    }
+    SABER_TRY(sync_all(c));
     unsigned long long h[kCtr];
     HIP_TRY(hipMemcpy(h, c->counters, sizeof(h), hipMemcpyDeviceToHost));
     c->stats.nnz_cd = (int64_t)h[1]; c->stats.next_row_entries = (int64_t)h[2]; c->stats.next_row_fetch = (int64_t)h[3];
@@ -908,6 +961,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     for (int64_t t = 0; t < T; t++) n_v[(size_t)word_ids[t]]++;
     const bool light_ok = c->staged && c->z16 && c->opt.light_word_tokens > 0;
     const saber_ctx *par = c->parent;   // then the model's word classes are taken over
+    c->joined = light_ok && !par && c->n_slots == 0 && c->opt.ablation == 0 && K <= kJoinedTopics && D + V <= kJoinedSegments && T <= kJoinedTokens;
     // a packed entry of a sparse row has at least 16 count bits when the assignments are 16-bit
     c->opt.light_word_tokens = std::min(c->opt.light_word_tokens, 65536);
     c->h_word_row.assign((size_t)V, 0);
@@ -968,6 +1022,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         }
     }
     c->stats.stream_workers = c->n_slots;
+    c->joined = c->joined && c->n_slots == 0 && c->V_light > 0 && T > 0;
 
     // ---- word-major token arrays and tiles per chunk (host counting sort; layout only) ----
     // position of every word's segment in the word-major order (light words first, then dense rows) and the
@@ -982,7 +1037,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     {
         for (int32_t li = 0; li < c->V_light; li++) wm_ptr[(size_t)h_light_words[(size_t)li]] = h_light_tok_ptr[(size_t)li];
         int64_t pos = c->T_light;
-        const int64_t slab = 131072;
+        const int64_t slab = c->joined ? joined_share(c) : 131072;
         for (int32_t r = 0; r < c->V_dense; r++) {
             const int32_t v = h_row_word[(size_t)r];
             wm_ptr[(size_t)v] = pos;
@@ -1141,7 +1196,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         c->phi = par->phi; c->l3 = par->l3; c->l3_64 = par->l3_64; c->sumphi = par->sumphi;
         c->wrec = par->wrec; c->lw_ent = par->lw_ent; c->lw_phi = par->lw_phi;
     } else {
-    SABER_TRY(dev_alloc(c->hooks, &c->cwk, vk)); SABER_TRY(dev_alloc(c->hooks, &c->ck, (size_t)K)); SABER_TRY(dev_alloc(c->hooks, &c->ck_acc, (size_t)K)); SABER_TRY(dev_alloc(c->hooks, &c->denom, (size_t)c->Kpad));
+    SABER_TRY(dev_alloc(c->hooks, &c->cwk, vk)); SABER_TRY(dev_alloc(c->hooks, &c->ck, (size_t)K)); SABER_TRY(dev_alloc(c->hooks, &c->ck_acc, (size_t)K + 1)); SABER_TRY(dev_alloc(c->hooks, &c->denom, (size_t)c->Kpad));
     SABER_TRY(dev_alloc(c->hooks, &c->phi, vk)); SABER_TRY(dev_alloc(c->hooks, &c->l3_64, ((size_t)V + 1) * (size_t)c->n3));
     SABER_TRY(dev_alloc(c->hooks, &c->row_word, h_row_word.size())); SABER_TRY(dev_alloc(c->hooks, &c->light_words, h_light_words.size()));
     SABER_TRY(dev_alloc(c->hooks, &c->light_short, h_light_short.size())); SABER_TRY(dev_alloc(c->hooks, &c->light_long, h_light_long.size()));
@@ -1203,7 +1258,6 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     if (!c->n_slots) SABER_TRY(launch_init_z(c, c->z, 0, 0, T));   // with host streaming: chunk by chunk, in full_mstep
     SABER_TRY(full_mstep(c));
     if (par) return SABER_OK;
-    SABER_TRY(refresh_workload_stats(c));
     c->stats.words_present = 0;
     for (const Chunk &ch : c->chunks) c->stats.words_present += ch.words_present;
     c->stats.light_tokens = c->T_light;
@@ -1380,6 +1434,12 @@ extern "C" int saber_iterate(saber_ctx *c, int32_t n) {
             }
             if (prof) HIP_TRY(hipEventRecord(ev[EV_SAMPLE], c->stream));
             // M-step
+            const unsigned long long *slots = c->dense_slots + (size_t)kDenseSlots * b;
+            if (c->joined) {
+                SABER_TRY(launch_joined_mstep(c, slots, c->counters + kCtr * b, prof ? ev[EV_DZ] : nullptr));
+                if (prof) { HIP_TRY(hipEventRecord(ev[EV_CK], c->stream)); HIP_TRY(hipEventRecord(ev[EV_PHI], c->stream)); }
+                continue;
+            }
             if (c->n_slots) SABER_TRY(launch_segmented_count(c, SegLists{}, own_light_segments(c)));
             else SABER_TRY(launch_counts(c));
             if (prof) HIP_TRY(hipEventRecord(ev[EV_DZ], c->stream));
@@ -1388,7 +1448,7 @@ extern "C" int saber_iterate(saber_ctx *c, int32_t n) {
             SABER_TRY(launch_phi(c));
             SABER_TRY(launch_light_words(c));
             if (prof) HIP_TRY(hipEventRecord(ev[EV_PHI], c->stream));
-            SABER_TRY(launch_stats(c, c->dense_slots + (size_t)kDenseSlots * b, c->counters + kCtr * b));
+            SABER_TRY(launch_stats(c, slots, c->counters + kCtr * b));
         }
         SABER_TRY(sync_all(c));
         unsigned long long h[kMaxTimedIters * kCtr];
@@ -1873,7 +1933,6 @@ extern "C" int saber_set_z(saber_ctx *c, const int32_t *z, uint32_t iter) {
     c->iter = iter;
     try { SABER_TRY(full_mstep(c, c->n_slots ? z : nullptr)); }
     catch (const std::bad_alloc &) { return fail(SABER_ENOMEM, "saber_set_z: out of host memory"); }
-    SABER_TRY(refresh_workload_stats(c));
     return SABER_OK;
 }
 

@@ -967,24 +967,24 @@ __global__ void prefix_export_kernel(const float *rows, const double *l3_64, con
 // ---------------------------------------------------------------------------------------------
 struct VzItem { int32_t row; int32_t count; int64_t begin; };   // slab: count tokens from z_wm[begin] on
 
-// f(topic) for each of the n assignments at zs, the workgroup's threads sharing the work: 16-byte loads (8 or 4
+// f(topic) for each of the n assignments at zs, nt threads sharing the work (this is thread i0): 16-byte loads (8 or 4
 // assignments per lane and load) over the aligned middle, single loads for the unaligned head and the tail.
 // A one-assignment-per-load loop is bound by the latency of its dependent loads, not by bandwidth.
 template <typename ZT, typename F>
-__device__ __forceinline__ void block_for_each_z(const ZT *__restrict__ zs, int64_t n, F f) {
+__device__ __forceinline__ void for_each_z(const ZT *__restrict__ zs, int64_t n, int i0, int nt, F f) {
     constexpr int kPer = 16 / (int)sizeof(ZT);
     int64_t head = (int64_t)(((16u - (unsigned)(reinterpret_cast<uintptr_t>(zs) & 15u)) & 15u) / sizeof(ZT));
     if (head > n) head = n;
-    for (int64_t i = threadIdx.x; i < head; i += blockDim.x) f((uint32_t)zs[i]);
+    for (int64_t i = i0; i < head; i += nt) f((uint32_t)zs[i]);
     const int64_t nvec = (n - head) / kPer;
     const uint4 *__restrict__ v = reinterpret_cast<const uint4 *>(zs + head);
     // the next 16 bytes are requested before the current ones are handed to f: f's work (LDS atomics, as a rule)
     // does not depend on them, so their latency passes under it
-    int64_t j = threadIdx.x;
+    int64_t j = i0;
     uint4 q = make_uint4(0u, 0u, 0u, 0u);
     if (j < nvec) q = v[j];
     while (j < nvec) {
-        const int64_t jn = j + blockDim.x;
+        const int64_t jn = j + nt;
         uint4 qn = make_uint4(0u, 0u, 0u, 0u);
         if (jn < nvec) qn = v[jn];
         if (sizeof(ZT) == 2) {
@@ -995,7 +995,22 @@ __device__ __forceinline__ void block_for_each_z(const ZT *__restrict__ zs, int6
         }
         q = qn; j = jn;
     }
-    for (int64_t i = head + nvec * kPer + threadIdx.x; i < n; i += blockDim.x) f((uint32_t)zs[i]);
+    for (int64_t i = head + nvec * kPer + i0; i < n; i += nt) f((uint32_t)zs[i]);
+}
+
+template <typename ZT, typename F>
+__device__ __forceinline__ void block_for_each_z(const ZT *__restrict__ zs, int64_t n, F f) { for_each_z(zs, n, (int)threadIdx.x, (int)blockDim.x, f); }
+
+// hist[k - k0] = assignments of topic k in [k0, k0 + n) among the len at zs; add(k - k0, count) for those that are not zero.
+template <typename ZT, typename F>
+__device__ __forceinline__ void count_slab(const ZT *__restrict__ zs, int64_t len, uint32_t *hist, int k0, int n, bool all_topics, F add) {
+    for (int k = threadIdx.x; k < n; k += blockDim.x) hist[k] = 0u;
+    __syncthreads();
+    if (all_topics) block_for_each_z(zs, len, [&](uint32_t k) { atomicAdd(&hist[k], 1u); });
+    else block_for_each_z(zs, len, [&](uint32_t k) { if (k - (uint32_t)k0 < (uint32_t)n) atomicAdd(&hist[k - (uint32_t)k0], 1u); });
+    __syncthreads();
+    for (int k = threadIdx.x; k < n; k += blockDim.x)
+        if (const uint32_t h = hist[k]) add(k, h);
 }
 
 template <typename ZT>
@@ -1003,28 +1018,13 @@ __global__ void __launch_bounds__(1024) count_slabs_kernel(const ZT *z, int64_t 
                                                            const VzItem *items, const ZT *z_wm, int32_t *cwk, int K, int Kpad, int range) {
     extern __shared__ uint32_t slab_hist[];
     const int k0 = (int)blockIdx.y * range, n = min(range, K - k0);
-    const bool totals = (int)blockIdx.x < n_tot;
-    const ZT *__restrict__ zs;
-    int64_t len;
-    int32_t *row = nullptr;
-    if (totals) {
-        zs = z + (int64_t)blockIdx.x * per_block;
-        len = min(per_block, T - (int64_t)blockIdx.x * per_block);
+    if ((int)blockIdx.x < n_tot) {
+        const int64_t first = (int64_t)blockIdx.x * per_block;
+        count_slab(z + first, min(per_block, T - first), slab_hist, k0, n, gridDim.y == 1, [&](int k, uint32_t h) { atomicAdd(&tot[k0 + k], (unsigned long long)h); });
     } else {
         const VzItem it = items[(int)blockIdx.x - n_tot];
-        zs = z_wm + it.begin; len = it.count;
-        row = cwk + (size_t)it.row * (size_t)Kpad + k0;
-    }
-    for (int k = threadIdx.x; k < n; k += blockDim.x) slab_hist[k] = 0u;
-    __syncthreads();
-    if (gridDim.y == 1) block_for_each_z(zs, len, [&](uint32_t k) { atomicAdd(&slab_hist[k], 1u); });
-    else block_for_each_z(zs, len, [&](uint32_t k) { if (k - (uint32_t)k0 < (uint32_t)n) atomicAdd(&slab_hist[k - (uint32_t)k0], 1u); });
-    __syncthreads();
-    for (int k = threadIdx.x; k < n; k += blockDim.x) {
-        const uint32_t h = slab_hist[k];
-        if (!h) continue;
-        if (totals) atomicAdd(&tot[k0 + k], (unsigned long long)h);
-        else atomicAdd(&row[k], (int)h);
+        int32_t *row = cwk + (size_t)it.row * (size_t)Kpad + k0;
+        count_slab(z_wm + it.begin, (int64_t)it.count, slab_hist, k0, n, gridDim.y == 1, [&](int k, uint32_t h) { atomicAdd(&row[k], (int)h); });
     }
 }
 
@@ -1192,46 +1192,37 @@ __device__ __forceinline__ void count_segment_wave(const ZT *__restrict__ zs, in
 // rec[s].x * 32 on, its length to rec[s].y.
 struct SegGroup { const int32_t *list; const int64_t *ptr; const void *z; int64_t z_first; uint2 *rec; uint32_t *ent; };
 
-// The first na workgroups count the segments of group a, the others those of group b: documents and light words share a
-// launch, which spares a small corpus two of them.
-template <typename ZT>
-__global__ void __launch_bounds__(1024) count_dz_kernel(SegGroup a, int64_t na, SegGroup b, uint32_t topic_bits, int nwords,
-                                                        int lds_entries) {
-    extern __shared__ uint32_t lds_u32[];
-    __shared__ uint32_t scan_scratch[20];
-    uint32_t *bitmap = lds_u32;            // [nwords]
-    uint32_t *wpre = lds_u32 + nwords;     // [nwords] exclusive popcount prefix
-    uint32_t *ent_lds = wpre + nwords;     // [lds_entries]
-    const bool first_group = (int64_t)blockIdx.x < na;
-    const SegGroup &g = first_group ? a : b;
-    uint2 *docrec = g.rec;
-    uint32_t *cd_ent = g.ent;
-    const int d = g.list[(int64_t)blockIdx.x - (first_group ? 0 : na)];
-    const int64_t begin = g.ptr[d];
-    const int len = (int)(g.ptr[d + 1] - begin);
-    if (len == 0) { if (threadIdx.x == 0) docrec[d].y = 0u; return; }
-    const ZT *__restrict__ zd = reinterpret_cast<const ZT *>(g.z) + (begin - g.z_first);
-    if (blockDim.x == kWave && len <= 2 * kWave) {   // a short segment and a single wavefront: sorted in registers
-        uint32_t *row = cd_ent + (size_t)docrec[d].x * 32u;
-        if (len <= kWave) count_segment_wave<ZT, 1>(zd, len, docrec + d, row, topic_bits);
-        else count_segment_wave<ZT, 2>(zd, len, docrec + d, row, topic_bits);
-        return;
-    }
+// What a wavefront wrote to its own part of LDS is in LDS order before what it reads there next; this keeps the compiler to it.
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
-    for (int w = threadIdx.x; w < nwords; w += blockDim.x) bitmap[w] = 0u;
-    __syncthreads();
-    block_for_each_z(zd, (int64_t)len, [&](uint32_t k) { atomicOr(&bitmap[k >> 5], 1u << (k & 31u)); });
-    __syncthreads();
+// One segment of len > 0 assignments at zd by the whole workgroup, or (WAVE) by one wavefront of it; lds: bitmap, rank prefixes
+// (nwords words each), lds_entries entries of the row; scan_scratch: a word per wavefront and one more.
+template <typename ZT, bool WAVE = false>
+__device__ __forceinline__ void count_segment_block(const ZT *__restrict__ zd, int len, uint2 *rec, uint32_t *__restrict__ row, uint32_t topic_bits,
+                                                    int nwords, int lds_entries, uint32_t *lds, uint32_t *scan_scratch) {
+    const int tid = WAVE ? lane_id() : (int)threadIdx.x, nt = WAVE ? kWave : (int)blockDim.x;
+    auto barrier = [] { if (WAVE) wave_lds_fence(); else __syncthreads(); };
+    uint32_t *bitmap = lds;                // [nwords]
+    uint32_t *wpre = lds + nwords;         // [nwords] exclusive popcount prefix
+    uint32_t *ent_lds = wpre + nwords;     // [lds_entries]
+    for (int w = tid; w < nwords; w += nt) bitmap[w] = 0u;
+    barrier();
+    for_each_z(zd, (int64_t)len, tid, nt, [&](uint32_t k) { atomicOr(&bitmap[k >> 5], 1u << (k & 31u)); });
+    barrier();
     // ranks: exclusive prefix of popcounts over the bitmap words.  Every thread takes a contiguous piece of the
     // bitmap (ascending topics), so one scan over the threads' totals serves all words
-    const int wpt = (nwords + (int)blockDim.x - 1) / (int)blockDim.x;
-    const int wb = min((int)threadIdx.x * wpt, nwords), we = min(wb + wpt, nwords);
+    const int wpt = (nwords + nt - 1) / nt;
+    const int wb = min(tid * wpt, nwords), we = min(wb + wpt, nwords);
     uint32_t mine = 0;
     for (int w = wb; w < we; w++) mine += (uint32_t)__popc(bitmap[w]);
     uint32_t total;
-    const uint32_t first = block_excl_scan(mine, scan_scratch, &total);
+    uint32_t first;
+    if (WAVE) {
+        const uint32_t incl = wave_incl_scan(mine);
+        total = readlane_u32(incl, kWave - 1);
+        first = incl - mine;
+    } else first = block_excl_scan(mine, scan_scratch, &total);
     const int kd = (int)total;
-    uint32_t *row = cd_ent + (size_t)docrec[d].x * 32u;
     const bool in_lds = kd <= lds_entries;
     uint32_t *ent = in_lds ? ent_lds : row;
     // slot r of the row starts as (topic, count 0): enumerate the set bits of the thread's words
@@ -1243,22 +1234,45 @@ __global__ void __launch_bounds__(1024) count_dz_kernel(SegGroup a, int64_t na, 
             while (m) { const int b = __ffs((int)m) - 1; m &= m - 1u; ent[r++] = (uint32_t)(w * 32 + b); }
         }
     }
-    __syncthreads();
-    block_for_each_z(zd, (int64_t)len, [&](uint32_t k) {
+    barrier();
+    for_each_z(zd, (int64_t)len, tid, nt, [&](uint32_t k) {
         const uint32_t wd = bitmap[k >> 5];
         const uint32_t r = wpre[k >> 5] + (uint32_t)__popc(wd & ((1u << (k & 31u)) - 1u));
         atomicAdd(&ent[r], 1u << topic_bits);
     });
-    __syncthreads();
+    barrier();
     if (in_lds)
-        for (int r = threadIdx.x; r < kd; r += blockDim.x) row[r] = ent_lds[r];
+        for (int r = tid; r < kd; r += nt) row[r] = ent_lds[r];
     // pad to the next multiple of 4 entries with (last topic, count 0): the sampler reads rows in 16-byte pieces,
     // and a draw that rounding pushes past the end of the row then still lands on the last topic
-    if (threadIdx.x < 4) {
-        const int r = kd + (int)threadIdx.x;
+    if (tid < 4) {
+        const int r = kd + tid;
         if (r < ((kd + 3) & ~3)) row[r] = ent[kd - 1] & ((1u << topic_bits) - 1u);
     }
-    if (threadIdx.x == 0) docrec[d].y = (uint32_t)kd;
+    if (tid == 0) rec->y = (uint32_t)kd;
+}
+
+// The first na workgroups count the segments of group a, the others those of group b: documents and light words share a
+// launch, which spares a small corpus two of them.
+template <typename ZT>
+__global__ void __launch_bounds__(1024) count_dz_kernel(SegGroup a, int64_t na, SegGroup b, uint32_t topic_bits, int nwords,
+                                                        int lds_entries) {
+    extern __shared__ uint32_t lds_u32[];
+    __shared__ uint32_t scan_scratch[20];
+    const bool first_group = (int64_t)blockIdx.x < na;
+    const SegGroup &g = first_group ? a : b;
+    const int d = g.list[(int64_t)blockIdx.x - (first_group ? 0 : na)];
+    const int64_t begin = g.ptr[d];
+    const int len = (int)(g.ptr[d + 1] - begin);
+    if (len == 0) { if (threadIdx.x == 0) g.rec[d].y = 0u; return; }
+    const ZT *__restrict__ zd = reinterpret_cast<const ZT *>(g.z) + (begin - g.z_first);
+    uint32_t *row = g.ent + (size_t)g.rec[d].x * 32u;
+    if (blockDim.x == kWave && len <= 2 * kWave) {   // a short segment and a single wavefront: sorted in registers
+        if (len <= kWave) count_segment_wave<ZT, 1>(zd, len, g.rec + d, row, topic_bits);
+        else count_segment_wave<ZT, 2>(zd, len, g.rec + d, row, topic_bits);
+        return;
+    }
+    count_segment_block(zd, len, g.rec + d, row, topic_bits, nwords, lds_entries, lds_u32, scan_scratch);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1296,18 +1310,15 @@ struct PhiRow { int32_t word; int32_t count; int64_t begin; };
 constexpr int kPhiSteps = 2;   // steps of 4 columns per thread that share one histogram and one exchange of running sums
 
 template <typename ZT>
-__global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, const ZT *z_wm, int32_t *cwk, const float *denom,
-                                                        float *phi, float *l3, double *l3_64, float *sumphi, int Kpad,
-                                                        int n3, int n3pad, float beta, int range) {
+__device__ __forceinline__ void phi_row(const PhiRow pr, size_t row, const ZT *z_wm, int32_t *cwk, const float *denom, float *phi, float *l3,
+                                        double *l3_64, float *sumphi, int Kpad, int n3, int n3pad, float beta, int range, int4 *phi_hist4) {
     constexpr int kHeld = 4;               // assignments per thread that are read once and held
-    extern __shared__ int4 phi_hist4[];
     uint32_t *phi_hist = reinterpret_cast<uint32_t *>(phi_hist4);
     __shared__ double wave_tot[kPhiSteps * 16];
     __shared__ float row_total;
-    const PhiRow pr = rows[blockIdx.x];
     const int v = pr.word, step = 4 * (int)blockDim.x;
     const int lane = lane_id(), wave = threadIdx.x / kWave, nwaves = blockDim.x / kWave;
-    const size_t rbase = (size_t)blockIdx.x * (size_t)Kpad;
+    const size_t rbase = row * (size_t)Kpad;
     const bool own = pr.count >= 0, held = own && pr.count <= kHeld * (int)blockDim.x;
     const ZT *__restrict__ zs = z_wm + pr.begin;
     uint32_t zr[kHeld];
@@ -1387,6 +1398,14 @@ __global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, c
     if (threadIdx.x == 0) sumphi[v] = total;
 }
 
+template <typename ZT>
+__global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, const ZT *z_wm, int32_t *cwk, const float *denom,
+                                                        float *phi, float *l3, double *l3_64, float *sumphi, int Kpad,
+                                                        int n3, int n3pad, float beta, int range) {
+    extern __shared__ int4 phi_lds[];
+    phi_row(rows[blockIdx.x], (size_t)blockIdx.x, z_wm, cwk, denom, phi, l3, l3_64, sumphi, Kpad, n3, n3pad, beta, range, phi_lds);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Preprocess + BuildTree for the light words (one wavefront per word).  Their Bhat row is the base vector
 // except at the word's non-zeros, so only those are evaluated (Eq. 2, same three binary32 operations) and
@@ -1395,21 +1414,31 @@ __global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, c
 // sum of the same binary32 numbers as for a dense row, associated differently.
 // LDS: n3 doubles (cumulative difference at the last non-zero of each block) + n3 flags.
 // ---------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(64) light_tree_kernel(const int32_t *light_words, const uint2 *wrec,
-                                                        const uint32_t *lw_ent, float *lw_phi, const float *denom,
-                                                        const float *base, const double *basecum, float *l3,
-                                                        double *l3_64, float *sumphi, int n3, int n3pad,
-                                                        uint32_t topic_bits, float beta) {
-    extern __shared__ double lds_dcum[];
+struct LightParams {
+    const int32_t *light_words; const uint2 *wrec; const uint32_t *lw_ent; float *lw_phi;
+    const float *denom, *base; const double *basecum; float *l3; double *l3_64; float *sumphi;
+    int n3, n3pad; uint32_t topic_bits; float beta;
+};
+__host__ __device__ inline size_t light_lds_bytes(int n3) { return ((size_t)n3 * 12u + 7u) & ~(size_t)7u; }
+
+// the light word number li, by one wavefront with light_lds_bytes(n3) of LDS at lds_dcum
+__device__ __forceinline__ void light_word(const LightParams &p, int li, double *lds_dcum) {
+    const int n3 = p.n3, n3pad = p.n3pad;
+    const uint32_t topic_bits = p.topic_bits;
+    const float beta = p.beta;
+    const float *__restrict__ denom = p.denom, *__restrict__ base = p.base;
+    const double *__restrict__ basecum = p.basecum;
+    float *l3 = p.l3, *sumphi = p.sumphi;
+    double *l3_64 = p.l3_64;
     int *written = reinterpret_cast<int *>(lds_dcum + n3);
-    const int v = light_words[blockIdx.x], lane = lane_id();
-    const uint2 wr = wrec[blockIdx.x];
+    const int v = p.light_words[li], lane = lane_id();
+    const uint2 wr = p.wrec[li];
     const int nnz = (int)wr.y;
-    const uint32_t *__restrict__ ent = lw_ent + (size_t)wr.x * 32u;
-    float *__restrict__ val = lw_phi + (size_t)wr.x * 32u;
+    const uint32_t *__restrict__ ent = p.lw_ent + (size_t)wr.x * 32u;
+    float *__restrict__ val = p.lw_phi + (size_t)wr.x * 32u;
     const uint32_t tmask = (1u << topic_bits) - 1u;
     for (int i = lane; i < n3; i += kWave) written[i] = 0;
-    __syncthreads();
+    wave_lds_fence();
     double carry = 0.0;
     for (int j0 = 0; j0 < nnz; j0 += kWave) {
         const int j = j0 + lane;
@@ -1428,7 +1457,7 @@ __global__ void __launch_bounds__(64) light_tree_kernel(const int32_t *light_wor
         if (valid && blk != next_blk) { lds_dcum[blk] = incl; written[blk] = 1; }
         carry = readlane_f64(incl, 63);
     }
-    __syncthreads();
+    wave_lds_fence();
     int last = -1;   // last block at or before the current one that holds a non-zero
     float total = 0.f;
     for (int i0 = 0; i0 < n3; i0 += kWave) {
@@ -1446,6 +1475,11 @@ __global__ void __launch_bounds__(64) light_tree_kernel(const int32_t *light_wor
     total = readlane_f32(total, (n3 - 1) & (kWave - 1));
     for (int i = n3 + lane; i < n3pad; i += kWave) l3[(size_t)v * (size_t)n3pad + i] = total;
     if (lane == 0) sumphi[v] = total;
+}
+
+__global__ void __launch_bounds__(64) light_tree_kernel(LightParams p) {
+    extern __shared__ double lds_dcum[];
+    light_word(p, (int)blockIdx.x, lds_dcum);
 }
 
 // Bhat rows of the words asked for, out[i][k], one workgroup each: a dense row is copied, a light word's is the base vector
@@ -1471,19 +1505,24 @@ __global__ void __launch_bounds__(256) phi_export_kernel(const int32_t *rows, co
 // tokens of one (word, document) pair share the row); non-zeros of the sparse rows of B (what the next E-step stages for
 // the light words).  A workgroup ends with one atomic per sum: a few hundred of them, since they are all to the same
 // addresses (1,024 took 15 us).
-__global__ void __launch_bounds__(256) stats_kernel(const unsigned long long *slots, int n_slots, const uint2 *docrec,
-                                                    const int64_t *doc_ptr, const uint32_t *doc_words, int64_t D,
-                                                    const uint2 *wrec, int n_light, unsigned long long *out) {
+struct StatsParams {
+    const unsigned long long *slots; int n_slots;
+    const uint2 *docrec; const int64_t *doc_ptr; const uint32_t *doc_words; int64_t D;
+    const uint2 *wrec; int n_light; unsigned long long *out;
+};
+
+// the share of workgroup `block` of `nblocks`
+__device__ __forceinline__ void stats_share(const StatsParams &p, int block, int nblocks) {
     double sums[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < n_slots; i += blockDim.x) sums[0] += (double)slots[i];
-    for (int64_t d = first; d < D; d += stride) {
-        const double kd = (double)docrec[d].y;
-        sums[1] += kd; sums[2] += kd * (double)(doc_ptr[d + 1] - doc_ptr[d]); sums[3] += kd * (double)doc_words[d];
+    const int64_t first = (int64_t)block * blockDim.x + threadIdx.x, stride = (int64_t)nblocks * blockDim.x;
+    if (block == 0)
+        for (int i = threadIdx.x; i < p.n_slots; i += blockDim.x) sums[0] += (double)p.slots[i];
+    for (int64_t d = first; d < p.D; d += stride) {
+        const double kd = (double)p.docrec[d].y;
+        sums[1] += kd; sums[2] += kd * (double)(p.doc_ptr[d + 1] - p.doc_ptr[d]); sums[3] += kd * (double)p.doc_words[d];
     }
-    for (int64_t i = first; i < n_light; i += stride) sums[4] += (double)wrec[i].y;
-    __shared__ double part[5][4];
+    for (int64_t i = first; i < p.n_light; i += stride) sums[4] += (double)p.wrec[i].y;
+    __shared__ double part[5][16];
 #pragma unroll
     for (int q = 0; q < 5; q++) {
         const double w = readlane_f64(wave_incl_scan(sums[q]), 63);
@@ -1491,9 +1530,111 @@ __global__ void __launch_bounds__(256) stats_kernel(const unsigned long long *sl
     }
     __syncthreads();
     if (threadIdx.x < 5) {
-        const double sum = ((part[threadIdx.x][0] + part[threadIdx.x][1]) + part[threadIdx.x][2]) + part[threadIdx.x][3];
-        if (sum > 0.0) atomicAdd(&out[threadIdx.x], (unsigned long long)sum);
+        double sum = 0.0;
+        for (int w = 0; w < (int)(blockDim.x / kWave); w++) sum += part[threadIdx.x][w];
+        if (sum > 0.0) atomicAdd(&p.out[threadIdx.x], (unsigned long long)sum);
     }
+}
+__global__ void __launch_bounds__(256) stats_kernel(StatsParams p) { stats_share(p, (int)blockIdx.x, (int)gridDim.x); }
+
+// ---------------------------------------------------------------------------------------------
+// The M-step of a small corpus (16-bit assignments, some words light) in two launches.  A launch behind another costs 4.5 us whatever it does, and six or seven of
+// them were half of an iteration at T = 100 K, K = 100, a quarter at T = 2.3 M, K = 777.
+//
+// First everything that counts: shares of the topic totals, slabs of the longest dense rows and long segments (documents and
+// light words), a workgroup each, and the shorter segments, a wavefront each.  The workgroup that finishes the
+// last share of the totals - it draws the last ticket, after its additions have reached memory - forms the denominators and
+// the base vector with its running sums, under the rest of the launch.  Shares come first in the grid for that.
+// ---------------------------------------------------------------------------------------------
+struct MCounts {
+    SegGroup docs, words;                   // (list: of the long segments)
+    const int32_t *short_docs, *short_words;
+    int n_tot, n_items, n_long_docs, n_long_words, n_short_docs, n_short_words;
+    int64_t T, per_block;
+    unsigned long long *acc, *ck;           // accumulators of the totals (zero again at the end), totals
+    unsigned *ticket;                       // zero before and after
+    const VzItem *items; int32_t *cwk;
+    uint32_t topic_bits; int nwords, lds_entries, wave_entries;   // entries of a row in LDS: of a workgroup, of a wavefront
+    float vbeta, beta, *denom, *phi, *l3, *sumphi; double *l3_64;
+    int K, Kpad, n3, n3pad, range, base_row, base_word;
+};
+
+__global__ void __launch_bounds__(256, 8) mstep_counts_kernel(MCounts p) {
+    extern __shared__ int4 mc_lds4[];
+    uint32_t *lds = reinterpret_cast<uint32_t *>(mc_lds4);
+    __shared__ uint32_t scan_scratch[20];
+    const uint16_t *z = reinterpret_cast<const uint16_t *>(p.docs.z), *z_wm = reinterpret_cast<const uint16_t *>(p.words.z);
+    int b = (int)blockIdx.x;
+    if (b < p.n_tot) {
+        const int64_t first = (int64_t)b * p.per_block;
+        count_slab(z + first, min(p.per_block, p.T - first), lds, 0, p.K, true, [&](int k, uint32_t h) { atomicAdd(&p.acc[k], (unsigned long long)h); });
+        __threadfence();
+        __syncthreads();
+        if (threadIdx.x == 0) scan_scratch[0] = atomicAdd(p.ticket, 1u);
+        __syncthreads();
+        if (scan_scratch[0] != (uint32_t)p.n_tot - 1u) return;
+        __threadfence();
+        if (threadIdx.x == 0) *p.ticket = 0u;
+        for (int k = threadIdx.x; k < p.Kpad; k += blockDim.x) {   // (pad columns: Bhat comes out as zero)
+            float d = __builtin_inff();
+            if (k < p.K) {
+                const unsigned long long c = __hip_atomic_load(&p.acc[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                p.acc[k] = 0ull; p.ck[k] = c;
+                d = (float)c + p.vbeta;
+            }
+            p.denom[k] = d;
+        }
+        __syncthreads();
+        phi_row(PhiRow{p.base_word, 0, 0}, (size_t)p.base_row, z_wm, p.cwk, p.denom, p.phi, p.l3, p.l3_64, p.sumphi, p.Kpad, p.n3, p.n3pad, p.beta,
+                p.range, mc_lds4);
+        return;
+    }
+    b -= p.n_tot;
+    if (b < p.n_items) {
+        const VzItem it = p.items[b];
+        int32_t *row = p.cwk + (size_t)it.row * (size_t)p.Kpad;
+        count_slab(z_wm + it.begin, (int64_t)it.count, lds, 0, p.K, true, [&](int k, uint32_t h) { atomicAdd(&row[k], (int)h); });
+        return;
+    }
+    b -= p.n_items;
+    const int n_long = p.n_long_docs + p.n_long_words;
+    const bool whole = b < n_long;         // the workgroup's own segment, or one per wavefront
+    const int nw = (int)(blockDim.x / kWave);
+    int i = whole ? b : (b - n_long) * nw + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int n_docs = whole ? p.n_long_docs : p.n_short_docs, n_words = whole ? p.n_long_words : p.n_short_words;
+    if (i >= n_docs + n_words) return;
+    const bool doc = i < n_docs;
+    const SegGroup &g = doc ? p.docs : p.words;
+    const int32_t *list = whole ? g.list : doc ? p.short_docs : p.short_words;
+    const int d = list[doc ? i : i - n_docs];
+    const int64_t begin = g.ptr[d];
+    const int len = (int)(g.ptr[d + 1] - begin);
+    const uint16_t *zd = (doc ? z : z_wm) + begin;
+    uint32_t *row = g.ent + (size_t)g.rec[d].x * 32u;
+    if (whole) count_segment_block(zd, len, g.rec + d, row, p.topic_bits, p.nwords, p.lds_entries, lds, scan_scratch);
+    else if (len > 2 * kWave) {
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+        count_segment_block<uint16_t, true>(zd, len, g.rec + d, row, p.topic_bits, p.nwords, p.wave_entries,
+                                            lds + wave * (2 * p.nwords + p.wave_entries), nullptr);
+    } else if (len > kWave) count_segment_wave<uint16_t, 2>(zd, len, g.rec + d, row, p.topic_bits);
+    else if (len > 0) count_segment_wave<uint16_t, 1>(zd, len, g.rec + d, row, p.topic_bits);
+    else if (lane_id() == 0) g.rec[d].y = 0u;
+}
+
+// Then everything that follows from the counts: dense rows of Bhat, a workgroup each, the statistics, and the light words, a
+// wavefront each.
+__global__ void __launch_bounds__(1024, 8) mstep_rows_kernel(const PhiRow *rows, int n_rows, const uint16_t *z_wm, int32_t *cwk, float *phi, int Kpad,
+                                                             int range, StatsParams st, int n_stats, LightParams lp, int n_light) {
+    extern __shared__ int4 mr_lds4[];
+    int b = (int)blockIdx.x;
+    if (b < n_stats) { stats_share(st, b, n_stats); return; }
+    b -= n_stats;
+    if (b < n_rows) {
+        phi_row(rows[b], (size_t)b, z_wm, cwk, lp.denom, phi, lp.l3, lp.l3_64, lp.sumphi, Kpad, lp.n3, lp.n3pad, lp.beta, range, mr_lds4);
+        return;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), li = (b - n_rows) * (int)(blockDim.x / kWave) + wave;
+    if (li < n_light) light_word(lp, li, reinterpret_cast<double *>(reinterpret_cast<char *>(mr_lds4) + (size_t)wave * light_lds_bytes(lp.n3)));
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -102,6 +102,40 @@ def test_topic_totals_and_word_counts_at_the_edges_of_an_lds_histogram(K, T):
     g.close()
 
 
+@pytest.mark.parametrize("K", [5, 1024, 1025, 4096, 4097])
+def test_m_step_of_a_small_corpus(K):
+    """Counts in one launch, what follows from them in another (up to 4,096 topics): documents and light words of lengths on
+    both sides of what a wavefront sorts in one register and in two and counts in LDS, empty ones, one that takes a workgroup,
+    frequent words' slabs, several shares of the totals.  Counts and Bhat against the oracle, twice in a row."""
+    edges = np.array([0, 1, 3, 63, 64, 65, 127, 128, 129, 511, 512, 513, 700])
+    lens = np.r_[np.repeat(edges, 9), 40_000, 0]
+    doc_ptr = np.r_[0, np.cumsum(lens)].astype(np.int64)
+    rng = np.random.default_rng(K)
+    counts = np.r_[np.repeat(edges, 7), 0, 21_000]                     # (the last two have dense rows)
+    counts[-2] = doc_ptr[-1] - counts.sum()
+    words = np.repeat(np.arange(counts.size, dtype=np.int32), counts)
+    rng.shuffle(words)
+    pk, V = saber(), counts.size
+    g = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 4, light_word_tokens=1000)
+    o = oracle.Model(doc_ptr, words, V, K, 0.1, 0.01, 4)
+    for state in (0, 1):
+        z = np.minimum((K * rng.random(words.size) ** 3).astype(np.int32), K - 1)
+        g.set_z(z, 1)
+        o.set_z(z, it=1)
+        cd_ptr, topic, count, cwk, ck = g.counts()
+        assert np.array_equal(cd_ptr, o.cd[0]) and np.array_equal(topic, o.cd[1]) and np.array_equal(count, o.cd[2])
+        assert np.array_equal(cwk, o.cwk) and np.array_equal(ck, o.ck)
+        phi, prefix = g.get_phi(np.arange(V, dtype=np.int32))
+        assert np.array_equal(phi, o.phi)
+        assert np.mean(prefix != o.c32) < 1e-5 and np.allclose(prefix, o.c32, rtol=1.2e-7, atol=0)
+        st = g.get_stats()
+        assert st["nnz_cd"] == topic.size and st["next_row_entries"] == int((np.diff(cd_ptr) * np.diff(doc_ptr)).sum())
+        assert st["next_light_entries"] == np.count_nonzero(cwk[counts < 1000])
+    assert_estep_parity(g, o)
+    g.close()
+    o.close()
+
+
 @pytest.mark.parametrize("K", [63, 1024, 1025, 2049, 8192, 8193, 16385, 70000])
 def test_dense_rows_counted_where_they_are_normalised(K):
     """Rows on both sides of what a workgroup holds in registers (4 assignments per thread), counts itself (32 per thread)

@@ -156,6 +156,25 @@ def test_threads_of_a_workgroup_whose_row_is_not_staged(host, K, threads):
     """ % (K, threads))
 
 
+@pytest.mark.parametrize("D,V,K,opts,joined", [(3, 40, 4096, {}, True), (3, 40, 4097, {}, False),
+                                               ((384 << 10) - 40, 40, 400, {}, True), ((384 << 10) - 39, 40, 400, {}, False),
+                                               (3, 40, 100, {"light_word_tokens": -1}, False),
+                                               (3, 40, 400, {"stream_workers": 2}, False)])
+def test_which_m_steps_take_two_launches(host, D, V, K, opts, joined):
+    """Those of small resident corpora with light words."""
+    host("""
+        D, V, K, opts, joined = %r
+        words = np.arange(5000, dtype=np.int32) %% V
+        doc_ptr = np.zeros(D + 1, np.int64)
+        doc_ptr[1:] = np.minimum(np.arange(1, D + 1) * 2000, words.size)
+        g = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 3, **opts)
+        fake.fake_clear()
+        g.iterate(2)
+        assert launches("mstep_counts")[0] == launches("mstep_rows")[0] == (2 if joined else 0)
+        assert (launches("denominators")[0], launches("phi_tree")[0], launches("stats_kernel")[0]) == 3 * (0 if joined else 2,)
+    """ % ((D, V, K, opts, joined),))
+
+
 @pytest.mark.parametrize("T,edges", [(5000, {64: 1724, 128: 3612, 256: 8024, 512: 20124}),
                                      (4_300_000, {64: 1220, 128: 2732, 256: 6640, 512: 13316})])
 def test_threads_and_tiles_of_a_workgroup_whose_row_is_staged(host, T, edges):
