@@ -62,7 +62,8 @@ typedef struct saber_options {
     int32_t block_threads;  /* threads per workgroup of the sampling kernel (multiple of 64 up to 1024);
                                default: the smallest size with which a CU still holds most of its 32 wavefronts given the
                                LDS the Bhat row takes (with tile_tokens given: the one with the most wavefronts);
-                               when the row is not kept in LDS, 256 up to K = 2,048 and 1,024 beyond */
+                               when the row is not kept in LDS, 256 up to K = 2,048 and 1,024 beyond, but 256 if
+                               it cannot be and a chunk has fewer than 8 M tokens */
     int32_t tile_tokens;    /* most tokens of one word handled by one workgroup; default 0: a 32,768th of a chunk's tokens per
                                wavefront of the workgroup (at most four), not below K / 16 (64 to 256) and not above
                                32,768; with more than 2^19 words a 2560th, not below 8,192.  Larger where a document is far longer than a chunk's share, so that a chunk
@@ -80,7 +81,10 @@ typedef struct saber_options {
                                and when that is not given either but tile_tokens is, sized by the tile for light words */
     int32_t light_word_tokens;  /* words with fewer tokens than this keep their row of B sparse (rebuilt by a segmented
                                    count, like a row of A) and their Bhat row is formed in LDS from a base vector and
-                                   the non-zeros; default K/2; negative: every word keeps a dense row */
+                                   the non-zeros, or where LDS cannot hold a row (stage_phi = 1 and K beyond 37,800) read
+                                   from the base vector with marks at the non-zeros; default K/2, for such K at most
+                                   8,192 in chunks below 8 M tokens; at most 65,536, or 2^(32 - bits of a topic);
+                                   negative: every word keeps a dense row */
     int32_t stream_workers;     /* 1..8: host streaming (Sec. 3.1.2) with this many workers: the chunks' token lists stay
                                    in pinned host memory (4 bytes per token) and each chunk is copied into one of this
                                    many device buffers for its pass, so that with two or more the copy of one chunk

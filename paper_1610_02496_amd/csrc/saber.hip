@@ -136,6 +136,7 @@ struct saber_ctx {
     uint64_t seed = 0;
     uint32_t iter = 0, topic_bits = 0, topic_mask = 0;
     bool z16 = false, staged = false, b16 = false;
+    bool overlay = false;             // rows do not fit LDS: light words are read from memory with marks in LDS (Overlay)
     bool auto_light_block = false;    // neither workgroup size was given: those of light words' tiles follow the tile
     int lds_per_cu = 64 * 1024;
     saber_options opt{};
@@ -324,6 +325,7 @@ static size_t estep_row_bytes(const saber_ctx *c) {
 // dynamic LDS of a sampling workgroup: the row when staged, 16 bytes of control words, and in log-likelihood mode
 // one double per wavefront
 static size_t estep_lds_bytes(const saber_ctx *c, int mode) {
+    if (c->overlay) return 16 + 16 * sizeof(double) + (size_t)c->nwords * sizeof(uint2);
     return (c->staged ? estep_row_bytes(c) : 0) + 16 + (mode == MODE_LOGLIK ? 16 * sizeof(double) : 0);
 }
 
@@ -388,7 +390,7 @@ static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
 // Wavefronts a CU holds of a sampling kernel with `block` threads per workgroup, given its LDS (handed out in 512-byte
 // pieces) and the 32 wavefronts a CU can hold.
 static int estep_waves_per_cu(const saber_ctx *c, int block) {
-    const size_t need = c->staged ? ((estep_lds_bytes(c, MODE_SAMPLE) + 144 + 511) / 512) * 512 : 512;
+    const size_t need = c->staged || c->overlay ? ((estep_lds_bytes(c, MODE_SAMPLE) + 144 + 511) / 512) * 512 : 512;
     const int by_lds = (int)std::min<size_t>(64, (size_t)c->lds_per_cu / need), by_waves = 32 / (block / 64);
     return std::min(by_lds, by_waves) * (block / 64);
 }
@@ -414,7 +416,13 @@ static int estep_waves_per_cu(const saber_ctx *c, int block) {
 // 2.81, K = 3,000 4.74, 4.00 and 3.47, K = 10,000 9.16, 7.00 and 6.01, K = 45,000 15.6, 12.9 and 10.6; at V = 100,000,
 // T = 3 M, where most words have few tokens: K = 1,000 0.66, 0.77 and 0.98, K = 3,000 2.16, 2.07 and 2.26 in the
 // first iterations and 1.41, 1.43 and 1.62 in later ones, K = 45,000 15.8, 13.8 and 12.7, and 6.98, 6.96 and 7.21.
+//
+// With marks for light words instead (Overlay) the base vector, which all of them share, fills the caches, and 256, 512 and
+// 1,024 threads take 0.52, 0.53 and 0.56 ms at T = 1.5 M, K = 70,000, 0.96, 1.06 and 1.27 at T = 3 M, K = 45,000, but 8.8, 8.1 and
+// 7.8 ms at T = 20 M, where the words with dense rows have most of the tokens.
+constexpr int64_t kLargeChunk = 8ll << 20;
 static int estep_auto_block(const saber_ctx *c, int64_t per_chunk) {
+    if (c->overlay && per_chunk < kLargeChunk) return 256;
     if (!c->staged) return c->K <= 2048 ? 256 : 1024;
     if (c->tile_tokens_asked > 0) {
         int best = 256;
@@ -959,11 +967,11 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     // traffic per iteration.  Needs the LDS-staged sampler and 16-bit assignments.
     std::vector<int64_t> n_v((size_t)V, 0);
     for (int64_t t = 0; t < T; t++) n_v[(size_t)word_ids[t]]++;
-    const bool light_ok = c->staged && c->z16 && c->opt.light_word_tokens > 0;
+    const bool light_ok = (c->staged ? c->z16 : c->overlay) && c->opt.light_word_tokens > 0;
     const saber_ctx *par = c->parent;   // then the model's word classes are taken over
-    c->joined = light_ok && !par && c->n_slots == 0 && c->opt.ablation == 0 && K <= kJoinedTopics && D + V <= kJoinedSegments && T <= kJoinedTokens;
-    // a packed entry of a sparse row has at least 16 count bits when the assignments are 16-bit
-    c->opt.light_word_tokens = std::min(c->opt.light_word_tokens, 65536);
+    c->joined = light_ok && c->z16 && !par && c->n_slots == 0 && c->opt.ablation == 0 && K <= kJoinedTopics && D + V <= kJoinedSegments && T <= kJoinedTokens;
+    // (as many counts as a packed entry of a sparse row has bits for)
+    c->opt.light_word_tokens = std::min(c->opt.light_word_tokens, 1 << std::min(16u, 32 - c->topic_bits));
     c->h_word_row.assign((size_t)V, 0);
     std::vector<int32_t> h_row_word, h_light_words, h_light_short, h_light_long;
     std::vector<int64_t> h_light_tok_ptr(1, 0);
@@ -1330,6 +1338,7 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
     if (opt.ablation & 5) opt.light_word_tokens = -1;   // document order gathers Bhat from dense rows; alias tables are built from them
     if ((opt.ablation & 4) && alias_lds_bytes(K) > 159 * 1024)
         return fail(SABER_ERANGE, "saber_init: the alias-table variant needs 12 K bytes of LDS per workgroup, K = %d is beyond 13,500", K);
+    const int32_t light_asked = opt.light_word_tokens;
     if (opt.light_word_tokens == 0) opt.light_word_tokens = std::max(1, K / 2);   // < 0 keeps every word dense
     // automatic: chunks of about 80 M tokens (T / 80 M, rounded to the nearest whole number).  The sampling pass of a
     // chunk reads every row of A of the chunk once per word of the document; at 0.4 to 0.7 non-zeros per token these rows
@@ -1370,6 +1379,13 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
     const size_t stage_limit = std::min<size_t>(150 * 1024, (size_t)c->lds_per_cu > 10 * 1024 ? (size_t)c->lds_per_cu - 10 * 1024 : 0);
     c->staged = opt.stage_phi && estep_row_bytes(c) <= std::max<size_t>(stage_limit, 54 * 1024);
     const int64_t per_chunk = T / std::max(1, c->opt.n_chunks);
+    // Rows too long for LDS: light words are read from memory with marks in LDS instead of from a full row in memory, whose
+    // 4 K bytes per word would have to be written and read in every iteration.  An iteration with all words dense and so:
+    // T = 1.5 M, K = 70,000, V = 4,001 1.12 and 0.47 ms; 3 M, K = 45,000, V = 60,000 5.5 and 0.95; 20 M, V = 50,000 16.7 and 7.7.
+    // In small chunks the longest words are cheaper with a dense row: counting a sparse one is the work of one workgroup
+    // (T = 1.5 M: 0.53 ms with words of up to 32,768 tokens light, 0.47 with 8,192, 0.61 with 1,024; 20 M: 8.8, 10.9, 16.0).
+    c->overlay = !c->staged && opt.stage_phi && opt.light_word_tokens > 0;
+    if (c->overlay && light_asked == 0 && per_chunk < kLargeChunk) c->opt.light_word_tokens = std::min(c->opt.light_word_tokens, 8192);
     if (opt_in == nullptr || opt_in->block_threads <= 0) {
         c->opt.block_threads = estep_auto_block(c, per_chunk);
         c->auto_light_block = c->opt.light_block_threads <= 0;

@@ -245,6 +245,11 @@ __device__ __forceinline__ float row16_incl_scan(float v) {
     return v;
 }
 
+// A light word's Bhat row where LDS cannot hold one: the base vector in memory, and for each of the word's non-zeros a mark in
+// LDS, marks[k / 32] = {bit k mod 32 set where topic k has a count, number of the non-zeros before the first of these}, which
+// leads to its value.  light: wave-uniform; without it the row is read as it is.
+struct Overlay { const uint2 *marks = nullptr; const float *val = nullptr; bool light = false; };
+
 // Dense branch (problem 2, Sec. 2.3): position of x in the prefix sums of the word's Bhat row, four tokens per
 // call: the 16 lanes of DPP row g serve the token whose x they hold (all lanes of a row hold the same x).
 // The descent follows Sec. 3.2.4 with the stored level l3 (binary32 prefix sum at the end of every 64-topic
@@ -259,7 +264,7 @@ __device__ __forceinline__ float row16_incl_scan(float v) {
 // base) is skipped; otherwise (a few calls in a hundred at K = 10,000) the exact numbers decide.
 // Returns the topic in every lane of the row.
 __device__ __forceinline__ uint32_t dense_query4(const float *phi_row, int phi_len, const float *l3,
-                                                 const double *__restrict__ l3_64, int n3, int K, float x, int li) {
+                                                 const double *__restrict__ l3_64, int n3, int K, float x, int li, const Overlay &ov = Overlay()) {
     // 16-ary descent over l3: lane li looks at the last entry of the li-th sub-range of the current window; the
     // number of sub-ranges lying wholly below x is the index of the one holding the position
     int stride = 1;
@@ -273,6 +278,15 @@ __device__ __forceinline__ uint32_t dense_query4(const float *phi_row, int phi_l
     const int k0 = blk * kWave + li * 4;
     float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
     if (k0 < phi_len) f = *reinterpret_cast<const float4 *>(phi_row + k0);   // columns K..phi_len-1 hold zeros
+    if (ov.light && k0 < K) {                               // four topics of one word of the bitmap
+        const uint2 m = ov.marks[k0 >> 5];
+        const uint32_t sh = (uint32_t)k0 & 31u, four = (m.x >> sh) & 15u;
+        const float *v = ov.val + m.y + __popc(m.x & ((1u << sh) - 1u));
+        if (four & 1u) f.x = *v++;
+        if (four & 2u) f.y = *v++;
+        if (four & 4u) f.z = *v++;
+        if (four & 8u) f.w = *v;
+    }
     const float t0 = f.x, t1 = t0 + f.y, t2 = t1 + f.z, t3 = t2 + f.w;
     const float a2 = (blk > 0 ? l3[blk - 1] : 0.f) + (row16_incl_scan(t3) - t3);
     const float c0 = a2 + t0, c1 = a2 + t1, c2 = a2 + t2, c3 = a2 + t3;
@@ -426,7 +440,7 @@ __device__ __forceinline__ float group_incl_scan(float v) {
 // Bhat value of the entry's topic.  With 16/16 packing and the row in LDS the byte offset (topic * 4) is formed
 // by one shift that reads the low half of the entry.
 template <bool STAGED, bool B16>
-__device__ __forceinline__ float phi_of(uint32_t e, uint32_t tmask, const float *lds_phi, const float *__restrict__ phi_row) {
+__device__ __forceinline__ float phi_of(uint32_t e, uint32_t tmask, const float *lds_phi, const float *__restrict__ phi_row, const Overlay &ov) {
     if (STAGED && B16) {
         uint32_t off;
         asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
@@ -435,17 +449,25 @@ __device__ __forceinline__ float phi_of(uint32_t e, uint32_t tmask, const float 
         typedef __attribute__((address_space(3))) const float lds_cfloat;
         return *reinterpret_cast<lds_cfloat *>(off);
     }
-    return STAGED ? lds_phi[e & tmask] : phi_row[e & tmask];
+    if (STAGED) return lds_phi[e & tmask];
+    const uint32_t k = e & tmask;
+    const float *src = phi_row + k;
+    if (ov.light) {   // the value is where the mark says: one load either way
+        const uint2 m = ov.marks[k >> 5];
+        const uint32_t below = (1u << (k & 31u)) - 1u;
+        if ((m.x >> (k & 31u)) & 1u) src = ov.val + (m.y + __popc(m.x & below));
+    }
+    return *src;
 }
 
 // element-wise product A_d (.) Bhat_v of the lane's four entries as running sums, and their scan over the group
 template <bool STAGED, bool B16, int G = kWave>
 __device__ __forceinline__ void block_products(const uint4 e, uint32_t bits, uint32_t tmask,
-                                               const float *lds_phi, const float *__restrict__ phi_row, RowBlock &b) {
-    const float f0 = phi_of<STAGED, B16>(e.x, tmask, lds_phi, phi_row);
-    const float f1 = phi_of<STAGED, B16>(e.y, tmask, lds_phi, phi_row);
-    const float f2 = phi_of<STAGED, B16>(e.z, tmask, lds_phi, phi_row);
-    const float f3 = phi_of<STAGED, B16>(e.w, tmask, lds_phi, phi_row);
+                                               const float *lds_phi, const float *__restrict__ phi_row, RowBlock &b, const Overlay &ov = Overlay()) {
+    const float f0 = phi_of<STAGED, B16>(e.x, tmask, lds_phi, phi_row, ov);
+    const float f1 = phi_of<STAGED, B16>(e.y, tmask, lds_phi, phi_row, ov);
+    const float f2 = phi_of<STAGED, B16>(e.z, tmask, lds_phi, phi_row, ov);
+    const float f3 = phi_of<STAGED, B16>(e.w, tmask, lds_phi, phi_row, ov);
     b.a0 = (float)(e.x >> bits) * f0;
     b.a1 = __builtin_fmaf((float)(e.y >> bits), f1, b.a0);
     b.a2 = __builtin_fmaf((float)(e.z >> bits), f2, b.a1);
@@ -468,8 +490,8 @@ __device__ __forceinline__ uint32_t search_block(const uint4 e, const RowBlock &
 
 // New assignments are written twice: to z (canonical order) and to z_wm (word-major, coalesced), from which the
 // M-step counts B; the sampler itself adds nothing to B.
-// A light word keeps B sparse: its Bhat row is built in LDS from the base vector and the word's non-zeros (staged rows and
-// 16-bit assignments only).  Tiles of both kinds share a launch: a launch of its own for the light words cost a small
+// A light word keeps B sparse: its Bhat row is built in LDS from the base vector and the word's non-zeros (staged rows have
+// 16-bit assignments then), or where LDS cannot hold a row read from memory with marks in LDS (Overlay).  Tiles of both kinds share a launch: a launch of its own for the light words cost a small
 // corpus 10 of its 47 us per iteration (T = 100 K, K = 100), a large one the tail of the other.
 template <int MODE, bool STAGED, typename ZT, bool B16>
 __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
@@ -479,6 +501,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     //   [4] words: batch ticket, dense-branch tokens of the workgroup, 0, 0 (the last one doubles as the tree level's
     //           entry "before the first", which the dense branch reads for the first block)
     //   STAGED: [n3 rounded to 4] floats: the tree level above the bottom;  LOGLIK: [16] doubles, one per wavefront
+    //   not STAGED, if some words are light: after room for these 16 doubles, a pair of words per 32 topics (Overlay)
     // The footprint is kept minimal because it decides how many wavefronts a CU can hold: at K = 10,000 it is
     // 40,656 bytes, which lets four 512-thread workgroups (32 wavefronts) share the 160 KB of a CU.
     const int K4 = STAGED ? (p.K + 3) & ~3 : 0;
@@ -489,7 +512,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     unsigned int &wg_dense = reinterpret_cast<unsigned int *>(ctrl)[1];   // dense-branch tokens of this workgroup
     double *ll_wave = reinterpret_cast<double *>(lds_l3 + (STAGED ? (p.n3 + 3) & ~3 : 0));
     const Tile tile = p.tiles[blockIdx.x];
-    const bool light = STAGED && sizeof(ZT) == 2 && (int)blockIdx.x >= p.first_light;
+    const bool light = (!STAGED || sizeof(ZT) == 2) && (int)blockIdx.x >= p.first_light;
     const int K = p.K;
     const float *__restrict__ phi_row = light ? p.base : p.phi + (size_t)tile.row * (size_t)p.Kpad;
     const float *__restrict__ l3_row = p.l3 + (size_t)tile.word * (size_t)p.n3pad;
@@ -533,7 +556,21 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     }
     uint2 rec = make_uint2(p.row_unit0, 0u);
     if (d >= 0) rec = p.docrec[d];
-    if (light) {
+    Overlay ov;
+    if (!STAGED && light) {
+        uint2 *marks = reinterpret_cast<uint2 *>(lds_l3 + 32);
+        const uint2 wr = p.wrec[tile.row];
+        const uint32_t *__restrict__ ent = p.lw_ent + (size_t)wr.x * 32u;
+        for (int i = threadIdx.x; i < (K + 31) >> 5; i += blockDim.x) marks[i].x = 0u;
+        __syncthreads();
+        for (int j = threadIdx.x; j < (int)wr.y; j += blockDim.x) {   // (ascending topics)
+            const uint32_t k = ent[j] & p.topic_mask, before = j ? ent[j - 1] & p.topic_mask : 0xffffffffu;
+            atomicOr(&marks[k >> 5].x, 1u << (k & 31u));
+            if (before >> 5 != k >> 5) marks[k >> 5].y = (uint32_t)j;
+        }
+        ov = Overlay{marks, p.lw_phi + (size_t)wr.x * 32u, true};
+    }
+    if (STAGED && light) {
         // the staged row is the base vector so far; overwrite the topics this word has counts for.  The word's first
         // entries, one per thread, are requested before the barrier as well: with few tokens per workgroup the chain of
         // dependent loads shows (T = 15 M, K = 20,011, 76 tokens per light word: pass 1.920 -> 1.829 ms; elsewhere within 0.5 %).
@@ -636,7 +673,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             };
             auto compute = [&](const int ps, const uint4 &cur, const uint32_t pk) {
                 RowBlock b;
-                block_products<STAGED, B16, G>(cur, bits, tmask, lds_phi, phi_row, b);
+                block_products<STAGED, B16, G>(cur, bits, tmask, lds_phi, phi_row, b, ov);
                 // S of the group's run in all its lanes
                 const float S = G == 16 ? dpp_f32<0x15f, 0xf>(b.incl)                    // row_newbcast:15
                                         : lane_pull(b.incl, (uint32_t)(lane | (G - 1)) << 2);
@@ -740,7 +777,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             const unsigned long long in_run = (~0ull >> (kWave - s_end)) & (~0ull << s);   // 0 <= s < s_end <= 64
             // element-wise product A_d (.) Bhat_v, its prefix sums and its sum S (Alg. 2, product loop)
             RowBlock b0;
-            block_products<STAGED, B16>(cur, bits, tmask, lds_phi, phi_row, b0);
+            block_products<STAGED, B16>(cur, bits, tmask, lds_phi, phi_row, b0, ov);
             const float t0 = readlane_f32(b0.incl, 63);
             if (cur_bytes <= 16u * kWave) {
                 // the whole row sits in this block (the common case): straight-line coin and search
@@ -777,13 +814,13 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             const int nblk = (kd + 4 * kWave - 1) / (4 * kWave);
             const uint4 e1 = cur2;
             RowBlock b1;
-            block_products<STAGED, B16>(e1, bits, tmask, lds_phi, phi_row, b1);
+            block_products<STAGED, B16>(e1, bits, tmask, lds_phi, phi_row, b1, ov);
             const float t1 = readlane_f32(b1.incl, 63);
             float S = t0 + t1;
             for (int blk = 2; blk < nblk; blk++) {
                 RowBlock bb;
                 block_products<STAGED, B16>(load_block(row + blk * 4 * kWave, kd - blk * 4 * kWave, lane), bits, tmask,
-                                            lds_phi, phi_row, bb);
+                                            lds_phi, phi_row, bb, ov);
                 S = S + readlane_f32(bb.incl, 63);
             }
             if (MODE == MODE_SAMPLE) {
@@ -804,7 +841,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
                                 const int rel = kd - blk * 4 * kWave;
                                 const uint4 e = load_block(row + blk * 4 * kWave, rel, lane);
                                 RowBlock bb;
-                                block_products<STAGED, B16>(e, bits, tmask, lds_phi, phi_row, bb);
+                                block_products<STAGED, B16>(e, bits, tmask, lds_phi, phi_row, bb, ov);
                                 const float tot = readlane_f32(bb.incl, 63);
                                 if (blk == nblk - 1 || carry + tot >= x) { topic = search_block(e, bb, carry, x, rel, tmask); break; }
                                 carry = carry + tot;
@@ -891,7 +928,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
                 }
                 const int mine = g == 0 ? tl[0] : g == 1 ? tl[1] : g == 2 ? tl[2] : tl[3];
                 const float x = __int_as_float(__builtin_amdgcn_ds_bpermute((mine < 0 ? lane : mine) << 2, __float_as_int(xd)));
-                const uint32_t k = dense_query4(phi_row, p.Kpad, l3_row, l3_64_row, p.n3, K, x, (int)li);
+                const uint32_t k = dense_query4(phi_row, p.Kpad, l3_row, l3_64_row, p.n3, K, x, (int)li, ov);
 #pragma unroll
                 for (int q = 0; q < 4; q++)
                     if (tl[q] >= 0) my_z = llvm_amdgcn_writelane_u32(readlane_u32(k, 16 * q), (unsigned)tl[q], my_z);
@@ -1437,6 +1474,11 @@ __device__ __forceinline__ void light_word(const LightParams &p, int li, double 
     const uint32_t *__restrict__ ent = p.lw_ent + (size_t)wr.x * 32u;
     float *__restrict__ val = p.lw_phi + (size_t)wr.x * 32u;
     const uint32_t tmask = (1u << topic_bits) - 1u;
+    // the base vector's running sums of the first steps, requested under the chain of loads that leads to the non-zeros
+    constexpr int kSteps = 4;
+    double cum[kSteps];
+#pragma unroll
+    for (int st = 0; st < kSteps; st++) cum[st] = basecum[min(st * kWave + lane, n3 - 1)];
     for (int i = lane; i < n3; i += kWave) written[i] = 0;
     wave_lds_fence();
     double carry = 0.0;
@@ -1460,17 +1502,25 @@ __device__ __forceinline__ void light_word(const LightParams &p, int li, double 
     wave_lds_fence();
     int last = -1;   // last block at or before the current one that holds a non-zero
     float total = 0.f;
-    for (int i0 = 0; i0 < n3; i0 += kWave) {
-        const int i = i0 + lane;
-        const int w = (i < n3 && written[i]) ? i : -1;
-        const int idx = max(wave_incl_scan_max(w), last);
-        if (i < n3) {
-            const double run = basecum[i] + (idx >= 0 ? lds_dcum[idx] : 0.0);
-            l3_64[(size_t)v * (size_t)n3 + (size_t)i] = run;
-            l3[(size_t)v * (size_t)n3pad + (size_t)i] = (float)run;
-            if (i == n3 - 1) total = (float)run;
+    for (int i0 = 0; i0 < n3; i0 += kSteps * kWave) {
+        int idx[kSteps];                   // of each step alone, then with what lies before it: the steps wait for one another only there
+#pragma unroll
+        for (int st = 0; st < kSteps; st++) {
+            const int i = i0 + st * kWave + lane;
+            idx[st] = i0 + st * kWave < n3 ? wave_incl_scan_max(i < n3 && written[i] ? i : -1) : -1;
         }
-        last = __builtin_amdgcn_readlane(idx, 63);
+#pragma unroll
+        for (int st = 0; st < kSteps; st++) {
+            if (i0 + st * kWave >= n3) break;   // uniform
+            const int i = i0 + st * kWave + lane, at = max(idx[st], last);
+            if (i < n3) {
+                const double run = (i0 ? basecum[i] : cum[st]) + (at >= 0 ? lds_dcum[at] : 0.0);
+                l3_64[(size_t)v * (size_t)n3 + (size_t)i] = run;
+                l3[(size_t)v * (size_t)n3pad + (size_t)i] = (float)run;
+                if (i == n3 - 1) total = (float)run;
+            }
+            last = __builtin_amdgcn_readlane(at, 63);
+        }
     }
     total = readlane_f32(total, (n3 - 1) & (kWave - 1));
     for (int i = n3 + lane; i < n3pad; i += kWave) l3[(size_t)v * (size_t)n3pad + i] = total;

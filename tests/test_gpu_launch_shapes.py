@@ -136,6 +136,45 @@ def test_m_step_of_a_small_corpus(K):
     o.close()
 
 
+@pytest.mark.parametrize("K", [37_889, 65_536, 65_537, 70_000, 262_144])
+def test_light_words_where_lds_cannot_hold_a_row(K):
+    """Light words are read from the base vector and marks in LDS: none, one, all 32 topics of a mark and neighbours across its
+    ends, the lowest and the highest topic; frequent words beside them.  Against the
+    oracle, and against dense rows for every word (whose prefix sums are associated differently)."""
+    rng = np.random.default_rng(K)
+    counts = np.r_[0, 1, 2, 33, 64, 65, 500, 900, 3000, 9000, 20_000, 400]
+    words = np.repeat(np.arange(counts.size, dtype=np.int32), counts)
+    rng.shuffle(words)
+    lens = np.r_[0, 500, rng.integers(0, 200, 2 * words.size // 200)]
+    doc_ptr = np.r_[0, np.minimum(np.cumsum(lens), words.size)].astype(np.int64)
+    doc_ptr = np.r_[doc_ptr, np.arange(doc_ptr[-1], words.size, 199)[1:], words.size].astype(np.int64)
+    few = np.r_[np.arange(31, 66), 0, K - 33, K - 2, K - 1, 1000, K // 2]
+    z = np.where(rng.random(words.size) < 0.7, rng.choice(few, words.size), rng.integers(0, K, words.size)).astype(np.int32)
+    pk, V, alpha = saber(), counts.size, 50.0 / K
+    tok = rng.integers(0, words.size, 3000)
+    g = pk.Saber(doc_ptr, words, V, K, alpha, 0.01, 3, light_word_tokens=9500)
+    p = pk.Saber(doc_ptr, words, V, K, alpha, 0.01, 3, light_word_tokens=-1)
+    o = oracle.Model(doc_ptr, words, V, K, alpha, 0.01, 3)
+    assert g.get_stats()["light_tokens"] == counts[counts < 9500].sum()
+    for m in (g, p):
+        m.set_z(z, 1)
+    o.set_z(z, it=1)
+    phi, prefix = g.get_phi(np.arange(V, dtype=np.int32))
+    assert np.array_equal(phi, o.phi)
+    assert np.mean(prefix != o.c32) < 1e-5 and np.allclose(prefix, o.c32, rtol=1.2e-7, atol=0)
+    for a, b in zip(g.token_probs(tok), p.token_probs(tok)):
+        assert np.allclose(a, b, rtol=1.2e-7, atol=0)                # S the same sums, Q from totals of other association
+    assert abs(g.loglik() - o.loglik()) <= 1e-6 * abs(o.loglik())
+    assert_estep_parity(g, o)
+    p.iterate(1)
+    assert np.mean(g.get_z() != p.get_z()) <= 1e-4
+    obs = (np.arange(words.size) % 2).astype(np.uint8)
+    a, b = (m.holdout_loglik(doc_ptr, words, obs, 1, 5) for m in (g, p))
+    assert a[1] == b[1] and np.mean(a[2] != b[2]) <= 1e-3 and abs(a[0] - b[0]) <= 1e-5 * abs(b[0])
+    for m in (g, p, o):
+        m.close()
+
+
 @pytest.mark.parametrize("K", [63, 1024, 1025, 2049, 8192, 8193, 16385, 70000])
 def test_dense_rows_counted_where_they_are_normalised(K):
     """Rows on both sides of what a workgroup holds in registers (4 assignments per thread), counts itself (32 per thread)

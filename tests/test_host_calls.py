@@ -199,6 +199,24 @@ def test_threads_and_tiles_of_a_workgroup_whose_row_is_staged(host, T, edges):
     """ % (T, edges))
 
 
+@pytest.mark.parametrize("K,T,opts,light,block", [(70_000, 500_000, {}, True, 256), (70_000, 9_000_000, {}, True, 1024), (70_000, 500_000, {"light_word_tokens": -1}, False, 1024),
+                                                  (70_000, 500_000, {"stage_phi": 0}, False, 1024), (37_000, 500_000, {}, True, 1024)])
+def test_light_words_where_lds_cannot_hold_a_row(host, K, T, opts, light, block):
+    """They are read with marks in LDS, unless the caller wants dense rows, or rows gathered from memory."""
+    host("""
+        K, T, opts, light, block = %r
+        words = (np.arange(T) %% 400).astype(np.int32)
+        words[:8500] = 0
+        words[-100:] = 401
+        g = pk.Saber(np.r_[np.arange(0, T, 1000), T], words, 402, K, 0.1, 0.01, 3, **opts)
+        g.iterate(1)
+        n = np.bincount(words)
+        most = (8192 if K == 70_000 else K // 2) if T < 8 << 20 else 1 << 15
+        assert g.get_stats()["light_tokens"] == (n[n < most].sum() if light else 0), g.get_stats()
+        assert fake.fake_block(b"estep_kernel") == block
+    """ % ((K, T, opts, light, block),))
+
+
 @pytest.mark.parametrize("K,T,least,most", [(100, 1 << 20, 0, 0), (100, (1 << 20) + 1, 1, 1 << 19), (100, 2 << 20, 1, 1 << 19),
                                             (100, (2 << 20) + 1, 3 << 20, 13 << 20), (70000, 2 << 20, 0, 0),
                                             (70000, (2 << 20) + 1, 3 << 20, 13 << 20)])
