@@ -155,15 +155,41 @@ __global__ void z_from_i32_kernel(ZT *z, const int32_t *src, int64_t T) {
     for (; t < T; t += stride) z[t] = (ZT)src[t];
 }
 
+// Inspection of a few of a chunk's tokens: marks[t / 32] = {bit t mod 32 set for the tokens t that are asked for, number of the first
+// of them among all that are asked for}.  First the bits ...
+__global__ void mark_tokens_kernel(const int64_t *idx, int64_t m, int64_t t0, int64_t n, uint2 *marks) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= m) return;
+    const int64_t r = idx[i] - t0;
+    if (r >= 0 && r < n) atomicOr(&marks[r >> 5].x, 1u << (r & 31));
+}
+// ... then the numbers: in order inside a workgroup of 256 threads, the workgroups one after the other as they come (*next).
+__global__ void __launch_bounds__(256) number_tokens_kernel(uint2 *marks, int64_t words, uint32_t *next) {
+    __shared__ uint32_t wave_sum_of[4], base;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t mine = i < words ? (uint32_t)__popc(marks[i].x) : 0u, incl = wave_incl_scan(mine);
+    const int wave = threadIdx.x / kWave;
+    if (lane_id() == kWave - 1) wave_sum_of[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0u, all = 0u;
+    for (int w = 0; w < 4; w++) { if (w < wave) before += wave_sum_of[w]; all += wave_sum_of[w]; }
+    if (threadIdx.x == 0 && all) base = atomicAdd(next, all);
+    __syncthreads();
+    if (mine) marks[i].y = base + before + (incl - mine);
+}
+__device__ __forceinline__ bool token_marked(const uint2 m, uint32_t t) { return (m.x >> (t & 31u)) & 1u; }
+__device__ __forceinline__ uint32_t token_number(const uint2 m, uint32_t t) { return m.y + (uint32_t)__popc(m.x & ((1u << (t & 31u)) - 1u)); }
+
 // Normalisers of Alg. 2 for the requested tokens that lie in the chunk [t0, t0 + n): S and Q as the sampling
-// kernel's inspection mode left them (indexed by the token's position in the chunk) and the probability of the
-// sparse branch, S / (S + Q).
-__global__ void gather_probs_kernel(const float *S, const float *Q, const int64_t *idx, int64_t m, int64_t t0, int64_t n,
+// kernel's inspection mode left them (indexed by the token's position in the chunk, or by its number among the marked ones) and
+// the probability of the sparse branch, S / (S + Q).
+__global__ void gather_probs_kernel(const float *S, const float *Q, const uint2 *marks, const int64_t *idx, int64_t m, int64_t t0, int64_t n,
                                     float *out_S, float *out_Q, float *out_p) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m) return;
-    const int64_t r = idx[i] - t0;
+    int64_t r = idx[i] - t0;
     if (r < 0 || r >= n) return;
+    if (marks) r = token_number(marks[r >> 5], (uint32_t)(r & 31));
     const float s = S[r], q = Q[r];
     out_S[i] = s; out_Q[i] = q; out_p[i] = s / (s + q);
 }
@@ -204,7 +230,8 @@ struct EStepParams {
     void *z_wm;                 // [T] new assignments in word-major order (light words first): input of CountByVZ
     const uint2 *alias_table;   // null, or [dense rows][K] {prob bits, alias}: the dense term is then drawn from these
                                 // alias tables instead of the prefix-sum tree (measurement variant, Sec. 3.2.3)
-    float *out_S;               // probs mode: S per token of the chunk, indexed by the token's position in the chunk
+    const uint2 *marks;         // probs mode: null, or the only tokens that S and Q are asked for (mark_tokens_kernel)
+    float *out_S;               // probs mode: S per token of the chunk, indexed by its position in the chunk or its number among the marked
     float *out_Q;               // probs mode: Q likewise
     double *out_ll;             // loglik mode: one partial sum per tile
     unsigned long long *n_dense;// sample mode: kDenseSlots dense-branch token counters (workgroup b adds to slot b mod
@@ -498,8 +525,8 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     extern __shared__ float4 lds_f4[];
     // LDS, all of it dynamic so that the Bhat row starts at address 0 and a gather needs no base added:
     //   STAGED: [K rounded to 4] floats: the word's Bhat row
-    //   [4] words: batch ticket, dense-branch tokens of the workgroup, 0, 0 (the last one doubles as the tree level's
-    //           entry "before the first", which the dense branch reads for the first block)
+    //   [4] words: batch ticket, dense-branch tokens of the workgroup, whether a token is asked for (probs mode), 0 (the tree
+    //           level's entry "before the first", which the dense branch reads for the first block)
     //   STAGED: [n3 rounded to 4] floats: the tree level above the bottom;  LOGLIK: [16] doubles, one per wavefront
     //   not STAGED, if some words are light: after room for these 16 doubles, a pair of words per 32 topics (Overlay)
     // The footprint is kept minimal because it decides how many wavefronts a CU can hold: at K = 10,000 it is
@@ -514,6 +541,18 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     const Tile tile = p.tiles[blockIdx.x];
     const bool light = (!STAGED || sizeof(ZT) == 2) && (int)blockIdx.x >= p.first_light;
     const int K = p.K;
+    if (MODE == MODE_PROBS && p.marks) {   // nothing to do, and no row to stage, where none of the tile's tokens is asked for
+        if (threadIdx.x == 0) ctrl[2] = 0;
+        __syncthreads();
+        bool any = false;
+        for (int i = threadIdx.x; i < tile.count; i += blockDim.x) {
+            const uint32_t tt = p.tok_t[tile.begin + i];
+            any |= token_marked(p.marks[tt >> 5], tt);
+        }
+        if (any) ctrl[2] = 1;
+        __syncthreads();
+        if (ctrl[2] == 0) return;
+    }
     const float *__restrict__ phi_row = light ? p.base : p.phi + (size_t)tile.row * (size_t)p.Kpad;
     const float *__restrict__ l3_row = p.l3 + (size_t)tile.word * (size_t)p.n3pad;
     const double *__restrict__ l3_64_row = p.l3_64 + (size_t)tile.word * (size_t)p.n3;
@@ -533,7 +572,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         d = p.tok_doc[tile.begin + batch + lane];
         t = p.tok_t[tile.begin + batch + lane];
     }
-    if (threadIdx.x == 0) { next_batch = nwaves; wg_dense = 0u; ctrl[2] = 0; ctrl[3] = 0; }
+    if (threadIdx.x == 0) { next_batch = nwaves; wg_dense = 0u; ctrl[3] = 0; }
     if (STAGED) {
         // eight 16-byte loads per thread are requested before the first of them is written to LDS: one load, one
         // wait, one write at a time left a workgroup's start waiting for memory five times over at K = 10,000.
@@ -600,7 +639,8 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     for (int round = 0;; round++) {
         if (batch >= tile.count) break;
         const int n = __builtin_amdgcn_readfirstlane(min(bs, tile.count - batch));   // wave-uniform by construction
-        const bool act = lane < n;
+        bool act = lane < n;
+        if (MODE == MODE_PROBS && p.marks && act) act = token_marked(p.marks[t >> 5], t);   // each of them a run of its own
         float u0 = 0.f, u1 = 0.f;
         if (MODE == MODE_SAMPLE) {
             Rand2 r = philox_token(p.seed_lo, p.seed_hi, (uint64_t)(p.t_base + (int64_t)t), p.iter);
@@ -611,8 +651,8 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
 
         // Runs: bit i of `starts` marks a lane where the tokens of another document begin.
         const int d_prev = __builtin_amdgcn_update_dpp(-2, d, 0x138, 0xf, 0xf, false);   // wave_shr:1
-        const bool first_of_run = act && d != d_prev;
-        const unsigned long long starts = __builtin_amdgcn_ballot_w64(first_of_run) | 1ull;
+        const bool first_of_run = act && (d != d_prev || (MODE == MODE_PROBS && p.marks));
+        const unsigned long long starts = __builtin_amdgcn_ballot_w64(first_of_run) | (MODE == MODE_PROBS && p.marks ? 0ull : 1ull);
         // the row of the lane's document: byte offset inside the chunk's rows and padded length in bytes
         const uint32_t row_off = (rec.x - p.row_unit0) << 7;
         const uint32_t row_bytes = ((rec.y + 3u) & ~3u) << 2;
@@ -943,7 +983,8 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
                 asm volatile("" : "+v"(pos));
                 reinterpret_cast<ZT *>(p.z_wm)[tile.wm_begin + (int64_t)pos] = (ZT)my_z;
             } else if (MODE == MODE_PROBS) {
-                p.out_S[t_late] = my_S; p.out_Q[t_late] = Q;
+                const uint32_t at = p.marks ? token_number(p.marks[t_late >> 5], t_late) : t_late;
+                p.out_S[at] = my_S; p.out_Q[at] = Q;
             } else {
                 ll_acc += log((double)(my_S + Q));
             }

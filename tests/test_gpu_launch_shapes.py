@@ -258,3 +258,24 @@ def test_frequent_words_cut_by_ranges_of_documents(T, K, opts):
     assert abs(g.loglik() - p.loglik()) <= 1e-11 * abs(p.loglik())
     g.close()
     p.close()
+
+
+@pytest.mark.parametrize("K,opts", [(60, {}), (1000, {}), (9000, {}), (40_000, {}), (1000, {"stage_phi": 0}), (70_000, {}), (300, {"n_chunks": 3}),
+                                    (300, {"n_chunks": 3, "stream_workers": 2})])
+def test_normalisers_of_a_few_tokens(K, opts):
+    """Fewer than an eighth of the tokens are marked and worked on alone: the same numbers as where all are asked for, which
+    the oracle checks; none in a tile or a batch, one, all of a run, a word's all; repeats; tokens on both sides of what a
+    mark holds; both sides of an eighth; a large request between two small ones."""
+    rng = np.random.default_rng(K)
+    edges = [1, 2, 63, 64, 65, 129, 400, 700]
+    doc_ptr, words = corpus_of_word_counts(np.r_[np.repeat(edges, 9), 4000, 9000], 260, K)
+    words[doc_ptr[7]: doc_ptr[7] + 40] = 3                            # runs of more than one token
+    T, V = words.size, int(words.max()) + 1
+    g = saber().Saber(doc_ptr, words, V, K, 50.0 / K, 0.01, 11, **opts)
+    g.iterate(2)
+    every = g.token_probs(np.arange(T))
+    for tok in (np.array([T - 1]), np.array([0, 31, 32, 63, 64, T - 1, 0, 32]), rng.integers(0, T, 300), np.arange(doc_ptr[7], doc_ptr[8]),
+                np.arange(T), np.nonzero(words == V - 1)[0][:T // 9], np.arange(T // 8 - 1), np.arange(T // 8), rng.permutation(T)[:T // 8 - 1]):
+        for a, b in zip(g.token_probs(tok), every):
+            assert np.array_equal(a, b[tok])
+    g.close()
