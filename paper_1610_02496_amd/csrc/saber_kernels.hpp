@@ -115,16 +115,23 @@ __device__ __forceinline__ void lds_barrier() {
 // counter = (token lo, token hi, iteration, 0), key = (seed lo, seed hi).
 // ---------------------------------------------------------------------------------------------
 struct Rand2 { uint32_t r0, r1; };
+// Bound by instruction issue: 4.5 cycles for a product of either half or of both, so one v_mad_u64_u32 forms both.  The key is
+// opaque at every call: otherwise the compiler computes the 20 round keys once per kernel, has no scalar registers for them,
+// and parks them in lanes of a vector register at 4.5 cycles a move, where the scalar unit adds them up for nothing.
+__device__ __forceinline__ uint64_t mul_wide(uint32_t a, uint32_t b) {
+    uint64_t r;
+    asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(r) : "s"(a), "v"(b) : "vcc");
+    return r;
+}
 __device__ __forceinline__ Rand2 philox_token(uint32_t seed_lo, uint32_t seed_hi, uint64_t t, uint32_t iter) {
     uint32_t c0 = (uint32_t)t, c1 = (uint32_t)(t >> 32), c2 = iter, c3 = 0u;
     uint32_t k0 = seed_lo, k1 = seed_hi;
+    asm volatile("" : "+s"(k0), "+s"(k1));
 #pragma unroll
     for (int r = 0; r < 10; r++) {
-        const uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
-        uint32_t hi0 = __umulhi(M0, c0), lo0 = M0 * c0;
-        uint32_t hi1 = __umulhi(M1, c2), lo1 = M1 * c2;
-        uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
-        c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
+        const uint64_t p0 = mul_wide(0xD2511F53u, c0), p1 = mul_wide(0xCD9E8D57u, c2);
+        uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0, n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        c0 = n0; c1 = (uint32_t)p1; c2 = n2; c3 = (uint32_t)p0;
         k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
     }
     return Rand2{c0, c1};
@@ -515,6 +522,18 @@ __device__ __forceinline__ uint32_t search_block(const uint4 e, const RowBlock &
     return readlane_u32(sel, L) & tmask;
 }
 
+// The kernel's parameters where the hardware left them, read again from there (constant memory, scalar loads).  The compiler reads
+// them once, at the top, and has no scalar registers for what the batch loop needs only now and then: it parked 64 of them in
+// the lanes of a vector register, and moved them there and back at 4.5 cycles of the vector unit each, 64 moves when a wavefront
+// starts and 80 per batch.  With the round keys of philox_token out of them too: T = 10 M, K = 1,000 an iteration of 654 -> 643
+// us, T = 15 M, K = 20,011 2,000 -> 1,977, T = 100 M, K = 10,000 7,618 -> 7,585.
+typedef __attribute__((address_space(4))) const EStepParams EStepParamsConst;
+__device__ __forceinline__ EStepParamsConst *params_again() {
+    auto *q = (EStepParamsConst *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(q));   // (a pointer the compiler knows nothing of: nothing read through it earlier is kept)
+    return q;
+}
+
 // New assignments are written twice: to z (canonical order) and to z_wm (word-major, coalesced), from which the
 // M-step counts B; the sampler itself adds nothing to B.
 // A light word keeps B sparse: its Bhat row is built in LDS from the base vector and the word's non-zeros (staged rows have
@@ -636,14 +655,17 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
 
     // `batch`, and d, t, rec of its tokens, are in hand at the top of every turn: those of the first batch from above,
     // those of the later ones from the bottom of the turn before
+    const int count = tile.count;
+    if (batch < count)
     for (int round = 0;; round++) {
-        if (batch >= tile.count) break;
-        const int n = __builtin_amdgcn_readfirstlane(min(bs, tile.count - batch));   // wave-uniform by construction
+        const int n = __builtin_amdgcn_readfirstlane(min(bs, count - batch));   // wave-uniform by construction
         bool act = lane < n;
         if (MODE == MODE_PROBS && p.marks && act) act = token_marked(p.marks[t >> 5], t);   // each of them a run of its own
         float u0 = 0.f, u1 = 0.f;
+        EStepParamsConst *q = params_again();
+        const uint32_t row_unit0 = q->row_unit0;
         if (MODE == MODE_SAMPLE) {
-            Rand2 r = philox_token(p.seed_lo, p.seed_hi, (uint64_t)(p.t_base + (int64_t)t), p.iter);
+            Rand2 r = philox_token(q->seed_lo, q->seed_hi, (uint64_t)(q->t_base + (int64_t)t), q->iter);
             u0 = unit24(r.r0); u1 = unit24(r.r1);
         }
         uint32_t my_z = 0; float my_S = 0.f;
@@ -654,18 +676,19 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         const bool first_of_run = act && (d != d_prev || (MODE == MODE_PROBS && p.marks));
         const unsigned long long starts = __builtin_amdgcn_ballot_w64(first_of_run) | (MODE == MODE_PROBS && p.marks ? 0ull : 1ull);
         // the row of the lane's document: byte offset inside the chunk's rows and padded length in bytes
-        const uint32_t row_off = (rec.x - p.row_unit0) << 7;
+        const uint32_t row_off = (rec.x - row_unit0) << 7;
         const uint32_t row_bytes = ((rec.y + 3u) & ~3u) << 2;
         // position of the token inside its run
         const uint32_t jpos = (uint32_t)(lane - wave_incl_scan_max(first_of_run || lane == 0 ? lane : -1));
         // rows that fit a quarter or a half of the wavefront; runs are cut into pieces of at most G tokens there
-        unsigned long long m16 = __builtin_amdgcn_ballot_w64(act && row_bytes <= p.quarter_row_bytes);
-        unsigned long long m32 = __builtin_amdgcn_ballot_w64(act && row_bytes <= p.half_row_bytes) & ~m16;
+        const uint32_t quarter = q->quarter_row_bytes, half = q->half_row_bytes;
+        unsigned long long m16 = __builtin_amdgcn_ballot_w64(act && row_bytes <= quarter);
+        unsigned long long m32 = __builtin_amdgcn_ballot_w64(act && row_bytes <= half) & ~m16;
         const unsigned long long cuts16 = __builtin_amdgcn_ballot_w64(act && (jpos & 15u) == 0u);   // where pieces begin
         const unsigned long long cuts32 = __builtin_amdgcn_ballot_w64(act && (jpos & 31u) == 0u);
         // a pass serves four (two) runs at the cost of about one: a class that would not fill most of one pass goes
         // with the next wider one
-        if (__builtin_popcountll(m16 & cuts16) < 3) { if (p.half_row_bytes >= p.quarter_row_bytes) m32 |= m16; m16 = 0ull; }
+        if (__builtin_popcountll(m16 & cuts16) < 3) { if (half >= quarter) m32 |= m16; m16 = 0ull; }
         if (__builtin_popcountll(m32 & cuts32) < 2) m32 = 0ull;
         const unsigned long long cm16 = m16 & cuts16, cm32 = m32 & cuts32;
         unsigned long long wide_rest = starts & ~(m16 | m32);
@@ -910,16 +933,18 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         // register limit; the 4 bytes come from a cache line this wavefront loaded at the top of the batch).  Requested
         // here, it arrives while the dense branch below is served.
         uint32_t t_late = 0u;
+        q = params_again();
+        const Tile *tile_now = q->tiles + blockIdx.x;
         if (MODE != MODE_LOGLIK) {
             uint32_t pos_t = (uint32_t)(batch + lane);
             asm volatile("" : "+v"(pos_t));
-            if (act) t_late = p.tok_t[tile.begin + (int)pos_t];
+            if (act) t_late = q->tok_t[tile_now->begin + (int)pos_t];
         }
 
         if (MODE == MODE_SAMPLE && dense_mask) {
             // problem 2 for the tokens whose coin chose it: DPP row g (16 lanes) serves the g-th of up to four tokens
             if (lane == 0) atomicAdd(&wg_dense, (unsigned int)__builtin_popcountll(dense_mask));   // statistic only
-            if (p.alias_table != nullptr) {   // (every word then keeps a dense row)
+            if (q->alias_table != nullptr) {   // (every word then keeps a dense row)
                 // Walker's alias method for all these tokens at once: the bucket is floor(u1 K), taken in integers from
                 // the 24 random bits behind u1; the bucket's own topic if the fraction of u1 K lies below its
                 // probability, its alias otherwise
@@ -928,7 +953,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
                 const uint32_t bucket = (hi << 8) | (lo >> 24);
                 const float frac = (float)(lo & 0xffffffu) * (1.0f / 16777216.0f);
                 if (__builtin_amdgcn_inverse_ballot_w64(dense_mask)) {
-                    const uint2 e = p.alias_table[(size_t)tile.row * (size_t)K + bucket];
+                    const uint2 e = q->alias_table[(size_t)tile_now->row * (size_t)K + bucket];
                     my_z = frac < __uint_as_float(e.x) ? bucket : e.y;
                 }
                 dense_mask = 0ull;
@@ -977,14 +1002,14 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
 
         if (act) {
             if (MODE == MODE_SAMPLE) {
-                reinterpret_cast<ZT *>(p.z)[p.z_rel + (int64_t)t_late] = (ZT)my_z;
+                reinterpret_cast<ZT *>(q->z)[q->z_rel + (int64_t)t_late] = (ZT)my_z;
                 // the second copy, in word-major order, is what CountByVZ reads (coalesced here and there)
                 uint32_t pos = (uint32_t)(batch + lane);   // of the token inside the tile
                 asm volatile("" : "+v"(pos));
-                reinterpret_cast<ZT *>(p.z_wm)[tile.wm_begin + (int64_t)pos] = (ZT)my_z;
+                reinterpret_cast<ZT *>(q->z_wm)[tile_now->wm_begin + (int64_t)pos] = (ZT)my_z;
             } else if (MODE == MODE_PROBS) {
-                const uint32_t at = p.marks ? token_number(p.marks[t_late >> 5], t_late) : t_late;
-                p.out_S[at] = my_S; p.out_Q[at] = Q;
+                const uint32_t at = q->marks ? token_number(q->marks[t_late >> 5], t_late) : t_late;
+                q->out_S[at] = my_S; q->out_Q[at] = Q;
             } else {
                 ll_acc += log((double)(my_S + Q));
             }
@@ -995,11 +1020,14 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         if (MODE == MODE_LOGLIK) ticket = (round + 1) * nwaves + wave;   // fixed assignment: the sums come out bit-identical every time
         else if (lane == 0) ticket = atomicAdd(&next_batch, 1);
         batch = __builtin_amdgcn_readfirstlane(ticket) * bs;   // wave-uniform: loop control stays scalar
-        d = -1; t = 0u; rec = make_uint2(p.row_unit0, 0u);
-        if (lane < min(bs, tile.count - batch)) {
-            d = p.tok_doc[tile.begin + batch + lane];
-            t = p.tok_t[tile.begin + batch + lane];
-            rec = p.docrec[d];
+        if (batch >= count) break;
+        q = params_again();
+        d = -1; t = 0u; rec = make_uint2(q->row_unit0, 0u);
+        if (lane < min(bs, count - batch)) {
+            const int at = tile_now->begin + batch + lane;
+            d = q->tok_doc[at];
+            t = q->tok_t[at];
+            rec = q->docrec[d];
         }
     }
 
