@@ -364,6 +364,30 @@ static int check_estep_lds_layout() {
     return SABER_OK;
 }
 
+// Wavefronts a CU holds of a sampling kernel with `block` threads per workgroup, given its LDS (handed out in 512-byte
+// pieces) and the 32 wavefronts a CU can hold.
+static int estep_waves_per_cu(const saber_ctx *c, int block) {
+    const size_t need = c->staged || c->overlay ? ((estep_lds_bytes(c, MODE_SAMPLE) + 144 + 511) / 512) * 512 : 512;
+    const int by_lds = (int)std::min<size_t>(64, (size_t)c->lds_per_cu / need), by_waves = 32 / (block / 64);
+    return std::min(by_lds, by_waves) * (block / 64);
+}
+
+// Workgroups that n tiles of light words are dealt to, every so-manieth tile to each (the tiles are sorted by size: the shares are
+// alike).  The Bhat rows of light words differ in a few topics, so a workgroup that works on several stages the base vector
+// once and exchanges these topics: T = 15 M, K = 20,011, 80 KB per row and 90 tokens per tile, 2.03 ms per iteration with one
+// tile per workgroup, 1.70, 1.67 and 1.72 with 4, 12 and 64; T = 36 M, K = 5,000 2.49, 2.40 with 4, 2.43 with 8 and 2.59 with
+// 64; T = 100 M, K = 10,000 7.44, 7.28, 7.35 with 12 and 7.99 with 64.  What many per workgroup lose is the tail of
+// the launch: every place on the chip gets 16 workgroups in turn or more, and 8 tiles are the most.  With
+// one wavefront per workgroup and rows of 4 KB (T = 10 M, K = 1,000) no number of tiles changes anything.  The log-likelihood
+// pass has no registers for it, and gained nothing.
+constexpr int64_t kWalkTiles = 8, kWalkRounds = 16, kCus = 256;
+static int32_t walkers_for(const saber_ctx *c, int mode, int64_t n, int block) {
+    if (!c->staged || !c->z16 || mode != MODE_SAMPLE || n <= 0) return (int32_t)n;
+    const int64_t places = kCus * estep_waves_per_cu(c, block) / (block / 64);
+    const int64_t tiles = std::max<int64_t>(1, std::min(kWalkTiles, n / (kWalkRounds * places)));
+    return (int32_t)((n + tiles - 1) / tiles);
+}
+
 // One E-step launch per tile class (tile_classes() below).  All stage the row in LDS when it fits.
 template <int MODE>
 static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
@@ -374,7 +398,9 @@ static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
             p.tiles = p0.tiles + cl.first + i;
             if (p0.out_ll) p.out_ll = p0.out_ll + cl.first + i;
             p.first_light = (int32_t)std::max<int64_t>(0, std::min(cl.n_dense - i, n));
-            const dim3 grid((unsigned)n), block((unsigned)cl.block);
+            p.n_tiles = (int32_t)n;
+            p.walkers = walkers_for(c, MODE, n - p.first_light, cl.block);
+            const dim3 grid((unsigned)(p.first_light + p.walkers)), block((unsigned)cl.block);
             const size_t lds = estep_lds_bytes(c, MODE);
             if (c->staged) {
                 if (c->z16) launch_estep_b16<MODE, true, uint16_t>(c, grid, block, lds, p);
@@ -387,14 +413,6 @@ static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
         }
     }
     return SABER_OK;
-}
-
-// Wavefronts a CU holds of a sampling kernel with `block` threads per workgroup, given its LDS (handed out in 512-byte
-// pieces) and the 32 wavefronts a CU can hold.
-static int estep_waves_per_cu(const saber_ctx *c, int block) {
-    const size_t need = c->staged || c->overlay ? ((estep_lds_bytes(c, MODE_SAMPLE) + 144 + 511) / 512) * 512 : 512;
-    const int by_lds = (int)std::min<size_t>(64, (size_t)c->lds_per_cu / need), by_waves = 32 / (block / 64);
-    return std::min(by_lds, by_waves) * (block / 64);
 }
 
 // Threads of a sampling workgroup where the caller leaves them open.

@@ -244,6 +244,7 @@ struct EStepParams {
     unsigned long long *n_dense;// sample mode: kDenseSlots dense-branch token counters (workgroup b adds to slot b mod
                                 // kDenseSlots: one hot address would serialise the atomics of the whole launch)
     int32_t first_light;        // tiles of the launch from this one on belong to light words
+    int32_t n_tiles, walkers;   // tiles of the launch; workgroups its light words' tiles are dealt to: each works on every walkers-th
     int64_t t_base;             // canonical index of the chunk's first token
     int64_t z_rel;              // position of that token in z
     int32_t K, Kpad, n3, n3pad;
@@ -534,6 +535,13 @@ __device__ __forceinline__ EStepParamsConst *params_again() {
     return q;
 }
 
+__device__ __forceinline__ float first_lane(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+
+// What a kernel only reads, read with the scalar unit where the address is the same for a whole wavefront (behind a store the
+// compiler takes the vector unit: the store might have changed it).
+template <typename T> using ConstMem = __attribute__((address_space(4))) const T;
+template <typename T> __device__ __forceinline__ ConstMem<T> *const_mem(const T *p) { return (ConstMem<T> *)(uintptr_t)p; }
+
 // New assignments are written twice: to z (canonical order) and to z_wm (word-major, coalesced), from which the
 // M-step counts B; the sampler itself adds nothing to B.
 // A light word keeps B sparse: its Bhat row is built in LDS from the base vector and the word's non-zeros (staged rows have
@@ -554,10 +562,10 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     float *lds_phi = reinterpret_cast<float *>(lds_f4);
     int *ctrl = reinterpret_cast<int *>(lds_phi + K4);
     float *lds_l3 = lds_phi + K4 + 4;
-    int &next_batch = ctrl[0];   // batches of a tile are handed out to wavefronts as they become free
-    unsigned int &wg_dense = reinterpret_cast<unsigned int *>(ctrl)[1];   // dense-branch tokens of this workgroup
     double *ll_wave = reinterpret_cast<double *>(lds_l3 + (STAGED ? (p.n3 + 3) & ~3 : 0));
-    const Tile tile = p.tiles[blockIdx.x];
+    constexpr bool kWalks = STAGED && sizeof(ZT) == 2 && MODE == MODE_SAMPLE;   // (see walkers_for() on the host)
+    int tile_at = (int)blockIdx.x;
+    const Tile tile = p.tiles[tile_at];
     const bool light = (!STAGED || sizeof(ZT) == 2) && (int)blockIdx.x >= p.first_light;
     const int K = p.K;
     if (MODE == MODE_PROBS && p.marks) {   // nothing to do, and no row to stage, where none of the tile's tokens is asked for
@@ -574,8 +582,8 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     }
     const float *__restrict__ phi_row = light ? p.base : p.phi + (size_t)tile.row * (size_t)p.Kpad;
     const float *__restrict__ l3_row = p.l3 + (size_t)tile.word * (size_t)p.n3pad;
-    const double *__restrict__ l3_64_row = p.l3_64 + (size_t)tile.word * (size_t)p.n3;
-    const int lane = lane_id(), nwaves = blockDim.x / kWave;
+    int lane = lane_id();
+    const int nwaves = blockDim.x / kWave;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     // batch size: 64 tokens per wavefront, fewer when the tile is too small to keep every wavefront busy
     int bs = (tile.count + nwaves - 1) / nwaves;
@@ -591,16 +599,16 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         d = p.tok_doc[tile.begin + batch + lane];
         t = p.tok_t[tile.begin + batch + lane];
     }
-    if (threadIdx.x == 0) { next_batch = nwaves; wg_dense = 0u; ctrl[3] = 0; }
-    if (STAGED) {
+    if (threadIdx.x == 0) { ctrl[0] = nwaves; ctrl[1] = 0; ctrl[3] = 0; }
+    auto stage_row = [&](const int tid, const float *src, const int K4) {
         // eight 16-byte loads per thread are requested before the first of them is written to LDS: one load, one
         // wait, one write at a time left a workgroup's start waiting for memory five times over at K = 10,000.
         // (No branch inside: past the end, the last piece is read and written once more.)
         typedef float quad_t __attribute__((ext_vector_type(4)));
-        const quad_t *qsrc = reinterpret_cast<const quad_t *>(phi_row);
+        const quad_t *qsrc = reinterpret_cast<const quad_t *>(src);
         quad_t *qdst = reinterpret_cast<quad_t *>(lds_phi);
         const int nq = K4 / 4, step = (int)blockDim.x;
-        for (int i0 = threadIdx.x; i0 < nq; i0 += 8 * step) {
+        for (int i0 = tid; i0 < nq; i0 += 8 * step) {
             const quad_t q0 = qsrc[min(i0, nq - 1)], q1 = qsrc[min(i0 + step, nq - 1)], q2 = qsrc[min(i0 + 2 * step, nq - 1)],
                          q3 = qsrc[min(i0 + 3 * step, nq - 1)], q4 = qsrc[min(i0 + 4 * step, nq - 1)],
                          q5 = qsrc[min(i0 + 5 * step, nq - 1)], q6 = qsrc[min(i0 + 6 * step, nq - 1)],
@@ -609,6 +617,9 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             qdst[min(i0 + 3 * step, nq - 1)] = q3; qdst[min(i0 + 4 * step, nq - 1)] = q4; qdst[min(i0 + 5 * step, nq - 1)] = q5;
             qdst[min(i0 + 6 * step, nq - 1)] = q6; qdst[min(i0 + 7 * step, nq - 1)] = q7;
         }
+    };
+    if (STAGED) {
+        stage_row((int)threadIdx.x, phi_row, K4);
         if (MODE == MODE_SAMPLE)
             for (int i = threadIdx.x; i < p.n3; i += blockDim.x) lds_l3[i] = l3_row[i];
     }
@@ -643,19 +654,15 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         for (int j = threadIdx.x + blockDim.x; j < (int)wr.y; j += blockDim.x) lds_phi[ent[j] & tm] = val[j];
     }
     __syncthreads();
-    const float sum_w = p.sumphi[tile.word];
-    const float Q = p.alpha * sum_w;
-    int l3_top_shift = 0;                      // the dense branch's descent over l3 starts with stride 16^(l3_top_shift / 4)
-    while ((16 << l3_top_shift) < p.n3) l3_top_shift += 4;
+    float sum_w = *const_mem(p.sumphi + tile.word);
+    float Q = first_lane(p.alpha * sum_w);
     const uint32_t bits = B16 ? 16u : p.topic_bits, tmask = B16 ? 0xffffu : p.topic_mask;
-    // all rows of A of the chunk behind one buffer descriptor: a row is addressed by its 32-bit byte offset
-    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.cd_rows), (short)0,
-                                                                          (int)p.rows_bytes, 0x00020000);
+    int count = tile.count;
+    for (;;) {   // the tiles of the workgroup
+    asm volatile("" : "+v"(lane));   // (values derived from the lane number are formed per tile, not held over all of them)
     double ll_acc = 0.0;
-
     // `batch`, and d, t, rec of its tokens, are in hand at the top of every turn: those of the first batch from above,
     // those of the later ones from the bottom of the turn before
-    const int count = tile.count;
     if (batch < count)
     for (int round = 0;; round++) {
         const int n = __builtin_amdgcn_readfirstlane(min(bs, count - batch));   // wave-uniform by construction
@@ -664,6 +671,9 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         float u0 = 0.f, u1 = 0.f;
         EStepParamsConst *q = params_again();
         const uint32_t row_unit0 = q->row_unit0;
+        // all rows of A of the chunk behind one buffer descriptor: a row is addressed by its 32-bit byte offset
+        const char *rows_base = reinterpret_cast<const char *>(q->cd_rows);
+        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(rows_base), (short)0, (int)q->rows_bytes, 0x00020000);
         if (MODE == MODE_SAMPLE) {
             Rand2 r = philox_token(q->seed_lo, q->seed_hi, (uint64_t)(q->t_base + (int64_t)t), q->iter);
             u0 = unit24(r.r0); u1 = unit24(r.r1);
@@ -799,7 +809,6 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         // ---- longer rows: one run [s, s_end) at a time over the whole wavefront ----
         // `cur` and `cur2` hold the first two blocks of the run's row (fetched during the previous run) and cur_bytes the
         // row's padded length; the next run's row is fetched into `nxt`, `nxt2` before this run's arithmetic starts.
-        const char *rows_base = reinterpret_cast<const char *>(p.cd_rows);
         auto fetch = [&](const int s, uint4 &blk, uint4 &blk2, uint32_t &bytes) {
             // Requested without any branch around the two loads: for s < 0 (no further run), and for the second
             // block of a short row, the descriptor's length makes every lane fall outside the row, which returns zeros
@@ -934,7 +943,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         // here, it arrives while the dense branch below is served.
         uint32_t t_late = 0u;
         q = params_again();
-        const Tile *tile_now = q->tiles + blockIdx.x;
+        auto *tile_now = const_mem(q->tiles + tile_at);
         if (MODE != MODE_LOGLIK) {
             uint32_t pos_t = (uint32_t)(batch + lane);
             asm volatile("" : "+v"(pos_t));
@@ -943,7 +952,9 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
 
         if (MODE == MODE_SAMPLE && dense_mask) {
             // problem 2 for the tokens whose coin chose it: DPP row g (16 lanes) serves the g-th of up to four tokens
-            if (lane == 0) atomicAdd(&wg_dense, (unsigned int)__builtin_popcountll(dense_mask));   // statistic only
+            const int K = q->K, n3 = q->n3, K4 = (K + 3) & ~3;
+            const double *l3_64_row = q->l3_64 + (size_t)tile_now->word * (size_t)n3;
+            if (lane == 0) atomicAdd(reinterpret_cast<unsigned int *>(lds_phi + (STAGED ? K4 : 0)) + 1, (unsigned int)__builtin_popcountll(dense_mask));   // statistic only
             if (q->alias_table != nullptr) {   // (every word then keeps a dense row)
                 // Walker's alias method for all these tokens at once: the bucket is floor(u1 K), taken in integers from
                 // the 24 random bits behind u1; the bucket's own topic if the fraction of u1 K lies below its
@@ -963,6 +974,8 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             asm volatile("" : "+v"(ln));               // (as above: lane-derived values formed where they are used)
             const uint32_t g = ln >> 4, li = ln & 15u;
             if (STAGED) {
+                int l3_top_shift = 0;   // the descent over l3 starts with stride 16^(l3_top_shift / 4)
+                while ((16 << l3_top_shift) < n3) l3_top_shift += 4;
                 while (dense_mask) {
                     // the next four tokens (fewer at the end: the spare rows then repeat the first token's query, and
                     // arrive at the same answer)
@@ -977,7 +990,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
                     const uint32_t packed = (tl[0] | (tl[1] << 8) | (tl[2] << 16) | (tl[3] << 24)) << 2;
                     const uint32_t mine4 = __builtin_amdgcn_ubfe(packed, g << 3, 8u);
                     const float x = lane_pull(xd, mine4);
-                    const uint32_t k = dense_query4_staged((uint32_t)K4 * 4u, (uint32_t)K4 * 4u + 16u, l3_64_row, p.n3, l3_top_shift, K,
+                    const uint32_t k = dense_query4_staged((uint32_t)K4 * 4u, (uint32_t)K4 * 4u + 16u, l3_64_row, n3, l3_top_shift, K,
                                                            x, li, ln & 48u);
                     // all 16 lanes of a row hold the row's answer and send it to the row's token
                     const uint32_t got = lane_push(k, mine4);
@@ -993,7 +1006,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
                 }
                 const int mine = g == 0 ? tl[0] : g == 1 ? tl[1] : g == 2 ? tl[2] : tl[3];
                 const float x = __int_as_float(__builtin_amdgcn_ds_bpermute((mine < 0 ? lane : mine) << 2, __float_as_int(xd)));
-                const uint32_t k = dense_query4(phi_row, p.Kpad, l3_row, l3_64_row, p.n3, K, x, (int)li, ov);
+                const uint32_t k = dense_query4(phi_row, q->Kpad, q->l3 + (size_t)tile_now->word * (size_t)q->n3pad, l3_64_row, n3, K, x, (int)li, ov);
 #pragma unroll
                 for (int q = 0; q < 4; q++)
                     if (tl[q] >= 0) my_z = llvm_amdgcn_writelane_u32(readlane_u32(k, 16 * q), (unsigned)tl[q], my_z);
@@ -1018,7 +1031,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         // records earlier, before the dense branch, changed nothing.)
         int ticket = 0;
         if (MODE == MODE_LOGLIK) ticket = (round + 1) * nwaves + wave;   // fixed assignment: the sums come out bit-identical every time
-        else if (lane == 0) ticket = atomicAdd(&next_batch, 1);
+        else if (lane == 0) ticket = atomicAdd(reinterpret_cast<int *>(lds_phi + (STAGED ? (q->K + 3) & ~3 : 0)), 1);   // (handed out as wavefronts become free)
         batch = __builtin_amdgcn_readfirstlane(ticket) * bs;   // wave-uniform: loop control stays scalar
         if (batch >= count) break;
         q = params_again();
@@ -1031,10 +1044,6 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         }
     }
 
-    if (MODE == MODE_SAMPLE) {
-        __syncthreads();
-        if (threadIdx.x == 0 && wg_dense) atomicAdd(p.n_dense + (blockIdx.x & (kDenseSlots - 1)), (unsigned long long)wg_dense);
-    }
     if (MODE == MODE_LOGLIK) {
         double tot = readlane_f64(wave_incl_scan(ll_acc), 63);
         if (lane == 0) ll_wave[wave] = tot;
@@ -1042,8 +1051,70 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         if (threadIdx.x == 0) {
             double sum = 0.0;
             for (int w = 0; w < nwaves; w++) sum += ll_wave[w];
-            p.out_ll[blockIdx.x] = sum;
+            p.out_ll[tile_at] = sum;
         }
+    }
+    if (!kWalks || !light) break;
+    EStepParamsConst *q = params_again();
+    const int next_at = tile_at + q->walkers;
+    if (next_at >= q->n_tiles) break;
+    // The next light word.  Everything its start needs from memory is requested before the barrier at which the workgroup's
+    // wavefronts come together; then the last word's topics get their base values back - the whole row is staged again where they
+    // are more than one per thread - and the new word's take their place.
+    auto *rec0 = const_mem(q->wrec + const_mem(q->tiles + tile_at)->row);
+    tile_at = next_at;
+    auto *tile = const_mem(q->tiles + tile_at);
+    auto *rec1 = const_mem(q->wrec + tile->row);
+    const uint2 wr0 = make_uint2(rec0->x, rec0->y), wr = make_uint2(rec1->x, rec1->y);
+    const uint32_t *ent0 = q->lw_ent + (size_t)wr0.x * 32u, *ent = q->lw_ent + (size_t)wr.x * 32u;
+    const float *val = q->lw_phi + (size_t)wr.x * 32u;
+    const float *l3_row = q->l3 + (size_t)tile->word * (size_t)q->n3pad;
+    count = tile->count;
+    bs = (count + nwaves - 1) / nwaves;
+    bs = __builtin_amdgcn_readfirstlane(bs > kWave ? kWave : bs);
+    batch = wave * bs;
+    d = -1; t = 0u; rec = make_uint2(q->row_unit0, 0u);
+    if (lane < min(bs, count - batch)) {
+        d = q->tok_doc[tile->begin + batch + lane];
+        t = q->tok_t[tile->begin + batch + lane];
+    }
+    const int tid = wave * kWave + lane;
+    const int nt = (int)blockDim.x, n3 = q->n3, K4 = (q->K + 3) & ~3;
+    float *lds_l3 = lds_phi + K4 + 4;
+    const bool restore = (int)wr0.y <= nt;
+    uint32_t k0 = 0u, e = 0u;
+    float b0 = 0.f, v = 0.f, c = 0.f;
+    if (tid < (int)wr.y) { e = ent[tid]; v = val[tid]; }
+    if (restore && tid < (int)wr0.y) { k0 = ent0[tid] & tmask; b0 = q->base[k0]; }
+    if (tid < n3) c = l3_row[tid];
+    if (d >= 0) rec = q->docrec[d];
+    sum_w = *const_mem(q->sumphi + tile->word);
+    Q = first_lane(q->alpha * sum_w);
+    lds_barrier();
+    if (restore) { if (tid < (int)wr0.y) lds_phi[k0] = b0; }
+    else {   // (two loads at a time: d, t and rec are in registers)
+        const float4 *src = reinterpret_cast<const float4 *>(q->base);
+        float4 *dst = reinterpret_cast<float4 *>(lds_phi);
+        const int nq = K4 / 4;
+        for (int i = tid; i < nq; i += 2 * nt) {
+            const float4 f0 = src[i], f1 = src[min(i + nt, nq - 1)];
+            dst[i] = f0; dst[min(i + nt, nq - 1)] = f1;
+        }
+    }
+    if (tid < n3) lds_l3[tid] = c;
+    for (int i = tid + nt; i < n3; i += nt) lds_l3[i] = l3_row[i];
+    if (tid == 0) reinterpret_cast<int *>(lds_phi)[K4] = nwaves;
+    lds_barrier();
+    if (tid < (int)wr.y) lds_phi[e & tmask] = v;
+    for (int j = tid + nt; j < (int)wr.y; j += nt) lds_phi[ent[j] & tmask] = val[j];
+    lds_barrier();
+    }
+
+    if (MODE == MODE_SAMPLE) {
+        __syncthreads();
+        EStepParamsConst *q = params_again();
+        const unsigned int wg_dense = reinterpret_cast<unsigned int *>(lds_phi + (STAGED ? (q->K + 3) & ~3 : 0))[1];   // dense-branch tokens of this workgroup
+        if (threadIdx.x == 0 && wg_dense) atomicAdd(q->n_dense + (blockIdx.x & (kDenseSlots - 1)), (unsigned long long)wg_dense);
     }
 }
 

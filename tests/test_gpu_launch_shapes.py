@@ -279,3 +279,23 @@ def test_normalisers_of_a_few_tokens(K, opts):
         for a, b in zip(g.token_probs(tok), every):
             assert np.array_equal(a, b[tok])
     g.close()
+
+
+@pytest.mark.parametrize("K,opts", [(9000, {}), (20_011, {}), (9000, {"tile_tokens": 64}), (20_011, {"tile_tokens": 64})])
+def test_workgroups_that_work_on_several_light_words(K, opts):
+    """Enough tiles of light words for several per workgroup, against chunks with too few: words of one token to more than a
+    workgroup has threads, whose topics it takes back one by one or by staging the row again; the numbers of tiles leave a
+    remainder.  With tiles of 64 tokens most are of words with more topics than threads."""
+    small, large = (2001, 1100) if opts else (45_001, 40)
+    counts = np.r_[np.resize([1, 2, 3, 1, 5, 90], small), np.resize([2600, 300, 4200], large), 14_000]
+    doc_ptr, words = corpus_of_word_counts(counts, counts.size // 10, K)
+    pk, V, alpha = saber(), counts.size, 50.0 / K
+    g = pk.Saber(doc_ptr, words, V, K, alpha, 0.01, 11, **opts)
+    p = pk.Saber(doc_ptr, words, V, K, alpha, 0.01, 11, n_chunks=60)
+    for _ in range(2):
+        g.iterate(1)
+        p.iterate(1)
+        assert np.array_equal(g.get_z(), p.get_z())
+    assert g.get_stats()["tiles"] > 32_768
+    g.close()
+    p.close()
