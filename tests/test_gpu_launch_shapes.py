@@ -299,3 +299,24 @@ def test_workgroups_that_work_on_several_light_words(K, opts):
     assert g.get_stats()["tiles"] > 32_768
     g.close()
     p.close()
+
+
+@pytest.mark.parametrize("K", [20_011, 70_000])
+def test_rows_of_many_blocks(K):
+    """Rows of A of one block of 256 entries to 67, on both sides of two, three, four and 64: the draw's block is found from the
+    sums through the blocks, from the 65th on by going through them."""
+    lens = np.r_[255, 256, 257, 511, 512, 513, 767, 768, 769, 1024, 1025, 1281, 16_383, 16_384, 16_385, 17_000]
+    doc_ptr = np.r_[0, np.cumsum(np.r_[lens, lens])].astype(np.int64)
+    rng = np.random.default_rng(K)
+    V, T = 300, int(doc_ptr[-1])
+    words = rng.integers(0, V, T).astype(np.int32)
+    # as many topics as tokens in the first half's documents, most mass on a document's last topics in the other's
+    z = np.concatenate([rng.permutation(K)[:n] if i < lens.size else np.minimum(rng.integers(K - 700, K, n), np.arange(n) % K)
+                        for i, n in enumerate(np.r_[lens, lens])]).astype(np.int32)
+    g = saber().Saber(doc_ptr, words, V, K, 50.0 / K, 0.01, 3)
+    o = oracle.Model(doc_ptr, words, V, K, 50.0 / K, 0.01, 3)
+    g.set_z(z, 1)
+    o.set_z(z, it=1)
+    assert_estep_parity(g, o)
+    g.close()
+    o.close()
