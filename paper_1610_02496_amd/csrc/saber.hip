@@ -378,11 +378,12 @@ static int estep_waves_per_cu(const saber_ctx *c, int block) {
 // tile per workgroup, 1.70, 1.67 and 1.72 with 4, 12 and 64; T = 36 M, K = 5,000 2.49, 2.40 with 4, 2.43 with 8 and 2.59 with
 // 64; T = 100 M, K = 10,000 7.44, 7.28, 7.35 with 12 and 7.99 with 64.  What many per workgroup lose is the tail of
 // the launch: every place on the chip gets 16 workgroups in turn or more, and 8 tiles are the most.  With
-// one wavefront per workgroup and rows of 4 KB (T = 10 M, K = 1,000) no number of tiles changes anything.  The log-likelihood
-// pass has no registers for it, and gained nothing.
+// rows of 4 and 8 KB (T = 10 M, K = 1,000; T = 20 M, K = 2,000) no number of tiles changes anything, so rows of 16 KB are the least.
+// The log-likelihood pass has no registers for it, and gained nothing.
 constexpr int64_t kWalkTiles = 8, kWalkRounds = 16, kCus = 256;
+constexpr size_t kWalkRow = 16 * 1024;
 static int32_t walkers_for(const saber_ctx *c, int mode, int64_t n, int block) {
-    if (!c->staged || !c->z16 || mode != MODE_SAMPLE || n <= 0) return (int32_t)n;
+    if (!c->staged || !c->z16 || mode != MODE_SAMPLE || n <= 0 || estep_row_bytes(c) < kWalkRow) return (int32_t)n;
     const int64_t places = kCus * estep_waves_per_cu(c, block) / (block / 64);
     const int64_t tiles = std::max<int64_t>(1, std::min(kWalkTiles, n / (kWalkRounds * places)));
     return (int32_t)((n + tiles - 1) / tiles);
