@@ -15,6 +15,8 @@
 #include <cstring>
 #include <memory>
 #include <new>
+#include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -554,6 +556,32 @@ static void order_tiles_by_range(Tile *tiles, int64_t n) {
     std::copy(out.begin(), out.end(), tiles);
 }
 
+// Tiles of dense-row words first, then those of light words; inside each group heavy tiles first, so the tail of a launch is made
+// of small ones (Sec. 3.4), and equal ones in the order they have.  Returns the number of the first kind.  (Counted into place: by
+// comparisons 30,000 tiles took 0.9 ms.)
+constexpr int32_t kTileBins = 1 << 16;
+static int64_t sort_tiles(std::vector<Tile> &tiles, size_t first, const std::vector<int32_t> &word_row) {
+    const size_t n = tiles.size() - first;
+    int32_t most = 0;
+    int64_t n_dense = 0;
+    for (size_t i = first; i < tiles.size(); i++) { most = std::max(most, tiles[i].count); n_dense += word_row[(size_t)tiles[i].word] >= 0; }
+    if (most >= kTileBins) {   // (larger tiles than the default's are the caller's)
+        std::stable_sort(tiles.begin() + (ptrdiff_t)first, tiles.end(), [&](const Tile &a, const Tile &b) {
+            const bool la = word_row[(size_t)a.word] < 0, lb = word_row[(size_t)b.word] < 0;
+            return la != lb ? lb : a.count > b.count;
+        });
+        return n_dense;
+    }
+    auto bin = [&](const Tile &t) { return (size_t)(most - t.count) + (word_row[(size_t)t.word] < 0 ? (size_t)most + 1 : 0); };
+    std::vector<size_t> at(2 * (size_t)most + 3, 0);
+    for (size_t i = first; i < tiles.size(); i++) at[bin(tiles[i]) + 1]++;
+    for (size_t b = 1; b < at.size(); b++) at[b] += at[b - 1];
+    std::vector<Tile> sorted(n);
+    for (size_t i = first; i < tiles.size(); i++) sorted[at[bin(tiles[i])]++] = tiles[i];
+    std::copy(sorted.begin(), sorted.end(), tiles.begin() + (ptrdiff_t)first);
+    return n_dense;
+}
+
 // Segmented count of up to two groupings of the assignments: documents over z (CountByDZ -> rows of A) and light words
 // over z_wm (CountByVZ -> sparse rows of B).  Two launches: short segments with one wavefront each, long ones
 // with 256 threads.
@@ -952,14 +980,33 @@ static int full_mstep(saber_ctx *c, const int32_t *user_z = nullptr) {
 // ------------------------------------------------------------------------------------------------
 // saber_init
 // ------------------------------------------------------------------------------------------------
-static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) {
+// What lay_out() makes on the host and upload() takes to the device.
+struct Layout {
+    std::vector<int32_t> row_word, light_words, light_short, light_long, short_docs, long_docs;
+    std::vector<int64_t> light_tok_ptr = std::vector<int64_t>(1, 0);
+    std::vector<uint2> wrec, docrec;
+    std::vector<VzItem> vz_items;
+    std::vector<PhiRow> phi_rows;
+    // the word-major token arrays: ordinary host memory on the way to the device, or with host streaming the pinned array that
+    // stays (tok_doc is then derived on the device)
+    std::vector<int32_t> v_tok_doc; std::vector<uint32_t> v_tok_t;
+    int32_t *tok_doc = nullptr; uint32_t *tok_t = nullptr;
+    std::vector<Tile> tiles;
+    std::vector<uint32_t> doc_words;
+};
+
+// (For a context on a trained model no call of the runtime is made: another thread may do it.)
+static int lay_out(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids, Layout &lay) {
     const int64_t D = c->D, T = c->T; const int32_t V = c->V, K = c->K;
-    if (c->hooks.have_stream) { c->stream = c->hooks.stream; c->own_stream = false; }
-    else { HIP_TRY(hipStreamCreate(&c->stream)); c->own_stream = true; }
-    if (c->opt.profile) {
-        for (auto &e : c->ev) HIP_TRY(hipEventCreate(&e));
-        c->have_events = true;
-    }
+    auto &h_row_word = lay.row_word, &h_light_words = lay.light_words, &h_light_short = lay.light_short, &h_light_long = lay.light_long;
+    auto &h_light_tok_ptr = lay.light_tok_ptr;
+    auto &h_wrec = lay.wrec;
+    auto &h_vz_items = lay.vz_items; auto &h_phi_rows = lay.phi_rows;
+    int32_t *&h_tok_doc = lay.tok_doc; uint32_t *&h_tok_t = lay.tok_t;
+    auto &v_tok_doc = lay.v_tok_doc; auto &v_tok_t = lay.v_tok_t;
+    auto &h_tiles = lay.tiles;
+    auto &h_rec = lay.docrec; auto &h_short = lay.short_docs, &h_long = lay.long_docs;
+    auto &h_doc_words = lay.doc_words;
     // ---- chunks: contiguous document ranges of about equal token count (Sec. 3.1.2) ----
     // A chunk also ends before its rows of A (128-byte aligned slots of capacity min(L_d, K)) would pass 4 GB: the
     // sampling kernel addresses them by 32-bit byte offsets.  That only happens with far fewer chunks than the default.
@@ -986,21 +1033,22 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     // A word with n tokens has at most n non-zero counts; below light_word_tokens tokens its sparse row
     // (8 bytes per non-zero, rebuilt by a segmented count like a row of A) is cheaper than 12*K bytes of dense B / Bhat
     // traffic per iteration.  Needs the LDS-staged sampler and 16-bit assignments.
-    std::vector<int64_t> n_v((size_t)V, 0);
-    for (int64_t t = 0; t < T; t++) n_v[(size_t)word_ids[t]]++;
     const bool light_ok = (c->staged ? c->z16 : c->overlay) && c->opt.light_word_tokens > 0;
     const saber_ctx *par = c->parent;   // then the model's word classes are taken over
     c->joined = light_ok && c->z16 && !par && c->n_slots == 0 && c->opt.ablation == 0 && K <= kJoinedTopics && D + V <= kJoinedSegments && T <= kJoinedTokens;
     // (as many counts as a packed entry of a sparse row has bits for)
     c->opt.light_word_tokens = std::min(c->opt.light_word_tokens, 1 << std::min(16u, 32 - c->topic_bits));
-    c->h_word_row.assign((size_t)V, 0);
-    std::vector<int32_t> h_row_word, h_light_words, h_light_short, h_light_long;
-    std::vector<int64_t> h_light_tok_ptr(1, 0);
-    std::vector<uint2> h_wrec;
-    {
+    std::vector<int64_t> n_v;
+    if (par) {
+        c->h_word_row = par->h_word_row;
+        c->V_dense = par->V_dense; c->V_light = par->V_light;
+    } else {
+        n_v.assign((size_t)V, 0);
+        for (int64_t t = 0; t < T; t++) n_v[(size_t)word_ids[t]]++;
+        c->h_word_row.assign((size_t)V, 0);
         int64_t lunits = 0;
         for (int32_t v = 0; v < V; v++) {
-            if (par ? par->h_word_row[(size_t)v] < 0 : (light_ok && n_v[(size_t)v] < c->opt.light_word_tokens)) {
+            if (light_ok && n_v[(size_t)v] < c->opt.light_word_tokens) {
                 const int32_t li = (int32_t)h_light_words.size();
                 c->h_word_row[(size_t)v] = -li - 1;
                 h_light_words.push_back(v);
@@ -1056,14 +1104,14 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     // ---- word-major token arrays and tiles per chunk (host counting sort; layout only) ----
     // position of every word's segment in the word-major order (light words first, then dense rows) and the
     // slabs CountByVZ cuts the dense rows' segments into
-    std::vector<int64_t> wm_ptr((size_t)V, 0), wm_seen((size_t)V, 0);   // wm_seen: tokens placed so far (chunk by chunk)
-    std::vector<VzItem> h_vz_items;
-    std::vector<PhiRow> h_phi_rows;
+    // (on a trained model nobody reads the word-major assignments: they lie as the tokens do)
+    std::vector<int64_t> wm_ptr, wm_seen;   // wm_seen: tokens placed so far (chunk by chunk)
     // phi_tree_kernel counts a row itself up to 32 tokens per thread of its workgroup; longer rows are cut into slabs for
     // count_slabs_kernel (phi group of T = 2.3 M, K = 777, 256 threads: 43 us with 8,192 tokens, 49 with 32,768; of T = 100 M,
     // K = 10,000, 1,024 threads: 343 us counting none, 323 with 8,192, 303 with 32,768, 298 with 131,072)
     const int64_t own_tokens = 32 * phi_block_threads(c);
-    {
+    if (!par) {
+        wm_ptr.assign((size_t)V, 0); wm_seen.assign((size_t)V, 0);
         for (int32_t li = 0; li < c->V_light; li++) wm_ptr[(size_t)h_light_words[(size_t)li]] = h_light_tok_ptr[(size_t)li];
         int64_t pos = c->T_light;
         const int64_t slab = c->joined ? joined_share(c) : 131072;
@@ -1080,10 +1128,6 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
                            return h_phi_rows[(size_t)it.row].count < 0; }) - h_vz_items.begin();
         c->n_vz_items = (int64_t)h_vz_items.size();
     }
-    // the word-major token arrays: ordinary host memory on the way to the device, or with host streaming the
-    // pinned arrays that stay
-    std::vector<int32_t> v_tok_doc; std::vector<uint32_t> v_tok_t;
-    int32_t *h_tok_doc; uint32_t *h_tok_t;
     if (c->n_slots) {
         const size_t n = (size_t)std::max<int64_t>(T, 1);
         HIP_TRY(hipHostMalloc((void **)&c->h_tok_t, n * sizeof(uint32_t), hipHostMallocDefault));
@@ -1092,7 +1136,6 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         v_tok_doc.resize((size_t)std::max<int64_t>(T, 1)); v_tok_t.resize((size_t)std::max<int64_t>(T, 1));
         h_tok_doc = v_tok_doc.data(); h_tok_t = v_tok_t.data();
     }
-    std::vector<Tile> h_tiles;
     std::vector<int64_t> wcount((size_t)V + 1);
     const int tile_tokens = c->opt.tile_tokens;
     for (Chunk &ch : c->chunks) {
@@ -1127,21 +1170,15 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
                 const int64_t end = split ? std::lower_bound(seg + s, seg + e, range_end[(size_t)r]) - seg : e;
                 while (s < end) {
                     const int32_t cnt = (int32_t)std::min<int64_t>(tile_tokens, end - s);
-                    h_tiles.push_back(Tile{v, (int32_t)s, cnt, row >= 0 ? row : -row - 1, wm_ptr[(size_t)v] + wm_seen[(size_t)v], split ? r + 1 : 0});
-                    wm_seen[(size_t)v] += cnt;
+                    h_tiles.push_back(Tile{v, (int32_t)s, cnt, row >= 0 ? row : -row - 1, par ? ch.t0 + s : wm_ptr[(size_t)v] + wm_seen[(size_t)v], split ? r + 1 : 0});
+                    if (!par) wm_seen[(size_t)v] += cnt;
                     s += cnt;
                 }
             }
         }
         // tiles of dense-row words first, then those of light words; inside each group heavy tiles first so the
         // tail of a launch is made of small ones (Sec. 3.4)
-        const std::vector<int32_t> &wr = c->h_word_row;
-        std::stable_sort(h_tiles.begin() + (ptrdiff_t)first_tile, h_tiles.end(), [&wr](const Tile &a, const Tile &b) {
-            const bool la = wr[(size_t)a.word] < 0, lb = wr[(size_t)b.word] < 0;
-            return la != lb ? lb : a.count > b.count;
-        });
-        int64_t n_dense = 0;
-        while (first_tile + (size_t)n_dense < h_tiles.size() && wr[(size_t)h_tiles[first_tile + (size_t)n_dense].word] >= 0) n_dense++;
+        const int64_t n_dense = sort_tiles(h_tiles, first_tile, c->h_word_row);
         if (n_ranges > 1) order_tiles_by_range(h_tiles.data() + first_tile, n_dense);
         ch.tile0 = (int64_t)first_tile; ch.ntiles = (int64_t)(h_tiles.size() - first_tile);
         tile_classes(c, ch, h_tiles.data() + first_tile, n_dense);
@@ -1149,10 +1186,9 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     }
     c->total_tiles = (int64_t)h_tiles.size();
     // ---- rows of A: fixed, 128-byte aligned slots of capacity min(L_d, K) (Sec. 3.4 aligns rows likewise) ----
-    std::vector<uint2> h_rec((size_t)std::max<int64_t>(D, 1));
-    std::vector<int32_t> h_short, h_long;
-    std::vector<uint32_t> h_doc_words((size_t)std::max<int64_t>(D, 1));
-    {   // distinct words per document (layout statistic for the bandwidth model)
+    h_rec.resize((size_t)std::max<int64_t>(D, 1));
+    if (!par) {   // distinct words per document (layout statistic for the bandwidth model)
+        h_doc_words.resize((size_t)std::max<int64_t>(D, 1));
         std::vector<int32_t> last_doc((size_t)V, -1);
         for (int64_t d = 0; d < D; d++) {
             uint32_t u = 0;
@@ -1185,7 +1221,28 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         c->slot_tokens = std::max(c->slot_tokens, ch.ntok);
     }
 
-    // ---- device memory ----
+    return SABER_OK;
+}
+
+static int upload(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids, const Layout &lay) {
+    const int64_t D = c->D, T = c->T; const int32_t V = c->V, K = c->K;
+    const saber_ctx *par = c->parent;
+    const auto &h_row_word = lay.row_word, &h_light_words = lay.light_words, &h_light_short = lay.light_short, &h_light_long = lay.light_long;
+    const auto &h_light_tok_ptr = lay.light_tok_ptr;
+    const auto &h_wrec = lay.wrec;
+    const auto &h_vz_items = lay.vz_items; const auto &h_phi_rows = lay.phi_rows;
+    const int32_t *h_tok_doc = lay.tok_doc; const uint32_t *h_tok_t = lay.tok_t;
+    const auto &h_tiles = lay.tiles;
+    const auto &h_rec = lay.docrec; const auto &h_short = lay.short_docs, &h_long = lay.long_docs;
+    const auto &h_doc_words = lay.doc_words;
+    if (c->hooks.have_stream) { c->stream = c->hooks.stream; c->own_stream = false; }
+    else { HIP_TRY(hipStreamCreate(&c->stream)); c->own_stream = true; }
+    if (c->opt.profile) {
+        for (auto &e : c->ev) HIP_TRY(hipEventCreate(&e));
+        c->have_events = true;
+    }
+    // ---- device memory (what a context without assignments of its own never reads stays out) ----
+    const bool state = !c->no_state;
     const size_t vk = ((size_t)c->V_dense + 1) * (size_t)c->Kpad;
     if (c->n_slots) {
         HIP_TRY(hipStreamCreateWithFlags(&c->s_in, hipStreamNonBlocking));
@@ -1214,12 +1271,16 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
             if (!ne.empty()) HIP_TRY(hipMemcpy(c->ne_doc, ne.data(), sizeof(int32_t) * ne.size(), hipMemcpyHostToDevice));
         }
     } else {
-        if (c->z16) SABER_TRY(dev_alloc(c->hooks, (uint16_t **)&c->z, (size_t)T)); else SABER_TRY(dev_alloc(c->hooks, (int32_t **)&c->z, (size_t)T));
+        if (state) {
+            if (c->z16) SABER_TRY(dev_alloc(c->hooks, (uint16_t **)&c->z, (size_t)T)); else SABER_TRY(dev_alloc(c->hooks, (int32_t **)&c->z, (size_t)T));
+        }
         SABER_TRY(dev_alloc(c->hooks, &c->tok_doc, (size_t)T)); SABER_TRY(dev_alloc(c->hooks, &c->tok_t, (size_t)T));
     }
-    SABER_TRY(dev_alloc(c->hooks, &c->tiles, h_tiles.size())); SABER_TRY(dev_alloc(c->hooks, &c->docrec, (size_t)D));
-    SABER_TRY(dev_alloc(c->hooks, &c->cd_ent, (size_t)c->cd_cap)); SABER_TRY(dev_alloc(c->hooks, &c->doc_ptr, (size_t)D + 1));
-    SABER_TRY(dev_alloc(c->hooks, &c->short_docs, h_short.size())); SABER_TRY(dev_alloc(c->hooks, &c->long_docs, h_long.size()));
+    SABER_TRY(dev_alloc(c->hooks, &c->tiles, h_tiles.size())); SABER_TRY(dev_alloc(c->hooks, &c->doc_ptr, (size_t)D + 1));
+    if (state) {
+        SABER_TRY(dev_alloc(c->hooks, &c->docrec, (size_t)D)); SABER_TRY(dev_alloc(c->hooks, &c->cd_ent, (size_t)c->cd_cap));
+        SABER_TRY(dev_alloc(c->hooks, &c->short_docs, h_short.size())); SABER_TRY(dev_alloc(c->hooks, &c->long_docs, h_long.size()));
+    }
     if (par) {
         // borrowed from the model: everything the sampler reads about words
         c->phi = par->phi; c->l3 = par->l3; c->l3_64 = par->l3_64; c->sumphi = par->sumphi;
@@ -1232,7 +1293,9 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
     SABER_TRY(dev_alloc(c->hooks, &c->light_tok_ptr, h_light_tok_ptr.size())); SABER_TRY(dev_alloc(c->hooks, &c->wrec, h_wrec.size()));
     SABER_TRY(dev_alloc(c->hooks, &c->lw_ent, (size_t)c->lw_cap)); SABER_TRY(dev_alloc(c->hooks, &c->lw_phi, (size_t)c->lw_cap));
     }
-    if (c->z16) SABER_TRY(dev_alloc(c->hooks, (uint16_t **)&c->z_wm, (size_t)T)); else SABER_TRY(dev_alloc(c->hooks, (int32_t **)&c->z_wm, (size_t)T));
+    if (state) {
+        if (c->z16) SABER_TRY(dev_alloc(c->hooks, (uint16_t **)&c->z_wm, (size_t)T)); else SABER_TRY(dev_alloc(c->hooks, (int32_t **)&c->z_wm, (size_t)T));
+    }
     if (!par) {
     SABER_TRY(dev_alloc(c->hooks, &c->vz_items, h_vz_items.size())); SABER_TRY(dev_alloc(c->hooks, &c->phi_rows, h_phi_rows.size()));
     HIP_TRY(hipMemcpy(c->phi_rows, h_phi_rows.data(), sizeof(PhiRow) * h_phi_rows.size(), hipMemcpyHostToDevice));
@@ -1247,7 +1310,7 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         if (!h_light_short.empty()) HIP_TRY(hipMemcpy(c->light_short, h_light_short.data(), sizeof(int32_t) * h_light_short.size(), hipMemcpyHostToDevice));
         if (!h_light_long.empty()) HIP_TRY(hipMemcpy(c->light_long, h_light_long.data(), sizeof(int32_t) * h_light_long.size(), hipMemcpyHostToDevice));
     }
-    SABER_TRY(dev_alloc(c->hooks, &c->doc_words, (size_t)D));
+    if (!par) SABER_TRY(dev_alloc(c->hooks, &c->doc_words, (size_t)D));
     if (c->opt.ablation & 1) {
         SABER_TRY(dev_alloc(c->hooks, &c->word_ids_d, (size_t)T)); SABER_TRY(dev_alloc(c->hooks, &c->word_row_d, (size_t)V));
         if (T) HIP_TRY(hipMemcpy(c->word_ids_d, word_ids, sizeof(int32_t) * (size_t)T, hipMemcpyHostToDevice));
@@ -1267,19 +1330,19 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
         SABER_TRY(hook_alloc(c->hooks, &c->sort_tmp, c->sort_tmp_bytes));
     }
     if (!par) { SABER_TRY(dev_alloc(c->hooks, &c->l3, ((size_t)V + 1) * (size_t)c->n3pad)); SABER_TRY(dev_alloc(c->hooks, &c->sumphi, (size_t)V + 1)); }
-    SABER_TRY(dev_alloc(c->hooks, &c->counters, (size_t)kMaxTimedIters * kCtr));
-    SABER_TRY(dev_alloc(c->hooks, &c->dense_slots, (size_t)kMaxTimedIters * kDenseSlots));
-    SABER_TRY(dev_alloc(c->hooks, &c->ll_partial, (size_t)std::max<int64_t>(c->max_chunk_tiles, 1) + kLlTail));
+    if (!par) SABER_TRY(dev_alloc(c->hooks, &c->counters, (size_t)kMaxTimedIters * kCtr));
+    if (state) SABER_TRY(dev_alloc(c->hooks, &c->dense_slots, (size_t)(par ? 1 : kMaxTimedIters) * kDenseSlots));
+    if (!par || !state) SABER_TRY(dev_alloc(c->hooks, &c->ll_partial, (size_t)std::max<int64_t>(c->max_chunk_tiles, 1) + kLlTail));
     if (T && !c->n_slots) {
         HIP_TRY(hipMemcpy(c->tok_doc, h_tok_doc, sizeof(int32_t) * (size_t)T, hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(c->tok_t, h_tok_t, sizeof(uint32_t) * (size_t)T, hipMemcpyHostToDevice));
     }
     if (!h_tiles.empty()) HIP_TRY(hipMemcpy(c->tiles, h_tiles.data(), sizeof(Tile) * h_tiles.size(), hipMemcpyHostToDevice));
-    if (D) HIP_TRY(hipMemcpy(c->docrec, h_rec.data(), sizeof(uint2) * (size_t)D, hipMemcpyHostToDevice));
-    if (D) HIP_TRY(hipMemcpy(c->doc_words, h_doc_words.data(), sizeof(uint32_t) * (size_t)D, hipMemcpyHostToDevice));
+    if (D && state) HIP_TRY(hipMemcpy(c->docrec, h_rec.data(), sizeof(uint2) * (size_t)D, hipMemcpyHostToDevice));
+    if (D && !par) HIP_TRY(hipMemcpy(c->doc_words, h_doc_words.data(), sizeof(uint32_t) * (size_t)D, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->doc_ptr, doc_ptr, sizeof(int64_t) * ((size_t)D + 1), hipMemcpyHostToDevice));
-    if (!h_short.empty()) HIP_TRY(hipMemcpy(c->short_docs, h_short.data(), sizeof(int32_t) * h_short.size(), hipMemcpyHostToDevice));
-    if (!h_long.empty()) HIP_TRY(hipMemcpy(c->long_docs, h_long.data(), sizeof(int32_t) * h_long.size(), hipMemcpyHostToDevice));
+    if (state && !h_short.empty()) HIP_TRY(hipMemcpy(c->short_docs, h_short.data(), sizeof(int32_t) * h_short.size(), hipMemcpyHostToDevice));
+    if (state && !h_long.empty()) HIP_TRY(hipMemcpy(c->long_docs, h_long.data(), sizeof(int32_t) * h_long.size(), hipMemcpyHostToDevice));
     c->stats.tokens = T; c->stats.tiles = c->total_tiles; c->stats.chunks = (int64_t)c->chunks.size();
     if (c->no_state) { HIP_TRY(hipStreamSynchronize(c->stream)); return SABER_OK; }
 
@@ -1295,8 +1358,8 @@ static int build(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) 
 
 static int static_scratch_init(int device);
 
-// saber_init_ex, or with `parent` a context for held-out documents that borrows the parent's model
-static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word_ids, int64_t D, int32_t V,
+// Checks and sizes of saber_init_ex, or with `parent` of a context for held-out documents that borrows the parent's model.
+static int make_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word_ids, int64_t D, int32_t V,
                       int32_t K, float alpha, float beta, uint64_t seed, const saber_options *opt_in,
                       const saber_ctx *parent, bool no_state) {
     if (out) *out = nullptr;
@@ -1315,7 +1378,9 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
     const int64_t T = doc_ptr[D];
     if (T >= (1ll << 40)) return fail(SABER_ERANGE, "saber_init: T = %lld tokens exceeds 2^40", (long long)T);
     if (T > 0 && !word_ids) return fail(SABER_EINVAL, "saber_init: word_ids is null");
-    for (int64_t t = 0; t < T; t++)
+    bool outside = false;   // (no way out of the loop: eight words at a time)
+    for (int64_t t = 0; t < T; t++) outside |= (uint32_t)word_ids[t] >= (uint32_t)V;
+    for (int64_t t = 0; outside && t < T; t++)
         if (word_ids[t] < 0 || word_ids[t] >= V)
             return fail(SABER_EINVAL, "saber_init: word id %d at token %lld is outside [0,%d)", word_ids[t], (long long)t, V);
     uint32_t bits = 1; while ((1u << bits) < (uint32_t)K) bits++;
@@ -1414,18 +1479,27 @@ static int create_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *wo
     if (c->opt.light_block_threads <= 0) c->opt.light_block_threads = c->opt.block_threads;
     if (c->opt.tile_tokens <= 0) c->opt.tile_tokens = auto_tile_tokens(c, per_chunk);
     c->vbeta = (float)V * beta;
-    int rc;
-    if ((rc = check_estep_lds_layout()) != SABER_OK) { delete c; return rc; }
-    try { rc = build(c, doc_ptr, word_ids); }
-    catch (const std::bad_alloc &) { rc = fail(SABER_ENOMEM, "saber_init: out of host memory"); }
-    if (rc != SABER_OK) { saber_free(c); return rc; }
+    const int rc = check_estep_lds_layout();
+    if (rc != SABER_OK) { delete c; return rc; }
     *out = c;
     return SABER_OK;
 }
 
 extern "C" int saber_init_ex(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word_ids, int64_t D, int32_t V,
                              int32_t K, float alpha, float beta, uint64_t seed, const saber_options *opt_in) {
-    return create_ctx(out, doc_ptr, word_ids, D, V, K, alpha, beta, seed, opt_in, nullptr, false);
+    if (!out) return fail(SABER_EINVAL, "saber_init: null argument");
+    saber_ctx *c = nullptr;
+    *out = nullptr;
+    int rc = make_ctx(&c, doc_ptr, word_ids, D, V, K, alpha, beta, seed, opt_in, nullptr, false);
+    if (rc != SABER_OK) return rc;
+    try {
+        Layout lay;
+        rc = lay_out(c, doc_ptr, word_ids, lay);
+        if (rc == SABER_OK) rc = upload(c, doc_ptr, word_ids, lay);
+    } catch (const std::bad_alloc &) { rc = fail(SABER_ENOMEM, "saber_init: out of host memory"); }
+    if (rc != SABER_OK) { saber_free(c); return rc; }
+    *out = c;
+    return SABER_OK;
 }
 
 extern "C" int saber_init(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word_ids, int64_t D, int32_t V,
@@ -1867,6 +1941,32 @@ static int foldin_iterate(saber_ctx *c, int32_t n) {
     return SABER_OK;
 }
 
+// lay_out() of a context on a trained model by another thread where that pays (1.5 ms for the 550,000 scored tokens of 3,300
+// documents, which the observed ones' layout and fold-in hide; a thread costs 0.03)
+struct BackgroundLayout {
+    Layout lay;
+    std::thread thread;
+    int rc = SABER_OK;
+    std::string error;
+    void start(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) {
+        auto work = [this, c, doc_ptr, word_ids] {
+            try {
+                rc = lay_out(c, doc_ptr, word_ids, lay);
+                if (rc != SABER_OK) error = g_err;
+            } catch (const std::bad_alloc &) { rc = SABER_ENOMEM; }
+        };
+        if (c->T >= 32768) {
+            try { thread = std::thread(work); return; } catch (const std::system_error &) {}   // no thread to be had
+        }
+        work();
+    }
+    int finish() {
+        if (thread.joinable()) thread.join();
+        return rc == SABER_OK ? rc : fail(rc, "%s", rc == SABER_ENOMEM && error.empty() ? "saber_holdout_loglik: out of host memory" : error.c_str());
+    }
+    ~BackgroundLayout() { if (thread.joinable()) thread.join(); }
+};
+
 extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const int32_t *word_ids,
                                     const uint8_t *observed, int64_t D, int32_t n_foldin, uint64_t seed,
                                     const int32_t *z_init, int32_t *z_out, double *loglik, int64_t *n_scored) {
@@ -1881,18 +1981,33 @@ extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const 
     saber_ctx *obs = nullptr, *scr = nullptr;
     int rc = SABER_OK;
     try {
-        // the observed part and the scored part as two corpora over the same documents
+        // the observed part and the scored part as two corpora over the same documents (every word is written to both and one
+        // of the two positions moves on: which one cannot be foretold)
         std::vector<int64_t> optr((size_t)D + 1, 0), sptr((size_t)D + 1, 0);
-        std::vector<int32_t> ow, sw;
-        ow.reserve((size_t)T / 2 + 1); sw.reserve((size_t)T / 2 + 1);
         for (int64_t d = 0; d < D; d++) {
-            for (int64_t t = doc_ptr[d]; t < doc_ptr[d + 1]; t++) (observed[t] ? ow : sw).push_back(word_ids[t]);
-            optr[(size_t)d + 1] = (int64_t)ow.size(); sptr[(size_t)d + 1] = (int64_t)sw.size();
+            int64_t n = 0;
+            for (int64_t t = doc_ptr[d]; t < doc_ptr[d + 1]; t++) n += observed[t] != 0;
+            optr[(size_t)d + 1] = optr[(size_t)d] + n; sptr[(size_t)d + 1] = doc_ptr[d + 1] - optr[(size_t)d + 1];
+        }
+        std::vector<int32_t> ow((size_t)optr[(size_t)D] + 1), sw((size_t)sptr[(size_t)D] + 1);
+        int32_t *po = ow.data(), *ps = sw.data();
+        for (int64_t t = 0; t < T; t++) {
+            const bool o = observed[t] != 0;
+            *po = *ps = word_ids[t];
+            po += o; ps += !o;
         }
         saber_options opt = m->opt;
         opt.profile = 0; opt.n_chunks = 1; opt.tile_tokens = m->tile_tokens_asked;   // (0: sized for these documents)
         if (m->auto_light_block) opt.block_threads = opt.light_block_threads = 0;
-        rc = create_ctx(&obs, optr.data(), ow.data(), D, m->V, m->K, m->alpha, m->beta, seed, &opt, m, false);
+        rc = make_ctx(&obs, optr.data(), ow.data(), D, m->V, m->K, m->alpha, m->beta, seed, &opt, m, false);
+        if (rc == SABER_OK) rc = make_ctx(&scr, sptr.data(), sw.data(), D, m->V, m->K, m->alpha, m->beta, seed, &opt, m, true);
+        Layout obs_lay;
+        BackgroundLayout scr_lay;
+        if (rc == SABER_OK) {
+            scr_lay.start(scr, sptr.data(), sw.data());
+            rc = lay_out(obs, optr.data(), ow.data(), obs_lay);
+        }
+        if (rc == SABER_OK) rc = upload(obs, optr.data(), ow.data(), obs_lay);
         if (rc == SABER_OK && z_init) rc = saber_set_z(obs, z_init, 0);
         if (rc == SABER_OK) rc = foldin_iterate(obs, n_foldin);
         if (rc == SABER_OK && z_out) {
@@ -1902,7 +2017,8 @@ extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const 
             rc = saber_get_z(obs, z_out);
             if (borrow) std::swap(obs->staging, m->staging);
         }
-        if (rc == SABER_OK) rc = create_ctx(&scr, sptr.data(), sw.data(), D, m->V, m->K, m->alpha, m->beta, seed, &opt, m, true);
+        if (rc == SABER_OK) rc = scr_lay.finish();
+        if (rc == SABER_OK) rc = upload(scr, sptr.data(), sw.data(), scr_lay.lay);
         double ll = 0.0;
         if (rc == SABER_OK && scr->T > 0) {
             // theta comes from the observed part: its rows of A, and its document lengths in the normaliser

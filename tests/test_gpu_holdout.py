@@ -122,3 +122,22 @@ def test_holdout_leaves_the_model_alone_and_edge_cases():
     with pytest.raises(pk.SaberError):
         g.holdout_loglik(dp, w, m, 0, 1, z_init=np.array([200], dtype=np.int32))      # topic outside [0, K)
     g.close(); twin.close(); o.close()
+
+
+@pytest.mark.parametrize("tile_tokens", [0, 64, 1 << 16])
+def test_held_out_layouts_of_any_size(tile_tokens):
+    """Scored documents laid out beside the observed ones' work (from 32,768 scored tokens on) or before it; masks of no
+    pattern, documents and halves without tokens; tiles sorted by counting (below 65,536 tokens) and by comparing."""
+    c, g, o = trained_pair(100, tile_tokens=tile_tokens)
+    V, rng = o.V, np.random.default_rng(3)
+    for scored in (32_767, 32_768, 90_000):
+        T = scored + 40_000
+        mask = np.zeros(T, np.uint8)
+        mask[rng.permutation(T)[:T - scored]] = rng.integers(1, 256, T - scored)   # (any value but 0 is "observed")
+        dp = np.r_[0, 0, np.sort(rng.integers(0, T, 200)), T].astype(np.int64)
+        words = np.minimum(rng.geometric(0.01, T) - 1, V - 1).astype(np.int32)
+        words[:70_000 if scored > 60_000 else 10] = 1
+        ll, n, z = g.holdout_loglik(dp, words, mask, 0, 77)
+        ll_o, n_o, z_o = o.holdout_loglik(dp, words, (mask != 0).astype(np.uint8), 0, 77)
+        assert n == n_o == scored and np.array_equal(z, z_o) and abs(ll - ll_o) <= 1e-6 * abs(ll_o)
+    g.close(); o.close()

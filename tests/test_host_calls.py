@@ -318,3 +318,32 @@ def test_host_memory_that_runs_out_is_a_status(host):
         L, m = binding.load_library(), 1 << 30
         assert L.saber_alias_build_probe(g._h, words.ctypes.data, m, out.ctypes.data, out.ctypes.data, out.ctypes.data, None) == -2
     """)
+
+
+def test_held_out_calls_that_break_off(host):
+    """The scored documents' layout is another thread's work from 32,768 tokens on: whatever fails meanwhile, the call ends with
+    a status and the next one works."""
+    host("""
+        V, K = 50, 100
+        words = np.arange(140_000, dtype=np.int32) % V
+        doc_ptr = np.r_[0, np.arange(999, words.size, 1000), words.size]
+        g = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 3)
+        for n in (1, 2, 3, 65_534, 65_536, 65_538, 140_000):
+            dp = np.minimum(doc_ptr, n)
+            observed = (np.arange(n) % 2).astype(np.uint8)
+            bad = words[:n].copy()
+            for i in (0, n - 1):
+                bad[:] = words[:n]
+                bad[i] = V
+                assert code_of(lambda: g.holdout_loglik(dp, bad, observed, 1, 5)) == -1
+            z = np.full(int(observed.sum()), K, np.int32)
+            assert code_of(lambda: g.holdout_loglik(dp, words[:n], observed, 1, 5, z)) == (-1 if z.size else 0)
+            for call in ("hipMalloc", "hipMemcpy:", "estep_kernel", "hipStreamCreate"):
+                for nth in range(1, 60):
+                    fake.fake_fail(call.encode(), nth)
+                    code = code_of(lambda: g.holdout_loglik(dp, words[:n], observed, 1, 5))
+                    if fake.fake_fail_pending(): break
+                    assert code in (-2, -3), (call, nth, code)
+                fake.fake_fail(b"", 0)
+            assert g.holdout_loglik(dp, words[:n], observed, 1, 5)[1] == n - observed.sum()
+    """)
