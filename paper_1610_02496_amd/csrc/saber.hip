@@ -757,9 +757,10 @@ static int launch_count_slabs(saber_ctx *c, int64_t n_items, bool totals) {
     const int range = hist_range(c);
     // every workgroup ends with up to K atomics into the K totals: no more than about 500 shares of z (128 where these
     // have fewer than 65,536 assignments: T = 10 M, K = 1,000 takes 17 us with 153 of them, 21 with 490), none with
-    // fewer than 16 assignments per topic (but 16,384 at least, and 262,144 are enough at any K) or more than 2^20, keep
-    // those from dominating
-    const int64_t least = std::max<int64_t>(16384, std::min<int64_t>(16 * (int64_t)c->K, 262144));
+    // fewer than 16 assignments per topic (but 16,384 at least, and 131,072 are enough at any K: an iteration at T = 1.5 M,
+    // K = 70,000 0.41 ms with 262,144, 0.39 with 131,072, 0.40 with 65,536 and 0.41 with fewer, at T = 15 M, K = 20,011 1.66, 1.65, 1.66
+    // and 1.66) or more than 2^20, keep those from dominating
+    const int64_t least = std::max<int64_t>(16384, std::min<int64_t>(16 * (int64_t)c->K, 131072));
     const int64_t share = std::max<int64_t>(c->T / 512, std::min<int64_t>(c->T / 128, 65536));
     const int64_t per_block = std::min<int64_t>(1 << 20, std::max<int64_t>(least, ((share + 4095) / 4096) * 4096));
     const int64_t n_tot = totals ? (c->T + per_block - 1) / per_block : 0;
