@@ -386,7 +386,7 @@ __device__ __forceinline__ uint32_t dense_query4_staged(uint32_t phi_bytes, uint
 }
 
 // ---------------------------------------------------------------------------------------------
-// E-step (Alg. 2).  One workgroup per tile; the word's Bhat row and the upper tree level are staged in
+// E-step (Alg. 2).  One workgroup per tile, or where rows are long per few tiles of light words; the word's Bhat row and the upper tree level are staged in
 // LDS (STAGED) or read from global memory.  Each wavefront takes a batch of up to 64 tokens: the
 // per-token scalars (document, row descriptor, Philox draws) are produced one token per lane.  Tokens are
 // ordered by (word, document), so repeated occurrences of a word in a document are neighbours (a "run"): they
@@ -658,7 +658,10 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     float Q = first_lane(p.alpha * sum_w);
     const uint32_t bits = B16 ? 16u : p.topic_bits, tmask = B16 ? 0xffffu : p.topic_mask;
     int count = tile.count;
-    for (;;) {   // the tiles of the workgroup
+    // The tiles of the workgroup.  More than one, and then of light words, is for sampling from staged rows with 16-bit assignments:
+    // bound by the chain from a tile's record to its rows of A, and by staging a row per tile before that (80 KB at K = 20,011:
+    // 2.03 -> 1.67 ms per iteration at T = 15 M).
+    for (;;) {
     asm volatile("" : "+v"(lane));   // (values derived from the lane number are formed per tile, not held over all of them)
     double ll_acc = 0.0;
     // `batch`, and d, t, rec of its tokens, are in hand at the top of every turn: those of the first batch from above,
