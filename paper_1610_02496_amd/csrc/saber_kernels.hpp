@@ -386,7 +386,7 @@ __device__ __forceinline__ uint32_t dense_query4_staged(uint32_t phi_bytes, uint
 }
 
 // ---------------------------------------------------------------------------------------------
-// E-step (Alg. 2).  One workgroup per tile, or where rows are long per few tiles of light words; the word's Bhat row and the upper tree level are staged in
+// E-step (Alg. 2).  One workgroup per tile, or per several tiles of light words where rows are long; the word's Bhat row and the upper tree level are staged in
 // LDS (STAGED) or read from global memory.  Each wavefront takes a batch of up to 64 tokens: the
 // per-token scalars (document, row descriptor, Philox draws) are produced one token per lane.  Tokens are
 // ordered by (word, document), so repeated occurrences of a word in a document are neighbours (a "run"): they
