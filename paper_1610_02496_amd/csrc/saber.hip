@@ -2097,8 +2097,8 @@ extern "C" int saber_get_iteration(saber_ctx *c, uint32_t *iter) {
 }
 
 // Device memory of one inspection call, cut from one block that the context keeps for the next call up to kWorkKept bytes (fresh
-// device memory for every call took 0.9 of 1.8 ms: 100,000 tokens of 5 M, 400 rows of 1,500 topics).  A call that breaks off
-// waits for what it has queued.
+// device memory for every call took 0.9 of 1.8 ms: 100,000 tokens of 5 M, 400 rows of 1,500 topics).  It is memory of the context's
+// device, whichever one the caller has current: later calls use it too.  A call that breaks off waits for what it has queued.
 constexpr size_t kWorkKept = (size_t)64 << 20;
 struct WorkSpace {
     saber_ctx *c;
@@ -2112,6 +2112,7 @@ struct WorkSpace {
     }
     static size_t rounded(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
     int reserve(size_t bytes) {
+        const DeviceScope scope(c->device);
         if (bytes > kWorkKept) { own = true; return hook_alloc(c->hooks, (void **)&base, bytes); }
         if (c->work_bytes < bytes) {
             dev_free(c->hooks, c->work);

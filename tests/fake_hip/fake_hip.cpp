@@ -27,6 +27,7 @@ std::map<const void *, size_t> vars;
 std::map<const void *, void *> var_mem;
 std::vector<Launch> launches;
 std::map<std::string, int64_t> calls;
+int64_t mallocs_on[2] = {};
 std::string fail_name;
 int fail_at = 0, imitate = 0;
 int64_t host_bytes = 0;
@@ -95,7 +96,8 @@ extern "C" {
 void fake_fail(const char *name, int nth) { std::lock_guard<std::mutex> lock(mu); fail_name = name; fail_at = nth; }   // the nth call (launch) whose name contains `name`
 int fake_fail_pending() { std::lock_guard<std::mutex> lock(mu); return fail_at; }
 void fake_imitate(int on) { imitate = on; }
-void fake_clear() { std::lock_guard<std::mutex> lock(mu); launches.clear(); calls.clear(); host_bytes = 0; }
+void fake_clear() { std::lock_guard<std::mutex> lock(mu); launches.clear(); calls.clear(); host_bytes = 0; mallocs_on[0] = mallocs_on[1] = 0; }
+int64_t fake_mallocs_on(int d) { std::lock_guard<std::mutex> lock(mu); return mallocs_on[d]; }   // of device memory, with device d current
 int64_t fake_host_bytes() { return host_bytes; }   // of pinned memory asked for
 int64_t fake_calls(const char *name) { std::lock_guard<std::mutex> lock(mu); return calls[name]; }   // of those that can be made to fail
 int64_t fake_launches(const char *name, uint64_t *most_threads) {   // launches of kernels whose name contains `name`
@@ -156,7 +158,12 @@ int hipGetSymbolAddress(void **p, const void *var) {
     return kOk;
 }
 int hipMemGetInfo(size_t *f, size_t *t) { *f = *t = (size_t)288 << 30; return kOk; }
-int hipMalloc(void **p, size_t n) { if (fails("hipMalloc")) return result(kOutOfMemory); *p = reserve(n); return *p ? kOk : result(kOutOfMemory); }
+int hipMalloc(void **p, size_t n) {
+    if (fails("hipMalloc")) return result(kOutOfMemory);
+    { std::lock_guard<std::mutex> lock(mu); mallocs_on[device]++; }
+    *p = reserve(n);
+    return *p ? kOk : result(kOutOfMemory);
+}
 int hipFree(void *p) { return result(release(p)); }
 int hipHostMalloc(void **p, size_t n, unsigned) { if (fails("hipHostMalloc")) return result(kOutOfMemory); host_bytes += (int64_t)n; *p = reserve(n); return *p ? kOk : result(kOutOfMemory); }
 int hipHostFree(void *p) { return result(release(p)); }

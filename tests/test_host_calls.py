@@ -347,3 +347,23 @@ def test_held_out_calls_that_break_off(host):
                 fake.fake_fail(b"", 0)
             assert g.holdout_loglik(dp, words[:n], observed, 1, 5)[1] == n - observed.sum()
     """)
+
+
+def test_kept_work_space_is_the_contexts_device(host):
+    """Inspection calls keep their work space for later ones: it lies on the context's device, also where the caller has
+    another one current, which stays so."""
+    host("""
+        now = ctypes.c_int()
+        for first in (lambda g: g.token_probs([3]), lambda g: g.get_phi([0]), lambda g: g.token_probs(np.arange(50_000)),
+                      lambda g: g.get_phi(np.zeros(90_000, np.int32))):      # (more than is kept)
+            words = np.zeros(50_000, np.int32)
+            g = pk.Saber(np.r_[0, 500, words.size], words, 1, 100, 0.1, 0.01, 3)
+            fake.fake_clear()
+            assert fake.hipSetDevice(1) == 0
+            first(g)
+            assert (fake.fake_mallocs_on(0), fake.fake_mallocs_on(1)) == (1, 0)
+            fake.hipGetDevice(ctypes.byref(now))
+            assert now.value == 1
+            assert fake.hipSetDevice(0) == 0
+            g.close()
+    """)
