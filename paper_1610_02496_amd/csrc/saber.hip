@@ -1549,7 +1549,7 @@ extern "C" int saber_iterate(saber_ctx *c, int32_t n) {
             const unsigned long long *slots = c->dense_slots + (size_t)kDenseSlots * b;
             if (c->joined) {
                 SABER_TRY(launch_joined_mstep(c, slots, c->counters + kCtr * b, prof ? ev[EV_DZ] : nullptr));
-                if (prof) { HIP_TRY(hipEventRecord(ev[EV_CK], c->stream)); HIP_TRY(hipEventRecord(ev[EV_PHI], c->stream)); }
+                if (prof) HIP_TRY(hipEventRecord(ev[EV_PHI], c->stream));   // (no EV_CK: the totals are counted with the rest)
                 continue;
             }
             if (c->n_slots) SABER_TRY(launch_segmented_count(c, SegLists{}, own_light_segments(c)));
@@ -1578,8 +1578,11 @@ extern "C" int saber_iterate(saber_ctx *c, int32_t n) {
             c->stats.next_light_entries = (int64_t)h[kCtr * b + 4];
             if (prof) {
                 hipEvent_t *ev = c->ev + (size_t)b * EV_PER_ITER;
-                float ms[4], tot;
-                for (int s = 0; s < 4; s++) HIP_TRY(hipEventElapsedTime(&ms[s], ev[s], ev[s + 1]));
+                float ms[4] = {}, tot;
+                for (int s = 0; s < 4; s++) {
+                    if (s == EV_DZ && c->joined) continue;
+                    HIP_TRY(hipEventElapsedTime(&ms[s], ev[s == EV_CK && c->joined ? EV_DZ : s], ev[s + 1]));
+                }
                 HIP_TRY(hipEventElapsedTime(&tot, ev[EV_BEGIN], ev[EV_PHI]));
                 c->stats.ms_sample += ms[0]; c->stats.ms_count_dz += ms[1]; c->stats.ms_ck += ms[2];
                 c->stats.ms_phi += ms[3]; c->stats.ms_total += tot;

@@ -16,7 +16,7 @@
 namespace {
 enum { kOk = 0, kInvalidValue = 1, kOutOfMemory = 2, kInvalidConfiguration = 9, kInvalidDevice = 101, kInvalidHandle = 400 };
 struct Dim { uint32_t x, y, z; };
-struct Object { int device; };
+struct Object { int device; int64_t launches; };   // (an event: launches in front of it)
 struct Launch { std::string name; Dim grid, block; };
 struct Config { Dim grid, block; size_t lds; Object *stream; };
 
@@ -170,18 +170,19 @@ int hipHostFree(void *p) { return result(release(p)); }
 int hipMemcpy(void *d, const void *s, size_t n, int) { if (fails("hipMemcpy:")) return result(kInvalidValue); memcpy(d, s, n); return kOk; }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int, Object *) { if (fails("hipMemcpyAsync")) return result(kInvalidValue); memcpy(d, s, n); return kOk; }
 int hipMemsetAsync(void *d, int v, size_t n, Object *) { memset(d, v, n); return kOk; }
-int hipStreamCreate(Object **s) { *s = new Object{device}; return kOk; }
+int hipStreamCreate(Object **s) { *s = new Object{device, 0}; return kOk; }
 int hipStreamCreateWithFlags(Object **s, unsigned) { return hipStreamCreate(s); }
 int hipStreamDestroy(Object *s) { delete s; return kOk; }
 int hipStreamSynchronize(Object *) { return kOk; }
 int hipStreamWaitEvent(Object *, Object *, unsigned) { return kOk; }
-int hipEventCreate(Object **e) { if (fails("hipEventCreate")) return result(kOutOfMemory); *e = new Object{device}; return kOk; }
+int hipEventCreate(Object **e) { if (fails("hipEventCreate")) return result(kOutOfMemory); *e = new Object{device, 0}; return kOk; }
 int hipEventCreateWithFlags(Object **e, unsigned) { return hipEventCreate(e); }
 int hipEventDestroy(Object *e) { delete e; return kOk; }
 int hipEventRecord(Object *e, Object *s) {   // both have to belong to one device
     if (fails("hipEventRecord")) return result(kInvalidValue);
+    { std::lock_guard<std::mutex> lock(mu); e->launches = (int64_t)launches.size(); }
     return e->device == (s ? s->device : device) ? kOk : result(kInvalidHandle);
 }
 int hipEventSynchronize(Object *) { return kOk; }
-int hipEventElapsedTime(float *ms, Object *, Object *) { *ms = 1.f; return kOk; }
+int hipEventElapsedTime(float *ms, Object *a, Object *b) { *ms = (float)(b->launches - a->launches); return kOk; }   // a launch takes a millisecond
 }

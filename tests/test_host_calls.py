@@ -367,3 +367,19 @@ def test_kept_work_space_is_the_contexts_device(host):
             assert fake.hipSetDevice(0) == 0
             g.close()
     """)
+
+
+@pytest.mark.parametrize("opts,times", [({}, (1, 1, 0, 1)),                                    # two launches
+                                        ({"light_word_tokens": -1}, (1, 1, 1, 2))])            # documents; totals; denominators and Bhat
+def test_profile_times_of_the_kernel_groups(host, opts, times):
+    """Each launch of an iteration is in the time of its group (here a launch takes a millisecond), also where a small corpus'
+    M-step takes two."""
+    host("""
+        opts, times = %r
+        words = np.arange(5000, dtype=np.int32) %% 40
+        g = pk.Saber(np.r_[0, 400, 800, words.size], words, 40, 400, 0.1, 0.01, 3, profile=1, long_doc_tokens=5000, **opts)
+        g.iterate(3)
+        s = g.get_stats()
+        assert (s["ms_sample"], s["ms_count_dz"], s["ms_ck"], s["ms_phi"]) == tuple(3.0 * t for t in times), s
+        assert s["ms_total"] == 3.0 * sum(times)
+    """ % ((opts, times),))
