@@ -2151,6 +2151,15 @@ extern "C" int saber_token_probs(saber_ctx *c, const int64_t *tok, int64_t m, fl
     uint2 *marks = few ? w.take<uint2>(words + 1) : nullptr;   // (the last pair: the next number)
     HIP_TRY(hipMemcpy(dtok, tok, sizeof(int64_t) * (size_t)m, hipMemcpyHostToDevice));
     w.queued = true;
+    // a thread per request: requests [i, i + n), as many as a grid takes, with f(i, n, grid)
+    auto by_pieces = [&](auto f) -> int {
+        for (int64_t i = 0, n; i < m; i += n) {
+            n = std::min(m - i, 256 * most_blocks(256));
+            f(i, n, dim3((unsigned)((n + 255) / 256)));
+            HIP_TRY(hipGetLastError());
+        }
+        return SABER_OK;
+    };
     for (const Chunk &ch : c->chunks) {
         if (ch.ntiles == 0) continue;
         int s = -1;
@@ -2158,8 +2167,9 @@ extern "C" int saber_token_probs(saber_ctx *c, const int64_t *tok, int64_t m, fl
         if (few) {
             hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_for(2 * (int64_t)words + 2, 256, 8192)), dim3(256), 0, c->stream, (uint32_t *)marks, 0u, 2 * words + 2);
             HIP_TRY(hipGetLastError());
-            hipLaunchKernelGGL(mark_tokens_kernel, dim3(grid_for(m, 256)), dim3(256), 0, c->stream, dtok, m, ch.t0, ch.ntok, marks);
-            HIP_TRY(hipGetLastError());
+            SABER_TRY(by_pieces([&](int64_t i, int64_t n, dim3 grid) {
+                hipLaunchKernelGGL(mark_tokens_kernel, grid, dim3(256), 0, c->stream, dtok + i, n, ch.t0, ch.ntok, marks);
+            }));
             hipLaunchKernelGGL(number_tokens_kernel, dim3(grid_for((int64_t)words, 256)), dim3(256), 0, c->stream, marks, (int64_t)words, &marks[words].x);
             HIP_TRY(hipGetLastError());
         }
@@ -2167,9 +2177,10 @@ extern "C" int saber_token_probs(saber_ctx *c, const int64_t *tok, int64_t m, fl
         p.marks = marks; p.out_S = dS; p.out_Q = dQ;
         SABER_TRY(launch_estep<MODE_PROBS>(c, ch, p));
         if (c->n_slots) SABER_TRY(stream_release(c, s));
-        hipLaunchKernelGGL(gather_probs_kernel, dim3(grid_for(m, 256)), dim3(256), 0, c->stream, dS, dQ, marks, dtok, m, ch.t0, ch.ntok,
-                           g3, g3 + m, g3 + 2 * m);
-        HIP_TRY(hipGetLastError());
+        SABER_TRY(by_pieces([&](int64_t i, int64_t n, dim3 grid) {
+            hipLaunchKernelGGL(gather_probs_kernel, grid, dim3(256), 0, c->stream, dS, dQ, marks, dtok + i, n, ch.t0, ch.ntok,
+                               g3 + i, g3 + m + i, g3 + 2 * m + i);
+        }));
     }
     HIP_TRY(hipStreamSynchronize(c->stream));
     w.queued = false;

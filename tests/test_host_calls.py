@@ -383,3 +383,15 @@ def test_profile_times_of_the_kernel_groups(host, opts, times):
         assert (s["ms_sample"], s["ms_count_dz"], s["ms_ck"], s["ms_phi"]) == tuple(3.0 * t for t in times), s
         assert s["ms_total"] == 3.0 * sum(times)
     """ % ((opts, times),))
+
+
+def test_normalisers_of_more_tokens_than_a_grid_was_cut_to(host):
+    """Every request has a thread that gathers its result (it used to be the first 268 million)."""
+    host("""
+        import paper_1610_02496_amd.binding as binding
+        L, m = binding.load_library(), 65535 * 16 * 256 + 1
+        g = pk.Saber(np.array([0, 1000]), np.zeros(1000, np.int32), 1, 10, 0.1, 0.01, 3)
+        tok = np.zeros(m, np.int64)                 # (read only: it takes no memory, its copy does)
+        assert L.saber_token_probs(g._h, tok.ctypes.data, m, None, None, None) == 0
+        assert fake.fake_blocks(b"gather_probs") == -(-m // 256)
+    """)
