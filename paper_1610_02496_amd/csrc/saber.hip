@@ -1946,44 +1946,38 @@ static int foldin_iterate(saber_ctx *c, int32_t n) {
 }
 
 // lay_out() of a context on a trained model by another thread where that pays (1.5 ms for the 550,000 scored tokens of 3,300
-// documents, which the observed ones' layout and fold-in hide; a thread costs 0.03)
+// documents, which the observed ones' layout and fold-in hide; a thread costs 0.03); by the calling one at finish() otherwise.
 struct BackgroundLayout {
     Layout lay;
     std::thread thread;
     int rc = SABER_OK;
+    bool no_memory = false;
     std::string error;
-    void start(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) {
-        auto work = [this, c, doc_ptr, word_ids] {
-            try {
-                rc = lay_out(c, doc_ptr, word_ids, lay);
-                if (rc != SABER_OK) error = g_err;
-            } catch (const std::bad_alloc &) { rc = SABER_ENOMEM; }
-        };
-        if (c->T >= 32768) {
-            try { thread = std::thread(work); return; } catch (const std::system_error &) {}   // no thread to be had
-        }
-        work();
+    void run(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) {
+        try {
+            rc = lay_out(c, doc_ptr, word_ids, lay);
+            if (rc != SABER_OK) error = g_err;
+        } catch (const std::bad_alloc &) { rc = SABER_ENOMEM; no_memory = true; }
     }
-    int finish() {
-        if (thread.joinable()) thread.join();
-        return rc == SABER_OK ? rc : fail(rc, "%s", rc == SABER_ENOMEM && error.empty() ? "saber_holdout_loglik: out of host memory" : error.c_str());
+    void start(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) {
+        if (c->T < 32768) return;
+        try { thread = std::thread([=] { run(c, doc_ptr, word_ids); }); } catch (const std::system_error &) {}   // no thread to be had
+    }
+    int finish(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids) {
+        if (thread.joinable()) thread.join(); else run(c, doc_ptr, word_ids);
+        return rc == SABER_OK ? rc : fail(rc, "%s", no_memory ? "saber_holdout_loglik: out of host memory" : error.c_str());
     }
     ~BackgroundLayout() { if (thread.joinable()) thread.join(); }
 };
 
-extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const int32_t *word_ids,
-                                    const uint8_t *observed, int64_t D, int32_t n_foldin, uint64_t seed,
-                                    const int32_t *z_init, int32_t *z_out, double *loglik, int64_t *n_scored) {
-    if (!m || !doc_ptr || !loglik || !n_scored || D < 0 || n_foldin < 0)
-        return fail(SABER_EINVAL, "saber_holdout_loglik: bad argument");
-    if (m->parent) return fail(SABER_EINVAL, "saber_holdout_loglik: the model must be a context made by saber_init");
-    if (doc_ptr[0] != 0) return fail(SABER_EINVAL, "saber_holdout_loglik: doc_ptr[0] must be 0");
-    for (int64_t d = 0; d < D; d++)
-        if (doc_ptr[d + 1] < doc_ptr[d]) return fail(SABER_EINVAL, "saber_holdout_loglik: doc_ptr decreases at document %lld", (long long)d);
+// The checked call.  *no_memory: host memory ran out.
+static int holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const int32_t *word_ids, const uint8_t *observed, int64_t D,
+                          int32_t n_foldin, uint64_t seed, const int32_t *z_init, int32_t *z_out, double *loglik, int64_t *n_scored,
+                          bool side_by_side, bool *no_memory) {
     const int64_t T = doc_ptr[D];
-    if (T > 0 && (!word_ids || !observed)) return fail(SABER_EINVAL, "saber_holdout_loglik: null token arrays");
     saber_ctx *obs = nullptr, *scr = nullptr;
     int rc = SABER_OK;
+    *no_memory = false;
     try {
         // the observed part and the scored part as two corpora over the same documents (every word is written to both and one
         // of the two positions moves on: which one cannot be foretold)
@@ -2005,13 +1999,13 @@ extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const 
         if (m->auto_light_block) opt.block_threads = opt.light_block_threads = 0;
         rc = make_ctx(&obs, optr.data(), ow.data(), D, m->V, m->K, m->alpha, m->beta, seed, &opt, m, false);
         if (rc == SABER_OK) rc = make_ctx(&scr, sptr.data(), sw.data(), D, m->V, m->K, m->alpha, m->beta, seed, &opt, m, true);
-        Layout obs_lay;
         BackgroundLayout scr_lay;
+        if (rc == SABER_OK && side_by_side) scr_lay.start(scr, sptr.data(), sw.data());
         if (rc == SABER_OK) {
-            scr_lay.start(scr, sptr.data(), sw.data());
-            rc = lay_out(obs, optr.data(), ow.data(), obs_lay);
+            Layout lay;
+            rc = lay_out(obs, optr.data(), ow.data(), lay);
+            if (rc == SABER_OK) rc = upload(obs, optr.data(), ow.data(), lay);
         }
-        if (rc == SABER_OK) rc = upload(obs, optr.data(), ow.data(), obs_lay);
         if (rc == SABER_OK && z_init) rc = saber_set_z(obs, z_init, 0);
         if (rc == SABER_OK) rc = foldin_iterate(obs, n_foldin);
         if (rc == SABER_OK && z_out) {
@@ -2021,7 +2015,7 @@ extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const 
             rc = saber_get_z(obs, z_out);
             if (borrow) std::swap(obs->staging, m->staging);
         }
-        if (rc == SABER_OK) rc = scr_lay.finish();
+        if (rc == SABER_OK) { rc = scr_lay.finish(scr, sptr.data(), sw.data()); *no_memory = scr_lay.no_memory; }
         if (rc == SABER_OK) rc = upload(scr, sptr.data(), sw.data(), scr_lay.lay);
         double ll = 0.0;
         if (rc == SABER_OK && scr->T > 0) {
@@ -2038,8 +2032,26 @@ extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const 
             *n_scored = scr->T;
             *loglik = ll;
         }
-    } catch (const std::bad_alloc &) { rc = fail(SABER_ENOMEM, "saber_holdout_loglik: out of host memory"); }
+    } catch (const std::bad_alloc &) { rc = fail(SABER_ENOMEM, "saber_holdout_loglik: out of host memory"); *no_memory = true; }
     saber_free(scr); saber_free(obs);
+    return rc;
+}
+
+extern "C" int saber_holdout_loglik(saber_ctx *m, const int64_t *doc_ptr, const int32_t *word_ids,
+                                    const uint8_t *observed, int64_t D, int32_t n_foldin, uint64_t seed,
+                                    const int32_t *z_init, int32_t *z_out, double *loglik, int64_t *n_scored) {
+    if (!m || !doc_ptr || !loglik || !n_scored || D < 0 || n_foldin < 0)
+        return fail(SABER_EINVAL, "saber_holdout_loglik: bad argument");
+    if (m->parent) return fail(SABER_EINVAL, "saber_holdout_loglik: the model must be a context made by saber_init");
+    if (doc_ptr[0] != 0) return fail(SABER_EINVAL, "saber_holdout_loglik: doc_ptr[0] must be 0");
+    for (int64_t d = 0; d < D; d++)
+        if (doc_ptr[d + 1] < doc_ptr[d]) return fail(SABER_EINVAL, "saber_holdout_loglik: doc_ptr decreases at document %lld", (long long)d);
+    if (doc_ptr[D] > 0 && (!word_ids || !observed)) return fail(SABER_EINVAL, "saber_holdout_loglik: null token arrays");
+    bool no_memory;
+    int rc = holdout_loglik(m, doc_ptr, word_ids, observed, D, n_foldin, seed, z_init, z_out, loglik, n_scored, true, &no_memory);
+    // where both layouts do not fit the host's memory: one after the other
+    if (rc != SABER_OK && no_memory)
+        rc = holdout_loglik(m, doc_ptr, word_ids, observed, D, n_foldin, seed, z_init, z_out, loglik, n_scored, false, &no_memory);
     return rc;
 }
 

@@ -14,6 +14,7 @@ fake = ctypes.CDLL(%r, mode=ctypes.RTLD_GLOBAL)   # in front of the real runtime
 fake.fake_launches.restype, fake.fake_launches.argtypes = ctypes.c_int64, [ctypes.c_char_p, ctypes.c_void_p]
 fake.fake_blocks.restype, fake.fake_blocks.argtypes = ctypes.c_uint64, [ctypes.c_char_p]
 fake.fake_calls.restype, fake.fake_calls.argtypes = ctypes.c_int64, [ctypes.c_char_p]
+fake.fake_new_limit.argtypes = [ctypes.c_int64]
 fake.fake_host_bytes.restype = fake.fake_mallocs_on.restype = ctypes.c_int64
 import numpy as np
 import paper_1610_02496_amd as pk

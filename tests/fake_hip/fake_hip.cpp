@@ -2,16 +2,30 @@
 // of the real ones.  Memory is host memory (reserved, touched on use), copies are memcpy, kernels do not run - their
 // launches are checked against the documented limits and logged.  A few kernels of the M-step can be imitated, and a
 // call can be made to fail.  Two devices; objects belong to the one that was current when they were made.
+#include <malloc.h>
 #include <sys/mman.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
+
+// Host memory in use by way of operator new, the library's included, and what it may grow to.
+static std::atomic<int64_t> new_bytes{0}, new_limit{INT64_MAX};
+void *operator new(size_t n) {
+    void *p = new_bytes.load() + (int64_t)n <= new_limit.load() ? malloc(n ? n : 1) : nullptr;
+    if (!p) throw std::bad_alloc();
+    new_bytes += (int64_t)malloc_usable_size(p);
+    return p;
+}
+void operator delete(void *p) noexcept { if (p) new_bytes -= (int64_t)malloc_usable_size(p); free(p); }
+void operator delete(void *p, size_t) noexcept { operator delete(p); }
 
 namespace {
 enum { kOk = 0, kInvalidValue = 1, kOutOfMemory = 2, kInvalidConfiguration = 9, kInvalidDevice = 101, kInvalidHandle = 400 };
@@ -98,6 +112,7 @@ int fake_fail_pending() { std::lock_guard<std::mutex> lock(mu); return fail_at; 
 void fake_imitate(int on) { imitate = on; }
 void fake_clear() { std::lock_guard<std::mutex> lock(mu); launches.clear(); calls.clear(); host_bytes = 0; mallocs_on[0] = mallocs_on[1] = 0; }
 int64_t fake_mallocs_on(int d) { std::lock_guard<std::mutex> lock(mu); return mallocs_on[d]; }   // of device memory, with device d current
+void fake_new_limit(int64_t bytes) { new_limit = bytes < 0 ? INT64_MAX : new_bytes + bytes; }   // operator new: so many bytes more than now
 int64_t fake_host_bytes() { return host_bytes; }   // of pinned memory asked for
 int64_t fake_calls(const char *name) { std::lock_guard<std::mutex> lock(mu); return calls[name]; }   // of those that can be made to fail
 int64_t fake_launches(const char *name, uint64_t *most_threads) {   // launches of kernels whose name contains `name`

@@ -395,3 +395,20 @@ def test_normalisers_of_more_tokens_than_a_grid_was_cut_to(host):
         assert L.saber_token_probs(g._h, tok.ctypes.data, m, None, None, None) == 0
         assert fake.fake_blocks(b"gather_probs") == -(-m // 256)
     """)
+
+
+def test_held_out_call_in_little_host_memory(host):
+    """Where both parts' layouts do not fit they are made one after the other: 8.5 bytes per token of documents of 1,000 tokens,
+    13.6 side by side."""
+    host("""
+        V, K, n = 50, 100, 1_000_000
+        words = np.arange(n, dtype=np.int32) % V
+        doc_ptr = np.r_[0, np.arange(999, n, 1000), n]
+        observed = (np.arange(n) % 2).astype(np.uint8)
+        g = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 3)
+        for per_token, code in ((9, 0), (7, -2), (9, 0), (20, 0)):
+            fake.fake_new_limit(per_token * n)
+            assert code_of(lambda: g.holdout_loglik(doc_ptr, words, observed, 1, 5)) == code, per_token
+        fake.fake_new_limit(-1)
+        assert g.holdout_loglik(doc_ptr, words, observed, 1, 5)[1] == n // 2
+    """)
