@@ -2148,12 +2148,13 @@ extern "C" int saber_token_probs(saber_ctx *c, const int64_t *tok, int64_t m, fl
     if (m == 0) return SABER_OK;
     // S and Q of the tokens of a chunk (inspection mode of the sampling kernel), then the requested tokens of that
     // chunk are picked out and S / (S + Q) is formed, all on the device; the work space is sized for one chunk.
-    // Fewer than an eighth of the tokens are marked, and only these worked on (5 M tokens, K = 1,500: 100 of
-    // them in 0.10 ms, 100,000 in 0.25, where a pass over all and its work space took 0.9); of more, S and Q of all
-    // tokens are formed, runs of tokens sharing theirs.
+    // Fewer than an eighth of the tokens are marked, and only these worked on: 5 M tokens, K = 1,500, 100 of them 98 us, where a
+    // pass over all took 221, 100,000 of them 0.25 ms, 600,000 1.04 and 1.07 (calls after a context's first).  Of more, S and Q of
+    // all tokens are formed, runs of tokens sharing theirs; in chunks below 400,000 tokens as well, whose pass costs less than the
+    // three launches that mark: T = 50,000, K = 68 66 us, 71 with marks; 200,000, K = 300 77 and 82; 500,000, K = 100 94 and 87.
     int64_t max_tok = 1;
     for (const Chunk &ch : c->chunks) max_tok = std::max(max_tok, ch.ntok);
-    const bool few = m < c->T / 8;
+    const bool few = m < c->T / 8 && max_tok >= 400'000;
     const size_t words = (size_t)(max_tok + 31) / 32, n = few ? (size_t)m : (size_t)max_tok;
     WorkSpace w(c);
     SABER_TRY(w.reserve(2 * w.rounded(n * sizeof(float)) + w.rounded(3 * (size_t)m * sizeof(float)) + w.rounded((size_t)m * sizeof(int64_t)) +

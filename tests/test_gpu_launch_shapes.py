@@ -263,12 +263,13 @@ def test_frequent_words_cut_by_ranges_of_documents(T, K, opts):
 @pytest.mark.parametrize("K,opts", [(60, {}), (1000, {}), (9000, {}), (40_000, {}), (1000, {"stage_phi": 0}), (70_000, {}), (300, {"n_chunks": 3}),
                                     (300, {"n_chunks": 3, "stream_workers": 2})])
 def test_normalisers_of_a_few_tokens(K, opts):
-    """Fewer than an eighth of the tokens are marked and worked on alone: the same numbers as where all are asked for, which
-    the oracle checks; none in a tile or a batch, one, all of a run, a word's all; repeats; tokens on both sides of what a
-    mark holds; both sides of an eighth; a large request between two small ones."""
+    """Fewer than an eighth of the tokens are marked and worked on alone, in chunks of 400,000 tokens and more: the same numbers
+    as where all are asked for, which the oracle checks; none in a tile or a batch, one, all of a run, a word's all; repeats;
+    tokens on both sides of what a mark holds; both sides of an eighth; a large request between two small ones."""
     rng = np.random.default_rng(K)
     edges = [1, 2, 63, 64, 65, 129, 400, 700]
-    doc_ptr, words = corpus_of_word_counts(np.r_[np.repeat(edges, 9), 4000, 9000], 260, K)
+    heavy = 600_000 if opts.get("n_chunks") else 200_000
+    doc_ptr, words = corpus_of_word_counts(np.r_[heavy, heavy, np.repeat(edges, 9), 4000, 9000], 4260, K)
     words[doc_ptr[7]: doc_ptr[7] + 40] = 3                            # runs of more than one token
     T, V = words.size, int(words.max()) + 1
     g = saber().Saber(doc_ptr, words, V, K, 50.0 / K, 0.01, 11, **opts)

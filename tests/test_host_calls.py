@@ -412,3 +412,16 @@ def test_held_out_call_in_little_host_memory(host):
         fake.fake_new_limit(-1)
         assert g.holdout_loglik(doc_ptr, words, observed, 1, 5)[1] == n // 2
     """)
+
+
+@pytest.mark.parametrize("T,opts,m,marked", [(400_000, {}, 49_999, 1), (400_000, {}, 50_000, 0), (399_999, {}, 100, 0), (399_999, {}, 49_999, 0),
+                                             (1_200_000, {"n_chunks": 3}, 100, 3), (1_197_000, {"n_chunks": 3}, 100, 0)])
+def test_which_requests_for_normalisers_are_marked(host, T, opts, m, marked):
+    """Fewer than an eighth of the tokens, in chunks whose pass costs more than marking them."""
+    host("""
+        T, opts, m, marked = %r
+        g = pk.Saber(np.r_[np.arange(0, T, 1000), T], np.zeros(T, np.int32), 1, 100, 0.1, 0.01, 3, **opts)
+        fake.fake_clear()
+        g.token_probs(np.arange(m))
+        assert launches("mark_tokens")[0] == launches("number_tokens")[0] == marked
+    """ % ((T, opts, m, marked),))
