@@ -425,3 +425,32 @@ def test_which_requests_for_normalisers_are_marked(host, T, opts, m, marked):
         g.token_probs(np.arange(m))
         assert launches("mark_tokens")[0] == launches("number_tokens")[0] == marked
     """ % ((T, opts, m, marked),))
+
+
+def test_first_inspection_calls_share_a_block(host):
+    """Fresh device memory costs more than a call: a sampler's first inspection calls allocate once where they need more than
+    a MB, and never more than what is kept."""
+    host("""
+        words = np.arange(500_000, dtype=np.int32) % 40
+        def mallocs(*calls):
+            g = pk.Saber(np.r_[np.arange(0, words.size, 1000), words.size], words, 40, 1000, 0.1, 0.01, 3)
+            fake.fake_clear()
+            for call in calls: call(g)
+            g.close()
+            return fake.fake_calls(b"hipMalloc")
+        probs = lambda m: lambda g: g.token_probs(np.arange(m) % words.size)
+        phi = lambda m: lambda g: g.get_phi(np.arange(m, dtype=np.int32) % 40)
+        assert mallocs(probs(60_000), phi(400)) == 1                    # 1.8 MB, 3.2 MB
+        assert mallocs(phi(400), probs(500_000), phi(1000)) == 2        # 14 MB the second
+        assert mallocs(phi(8000), phi(8400), phi(400), phi(8400)) == 3  # 64 MB; more than that lives as long as its call
+        assert mallocs(phi(8400), phi(8400)) == 2
+        # memory that is short: the size asked for if not the block, what is kept goes if a call needs more
+        for calls, refused, n in (((phi(400), phi(400)), 1, 2), ((phi(400), phi(8400)), 2, 3), ((phi(8400), phi(400)), 2, 3)):
+            fake.fake_fail(b"hipMalloc", 0)
+            g = pk.Saber(np.r_[np.arange(0, words.size, 1000), words.size], words, 40, 1000, 0.1, 0.01, 3)
+            fake.fake_clear()
+            fake.fake_fail(b"hipMalloc", refused)
+            for call in calls: call(g)
+            assert fake.fake_calls(b"hipMalloc") == n and fake.fake_fail_pending() == 0
+            g.close()
+    """)
