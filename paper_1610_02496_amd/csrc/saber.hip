@@ -140,7 +140,7 @@ struct saber_ctx {
     bool z16 = false, staged = false, b16 = false;
     bool overlay = false;             // rows do not fit LDS: light words are read from memory with marks in LDS (Overlay)
     bool auto_light_block = false;    // neither workgroup size was given: those of light words' tiles follow the tile
-    int lds_per_cu = 64 * 1024;
+    int lds_per_cu = 64 * 1024, cus = 256;
     saber_options opt{};
     int32_t tile_tokens_asked = 0;    // the caller's tile_tokens (0: automatic), before the default was filled in
     int64_t max_doc_len = 0;
@@ -382,11 +382,11 @@ static int estep_waves_per_cu(const saber_ctx *c, int block) {
 // the launch: every place on the chip gets 16 workgroups in turn or more, and 8 tiles are the most.  With
 // rows of 4 and 8 KB (T = 10 M, K = 1,000; T = 20 M, K = 2,000) no number of tiles changes anything, so rows of 16 KB are the least.
 // The log-likelihood pass has no registers for it, and gained nothing.
-constexpr int64_t kWalkTiles = 8, kWalkRounds = 16, kCus = 256;
+constexpr int64_t kWalkTiles = 8, kWalkRounds = 16;
 constexpr size_t kWalkRow = 16 * 1024;
 static int32_t walkers_for(const saber_ctx *c, int mode, int64_t n, int block) {
     if (!c->staged || !c->z16 || mode != MODE_SAMPLE || n <= 0 || estep_row_bytes(c) < kWalkRow) return (int32_t)n;
-    const int64_t places = kCus * estep_waves_per_cu(c, block) / (block / 64);
+    const int64_t places = c->cus * estep_waves_per_cu(c, block) / (block / 64);
     const int64_t tiles = std::max<int64_t>(1, std::min(kWalkTiles, n / (kWalkRounds * places)));
     return (int32_t)((n + tiles - 1) / tiles);
 }
@@ -1463,6 +1463,7 @@ static int make_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word
     // the word's Bhat row is staged in LDS when it fits a workgroup's share: up to 150 KB of the CU's 160 KB
     if (hipDeviceGetAttribute(&c->lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, 0) != hipSuccess || c->lds_per_cu <= 0)
         c->lds_per_cu = 64 * 1024;
+    if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || c->cus <= 0) c->cus = 256;
     const size_t stage_limit = std::min<size_t>(150 * 1024, (size_t)c->lds_per_cu > 10 * 1024 ? (size_t)c->lds_per_cu - 10 * 1024 : 0);
     c->staged = opt.stage_phi && estep_row_bytes(c) <= std::max<size_t>(stage_limit, 54 * 1024);
     const int64_t per_chunk = T / std::max(1, c->opt.n_chunks);

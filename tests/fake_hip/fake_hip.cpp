@@ -43,7 +43,7 @@ std::vector<Launch> launches;
 std::map<std::string, int64_t> calls;
 int64_t mallocs_on[2] = {};
 std::string fail_name;
-int fail_at = 0, imitate = 0;
+int fail_at = 0, imitate = 0, cus = 256;
 int64_t host_bytes = 0;
 thread_local int device = 0, last_error = 0;
 thread_local std::vector<Config> configs;
@@ -110,6 +110,7 @@ extern "C" {
 void fake_fail(const char *name, int nth) { std::lock_guard<std::mutex> lock(mu); fail_name = name; fail_at = nth; }   // the nth call (launch) whose name contains `name`
 int fake_fail_pending() { std::lock_guard<std::mutex> lock(mu); return fail_at; }
 void fake_imitate(int on) { imitate = on; }
+void fake_cus(int n) { cus = n; }
 void fake_clear() { std::lock_guard<std::mutex> lock(mu); launches.clear(); calls.clear(); host_bytes = 0; mallocs_on[0] = mallocs_on[1] = 0; }
 int64_t fake_mallocs_on(int d) { std::lock_guard<std::mutex> lock(mu); return mallocs_on[d]; }   // of device memory, with device d current
 void fake_new_limit(int64_t bytes) { new_limit = bytes < 0 ? INT64_MAX : new_bytes + bytes; }   // operator new: so many bytes more than now
@@ -163,7 +164,7 @@ const char *hipGetErrorString(int) { return "error of the stand-in runtime"; }
 int hipGetDeviceCount(int *n) { *n = 2; return kOk; }
 int hipGetDevice(int *d) { *d = device; return kOk; }
 int hipSetDevice(int d) { if (d < 0 || d > 1) return result(kInvalidDevice); device = d; return kOk; }
-int hipDeviceGetAttribute(int *v, int, int) { *v = 160 * 1024; return kOk; }
+int hipDeviceGetAttribute(int *v, int what, int) { *v = what == 63 ? cus : 160 * 1024; return kOk; }   // CUs; LDS of one
 int hipFuncGetAttributes(void *attr, const void *) { memset(attr, 0, 56); return kOk; }
 int hipFuncSetAttribute(const void *, int, int) { return kOk; }
 int hipGetSymbolAddress(void **p, const void *var) {

@@ -454,3 +454,22 @@ def test_first_inspection_calls_share_a_block(host):
             assert fake.fake_calls(b"hipMalloc") == n and fake.fake_fail_pending() == 0
             g.close()
     """)
+
+
+@pytest.mark.parametrize("K,opts,cus,walkers", [(9000, {}, 256, 20_000), (9000, {}, 64, 5000), (9000, {}, 8, 2500), (3900, {}, 8, 20_000),
+                                                (9000, {"stage_phi": 0}, 8, 20_000), (20_011, {}, 256, 10_000), (20_011, {}, 8, 2500)])
+def test_workgroups_that_light_words_are_dealt_to(host, K, opts, cus, walkers):
+    """20,000 tiles of light words, K = 9,000: four workgroups of 512 threads fit a CU, and every place gets 16 or more in turn; at
+    most eight tiles each; one where rows are short or not staged.  K = 20,011: two of 1,024."""
+    host("""
+        K, opts, cus, walkers = %r
+        fake.fake_cus(cus)
+        words = np.repeat(np.arange(20_000, dtype=np.int32), 5)
+        g = pk.Saber(np.r_[np.arange(0, words.size, 1000), words.size], words, 20_000, K, 0.1, 0.01, 3, **opts)
+        fake.fake_clear()
+        g.iterate(1)
+        assert fake.fake_blocks(b"estep_kernel") == walkers
+        fake.fake_clear()
+        g.loglik()
+        assert fake.fake_blocks(b"estep_kernel") == g.get_stats()["tiles"] == 20_000
+    """ % ((K, opts, cus, walkers),))
