@@ -136,7 +136,7 @@ def test_held_out_layouts_of_any_size(tile_tokens):
         mask[rng.permutation(T)[:T - scored]] = rng.integers(1, 256, T - scored)   # (any value but 0 is "observed")
         dp = np.r_[0, 0, np.sort(rng.integers(0, T, 200)), T].astype(np.int64)
         words = np.minimum(rng.geometric(0.01, T) - 1, V - 1).astype(np.int32)
-        words[:70_000 if scored > 60_000 else 10] = 1
+        words[:115_000 if scored > 60_000 else 10] = 1   # (about 80,000 of them scored: more than the largest tile)
         ll, n, z = g.holdout_loglik(dp, words, mask, 0, 77)
         ll_o, n_o, z_o = o.holdout_loglik(dp, words, (mask != 0).astype(np.uint8), 0, 77)
         assert n == n_o == scored and np.array_equal(z, z_o) and abs(ll - ll_o) <= 1e-6 * abs(ll_o)
