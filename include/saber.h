@@ -27,10 +27,15 @@
  *     word and 8 bytes per non-zero count of the others when everything is resident; about 6 bytes per token
  *     and 4 bytes per token of pinned host memory with host streaming (saber_options.stream_workers).
  *   - Threads and host memory: saber_counts, saber_get_z and the z_out of saber_holdout_loglik start up to eight
- *     threads for results of more than 8 MB (they write the caller's buffers and end before the call returns; where
- *     none can be started the calling thread does the work), and then keep up to 12 MB of pinned host memory per context
- *     until saber_free; 0.5 MB for smaller results, none up to 4 MB of assignments or of B and 1 MB of A (ordinary
- *     memory where pinned memory is refused).  No other call starts threads.
+ *     threads for results of more than 8 MB (once they have, for more than 1 MB of A or of B; they write the caller's
+ *     buffers and end before the call returns; where none can be started the calling thread does the work), and then keep
+ *     up to 12 MB of pinned host memory per context until saber_free; 0.5 MB for smaller results, none up to 4 MB of
+ *     assignments or of B and 1 MB of A (ordinary memory where pinned memory is refused).  saber_holdout_loglik starts one
+ *     thread from 32,768 scored tokens on, whatever z_out is: it prepares these while the calling one works on the observed
+ *     tokens, and ends before the call returns (one after the other where there is no thread, or no memory for both:
+ *     5 bytes per held-out token).  No other call starts threads.
+ *   - Device memory kept: saber_token_probs and saber_get_phi keep a work space of up to 64 MB per context (from the
+ *     caller's allocator where there is one) from their first call until saber_free.
  */
 #ifndef SABER_H
 #define SABER_H
@@ -66,8 +71,9 @@ typedef struct saber_options {
                                it cannot be and a chunk has fewer than 8 M tokens */
     int32_t tile_tokens;    /* most tokens of one word handled by one workgroup; default 0: a 32,768th of a chunk's tokens per
                                wavefront of the workgroup (at most four), not below K / 16 (64 to 256) and not above
-                               32,768; with more than 2^19 words a 2560th, not below 8,192.  Larger where a document is far longer than a chunk's share, so that a chunk
-                               of up to 2^19 words has at most 2^20 tiles (saber_loglik_static) */
+                               32,768; with more than 2^19 words a 2560th, not below 8,192.  Larger where a document is far
+                               longer than a chunk's share, so that a chunk of up to 2^19 words has at most 2^20 tiles
+                               (saber_loglik_static) */
     int32_t stage_phi;      /* 1: keep the word's Bhat row in LDS when it fits (up to 150 KB: K <= 37,800), 0: always
                                gather from global; default 1 */
     int32_t profile;        /* 1: time every kernel group with HIP events (see saber_get_stats); default 0 */

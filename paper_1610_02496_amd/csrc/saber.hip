@@ -295,7 +295,7 @@ static ZView z_view(const saber_ctx *c, const Chunk &ch, int slot) {
 }
 
 // The rows of A the sampling kernel reads for the documents of chunk `ch` of context `theta`: all of them sit behind
-// one buffer descriptor and are addressed by 32-bit byte offsets (build() keeps every chunk's rows below 4 GB).
+// one buffer descriptor and are addressed by 32-bit byte offsets (lay_out() keeps every chunk's rows below 4 GB).
 static void set_rows(EStepParams &p, const saber_ctx *theta, const Chunk &ch) {
     p.docrec = theta->docrec;
     p.cd_rows = theta->cd_ent + (size_t)ch.row_unit0 * 32u;
@@ -441,8 +441,8 @@ static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
 // first iterations and 1.41, 1.43 and 1.62 in later ones, K = 45,000 15.8, 13.8 and 12.7, and 6.98, 6.96 and 7.21.
 //
 // With marks for light words instead (Overlay) the base vector, which all of them share, fills the caches, and 256, 512 and
-// 1,024 threads take 0.52, 0.53 and 0.56 ms at T = 1.5 M, K = 70,000, 0.96, 1.06 and 1.27 at T = 3 M, K = 45,000, but 8.8, 8.1 and
-// 7.8 ms at T = 20 M, where the words with dense rows have most of the tokens.
+// 1,024 threads take 0.44, 0.45 and 0.48 ms at T = 1.5 M, K = 70,000, 0.91, 1.00 and 1.19 at T = 3 M, K = 45,000, but 8.7, 8.0 and
+// 7.7 ms at T = 20 M, where the words with dense rows have most of the tokens (iterations 6 to 15).
 constexpr int64_t kLargeChunk = 8ll << 20;
 static int estep_auto_block(const saber_ctx *c, int64_t per_chunk) {
     if (c->overlay && per_chunk < kLargeChunk) return 256;
@@ -676,8 +676,10 @@ static int stream_acquire(saber_ctx *c, const Chunk &ch, int *slot) {
     *slot = s;
     if (ch.ntok == 0) return SABER_OK;
     HIP_TRY(hipMemcpyAsync(c->slot_tok_t[s], c->h_tok_t + ch.t0, (size_t)ch.ntok * sizeof(uint32_t), hipMemcpyHostToDevice, c->s_in));
-    // on the copy stream as well: the look-ups of this kernel wait for memory most of the time and run beside the
-    // sampling of the chunk before (1.7 ms per 123 M tokens of short documents when it ran in line with it)
+    // on the copy stream as well: the look-ups of this kernel wait for memory most of the time, and where the copy ends early
+    // enough they run beside the sampling of the chunk before (1.7 ms per 123 M tokens of short documents when it ran in line
+    // with it).  At T = 20 M in four chunks, K = 2,000, where the link is the slower one, 43 % of its 54 us per chunk do; the
+    // rest lies between two sampling passes, and the next chunk's copy waits for all of it.
     hipLaunchKernelGGL(expand_tok_doc_kernel, dim3(grid_for(ch.ntok, 256)), dim3(256), 0, c->s_in, c->slot_tok_t[s],
                        ch.ntok, ch.t0, c->doc_blocks, c->ne_doc, c->slot_tok_doc[s]);
     HIP_TRY(hipGetLastError());
@@ -757,7 +759,7 @@ static int launch_count_slabs(saber_ctx *c, int64_t n_items, bool totals) {
     const int range = hist_range(c);
     // every workgroup ends with up to K atomics into the K totals: no more than about 500 shares of z (128 where these
     // have fewer than 65,536 assignments: T = 10 M, K = 1,000 takes 17 us with 153 of them, 21 with 490), none with
-    // fewer than 16 assignments per topic (but 16,384 at least, and 131,072 are enough at any K: an iteration at T = 1.5 M,
+    // fewer than 16 assignments per topic (but 16,384 at least, and 131,072 are enough at any K: a late iteration at T = 1.5 M,
     // K = 70,000 0.41 ms with 262,144, 0.39 with 131,072, 0.40 with 65,536 and 0.41 with fewer, at T = 15 M, K = 20,011 1.66, 1.65, 1.66
     // and 1.66) or more than 2^20, keep those from dominating
     const int64_t least = std::max<int64_t>(16384, std::min<int64_t>(16 * (int64_t)c->K, 131072));
@@ -1033,7 +1035,7 @@ static int lay_out(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids
     // ---- words: dense rows of B for the frequent ones, sparse rows for the rest ----
     // A word with n tokens has at most n non-zero counts; below light_word_tokens tokens its sparse row
     // (8 bytes per non-zero, rebuilt by a segmented count like a row of A) is cheaper than 12*K bytes of dense B / Bhat
-    // traffic per iteration.  Needs the LDS-staged sampler and 16-bit assignments.
+    // traffic per iteration.  Needs a Bhat row in LDS (16-bit assignments, then), or marks in LDS where it cannot hold a row (Overlay).
     const bool light_ok = (c->staged ? c->z16 : c->overlay) && c->opt.light_word_tokens > 0;
     const saber_ctx *par = c->parent;   // then the model's word classes are taken over
     c->joined = light_ok && c->z16 && !par && c->n_slots == 0 && c->opt.ablation == 0 && K <= kJoinedTopics && D + V <= kJoinedSegments && T <= kJoinedTokens;
@@ -1105,7 +1107,8 @@ static int lay_out(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids
     // ---- word-major token arrays and tiles per chunk (host counting sort; layout only) ----
     // position of every word's segment in the word-major order (light words first, then dense rows) and the
     // slabs CountByVZ cuts the dense rows' segments into
-    // (on a trained model nobody reads the word-major assignments: they lie as the tokens do)
+    // (on a trained model nobody reads the word-major assignments: they lie as the tokens do.  The sampling kernel folds in as it
+    // trains, and writes them all the same: 1.1 MB in a row per iteration of 550,000 tokens, 0.2 us, are not worth a test per batch)
     std::vector<int64_t> wm_ptr, wm_seen;   // wm_seen: tokens placed so far (chunk by chunk)
     // phi_tree_kernel counts a row itself up to 32 tokens per thread of its workgroup; longer rows are cut into slabs for
     // count_slabs_kernel (phi group of T = 2.3 M, K = 777, 256 threads: 43 us with 8,192 tokens, 49 with 32,768; of T = 100 M,
@@ -1468,10 +1471,10 @@ static int make_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word
     c->staged = opt.stage_phi && estep_row_bytes(c) <= std::max<size_t>(stage_limit, 54 * 1024);
     const int64_t per_chunk = T / std::max(1, c->opt.n_chunks);
     // Rows too long for LDS: light words are read from memory with marks in LDS instead of from a full row in memory, whose
-    // 4 K bytes per word would have to be written and read in every iteration.  An iteration with all words dense and so:
-    // T = 1.5 M, K = 70,000, V = 4,001 1.12 and 0.47 ms; 3 M, K = 45,000, V = 60,000 5.5 and 0.95; 20 M, V = 50,000 16.7 and 7.7.
+    // 4 K bytes per word would have to be written and read in every iteration.  An iteration (6 to 15) with all words dense and so:
+    // T = 1.5 M, K = 70,000, V = 4,001 1.09 and 0.44 ms; 3 M, K = 45,000, V = 60,000 5.4 and 0.91; 20 M, V = 50,000 16.7 and 7.7.
     // In small chunks the longest words are cheaper with a dense row: counting a sparse one is the work of one workgroup
-    // (T = 1.5 M: 0.53 ms with words of up to 32,768 tokens light, 0.47 with 8,192, 0.61 with 1,024; 20 M: 8.8, 10.9, 16.0).
+    // (T = 1.5 M: 0.50 ms with words of up to 32,768 tokens light, 0.44 with 8,192, 0.59 with 1,024; 20 M: 7.6, 8.4, 10.5).
     c->overlay = !c->staged && opt.stage_phi && opt.light_word_tokens > 0;
     if (c->overlay && light_asked == 0 && per_chunk < kLargeChunk) c->opt.light_word_tokens = std::min(c->opt.light_word_tokens, 8192);
     if (opt_in == nullptr || opt_in->block_threads <= 0) {
