@@ -136,8 +136,9 @@ struct saber_ctx {
     int32_t V = 0, K = 0, Kpad = 0, n3 = 0, n3pad = 0, nwords = 0;
     float alpha = 0, beta = 0, vbeta = 0;
     uint64_t seed = 0;
-    uint32_t iter = 0, topic_bits = 0, topic_mask = 0;
+    uint32_t iter = 0, topic_bits = 0, count_bits = 0;   // (a packed entry: the topic above the count)
     bool z16 = false, staged = false, b16 = false;
+    int pack = PACK_ANY;              // what the sampling kernel may take for granted of entries
     bool overlay = false;             // rows do not fit LDS: light words are read from memory with marks in LDS (Overlay)
     bool auto_light_block = false;    // neither workgroup size was given: those of light words' tiles follow the tile
     int lds_per_cu = 64 * 1024, cus = 256;
@@ -317,7 +318,7 @@ static EStepParams make_params(saber_ctx *c, const Chunk &ch, int slot = -1) {
     p.wrec = c->wrec; p.lw_ent = c->lw_ent; p.lw_phi = c->lw_phi; p.z_wm = c->z_wm;
     p.alias_table = c->alias_table;
     p.t_base = ch.t0; p.K = c->K; p.Kpad = c->Kpad; p.n3 = c->n3; p.n3pad = c->n3pad;
-    p.topic_bits = c->topic_bits; p.topic_mask = c->topic_mask; p.alpha = c->alpha;
+    p.count_bits = c->count_bits; p.alpha = c->alpha;
     p.seed_lo = (uint32_t)c->seed; p.seed_hi = (uint32_t)(c->seed >> 32); p.iter = c->iter;
     return p;
 }
@@ -342,9 +343,10 @@ static void launch_with_lds(Kern kern, dim3 grid, dim3 block, size_t lds, hipStr
 }
 
 template <int MODE, bool STAGED, typename ZT>
-static void launch_estep_b16(saber_ctx *c, dim3 grid, dim3 block, size_t lds, const EStepParams &p) {
-    if (c->b16) launch_with_lds(estep_kernel<MODE, STAGED, ZT, true>, grid, block, lds, c->stream, p);
-    else launch_with_lds(estep_kernel<MODE, STAGED, ZT, false>, grid, block, lds, c->stream, p);
+static void launch_estep_packed(saber_ctx *c, dim3 grid, dim3 block, size_t lds, const EStepParams &p) {
+    if (STAGED && c->pack == PACK_16_14) launch_with_lds(estep_kernel<MODE, STAGED, ZT, STAGED ? PACK_16_14 : PACK_16>, grid, block, lds, c->stream, p);
+    else if (c->pack != PACK_ANY) launch_with_lds(estep_kernel<MODE, STAGED, ZT, PACK_16>, grid, block, lds, c->stream, p);
+    else launch_with_lds(estep_kernel<MODE, STAGED, ZT, PACK_ANY>, grid, block, lds, c->stream, p);
 }
 
 // The staged 16/16 sampler addresses its Bhat row from LDS address 0: its kernels must have no static LDS in
@@ -356,13 +358,14 @@ static int static_lds_is_zero(F kernel) {
     if (a.sharedSizeBytes != 0) return fail(SABER_EDEVICE, "sampling kernel built with %zu bytes of static LDS", (size_t)a.sharedSizeBytes);
     return SABER_OK;
 }
+template <int PACK>
 static int check_estep_lds_layout() {
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, uint16_t, true>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_PROBS, true, uint16_t, true>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_LOGLIK, true, uint16_t, true>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, int32_t, true>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_PROBS, true, int32_t, true>));
-    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_LOGLIK, true, int32_t, true>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, uint16_t, PACK>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_PROBS, true, uint16_t, PACK>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_LOGLIK, true, uint16_t, PACK>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, int32_t, PACK>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_PROBS, true, int32_t, PACK>));
+    SABER_TRY(static_lds_is_zero(estep_kernel<MODE_LOGLIK, true, int32_t, PACK>));
     return SABER_OK;
 }
 
@@ -406,11 +409,11 @@ static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
             const dim3 grid((unsigned)(p.first_light + p.walkers)), block((unsigned)cl.block);
             const size_t lds = estep_lds_bytes(c, MODE);
             if (c->staged) {
-                if (c->z16) launch_estep_b16<MODE, true, uint16_t>(c, grid, block, lds, p);
-                else launch_estep_b16<MODE, true, int32_t>(c, grid, block, lds, p);
+                if (c->z16) launch_estep_packed<MODE, true, uint16_t>(c, grid, block, lds, p);
+                else launch_estep_packed<MODE, true, int32_t>(c, grid, block, lds, p);
             } else {
-                if (c->z16) launch_estep_b16<MODE, false, uint16_t>(c, grid, block, lds, p);
-                else launch_estep_b16<MODE, false, int32_t>(c, grid, block, lds, p);
+                if (c->z16) launch_estep_packed<MODE, false, uint16_t>(c, grid, block, lds, p);
+                else launch_estep_packed<MODE, false, int32_t>(c, grid, block, lds, p);
             }
             HIP_TRY(hipGetLastError());
         }
@@ -610,9 +613,9 @@ static int launch_segmented_count(saber_ctx *c, const SegLists &a, const SegList
             if (left) pa.list += i; else pb.list += i - na;
             const dim3 grid((unsigned)n), blk((unsigned)block);
             if (c->z16)
-                hipLaunchKernelGGL((count_dz_kernel<uint16_t>), grid, blk, lds, c->stream, pa, left, pb, c->topic_bits, c->nwords, entries);
+                hipLaunchKernelGGL((count_dz_kernel<uint16_t>), grid, blk, lds, c->stream, pa, left, pb, c->count_bits, c->nwords, entries);
             else
-                hipLaunchKernelGGL((count_dz_kernel<int32_t>), grid, blk, lds, c->stream, pa, left, pb, c->topic_bits, c->nwords, entries);
+                hipLaunchKernelGGL((count_dz_kernel<int32_t>), grid, blk, lds, c->stream, pa, left, pb, c->count_bits, c->nwords, entries);
             HIP_TRY(hipGetLastError());
         }
     }
@@ -638,11 +641,10 @@ static int launch_sort_rebuild(saber_ctx *c) {
     size_t bytes = c->sort_tmp_bytes;
     HIP_TRY(rocprim::radix_sort_keys(c->sort_tmp, bytes, c->sort_keys, c->sort_keys_out, (size_t)c->T, 0u, c->sort_end_bit,
                                      c->stream));
-    hipLaunchKernelGGL(sort_mark_kernel, grid, block, 0, c->stream, c->doc_ptr, c->sort_keys_out, c->D, c->topic_mask,
+    hipLaunchKernelGGL(sort_mark_kernel, grid, block, 0, c->stream, c->doc_ptr, c->sort_keys_out, c->D, c->count_bits,
                        c->docrec, c->cd_ent, c->sort_rank);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(sort_count_kernel, grid, block, 0, c->stream, c->doc_ptr, c->sort_rank, c->D, c->docrec, c->cd_ent,
-                       c->topic_bits);
+    hipLaunchKernelGGL(sort_count_kernel, grid, block, 0, c->stream, c->doc_ptr, c->sort_rank, c->D, c->docrec, c->cd_ent);
     HIP_TRY(hipGetLastError());
     return SABER_OK;
 }
@@ -702,7 +704,7 @@ static int sync_all(saber_ctx *c) {
 // Preprocess + BuildTree for the light words (sparse rows of B); needs the base vector, i.e. runs after launch_phi
 static LightParams light_params(const saber_ctx *c) {
     return LightParams{c->light_words, c->wrec, c->lw_ent, c->lw_phi, c->denom, c->phi + (size_t)c->V_dense * (size_t)c->Kpad,
-                       c->l3_64 + (size_t)c->V * (size_t)c->n3, c->l3, c->l3_64, c->sumphi, c->n3, c->n3pad, c->topic_bits, c->beta};
+                       c->l3_64 + (size_t)c->V * (size_t)c->n3, c->l3, c->l3_64, c->sumphi, c->n3, c->n3pad, c->count_bits, c->beta};
 }
 static int launch_light_words(saber_ctx *c) {
     if (c->V_light == 0) return SABER_OK;
@@ -852,7 +854,7 @@ static int launch_joined_mstep(saber_ctx *c, const unsigned long long *slots, un
     p.T = c->T; p.per_block = joined_share(c); p.n_tot = (int)((c->T + p.per_block - 1) / p.per_block); p.n_items = (int)c->n_vz_long;
     p.acc = c->ck_acc; p.ck = c->ck; p.ticket = (unsigned *)(c->ck_acc + c->K);
     p.items = c->vz_items; p.cwk = c->cwk;
-    p.topic_bits = c->topic_bits; p.nwords = c->nwords; p.lds_entries = std::min(c->opt.dz_lds_entries, c->K); p.wave_entries = std::min(c->opt.long_doc_tokens, c->K);
+    p.count_bits = c->count_bits; p.nwords = c->nwords; p.lds_entries = std::min(c->opt.dz_lds_entries, c->K); p.wave_entries = std::min(c->opt.long_doc_tokens, c->K);
     p.vbeta = c->vbeta; p.beta = c->beta; p.denom = c->denom; p.phi = c->phi; p.l3 = c->l3; p.sumphi = c->sumphi; p.l3_64 = c->l3_64;
     p.K = c->K; p.Kpad = c->Kpad; p.n3 = c->n3; p.n3pad = c->n3pad; p.range = std::min(c->Kpad, kPhiSteps * 4 * 256);
     p.base_row = c->V_dense; p.base_word = c->V;
@@ -905,7 +907,7 @@ static int launch_estep_docmajor(saber_ctx *c, unsigned long long *n_dense) {
     p.phi = c->phi; p.l3 = c->l3; p.sumphi = c->sumphi; p.l3_64 = c->l3_64;
     p.z = c->z; p.n_dense = n_dense; p.D = c->D;
     p.K = c->K; p.Kpad = c->Kpad; p.n3 = c->n3; p.n3pad = c->n3pad;
-    p.topic_bits = c->topic_bits; p.topic_mask = c->topic_mask; p.alpha = c->alpha;
+    p.count_bits = c->count_bits; p.alpha = c->alpha;
     p.seed_lo = (uint32_t)c->seed; p.seed_hi = (uint32_t)(c->seed >> 32); p.iter = c->iter;
     const dim3 grid((unsigned)((c->D + 3) / 4)), block(256);
     if (c->z16) hipLaunchKernelGGL((estep_docmajor_kernel<uint16_t>), grid, block, 0, c->stream, p);
@@ -1040,7 +1042,7 @@ static int lay_out(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids
     const saber_ctx *par = c->parent;   // then the model's word classes are taken over
     c->joined = light_ok && c->z16 && !par && c->n_slots == 0 && c->opt.ablation == 0 && K <= kJoinedTopics && D + V <= kJoinedSegments && T <= kJoinedTokens;
     // (as many counts as a packed entry of a sparse row has bits for)
-    c->opt.light_word_tokens = std::min(c->opt.light_word_tokens, 1 << std::min(16u, 32 - c->topic_bits));
+    c->opt.light_word_tokens = std::min(c->opt.light_word_tokens, 1 << std::min(16u, c->count_bits));
     std::vector<int64_t> n_v;
     if (par) {
         c->h_word_row = par->h_word_row;
@@ -1461,7 +1463,8 @@ static int make_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word
     c->n3pad = (c->n3 + 63) / 64 * 64;
     c->b16 = b16;
     c->nwords = (K + 31) / 32;
-    c->topic_bits = bits; c->topic_mask = (1u << bits) - 1u;
+    c->topic_bits = bits; c->count_bits = 32 - bits;
+    c->pack = !b16 ? PACK_ANY : maxlen < (1 << 14) ? PACK_16_14 : PACK_16;   // (no count exceeds its document's length)
     c->z16 = K <= 65536;
     // the word's Bhat row is staged in LDS when it fits a workgroup's share: up to 150 KB of the CU's 160 KB
     if (hipDeviceGetAttribute(&c->lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, 0) != hipSuccess || c->lds_per_cu <= 0)
@@ -1484,7 +1487,8 @@ static int make_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word
     if (c->opt.light_block_threads <= 0) c->opt.light_block_threads = c->opt.block_threads;
     if (c->opt.tile_tokens <= 0) c->opt.tile_tokens = auto_tile_tokens(c, per_chunk);
     c->vbeta = (float)V * beta;
-    const int rc = check_estep_lds_layout();
+    int rc = check_estep_lds_layout<PACK_16>();
+    if (rc == SABER_OK) rc = check_estep_lds_layout<PACK_16_14>();
     if (rc != SABER_OK) { delete c; return rc; }
     *out = c;
     return SABER_OK;
@@ -1765,6 +1769,7 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
                             int64_t *ck) {
     if (!c) return fail(SABER_EINVAL, "saber_counts: null context");
     if ((cd_topic || cd_count) && !cd_row_ptr) return fail(SABER_EINVAL, "saber_counts: cd_topic/cd_count need cd_row_ptr");
+    const uint32_t cmask = (1u << c->count_bits) - 1u;
     try {
         if (cd_row_ptr) {
             std::vector<uint2> rec((size_t)c->D);
@@ -1786,8 +1791,8 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
                         const uint32_t *row = (const uint32_t *)host + ((int64_t)rec[(size_t)d].x * 32 - cuts[(size_t)i]);
                         int64_t o = cd_row_ptr[d];
                         for (uint32_t j = 0; j < rec[(size_t)d].y; j++, o++) {
-                            if (cd_topic) cd_topic[o] = (int32_t)(row[j] & c->topic_mask);
-                            if (cd_count) cd_count[o] = (int32_t)(row[j] >> c->topic_bits);
+                            if (cd_topic) cd_topic[o] = (int32_t)(row[j] >> c->count_bits);
+                            if (cd_count) cd_count[o] = (int32_t)(row[j] & cmask);
                         }
                     }
                 }));
@@ -1836,7 +1841,7 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
                         int32_t *row = cwk + (size_t)lwords[(size_t)li] * (size_t)c->K;
                         memset(row, 0, sizeof(int32_t) * (size_t)c->K);
                         const uint32_t *e = (const uint32_t *)host + ((int64_t)wrec[(size_t)li].x * 32 - cuts[(size_t)i]);
-                        for (uint32_t j = 0; j < wrec[(size_t)li].y; j++) row[e[j] & c->topic_mask] = (int32_t)(e[j] >> c->topic_bits);
+                        for (uint32_t j = 0; j < wrec[(size_t)li].y; j++) row[e[j] >> c->count_bits] = (int32_t)(e[j] & cmask);
                     }
                 }));
             }
@@ -2244,7 +2249,7 @@ extern "C" int saber_get_phi(saber_ctx *c, const int32_t *words, int32_t m, floa
     for (int64_t i = 0, k; i < m; i += k) {
         k = std::min<int64_t>(m - i, most_blocks(256));
         hipLaunchKernelGGL(phi_export_kernel, dim3((unsigned)k), dim3(256), 0, c->stream, drow + i, c->phi,
-                           c->phi + (size_t)c->V_dense * (size_t)c->Kpad, c->wrec, c->lw_ent, c->lw_phi, c->K, c->Kpad, c->topic_bits,
+                           c->phi + (size_t)c->V_dense * (size_t)c->Kpad, c->wrec, c->lw_ent, c->lw_phi, c->K, c->Kpad, c->count_bits,
                            drows + (size_t)i * (size_t)c->K);
         HIP_TRY(hipGetLastError());
     }

@@ -22,7 +22,7 @@ struct DocMajorParams {
     unsigned long long *n_dense;
     int64_t D;
     int K, Kpad, n3, n3pad;
-    uint32_t topic_bits, topic_mask;
+    uint32_t count_bits;
     float alpha;
     uint32_t seed_lo, seed_hi, iter;
 };
@@ -41,7 +41,7 @@ __global__ void __launch_bounds__(256) estep_docmajor_kernel(DocMajorParams p) {
     const int kd = (int)rec.y;
     const uint32_t *row = p.cd_ent + (size_t)rec.x * 32u;
     const int nblk = (kd + 4 * kWave - 1) / (4 * kWave);
-    const uint32_t bits = p.topic_bits, tmask = p.topic_mask;
+    const uint32_t cbits = p.count_bits;
     const uint4 e0 = load_block(row, kd, lane);   // first 256 entries of the document's row stay in registers
     uint4 e1 = make_uint4(0u, 0u, 0u, 0u);
     if (nblk >= 2) e1 = load_block(row + 4 * kWave, kd - 4 * kWave, lane);
@@ -63,16 +63,16 @@ __global__ void __launch_bounds__(256) estep_docmajor_kernel(DocMajorParams p) {
             const float *__restrict__ phi_row = p.phi + (size_t)readlane_u32((uint32_t)my_row, j) * (size_t)p.Kpad;
             const float Q = p.alpha * readlane_f32(my_sum, j);
             RowBlock b0, b1;
-            block_products<false, false>(e0, bits, tmask, nullptr, phi_row, b0);
+            block_products<false, PACK_ANY>(e0, cbits, nullptr, phi_row, b0);
             const float t0 = readlane_f32(b0.incl, 63);
             float t1 = 0.f, S = t0;
             if (nblk >= 2) {
-                block_products<false, false>(e1, bits, tmask, nullptr, phi_row, b1);
+                block_products<false, PACK_ANY>(e1, cbits, nullptr, phi_row, b1);
                 t1 = readlane_f32(b1.incl, 63);
                 S = t0 + t1;
                 for (int blk = 2; blk < nblk; blk++) {
                     RowBlock bb;
-                    block_products<false, false>(load_block(row + blk * 4 * kWave, kd - blk * 4 * kWave, lane), bits, tmask,
+                    block_products<false, PACK_ANY>(load_block(row + blk * 4 * kWave, kd - blk * 4 * kWave, lane), cbits,
                                                  nullptr, phi_row, bb);
                     S = S + readlane_f32(bb.incl, 63);
                 }
@@ -81,8 +81,8 @@ __global__ void __launch_bounds__(256) estep_docmajor_kernel(DocMajorParams p) {
             if (u0j * (S + Q) < S) {
                 const float x = u1j * S;
                 uint32_t topic;
-                if (nblk == 1 || t0 >= x) topic = search_block(e0, b0, 0.f, x, kd, tmask);
-                else if (nblk == 2 || t0 + t1 >= x) topic = search_block(e1, b1, t0, x, kd - 4 * kWave, tmask);
+                if (nblk == 1 || t0 >= x) topic = search_block(e0, b0, 0.f, x, kd) >> cbits;
+                else if (nblk == 2 || t0 + t1 >= x) topic = search_block(e1, b1, t0, x, kd - 4 * kWave) >> cbits;
                 else {
                     float carry = t0 + t1;
                     topic = 0u;
@@ -90,9 +90,9 @@ __global__ void __launch_bounds__(256) estep_docmajor_kernel(DocMajorParams p) {
                         const int rel = kd - blk * 4 * kWave;
                         const uint4 e = load_block(row + blk * 4 * kWave, rel, lane);
                         RowBlock bb;
-                        block_products<false, false>(e, bits, tmask, nullptr, phi_row, bb);
+                        block_products<false, PACK_ANY>(e, cbits, nullptr, phi_row, bb);
                         const float tot = readlane_f32(bb.incl, 63);
-                        if (blk == nblk - 1 || carry + tot >= x) { topic = search_block(e, bb, carry, x, rel, tmask); break; }
+                        if (blk == nblk - 1 || carry + tot >= x) { topic = search_block(e, bb, carry, x, rel) >> cbits; break; }
                         carry = carry + tot;
                     }
                 }
@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(256) sort_keys_kernel(const int64_t *doc_ptr, 
 // wavefront per document: every first key of a topic opens an entry (topic, count 0) at its rank in the row, every
 // token notes the rank of its entry; the row's length and padding are written as CountByDZ does.
 __global__ void __launch_bounds__(256) sort_mark_kernel(const int64_t *doc_ptr, const uint64_t *keys, int64_t D,
-                                                        uint32_t topic_mask, uint2 *docrec, uint32_t *cd_ent,
+                                                        uint32_t count_bits, uint2 *docrec, uint32_t *cd_ent,
                                                         uint32_t *rank_of) {
     const int lane = lane_id();
     const int64_t d = (int64_t)blockIdx.x * (int64_t)(blockDim.x / kWave) + (int64_t)(threadIdx.x / kWave);
@@ -162,13 +162,13 @@ __global__ void __launch_bounds__(256) sort_mark_kernel(const int64_t *doc_ptr, 
     for (int64_t b = begin; b < end; b += kWave) {
         const int64_t t = b + lane;
         const bool act = t < end;
-        const uint32_t topic = act ? (uint32_t)keys[t] & topic_mask : 0xffffffffu;
+        const uint32_t topic = act ? (uint32_t)keys[t] & (0xffffffffu >> count_bits) : 0xffffffffu;
         uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)0, (int)topic, 0x138, 0xf, 0xf, false);   // wave_shr:1
         if (lane == 0) prev = prev_last;
         const uint32_t flag = (act && topic != prev) ? 1u : 0u;
         const uint32_t incl = wave_incl_scan(flag);
         const uint32_t rank = carry + incl - 1u;          // entry of this token (incl >= 1 for every active lane after the first key)
-        if (flag) row[rank] = topic;
+        if (flag) row[rank] = topic << count_bits;
         if (act) rank_of[t] = rank;
         carry += readlane_u32(incl, kWave - 1);
         const int n = (int)((end - b) < (int64_t)kWave ? (end - b) : (int64_t)kWave);
@@ -178,20 +178,20 @@ __global__ void __launch_bounds__(256) sort_mark_kernel(const int64_t *doc_ptr, 
     const int kd = (int)carry;
     if (lane < 4) {
         const int r = kd + lane;
-        if (r < ((kd + 3) & ~3)) row[r] = last_topic;
+        if (r < ((kd + 3) & ~3)) row[r] = last_topic << count_bits;
     }
     if (lane == 0) docrec[d].y = (uint32_t)kd;
 }
 
 // one count per token into the entry marked for it
 __global__ void __launch_bounds__(256) sort_count_kernel(const int64_t *doc_ptr, const uint32_t *rank_of, int64_t D,
-                                                         const uint2 *docrec, uint32_t *cd_ent, uint32_t topic_bits) {
+                                                         const uint2 *docrec, uint32_t *cd_ent) {
     const int lane = lane_id();
     const int64_t d = (int64_t)blockIdx.x * (int64_t)(blockDim.x / kWave) + (int64_t)(threadIdx.x / kWave);
     if (d >= D) return;
     const int64_t begin = doc_ptr[d], end = doc_ptr[d + 1];
     uint32_t *row = cd_ent + (size_t)docrec[d].x * 32u;
-    for (int64_t t = begin + lane; t < end; t += kWave) atomicAdd(&row[rank_of[t]], 1u << topic_bits);
+    for (int64_t t = begin + lane; t < end; t += kWave) atomicAdd(&row[rank_of[t]], 1u);
 }
 
 // ---- alias tables (the alternative to the tree that Sec. 3.2.3 weighs) ----

@@ -215,7 +215,7 @@ struct EStepParams {
     const int32_t *tok_doc;     // [chunk tokens] document of the token (global document id)
     const uint32_t *tok_t;      // [chunk tokens] canonical token index relative to t_base
     const uint2 *docrec;        // [D] {row start in units of 32 entries, K_d}
-    const uint32_t *cd_rows;    // packed rows of A (topic | count << topic_bits, ascending topic) from the first row of
+    const uint32_t *cd_rows;    // packed rows of A (count | topic << count_bits, ascending topic) from the first row of
                                 // the chunk's documents on: the row of document d starts (docrec[d].x - row_unit0) * 32
                                 // entries into it
     uint32_t row_unit0;         // row start of the chunk's first document
@@ -248,7 +248,7 @@ struct EStepParams {
     int64_t t_base;             // canonical index of the chunk's first token
     int64_t z_rel;              // position of that token in z
     int32_t K, Kpad, n3, n3pad;
-    uint32_t topic_bits, topic_mask;
+    uint32_t count_bits;        // low bits of an entry that hold its count
     float alpha;
     uint32_t seed_lo, seed_hi, iter;
 };
@@ -401,8 +401,14 @@ __device__ __forceinline__ uint32_t dense_query4_staged(uint32_t phi_bytes, uint
 //   * longer rows: one run at a time over all 64 lanes, in blocks of 256 entries.
 // A lane's 16 entries sit in the same order in all three layouts and a DPP scan never crosses the lanes of a
 // group, so the sums come out bit-identical whichever layout a row gets.
-// B16: entries are packed topic:16 | count:16 (compile-time shifts); otherwise topic_bits is a run-time value.
+// PACK: how an entry holds its topic (in the high bits) and its count (in the low ones).
 // ---------------------------------------------------------------------------------------------
+enum {
+    PACK_ANY = 0,     // count_bits is a run-time value
+    PACK_16 = 1,      // 16 bits each
+    PACK_16_14 = 2,   // 16 bits each, and all counts below 2^14: the entry shifted down by 14 is then the topic times 4
+};
+
 struct RowBlock { float a0, a1, a2, a3, incl; };   // running sums inside the lane; inclusive scan of lane sums
 
 // One 256-entry block of a row: lane l receives entries 4l..4l+3 through a buffer load whose descriptor ends
@@ -412,20 +418,6 @@ __device__ __forceinline__ uint4 load_block(const uint32_t *row, int rel_kd, int
     const int bytes = rel_kd > 0 ? ((rel_kd + 3) & ~3) * 4 : 0;
     __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)row, (short)0, bytes, 0x00020000);
     const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, 0, 0);
-    return make_uint4(v[0], v[1], v[2], v[3]);
-}
-
-// The same for a row given by its address and padded length in bytes (wave-uniform values).
-__device__ __forceinline__ uint4 load_block(const void *row, uint32_t row_bytes, int lane) {
-    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(row), (short)0, (int)row_bytes, 0x00020000);
-    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, 0, 0);
-    return make_uint4(v[0], v[1], v[2], v[3]);
-}
-
-// The second 256-entry block of the same row (same descriptor, 1 KB further on).
-__device__ __forceinline__ uint4 load_block2(const void *row, uint32_t row_bytes, int lane) {
-    __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(row), (short)0, (int)row_bytes, 0x00020000);
-    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16, 16 * kWave, 0);
     return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
@@ -442,6 +434,13 @@ __device__ __forceinline__ unsigned long long clear_bit(unsigned long long m, in
     return m;
 }
 
+// lowest set bit of a wave-uniform mask, -1 if there is none
+__device__ __forceinline__ int first_bit(unsigned long long m) {
+    int i;
+    asm("s_ff1_i32_b64 %0, %1" : "=s"(i) : "s"(m));
+    return i;
+}
+
 // lane permutations through the LDS crossbar (no LDS memory is touched); lane numbers are passed times 4
 __device__ __forceinline__ uint32_t lane_pull(uint32_t v, uint32_t src_lane4) {
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)src_lane4, (int)v);      // every lane reads lane src
@@ -452,6 +451,11 @@ __device__ __forceinline__ float lane_pull(float v, uint32_t src_lane4) {
 __device__ __forceinline__ uint32_t lane_push(uint32_t v, uint32_t dst_lane4) {
     return (uint32_t)__builtin_amdgcn_ds_permute((int)dst_lane4, (int)v);       // every lane writes lane dst; the
 }                                                                               // highest writer wins, unwritten lanes get 0
+
+// lane 31's value in lanes 0 to 31, lane 63's in the others (a fixed pattern takes 2.3 cycles of a CU's LDS, a pull 6.1)
+__device__ __forceinline__ float half_last(float v) {
+    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 31 << 5));
+}
 
 // number of set bits of a wave-uniform mask at this lane or below it
 __device__ __forceinline__ uint32_t bits_up_to_lane(unsigned long long m) {
@@ -472,20 +476,22 @@ __device__ __forceinline__ float group_incl_scan(float v) {
     return v;
 }
 
-// Bhat value of the entry's topic.  With 16/16 packing and the row in LDS the byte offset (topic * 4) is formed
-// by one shift that reads the low half of the entry.
-template <bool STAGED, bool B16>
-__device__ __forceinline__ float phi_of(uint32_t e, uint32_t tmask, const float *lds_phi, const float *__restrict__ phi_row, const Overlay &ov) {
-    if (STAGED && B16) {
+// Bhat value of the entry's topic.  With 16/16 packing and the row in LDS the byte offset (topic * 4) is formed by one shift: of the
+// entry where nothing of the count gets into it, otherwise one that reads the entry's high half (4.5 cycles of the vector unit
+// against 2.5).
+template <bool STAGED, int PACK>
+__device__ __forceinline__ float phi_of(uint32_t e, uint32_t cbits, const float *lds_phi, const float *__restrict__ phi_row, const Overlay &ov) {
+    if (STAGED && PACK != PACK_ANY) {
         uint32_t off;
-        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
-            : "=v"(off) : "v"(2u), "v"(e));
+        if (PACK == PACK_16_14) off = e >> 14;
+        else asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+                 : "=v"(off) : "v"(2u), "v"(e));
         // the staged row starts at LDS address 0 (the kernel has no static LDS; the host checks that at start-up)
         typedef __attribute__((address_space(3))) const float lds_cfloat;
         return *reinterpret_cast<lds_cfloat *>(off);
     }
-    if (STAGED) return lds_phi[e & tmask];
-    const uint32_t k = e & tmask;
+    const uint32_t k = e >> cbits;
+    if (STAGED) return lds_phi[k];
     const float *src = phi_row + k;
     if (ov.light) {   // the value is where the mark says: one load either way
         const uint2 m = ov.marks[k >> 5];
@@ -496,31 +502,34 @@ __device__ __forceinline__ float phi_of(uint32_t e, uint32_t tmask, const float 
 }
 
 // element-wise product A_d (.) Bhat_v of the lane's four entries as running sums, and their scan over the group
-template <bool STAGED, bool B16, int G = kWave>
-__device__ __forceinline__ void block_products(const uint4 e, uint32_t bits, uint32_t tmask,
-                                               const float *lds_phi, const float *__restrict__ phi_row, RowBlock &b, const Overlay &ov = Overlay()) {
-    const float f0 = phi_of<STAGED, B16>(e.x, tmask, lds_phi, phi_row, ov);
-    const float f1 = phi_of<STAGED, B16>(e.y, tmask, lds_phi, phi_row, ov);
-    const float f2 = phi_of<STAGED, B16>(e.z, tmask, lds_phi, phi_row, ov);
-    const float f3 = phi_of<STAGED, B16>(e.w, tmask, lds_phi, phi_row, ov);
-    b.a0 = (float)(e.x >> bits) * f0;
-    b.a1 = __builtin_fmaf((float)(e.y >> bits), f1, b.a0);
-    b.a2 = __builtin_fmaf((float)(e.z >> bits), f2, b.a1);
-    b.a3 = __builtin_fmaf((float)(e.w >> bits), f3, b.a2);
+template <bool STAGED, int PACK, int G = kWave>
+__device__ __forceinline__ void block_products(const uint4 e, uint32_t cbits, const float *lds_phi, const float *__restrict__ phi_row,
+                                               RowBlock &b, const Overlay &ov = Overlay()) {
+    const float f0 = phi_of<STAGED, PACK>(e.x, cbits, lds_phi, phi_row, ov);
+    const float f1 = phi_of<STAGED, PACK>(e.y, cbits, lds_phi, phi_row, ov);
+    const float f2 = phi_of<STAGED, PACK>(e.z, cbits, lds_phi, phi_row, ov);
+    const float f3 = phi_of<STAGED, PACK>(e.w, cbits, lds_phi, phi_row, ov);
+    const uint32_t cmask = PACK != PACK_ANY ? 0xffffu : (1u << cbits) - 1u;
+    b.a0 = (float)(e.x & cmask) * f0;
+    b.a1 = __builtin_fmaf((float)(e.y & cmask), f1, b.a0);
+    b.a2 = __builtin_fmaf((float)(e.z & cmask), f2, b.a1);
+    b.a3 = __builtin_fmaf((float)(e.w & cmask), f3, b.a2);
     b.incl = group_incl_scan<G>(b.a3);
 }
 
 // First entry of the block whose prefix sum (carry + sums inside the block) reaches x.  The lane is found
 // with one ballot over the lanes' inclusive sums, the entry inside it with three compares.  If rounding
-// leaves no entry, the choice falls on the block's last one (a row's padding repeats its last topic).
-__device__ __forceinline__ uint32_t search_block(const uint4 e, const RowBlock &b, float carry, float x, int rel_kd,
-                                                 uint32_t tmask) {
+// leaves no entry, the choice falls on the block's last one (a row's padding repeats its last topic).  Returns the entry.
+__device__ __forceinline__ uint32_t search_block(const uint4 e, const RowBlock &b, float carry, float x, int rel_kd) {
     const float base = carry + (b.incl - b.a3);
     const unsigned long long m3 = __builtin_amdgcn_ballot_w64(carry + b.incl >= x);
     const int nvalid = rel_kd < 4 * kWave ? rel_kd : 4 * kWave;
     const int L = m3 ? (int)__builtin_ctzll(m3) : ((nvalid - 1) >> 2);
-    const uint32_t sel = (base + b.a0 >= x) ? e.x : (base + b.a1 >= x) ? e.y : (base + b.a2 >= x) ? e.z : e.w;
-    return readlane_u32(sel, L) & tmask;
+    uint32_t sel = e.w;
+    sel = base + b.a2 >= x ? e.z : sel;
+    sel = base + b.a1 >= x ? e.y : sel;
+    sel = base + b.a0 >= x ? e.x : sel;
+    return readlane_u32(sel, L);
 }
 
 // The kernel's parameters where the hardware left them, read again from there (constant memory, scalar loads).  The compiler reads
@@ -547,7 +556,7 @@ template <typename T> __device__ __forceinline__ ConstMem<T> *const_mem(const T 
 // A light word keeps B sparse: its Bhat row is built in LDS from the base vector and the word's non-zeros (staged rows have
 // 16-bit assignments then), or where LDS cannot hold a row read from memory with marks in LDS (Overlay).  Tiles of both kinds share a launch: a launch of its own for the light words cost a small
 // corpus 10 of its 47 us per iteration (T = 100 K, K = 100), a large one the tail of the other.
-template <int MODE, bool STAGED, typename ZT, bool B16>
+template <int MODE, bool STAGED, typename ZT, int PACK>
 __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     extern __shared__ float4 lds_f4[];
     // LDS, all of it dynamic so that the Bhat row starts at address 0 and a gather needs no base added:
@@ -633,7 +642,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         for (int i = threadIdx.x; i < (K + 31) >> 5; i += blockDim.x) marks[i].x = 0u;
         __syncthreads();
         for (int j = threadIdx.x; j < (int)wr.y; j += blockDim.x) {   // (ascending topics)
-            const uint32_t k = ent[j] & p.topic_mask, before = j ? ent[j - 1] & p.topic_mask : 0xffffffffu;
+            const uint32_t k = ent[j] >> p.count_bits, before = j ? ent[j - 1] >> p.count_bits : 0xffffffffu;
             atomicOr(&marks[k >> 5].x, 1u << (k & 31u));
             if (before >> 5 != k >> 5) marks[k >> 5].y = (uint32_t)j;
         }
@@ -646,17 +655,17 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         const uint2 wr = p.wrec[tile.row];
         const uint32_t *__restrict__ ent = p.lw_ent + (size_t)wr.x * 32u;
         const float *__restrict__ val = p.lw_phi + (size_t)wr.x * 32u;
-        const uint32_t tm = B16 ? 0xffffu : p.topic_mask;
+        const uint32_t cb = PACK != PACK_ANY ? 16u : p.count_bits;
         uint32_t e0 = 0u; float v0 = 0.f;
         if ((int)threadIdx.x < (int)wr.y) { e0 = ent[threadIdx.x]; v0 = val[threadIdx.x]; }
         __syncthreads();
-        if ((int)threadIdx.x < (int)wr.y) lds_phi[e0 & tm] = v0;
-        for (int j = threadIdx.x + blockDim.x; j < (int)wr.y; j += blockDim.x) lds_phi[ent[j] & tm] = val[j];
+        if ((int)threadIdx.x < (int)wr.y) lds_phi[e0 >> cb] = v0;
+        for (int j = threadIdx.x + blockDim.x; j < (int)wr.y; j += blockDim.x) lds_phi[ent[j] >> cb] = val[j];
     }
     __syncthreads();
     float sum_w = *const_mem(p.sumphi + tile.word);
     float Q = first_lane(p.alpha * sum_w);
-    const uint32_t bits = B16 ? 16u : p.topic_bits, tmask = B16 ? 0xffffu : p.topic_mask;
+    const uint32_t cbits = PACK != PACK_ANY ? 16u : p.count_bits;
     int count = tile.count;
     // The tiles of the workgroup.  More than one, and then of light words, is for sampling from staged rows with 16-bit assignments:
     // bound by the chain from a tile's record to its rows of A, and by staging a row per tile before that (80 KB at K = 20,011:
@@ -682,29 +691,36 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             u0 = unit24(r.r0); u1 = unit24(r.r1);
         }
         uint32_t my_z = 0; float my_S = 0.f;
-        unsigned long long dense_mask = 0ull;
+        unsigned long long sparse_mask = 0ull;   // tokens that take the sparse branch
 
         // Runs: bit i of `starts` marks a lane where the tokens of another document begin.
         const int d_prev = __builtin_amdgcn_update_dpp(-2, d, 0x138, 0xf, 0xf, false);   // wave_shr:1
-        const bool first_of_run = act && (d != d_prev || (MODE == MODE_PROBS && p.marks));
-        const unsigned long long starts = __builtin_amdgcn_ballot_w64(first_of_run) | (MODE == MODE_PROBS && p.marks ? 0ull : 1ull);
+        // (masks of the active lanes by a scalar AND: a compare of both at once goes by way of a vector register)
+        const unsigned long long acts = __builtin_amdgcn_ballot_w64(act);
+        const bool alone = MODE == MODE_PROBS && p.marks;
+        const unsigned long long starts = ((alone ? ~0ull : __builtin_amdgcn_ballot_w64(d != d_prev)) & acts) | (alone ? 0ull : 1ull);
         // the row of the lane's document: byte offset inside the chunk's rows and padded length in bytes
         const uint32_t row_off = (rec.x - row_unit0) << 7;
         const uint32_t row_bytes = ((rec.y + 3u) & ~3u) << 2;
+        const int row_last = (int)(row_bytes >> 4) - 1;   // number of its last piece of 16 bytes
         // position of the token inside its run
-        const uint32_t jpos = (uint32_t)(lane - wave_incl_scan_max(first_of_run || lane == 0 ? lane : -1));
+        const uint32_t jpos = (uint32_t)(lane - wave_incl_scan_max(__builtin_amdgcn_inverse_ballot_w64(starts | 1ull) ? lane : -1));
         // rows that fit a quarter or a half of the wavefront; runs are cut into pieces of at most G tokens there
         const uint32_t quarter = q->quarter_row_bytes, half = q->half_row_bytes;
-        unsigned long long m16 = __builtin_amdgcn_ballot_w64(act && row_bytes <= quarter);
-        unsigned long long m32 = __builtin_amdgcn_ballot_w64(act && row_bytes <= half) & ~m16;
-        const unsigned long long cuts16 = __builtin_amdgcn_ballot_w64(act && (jpos & 15u) == 0u);   // where pieces begin
-        const unsigned long long cuts32 = __builtin_amdgcn_ballot_w64(act && (jpos & 31u) == 0u);
+        unsigned long long m16 = __builtin_amdgcn_ballot_w64(row_bytes <= quarter) & acts;
+        unsigned long long m32 = __builtin_amdgcn_ballot_w64(row_bytes <= half) & acts & ~m16;
+        const unsigned long long cuts16 = __builtin_amdgcn_ballot_w64((jpos & 15u) == 0u) & acts;   // where pieces begin
+        const unsigned long long cuts32 = __builtin_amdgcn_ballot_w64((jpos & 31u) == 0u) & acts;
         // a pass serves four (two) runs at the cost of about one: a class that would not fill most of one pass goes
         // with the next wider one
         if (__builtin_popcountll(m16 & cuts16) < 3) { if (half >= quarter) m32 |= m16; m16 = 0ull; }
         if (__builtin_popcountll(m32 & cuts32) < 2) m32 = 0ull;
         const unsigned long long cm16 = m16 & cuts16, cm32 = m32 & cuts32;
-        unsigned long long wide_rest = starts & ~(m16 | m32);
+        // longer rows: the tokens of those of one block (256 entries), and of several; the last token of each of their runs
+        unsigned long long wide = __builtin_amdgcn_ballot_w64(row_bytes <= 16u * kWave) & acts & ~(m16 | m32);
+        unsigned long long large = acts & ~(m16 | m32 | wide);
+        const unsigned long long ends = alone ? acts : (starts >> 1) | (1ull << (n - 1));
+        unsigned long long wide_ends = ends & wide, large_ends = ends & large;
 
         // ---- rows of at most 4 G entries: 64 / G runs at a time, one per group of G lanes ----
         // Token side: lane i holds token i of the batch.  Group side: the G lanes of group g hold the row of the
@@ -738,21 +754,21 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             const uint32_t jg4 = (jpos & (uint32_t)(G - 1)) << 2;           // and its place in it, times 4
             constexpr unsigned long long ONES = G == 16 ? 0x0001000100010001ull : 0x0000000100000001ull;   // first lane of every group
 
-            // request the rows of pass `ps` (past the last pass: nothing is moved)
-            auto issue = [&](const int ps, uint4 &blk, uint32_t &pk) {
-                uint32_t idx = (uint32_t)(ps * NG) + gi;
-                idx = idx < (uint32_t)nruns ? idx : (uint32_t)(nruns - 1);   // spare groups repeat the last run
-                pk = lane_pull(slot_pk, idx << 2);
-                const uint32_t off = lane_pull(slot_off, idx << 2);
-                const uint32_t lim = ps < npass ? pk & 0xffffu : 0u;
-                blk = load_rows_at(rows, li16 < lim ? off + li16 : 0xffffffffu);
+            // Request the rows of the next pass.  Slots that no piece was put in read as rows of length 0, which move no data
+            // (slot 63, and past the last of all, as some row of the batch): nothing is looked at of what a spare group gets.
+            uint32_t slot4 = gi << 2;
+            auto issue = [&](uint4 &blk, uint32_t &pk) {
+                pk = lane_pull(slot_pk, slot4);
+                const uint32_t off = lane_pull(slot_off, slot4);
+                slot4 += (uint32_t)NG << 2;
+                blk = load_rows_at(rows, li16 < (pk & 0xffffu) ? off + li16 : 0xffffffffu);
             };
             auto compute = [&](const int ps, const uint4 &cur, const uint32_t pk) {
                 RowBlock b;
-                block_products<STAGED, B16, G>(cur, bits, tmask, lds_phi, phi_row, b, ov);
+                block_products<STAGED, PACK, G>(cur, cbits, lds_phi, phi_row, b, ov);
                 // S of the group's run in all its lanes
                 const float S = G == 16 ? dpp_f32<0x15f, 0xf>(b.incl)                    // row_newbcast:15
-                                        : lane_pull(b.incl, (uint32_t)(lane | (G - 1)) << 2);
+                                        : half_last(b.incl);
                 // token side: is this token's piece part of the pass, and which lane will hold its result
                 const uint32_t gt = my_piece - (uint32_t)(ps * NG);
                 const bool in_pass = gt < (uint32_t)NG;
@@ -795,165 +811,194 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
                 my_S = in_pass ? St : my_S;
                 if (MODE == MODE_SAMPLE) {
                     const uint32_t zt = lane_pull(zacc, src4);
-                    my_z = in_pass ? zt & tmask : my_z;
+                    my_z = in_pass ? zt : my_z;
                 }
             };
             uint4 blk_a, blk_b; uint32_t pk_a, pk_b;
-            issue(0, blk_a, pk_a);
+            issue(blk_a, pk_a);
             for (int ps = 0;; ps += 2) {
-                issue(ps + 1, blk_b, pk_b);
+                issue(blk_b, pk_b);
                 compute(ps, blk_a, pk_a);
                 if (ps + 1 >= npass) break;
-                issue(ps + 2, blk_a, pk_a);
+                issue(blk_a, pk_a);
                 compute(ps + 1, blk_b, pk_b);
                 if (ps + 2 >= npass) break;
             }
         };
-        // ---- longer rows: one run [s, s_end) at a time over the whole wavefront ----
-        // `cur` and `cur2` hold the first two blocks of the run's row (fetched during the previous run) and cur_bytes the
-        // row's padded length; the next run's row is fetched into `nxt`, `nxt2` before this run's arithmetic starts.
-        auto fetch = [&](const int s, uint4 &blk, uint4 &blk2, uint32_t &bytes) {
-            // Requested without any branch around the two loads: for s < 0 (no further run), and for the second
-            // block of a short row, the descriptor's length makes every lane fall outside the row, which returns zeros
-            // and moves no data.  A load inside a branch would make the compiler wait for ALL outstanding loads where
-            // the branches meet, i.e. for the row just requested, before the current run's arithmetic.
-            const int src = s < 0 ? 0 : s;
-            bytes = s < 0 ? 0u : readlane_u32(row_bytes, src);
-            const void *row = rows_base + readlane_u32(row_off, src);
-            blk = load_block(row, bytes, lane);
-            blk2 = load_block2(row, bytes, lane);
+        // ---- longer rows: one run at a time over the whole wavefront ----
+        // `cur` holds the run's row (its first block), `last` the number of the row's last piece of 16 bytes; the next run's row
+        // is fetched into `nxt` before this run's arithmetic starts.  Rows of several blocks have a loop of their own, so that
+        // no load that is made for a longer row only is waited for on the way of the others.
+        float Qv = Q;
+        asm volatile("" : "+v"(Qv));   // (beside a run's S, which is in a scalar register, an addition takes no second one)
+        int lane16 = lane * 16;
+        // The row is a piece of the chunk's rows: its offset is the load's scalar one, its end the descriptor's length, so a lane
+        // past the end reads zeros and moves no data.
+        auto row_at = [&](const int last, const uint32_t off) {
+            return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(rows_base), (short)0, (int)(off + (uint32_t)(last + 1) * 16u), 0x00020000);
         };
-        auto next_wide = [&]() {
-            if (!wide_rest) return -1;
-            const int s = (int)__builtin_ctzll(wide_rest);
-            wide_rest = clear_bit(wide_rest, s);
-            return s;
+        auto fetch = [&](const int e, uint4 &blk, int &last, uint32_t &off) {
+            // Requested without any branch around the load: a load inside a branch would make the compiler wait for ALL
+            // outstanding loads where the branches meet, i.e. for the row just requested, before the current run's
+            // arithmetic.  Without a further run (e < 0) it is lane 63's row, which the batch has read as a rule, or nothing.
+            last = (int)readlane_u32((uint32_t)row_last, e);
+            off = readlane_u32(row_off, e);
+            asm volatile("" : "+v"(lane16));
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(row_at(last, off), lane16, (int)off, 0);
+            blk = make_uint4(v[0], v[1], v[2], v[3]);
         };
-        // the first of the long rows is requested now, so that it arrives while the short rows are worked on
-        int s_a = next_wide(), s_b = -1;
-        uint32_t bytes_a, bytes_b;
-        uint4 blk_a, blk_a2, blk_b, blk_b2;
-        fetch(s_a, blk_a, blk_a2, bytes_a);
+        // block 1, 2, ... of the same row (past its end: zeros, and no data moves)
+        auto fetch_more = [&](const int last, const uint32_t off, const int block) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(row_at(last, off), lane16, (int)(off + (uint32_t)block * 16u * kWave), 0);
+            return make_uint4(v[0], v[1], v[2], v[3]);
+        };
+        // the first rows are requested now, so that they arrive while the short rows are worked on
+        int e_a = first_bit(wide_ends), e_b, e_c = first_bit(large_ends), e_d, last_a, last_b, last_c, last_d;
+        uint32_t off_a, off_b, off_c, off_d;
+        uint4 blk_a, blk_b, blk_c, blk_c2, blk_d, blk_d2;
+        fetch(e_a, blk_a, last_a, off_a);
+        fetch(e_c, blk_c, last_c, off_c);
+        blk_c2 = fetch_more(last_c, off_c, 1);
 
         run_class(std::integral_constant<int, 16>{}, cm16, cuts16, __builtin_amdgcn_inverse_ballot_w64(m16));
         run_class(std::integral_constant<int, 32>{}, cm32, cuts32, __builtin_amdgcn_inverse_ballot_w64(m32));
         if (MODE == MODE_SAMPLE && (m16 | m32)) {
             // the coin of the tokens served above, all at once
-            const unsigned long long sparse = __builtin_amdgcn_ballot_w64(u0 * (my_S + Q) < my_S);
-            dense_mask = (m16 | m32) & ~sparse;
+            sparse_mask = __builtin_amdgcn_ballot_w64(u0 * (my_S + Q) < my_S) & (m16 | m32);
         }
 
-        // ---- longer rows: one run [s, s_end) at a time over the whole wavefront (its first fetch went out above) ----
-        auto do_run = [&](const int s, const uint4 &cur, const uint4 &cur2, const uint32_t cur_bytes, const int s_next, uint4 &nxt,
-                          uint4 &nxt2, uint32_t &nxt_bytes) {
-            fetch(s_next, nxt, nxt2, nxt_bytes);
-            const unsigned long long later = starts & (~1ull << s);           // run starts after lane s
-            const int s_end = later ? (int)__builtin_ctzll(later) : n;
-            const unsigned long long in_run = (~0ull >> (kWave - s_end)) & (~0ull << s);   // 0 <= s < s_end <= 64
+        // ---- longer rows (the first fetches went out above) ----
+        // Bound by instructions of both kinds: the vector unit takes 2.5 cycles (additions, shifts, products) or 4.3 to 4.6 (compares,
+        // DPP, SDWA, conversions, lane moves), and the scalar unit, one for a CU's four SIMDs, 4.3 per SIMD.  So the masks are walked
+        // by the runs' last tokens (a dozen scalar instructions per run and six per token, where a walk by first tokens took
+        // 42 and 8), and rows of one block share no code with longer ones.  Sampling pass, late iterations, with the shift in phi_of: T = 10 M,
+        // K = 1,000 0.61 -> 0.56 ms, T = 100 M, K = 10,000 6.71 -> 6.43.
+        // Takes the run that ends at lane e out of `tokens`: the lanes of the run (those before it have been taken).
+        auto take_run = [&](const int e, unsigned long long &tokens) {
+            const unsigned long long beyond = ~1ull << e, run = tokens & ~beyond;
+            tokens &= beyond;
+            return run;
+        };
+        auto do_wide = [&](const int e, const uint4 &cur, const int last, int &e_next, uint4 &nxt, int &nxt_last, uint32_t &nxt_off) {
+            wide_ends = clear_bit(wide_ends, e);
+            e_next = first_bit(wide_ends);
+            fetch(e_next, nxt, nxt_last, nxt_off);
+            const unsigned long long in_run = take_run(e, wide);
             // element-wise product A_d (.) Bhat_v, its prefix sums and its sum S (Alg. 2, product loop)
-            RowBlock b0;
-            block_products<STAGED, B16>(cur, bits, tmask, lds_phi, phi_row, b0, ov);
-            const float t0 = readlane_f32(b0.incl, 63);
-            if (cur_bytes <= 16u * kWave) {
-                // the whole row sits in this block (the common case): straight-line coin and search
-                if (MODE == MODE_SAMPLE) {
-                    unsigned long long sparse = __builtin_amdgcn_ballot_w64(u0 * (t0 + Q) < t0) & in_run;
-                    dense_mask |= in_run & ~sparse;       // problem 2 is served after the runs, four tokens at a time
-                    if (sparse) {
-                        const float xs = u1 * t0;
-                        const float base = b0.incl - b0.a3;
-                        const float p0 = base + b0.a0, p1 = base + b0.a1, p2 = base + b0.a2;
-                        // lanes past the row's end repeat its last inclusive sum: if rounding leaves no lane, the
-                        // choice falls on the last one, whose padding repeats the row's last topic
-                        const unsigned long long last_lane_bit = 1ull << ((cur_bytes >> 4) - 1u);
-                        do {
-                            // problem 1: position of x in the prefix sums of P
-                            const int r = (int)__builtin_ctzll(sparse);
-                            sparse = clear_bit(sparse, r);
-                            const float x = readlane_f32(xs, r);
-                            const int L = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(b0.incl >= x) | last_lane_bit);
-                            uint32_t sel = cur.w;
-                            sel = p2 >= x ? cur.z : sel;
-                            sel = p1 >= x ? cur.y : sel;
-                            sel = p0 >= x ? cur.x : sel;
-                            my_z = llvm_amdgcn_writelane_u32(readlane_u32(sel, L) & tmask, (unsigned)r, my_z);
-                        } while (sparse);
-                    }
-                } else {
-                    if (lane >= s && lane < s_end) my_S = t0;
-                }
+            RowBlock b;
+            block_products<STAGED, PACK>(cur, cbits, lds_phi, phi_row, b, ov);
+            const float S = readlane_f32(b.incl, 63);
+            if (MODE != MODE_SAMPLE) {
+                if (__builtin_amdgcn_inverse_ballot_w64(in_run)) my_S = S;
                 return;
             }
-            const int kd = (int)(cur_bytes >> 2);   // the row's length rounded up to 4 entries: the padding has count 0
-            const uint32_t *row = reinterpret_cast<const uint32_t *>(rows_base + readlane_u32(row_off, s));
-            const int nblk = (kd + 4 * kWave - 1) / (4 * kWave);
-            const uint4 e1 = cur2;
-            RowBlock b1;
-            block_products<STAGED, B16>(e1, bits, tmask, lds_phi, phi_row, b1, ov);
-            const float t1 = readlane_f32(b1.incl, 63);
-            float S = t0 + t1;
-            float through = -1.f;   // lane i: sum through block i, from the third on (rows of up to 64 blocks)
+            // every lane evaluates the coin and the position for its own token; lanes of this run are used
+            unsigned long long sparse = __builtin_amdgcn_ballot_w64(u0 * (S + Qv) < S) & in_run;
+            sparse_mask |= sparse;                  // problem 2 is served after the runs, four tokens at a time
+            if (sparse) {
+                const float xs = u1 * S;
+                const float base = b.incl - b.a3;
+                const float p0 = base + b.a0, p1 = base + b.a1, p2 = base + b.a2;
+                do {
+                    // problem 1: position of x in the prefix sums of P.  If rounding leaves no lane of the row's, the choice falls
+                    // on its last one, whose padding repeats the row's last topic
+                    const int r = first_bit(sparse);
+                    sparse = clear_bit(sparse, r);
+                    const float x = readlane_f32(xs, r);
+                    const int L = (int)min((uint32_t)first_bit(__builtin_amdgcn_ballot_w64(b.incl >= x)), (uint32_t)last);
+                    uint32_t sel = cur.w;
+                    sel = p2 >= x ? cur.z : sel;
+                    sel = p1 >= x ? cur.y : sel;
+                    sel = p0 >= x ? cur.x : sel;
+                    my_z = llvm_amdgcn_writelane_u32(readlane_u32(sel, L), (unsigned)r, my_z);
+                } while (sparse);
+            }
+        };
+        auto do_large = [&](const int e, const uint4 &cur, const uint4 &cur2, const int last, const uint32_t off, int &e_next, uint4 &nxt,
+                            uint4 &nxt2, int &nxt_last, uint32_t &nxt_off) {
+            large_ends = clear_bit(large_ends, e);
+            e_next = first_bit(large_ends);
+            fetch(e_next, nxt, nxt_last, nxt_off);
+            nxt2 = fetch_more(nxt_last, nxt_off, 1);
+            const unsigned long long in_run = take_run(e, large);
+            RowBlock b0, b1;
+            block_products<STAGED, PACK>(cur, cbits, lds_phi, phi_row, b0, ov);
+            block_products<STAGED, PACK>(cur2, cbits, lds_phi, phi_row, b1, ov);
+            const float t0 = readlane_f32(b0.incl, 63);
+            float S = t0 + readlane_f32(b1.incl, 63);
+            float through = S;      // lane i: sum through block i, from the second on (rows of up to 64 blocks)
+            const int nblk = (last >> 6) + 1;
             if (nblk > 2) {
                 // The row of a long document, in the first iterations above all: one block after the other, the next one
                 // requested before the arithmetic of this.  The sums through each are kept, so that a draw reads only the
                 // block that holds it.  First iteration at T = 15 M, K = 20,011 (documents of 1,000 tokens, weighted by
                 // length): 7.0 -> 5.1 ms, at T = 100 M, K = 10,000 20.0 -> 19.0.  (Requested before the second block's
                 // arithmetic, and then by rows of two blocks too, the third one costs later iterations 1 %.)
-                uint4 en = load_block(row + 8 * kWave, kd - 8 * kWave, lane);
+                through = __builtin_amdgcn_inverse_ballot_w64(2ull) ? S : -1.f;
+                uint4 en = fetch_more(last, off, 2);
                 for (int blk = 2; blk < nblk; blk++) {
-                    const uint4 e = en;
-                    en = load_block(row + (blk + 1) * 4 * kWave, kd - (blk + 1) * 4 * kWave, lane);   // (past the end: zeros, and no data moves)
+                    const uint4 ec = en;
+                    if (blk + 1 < nblk) en = fetch_more(last, off, blk + 1);
                     RowBlock bb;
-                    block_products<STAGED, B16>(e, bits, tmask, lds_phi, phi_row, bb, ov);
+                    block_products<STAGED, PACK>(ec, cbits, lds_phi, phi_row, bb, ov);
                     S = S + readlane_f32(bb.incl, 63);
                     if (MODE == MODE_SAMPLE && blk < kWave)
                         through = __uint_as_float(llvm_amdgcn_writelane_u32(__float_as_uint(S), (unsigned)blk, __float_as_uint(through)));
                 }
             }
-            if (MODE == MODE_SAMPLE) {
-                // every lane evaluates the coin and the position for its own token; lanes of this run are used
-                const unsigned long long sparse = __builtin_amdgcn_ballot_w64(u0 * (S + Q) < S);
-                const float xs = u1 * S;
-                dense_mask |= ~sparse & in_run;
-                for (int r = s; r < s_end; r++) {
-                    uint32_t topic;
-                    if ((sparse >> r) & 1ull) {
-                        const float x = readlane_f32(xs, r);
-                        if (t0 >= x) topic = search_block(cur, b0, 0.f, x, kd, tmask);
-                        else if (nblk == 2 || t0 + t1 >= x) topic = search_block(e1, b1, t0, x, kd - 4 * kWave, tmask);
-                        else {
-                            // the block that holds the position is known from the sums above (beyond 64 blocks it is looked for)
-                            const unsigned long long reach = __builtin_amdgcn_ballot_w64(through >= x);
-                            int blk = reach ? (int)__builtin_ctzll(reach) : min(nblk, kWave) - 1;
-                            float carry = blk == 2 ? t0 + t1 : readlane_f32(through, blk - 1);
-                            topic = 0u;
-                            for (; blk < nblk; blk++) {
-                                const int rel = kd - blk * 4 * kWave;
-                                const uint4 e = load_block(row + blk * 4 * kWave, rel, lane);
-                                RowBlock bb;
-                                block_products<STAGED, B16>(e, bits, tmask, lds_phi, phi_row, bb, ov);
-                                const float tot = readlane_f32(bb.incl, 63);
-                                if (blk == nblk - 1 || carry + tot >= x) { topic = search_block(e, bb, carry, x, rel, tmask); break; }
-                                carry = carry + tot;
-                            }
-                        }
-                        my_z = llvm_amdgcn_writelane_u32(topic, (unsigned)r, my_z);
+            if (MODE != MODE_SAMPLE) {
+                if (__builtin_amdgcn_inverse_ballot_w64(in_run)) my_S = S;
+                return;
+            }
+            unsigned long long sparse = __builtin_amdgcn_ballot_w64(u0 * (S + Qv) < S) & in_run;
+            sparse_mask |= sparse;
+            const float xs = u1 * S;
+            while (sparse) {
+                const int r = first_bit(sparse);
+                sparse = clear_bit(sparse, r);
+                const float x = readlane_f32(xs, r);
+                uint32_t sel;
+                if (t0 >= x) sel = search_block(cur, b0, 0.f, x, kWave * 4);
+                else if (nblk == 2 || readlane_f32(through, 1) >= x) sel = search_block(cur2, b1, t0, x, 4 * (last + 1 - kWave));
+                else {
+                    // the block that holds the position is known from the sums above (beyond 64 blocks it is looked for)
+                    const unsigned long long reach = __builtin_amdgcn_ballot_w64(through >= x);
+                    int blk = reach ? (int)__builtin_ctzll(reach) : min(nblk, kWave) - 1;
+                    float carry = readlane_f32(through, blk - 1);
+                    sel = 0u;
+                    for (; blk < nblk; blk++) {
+                        const uint4 ec = fetch_more(last, off, blk);
+                        RowBlock bb;
+                        block_products<STAGED, PACK>(ec, cbits, lds_phi, phi_row, bb, ov);
+                        const float tot = readlane_f32(bb.incl, 63);
+                        if (blk == nblk - 1 || carry + tot >= x) { sel = search_block(ec, bb, carry, x, 4 * (last + 1 - blk * kWave)); break; }
+                        carry = carry + tot;
                     }
                 }
-            } else {
-                if (lane >= s && lane < s_end) my_S = S;
+                my_z = llvm_amdgcn_writelane_u32(sel, (unsigned)r, my_z);
             }
         };
 
-        if (s_a >= 0) {
+        if (wide) {
             for (;;) {
-                s_b = next_wide();
-                do_run(s_a, blk_a, blk_a2, bytes_a, s_b, blk_b, blk_b2, bytes_b);
-                if (s_b < 0) break;
-                s_a = next_wide();
-                do_run(s_b, blk_b, blk_b2, bytes_b, s_a, blk_a, blk_a2, bytes_a);
-                if (s_a < 0) break;
+                do_wide(e_a, blk_a, last_a, e_b, blk_b, last_b, off_b);
+                if (!wide_ends) break;
+                do_wide(e_b, blk_b, last_b, e_a, blk_a, last_a, off_a);
+                if (!wide_ends) break;
             }
+        }
+        if (large) {
+            for (;;) {
+                do_large(e_c, blk_c, blk_c2, last_c, off_c, e_d, blk_d, blk_d2, last_d, off_d);
+                if (!large_ends) break;
+                do_large(e_d, blk_d, blk_d2, last_d, off_d, e_c, blk_c, blk_c2, last_c, off_c);
+                if (!large_ends) break;
+            }
+        }
+        unsigned long long dense_mask = 0ull;
+        if (MODE == MODE_SAMPLE) {
+            my_z >>= cbits;                               // (so far the entries that the draws fell on)
+            dense_mask = acts & ~sparse_mask;
         }
 
         // The token's number is read again rather than carried through the batch in a register (the kernel is at its
@@ -1103,7 +1148,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     uint32_t k0 = 0u, e = 0u;
     float b0 = 0.f, v = 0.f, c = 0.f;
     if (tid < (int)wr.y) { e = ent[tid]; v = val[tid]; }
-    if (restore && tid < (int)wr0.y) { k0 = ent0[tid] & tmask; b0 = q->base[k0]; }
+    if (restore && tid < (int)wr0.y) { k0 = ent0[tid] >> cbits; b0 = q->base[k0]; }
     if (tid < n3) c = l3_row[tid];
     if (d >= 0) rec = q->docrec[d];
     sum_w = *const_mem(q->sumphi + tile->word);
@@ -1123,8 +1168,8 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     for (int i = tid + nt; i < n3; i += nt) lds_l3[i] = l3_row[i];
     if (tid == 0) reinterpret_cast<int *>(lds_phi)[K4] = nwaves;
     lds_barrier();
-    if (tid < (int)wr.y) lds_phi[e & tmask] = v;
-    for (int j = tid + nt; j < (int)wr.y; j += nt) lds_phi[ent[j] & tmask] = val[j];
+    if (tid < (int)wr.y) lds_phi[e >> cbits] = v;
+    for (int j = tid + nt; j < (int)wr.y; j += nt) lds_phi[ent[j] >> cbits] = val[j];
     lds_barrier();
     }
 
@@ -1337,7 +1382,7 @@ __device__ __forceinline__ void merge128(uint32_t &v0, uint32_t &v1, int lane) {
 // R = 1: segments of at most 64 assignments; R = 2: of at most 128, two keys per lane (lane i holds keys i and 64 + i).
 template <typename ZT, int R>
 __device__ __forceinline__ void count_segment_wave(const ZT *__restrict__ zs, int len, uint2 *rec, uint32_t *__restrict__ row,
-                                                   uint32_t topic_bits) {
+                                                   uint32_t count_bits) {
     const int lane = lane_id();
     constexpr uint32_t kNone = 0xffffffffu;
     uint32_t v0 = lane < len ? (uint32_t)zs[lane] : kNone;
@@ -1360,17 +1405,17 @@ __device__ __forceinline__ void count_segment_wave(const ZT *__restrict__ zs, in
         const unsigned long long above = (h0 >> lane) >> 1;                // topic starts at the lanes above this one
         const int next = above ? lane + 1 + (int)__builtin_ctzll(above) : after0;
         const uint32_t slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(h0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)h0, 0u));
-        if (__builtin_amdgcn_inverse_ballot_w64(h0)) row[slot] = v0 | ((uint32_t)(next - lane) << topic_bits);
+        if (__builtin_amdgcn_inverse_ballot_w64(h0)) row[slot] = (v0 << count_bits) | (uint32_t)(next - lane);
     }
     if (R > 1 && h1) {
         const unsigned long long above = (h1 >> lane) >> 1;
         const int next = above ? lane + 1 + (int)__builtin_ctzll(above) : len - kWave;   // in v1's own numbering
         const uint32_t slot = (uint32_t)n0 + __builtin_amdgcn_mbcnt_hi((uint32_t)(h1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)h1, 0u));
-        if (__builtin_amdgcn_inverse_ballot_w64(h1)) row[slot] = v1 | ((uint32_t)(next - lane) << topic_bits);
+        if (__builtin_amdgcn_inverse_ballot_w64(h1)) row[slot] = (v1 << count_bits) | (uint32_t)(next - lane);
     }
     // pad to the next multiple of 4 entries with (last topic, count 0), as the kernel below does
     const uint32_t last = R > 1 && len > kWave ? readlane_u32(v1, len - kWave - 1) : readlane_u32(v0, len - 1);
-    if (lane < ((kd + 3) & ~3) - kd) row[kd + lane] = last;
+    if (lane < ((kd + 3) & ~3) - kd) row[kd + lane] = last << count_bits;
     if (lane == 0) rec->y = (uint32_t)kd;
 }
 
@@ -1393,7 +1438,7 @@ __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOM
 // One segment of len > 0 assignments at zd by the whole workgroup, or (WAVE) by one wavefront of it; lds: bitmap, rank prefixes
 // (nwords words each), lds_entries entries of the row; scan_scratch: a word per wavefront and one more.
 template <typename ZT, bool WAVE = false>
-__device__ __forceinline__ void count_segment_block(const ZT *__restrict__ zd, int len, uint2 *rec, uint32_t *__restrict__ row, uint32_t topic_bits,
+__device__ __forceinline__ void count_segment_block(const ZT *__restrict__ zd, int len, uint2 *rec, uint32_t *__restrict__ row, uint32_t count_bits,
                                                     int nwords, int lds_entries, uint32_t *lds, uint32_t *scan_scratch) {
     const int tid = WAVE ? lane_id() : (int)threadIdx.x, nt = WAVE ? kWave : (int)blockDim.x;
     auto barrier = [] { if (WAVE) wave_lds_fence(); else __syncthreads(); };
@@ -1426,14 +1471,14 @@ __device__ __forceinline__ void count_segment_block(const ZT *__restrict__ zd, i
         for (int w = wb; w < we; w++) {
             uint32_t m = bitmap[w];
             wpre[w] = r;
-            while (m) { const int b = __ffs((int)m) - 1; m &= m - 1u; ent[r++] = (uint32_t)(w * 32 + b); }
+            while (m) { const int b = __ffs((int)m) - 1; m &= m - 1u; ent[r++] = (uint32_t)(w * 32 + b) << count_bits; }
         }
     }
     barrier();
     for_each_z(zd, (int64_t)len, tid, nt, [&](uint32_t k) {
         const uint32_t wd = bitmap[k >> 5];
         const uint32_t r = wpre[k >> 5] + (uint32_t)__popc(wd & ((1u << (k & 31u)) - 1u));
-        atomicAdd(&ent[r], 1u << topic_bits);
+        atomicAdd(&ent[r], 1u);
     });
     barrier();
     if (in_lds)
@@ -1442,7 +1487,7 @@ __device__ __forceinline__ void count_segment_block(const ZT *__restrict__ zd, i
     // and a draw that rounding pushes past the end of the row then still lands on the last topic
     if (tid < 4) {
         const int r = kd + tid;
-        if (r < ((kd + 3) & ~3)) row[r] = ent[kd - 1] & ((1u << topic_bits) - 1u);
+        if (r < ((kd + 3) & ~3)) row[r] = ent[kd - 1] & ~((1u << count_bits) - 1u);
     }
     if (tid == 0) rec->y = (uint32_t)kd;
 }
@@ -1450,7 +1495,7 @@ __device__ __forceinline__ void count_segment_block(const ZT *__restrict__ zd, i
 // The first na workgroups count the segments of group a, the others those of group b: documents and light words share a
 // launch, which spares a small corpus two of them.
 template <typename ZT>
-__global__ void __launch_bounds__(1024) count_dz_kernel(SegGroup a, int64_t na, SegGroup b, uint32_t topic_bits, int nwords,
+__global__ void __launch_bounds__(1024) count_dz_kernel(SegGroup a, int64_t na, SegGroup b, uint32_t count_bits, int nwords,
                                                         int lds_entries) {
     extern __shared__ uint32_t lds_u32[];
     __shared__ uint32_t scan_scratch[20];
@@ -1463,11 +1508,11 @@ __global__ void __launch_bounds__(1024) count_dz_kernel(SegGroup a, int64_t na, 
     const ZT *__restrict__ zd = reinterpret_cast<const ZT *>(g.z) + (begin - g.z_first);
     uint32_t *row = g.ent + (size_t)g.rec[d].x * 32u;
     if (blockDim.x == kWave && len <= 2 * kWave) {   // a short segment and a single wavefront: sorted in registers
-        if (len <= kWave) count_segment_wave<ZT, 1>(zd, len, g.rec + d, row, topic_bits);
-        else count_segment_wave<ZT, 2>(zd, len, g.rec + d, row, topic_bits);
+        if (len <= kWave) count_segment_wave<ZT, 1>(zd, len, g.rec + d, row, count_bits);
+        else count_segment_wave<ZT, 2>(zd, len, g.rec + d, row, count_bits);
         return;
     }
-    count_segment_block(zd, len, g.rec + d, row, topic_bits, nwords, lds_entries, lds_u32, scan_scratch);
+    count_segment_block(zd, len, g.rec + d, row, count_bits, nwords, lds_entries, lds_u32, scan_scratch);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1612,14 +1657,14 @@ __global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, c
 struct LightParams {
     const int32_t *light_words; const uint2 *wrec; const uint32_t *lw_ent; float *lw_phi;
     const float *denom, *base; const double *basecum; float *l3; double *l3_64; float *sumphi;
-    int n3, n3pad; uint32_t topic_bits; float beta;
+    int n3, n3pad; uint32_t count_bits; float beta;
 };
 __host__ __device__ inline size_t light_lds_bytes(int n3) { return ((size_t)n3 * 12u + 7u) & ~(size_t)7u; }
 
 // the light word number li, by one wavefront with light_lds_bytes(n3) of LDS at lds_dcum
 __device__ __forceinline__ void light_word(const LightParams &p, int li, double *lds_dcum) {
     const int n3 = p.n3, n3pad = p.n3pad;
-    const uint32_t topic_bits = p.topic_bits;
+    const uint32_t count_bits = p.count_bits;
     const float beta = p.beta;
     const float *__restrict__ denom = p.denom, *__restrict__ base = p.base;
     const double *__restrict__ basecum = p.basecum;
@@ -1631,7 +1676,7 @@ __device__ __forceinline__ void light_word(const LightParams &p, int li, double 
     const int nnz = (int)wr.y;
     const uint32_t *__restrict__ ent = p.lw_ent + (size_t)wr.x * 32u;
     float *__restrict__ val = p.lw_phi + (size_t)wr.x * 32u;
-    const uint32_t tmask = (1u << topic_bits) - 1u;
+    const uint32_t cmask = (1u << count_bits) - 1u;
     // the base vector's running sums of the first steps, requested under the chain of loads that leads to the non-zeros
     constexpr int kSteps = 4;
     double cum[kSteps];
@@ -1644,16 +1689,16 @@ __device__ __forceinline__ void light_word(const LightParams &p, int li, double 
         const int j = j0 + lane;
         const bool valid = j < nnz;
         const uint32_t e = valid ? ent[j] : 0u;
-        const uint32_t k = e & tmask;
+        const uint32_t k = e >> count_bits;
         double delta = 0.0;
         if (valid) {
-            const float f = ((float)(e >> topic_bits) + beta) / denom[k];
+            const float f = ((float)(e & cmask) + beta) / denom[k];
             val[j] = f;
             delta = (double)f - (double)base[k];
         }
         const double incl = wave_incl_scan(delta) + carry;
         const int blk = (int)(k >> 6);
-        const int next_blk = (j + 1 < nnz) ? (int)((ent[j + 1] & tmask) >> 6) : -1;
+        const int next_blk = (j + 1 < nnz) ? (int)((ent[j + 1] >> count_bits) >> 6) : -1;
         if (valid && blk != next_blk) { lds_dcum[blk] = incl; written[blk] = 1; }
         carry = readlane_f64(incl, 63);
     }
@@ -1695,7 +1740,7 @@ __global__ void __launch_bounds__(64) light_tree_kernel(LightParams p) {
 // (One launch and one wait for all words: a copy or a launch, and two waits, per word took 6.4 ms for 400 words at K = 1,500.)
 __global__ void __launch_bounds__(256) phi_export_kernel(const int32_t *rows, const float *phi, const float *base, const uint2 *wrec,
                                                          const uint32_t *lw_ent, const float *lw_phi, int K, int Kpad,
-                                                         uint32_t topic_bits, float *out) {
+                                                         uint32_t count_bits, float *out) {
     const int row = rows[blockIdx.x];
     const float *__restrict__ src = row >= 0 ? phi + (size_t)row * (size_t)Kpad : base;
     float *__restrict__ dst = out + (size_t)blockIdx.x * (size_t)K;
@@ -1703,8 +1748,7 @@ __global__ void __launch_bounds__(256) phi_export_kernel(const int32_t *rows, co
     if (row >= 0) return;
     __syncthreads();
     const uint2 wr = wrec[-row - 1];
-    const uint32_t tmask = (1u << topic_bits) - 1u;
-    for (int j = threadIdx.x; j < (int)wr.y; j += blockDim.x) dst[lw_ent[(size_t)wr.x * 32u + j] & tmask] = lw_phi[(size_t)wr.x * 32u + j];
+    for (int j = threadIdx.x; j < (int)wr.y; j += blockDim.x) dst[lw_ent[(size_t)wr.x * 32u + j] >> count_bits] = lw_phi[(size_t)wr.x * 32u + j];
 }
 
 // Statistics for the bandwidth model (exact in binary64 below 2^53), added to out[0..4]: the dense-branch counter slots
@@ -1762,7 +1806,7 @@ struct MCounts {
     unsigned long long *acc, *ck;           // accumulators of the totals (zero again at the end), totals
     unsigned *ticket;                       // zero before and after
     const VzItem *items; int32_t *cwk;
-    uint32_t topic_bits; int nwords, lds_entries, wave_entries;   // entries of a row in LDS: of a workgroup, of a wavefront
+    uint32_t count_bits; int nwords, lds_entries, wave_entries;   // entries of a row in LDS: of a workgroup, of a wavefront
     float vbeta, beta, *denom, *phi, *l3, *sumphi; double *l3_64;
     int K, Kpad, n3, n3pad, range, base_row, base_word;
 };
@@ -1819,13 +1863,13 @@ __global__ void __launch_bounds__(256, 8) mstep_counts_kernel(MCounts p) {
     const int len = (int)(g.ptr[d + 1] - begin);
     const uint16_t *zd = (doc ? z : z_wm) + begin;
     uint32_t *row = g.ent + (size_t)g.rec[d].x * 32u;
-    if (whole) count_segment_block(zd, len, g.rec + d, row, p.topic_bits, p.nwords, p.lds_entries, lds, scan_scratch);
+    if (whole) count_segment_block(zd, len, g.rec + d, row, p.count_bits, p.nwords, p.lds_entries, lds, scan_scratch);
     else if (len > 2 * kWave) {
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-        count_segment_block<uint16_t, true>(zd, len, g.rec + d, row, p.topic_bits, p.nwords, p.wave_entries,
+        count_segment_block<uint16_t, true>(zd, len, g.rec + d, row, p.count_bits, p.nwords, p.wave_entries,
                                             lds + wave * (2 * p.nwords + p.wave_entries), nullptr);
-    } else if (len > kWave) count_segment_wave<uint16_t, 2>(zd, len, g.rec + d, row, p.topic_bits);
-    else if (len > 0) count_segment_wave<uint16_t, 1>(zd, len, g.rec + d, row, p.topic_bits);
+    } else if (len > kWave) count_segment_wave<uint16_t, 2>(zd, len, g.rec + d, row, p.count_bits);
+    else if (len > 0) count_segment_wave<uint16_t, 1>(zd, len, g.rec + d, row, p.count_bits);
     else if (lane_id() == 0) g.rec[d].y = 0u;
 }
 

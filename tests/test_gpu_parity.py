@@ -260,6 +260,37 @@ def test_document_longer_than_16_bit_counts():
         g.close(); o.close()
 
 
+@pytest.mark.parametrize("longest", [16383, 16384, 65535])
+@pytest.mark.parametrize("K", [40, 900])
+def test_counts_next_to_the_topic_of_an_entry(longest, K):
+    """Entries of 16 bits each hold the count below the topic.  Below 2^14 tokens in the longest document the sampling kernel forms
+    a topic's place in LDS by one shift of the entry, from there on without the count's upper bits: a document whose tokens are
+    nearly all of one topic, the last one, on both sides of the line, and held-out documents on the other side than the model's."""
+    rng = np.random.default_rng(longest + K)
+    lens = np.r_[longest, rng.integers(1, 300, 60)]
+    doc_ptr = np.r_[0, np.cumsum(lens)].astype(np.int64)
+    T = int(doc_ptr[-1])
+    words = rng.integers(0, 400, T).astype(np.int32)
+    pk = saber()
+    g = pk.Saber(doc_ptr, words, 400, K, 0.5, 0.01, 4)
+    o = oracle.Model(doc_ptr, words, 400, K, 0.5, 0.01, 4)
+    assert_estep_parity(g, o)
+    z = o.z.copy()
+    z[:longest] = K - 1
+    g.set_z(z, 1); o.set_z(z, 1)
+    assert o.cd[2].max() == longest
+    assert_counts_equal(g, o)
+    assert_estep_parity(g, o)
+    assert abs(g.loglik() - o.loglik()) <= 1e-6 * abs(o.loglik())
+    hp = np.array([0, 40_000], dtype=np.int64)
+    hw = rng.integers(0, 400, 40_000).astype(np.int32)
+    mask = (np.arange(40_000) % 2 == 0).astype(np.uint8)
+    z0 = np.full(20_000, K - 1, dtype=np.int32)
+    hg, ho = g.holdout_loglik(hp, hw, mask, 0, 5, z0), o.holdout_loglik(hp, hw, mask, 0, 5, z0)
+    assert hg[1] == ho[1] and np.array_equal(hg[2], ho[2]) and abs(hg[0] - ho[0]) <= 1e-6 * abs(ho[0])
+    g.close(); o.close()
+
+
 def test_empty_documents_and_single_tokens():
     doc_ptr = np.array([0, 0, 1, 1, 4, 4, 4, 9, 9], dtype=np.int64)
     word_ids = np.array([3, 0, 0, 2, 1, 1, 1, 3, 0], dtype=np.int32)
