@@ -139,6 +139,7 @@ struct saber_ctx {
     uint32_t iter = 0, topic_bits = 0, count_bits = 0;   // (a packed entry: the topic above the count)
     bool z16 = false, staged = false, b16 = false;
     int pack = PACK_ANY;              // what the sampling kernel may take for granted of entries
+    bool slots = false;               // sampling wavefronts have a part of LDS of their own (estep_kernel, SLOTS)
     bool overlay = false;             // rows do not fit LDS: light words are read from memory with marks in LDS (Overlay)
     bool auto_light_block = false;    // neither workgroup size was given: those of light words' tiles follow the tile
     int lds_per_cu = 64 * 1024, cus = 256;
@@ -327,11 +328,12 @@ static EStepParams make_params(saber_ctx *c, const Chunk &ch, int slot = -1) {
 static size_t estep_row_bytes(const saber_ctx *c) {
     return ((size_t)((c->K + 3) & ~3) + (size_t)((c->n3 + 3) & ~3)) * sizeof(float);
 }
-// dynamic LDS of a sampling workgroup: the row when staged, 16 bytes of control words, and in log-likelihood mode
-// one double per wavefront
-static size_t estep_lds_bytes(const saber_ctx *c, int mode) {
+// dynamic LDS of a sampling workgroup: the row when staged, 16 bytes of control words, in log-likelihood mode
+// one double per wavefront, and kSlotBytes for each where they are used
+static size_t estep_lds_bytes(const saber_ctx *c, int mode, int block) {
     if (c->overlay) return 16 + 16 * sizeof(double) + (size_t)c->nwords * sizeof(uint2);
-    return (c->staged ? estep_row_bytes(c) : 0) + 16 + (mode == MODE_LOGLIK ? 16 * sizeof(double) : 0);
+    return (c->staged ? estep_row_bytes(c) : 0) + 16 + (mode == MODE_LOGLIK ? 16 * sizeof(double) : 0) +
+           (c->slots && mode == MODE_SAMPLE ? (size_t)(block / 64) * kSlotBytes : 0);
 }
 
 // a workgroup may use more than the default 64 KB of LDS (up to the CU's 160 KB) once the kernel has been told so
@@ -344,7 +346,9 @@ static void launch_with_lds(Kern kern, dim3 grid, dim3 block, size_t lds, hipStr
 
 template <int MODE, bool STAGED, typename ZT>
 static void launch_estep_packed(saber_ctx *c, dim3 grid, dim3 block, size_t lds, const EStepParams &p) {
-    if (STAGED && c->pack == PACK_16_14) launch_with_lds(estep_kernel<MODE, STAGED, ZT, STAGED ? PACK_16_14 : PACK_16>, grid, block, lds, c->stream, p);
+    if (MODE == MODE_SAMPLE && STAGED && sizeof(ZT) == 2 && c->slots)
+        launch_with_lds(estep_kernel<MODE_SAMPLE, true, uint16_t, PACK_16_14, true>, grid, block, lds, c->stream, p);
+    else if (STAGED && c->pack == PACK_16_14) launch_with_lds(estep_kernel<MODE, STAGED, ZT, STAGED ? PACK_16_14 : PACK_16>, grid, block, lds, c->stream, p);
     else if (c->pack != PACK_ANY) launch_with_lds(estep_kernel<MODE, STAGED, ZT, PACK_16>, grid, block, lds, c->stream, p);
     else launch_with_lds(estep_kernel<MODE, STAGED, ZT, PACK_ANY>, grid, block, lds, c->stream, p);
 }
@@ -366,13 +370,14 @@ static int check_estep_lds_layout() {
     SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, int32_t, PACK>));
     SABER_TRY(static_lds_is_zero(estep_kernel<MODE_PROBS, true, int32_t, PACK>));
     SABER_TRY(static_lds_is_zero(estep_kernel<MODE_LOGLIK, true, int32_t, PACK>));
+    if (PACK == PACK_16_14) SABER_TRY(static_lds_is_zero(estep_kernel<MODE_SAMPLE, true, uint16_t, PACK_16_14, true>));
     return SABER_OK;
 }
 
-// Wavefronts a CU holds of a sampling kernel with `block` threads per workgroup, given its LDS (handed out in 512-byte
-// pieces) and the 32 wavefronts a CU can hold.
-static int estep_waves_per_cu(const saber_ctx *c, int block) {
-    const size_t need = c->staged || c->overlay ? ((estep_lds_bytes(c, MODE_SAMPLE) + 144 + 511) / 512) * 512 : 512;
+// Wavefronts a CU holds of a sampling kernel with `block` threads per workgroup, given its LDS (handed out in 1,280-byte pieces; the
+// choice of a workgroup's size reckons with 512) and the 32 wavefronts a CU can hold.
+static int estep_waves_per_cu(const saber_ctx *c, int block, size_t piece = 512) {
+    const size_t need = c->staged || c->overlay ? ((estep_lds_bytes(c, MODE_SAMPLE, block) + (piece == 512 ? 144 : 0) + piece - 1) / piece) * piece : 512;
     const int by_lds = (int)std::min<size_t>(64, (size_t)c->lds_per_cu / need), by_waves = 32 / (block / 64);
     return std::min(by_lds, by_waves) * (block / 64);
 }
@@ -407,7 +412,7 @@ static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
             p.n_tiles = (int32_t)n;
             p.walkers = walkers_for(c, MODE, n - p.first_light, cl.block);
             const dim3 grid((unsigned)(p.first_light + p.walkers)), block((unsigned)cl.block);
-            const size_t lds = estep_lds_bytes(c, MODE);
+            const size_t lds = estep_lds_bytes(c, MODE, cl.block);
             if (c->staged) {
                 if (c->z16) launch_estep_packed<MODE, true, uint16_t>(c, grid, block, lds, p);
                 else launch_estep_packed<MODE, true, int32_t>(c, grid, block, lds, p);
@@ -1485,6 +1490,15 @@ static int make_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word
         c->auto_light_block = c->opt.light_block_threads <= 0;
     }
     if (c->opt.light_block_threads <= 0) c->opt.light_block_threads = c->opt.block_threads;
+    // A part of LDS per sampling wavefront, where a CU still holds as many of them: an iteration at T = 2.3 M, K = 777 161 -> 149
+    // us, T = 10 M, K = 1,000 583 -> 573, T = 100 K, K = 100 32.5 -> 31.5, T = 20 M, K = 2,000 (streamed, the link is the slower
+    // one) 1,629 -> 1,628.  Not for the sake of it: T = 36 M, K = 5,000 2.36 ms with 32 wavefronts per CU and lane
+    // permutations, 2.51 with 24 of the same workgroups, 2.62 with 32 in larger ones; T = 100 M, K = 10,000 7.1 and 7.4.
+    if (c->staged && c->z16 && c->pack == PACK_16_14) {
+        const int without = estep_waves_per_cu(c, c->opt.block_threads, 1280), light = estep_waves_per_cu(c, c->opt.light_block_threads, 1280);
+        c->slots = true;
+        c->slots = estep_waves_per_cu(c, c->opt.block_threads, 1280) == without && estep_waves_per_cu(c, c->opt.light_block_threads, 1280) == light;
+    }
     if (c->opt.tile_tokens <= 0) c->opt.tile_tokens = auto_tile_tokens(c, per_chunk);
     c->vbeta = (float)V * beta;
     int rc = check_estep_lds_layout<PACK_16>();

@@ -441,6 +441,9 @@ __device__ __forceinline__ int first_bit(unsigned long long m) {
     return i;
 }
 
+// What a wavefront wrote to its own part of LDS is in LDS order before what it reads there next; this keeps the compiler to it.
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 // lane permutations through the LDS crossbar (no LDS memory is touched); lane numbers are passed times 4
 __device__ __forceinline__ uint32_t lane_pull(uint32_t v, uint32_t src_lane4) {
     return (uint32_t)__builtin_amdgcn_ds_bpermute((int)src_lane4, (int)v);      // every lane reads lane src
@@ -556,7 +559,11 @@ template <typename T> __device__ __forceinline__ ConstMem<T> *const_mem(const T 
 // A light word keeps B sparse: its Bhat row is built in LDS from the base vector and the word's non-zeros (staged rows have
 // 16-bit assignments then), or where LDS cannot hold a row read from memory with marks in LDS (Overlay).  Tiles of both kinds share a launch: a launch of its own for the light words cost a small
 // corpus 10 of its 47 us per iteration (T = 100 K, K = 100), a large one the tail of the other.
-template <int MODE, bool STAGED, typename ZT, int PACK>
+// SLOTS (sampling): a wavefront has kSlotBytes of LDS of its own, through which short rows' runs and their tokens exchange what
+// they need, instead of lane permutations.
+constexpr int kSpareSlots = 8;                                             // read ahead by the last passes
+constexpr uint32_t kSlotBytes = kWave * 4 + (kWave + kSpareSlots) * 8;     // a word per token, then a pair per piece of a run
+template <int MODE, bool STAGED, typename ZT, int PACK, bool SLOTS = false>
 __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     extern __shared__ float4 lds_f4[];
     // LDS, all of it dynamic so that the Bhat row starts at address 0 and a gather needs no base added:
@@ -564,6 +571,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     //   [4] words: batch ticket, dense-branch tokens of the workgroup, whether a token is asked for (probs mode), 0 (the tree
     //           level's entry "before the first", which the dense branch reads for the first block)
     //   STAGED: [n3 rounded to 4] floats: the tree level above the bottom;  LOGLIK: [16] doubles, one per wavefront
+    //   SLOTS: kSlotBytes per wavefront
     //   not STAGED, if some words are light: after room for these 16 doubles, a pair of words per 32 topics (Overlay)
     // The footprint is kept minimal because it decides how many wavefronts a CU can hold: at K = 10,000 it is
     // 40,656 bytes, which lets four 512-thread workgroups (32 wavefronts) share the 160 KB of a CU.
@@ -825,6 +833,81 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
                 if (ps + 2 >= npass) break;
             }
         };
+        // The same by way of the wavefront's part of LDS.  Bound by LDS: a lane permutation takes 6.1 cycles of it, a read of a few
+        // places 2.3 and a write by a few lanes 4.1: 42 cycles instead of 79 for two rows of at most 128 entries.
+        const uint32_t tok_at = SLOTS ? (uint32_t)(((q->K + 3) & ~3) + 4 + ((q->n3 + 3) & ~3)) * 4u + (uint32_t)wave * kSlotBytes : 0u;
+        typedef uint32_t pair_t __attribute__((ext_vector_type(2)));
+        typedef __attribute__((address_space(3))) pair_t lds_pair;
+        typedef __attribute__((address_space(3))) uint32_t lds_word;
+        auto run_class_slots = [&](auto G_, const unsigned long long in_class, const unsigned long long cm, const unsigned long long cuts) {
+            constexpr int G = decltype(G_)::value, NG = kWave / G, LG = G == 16 ? 4 : 5;
+            const int nruns = (int)__builtin_popcountll(cm);   // wave-uniform
+            if (nruns == 0) return;
+            const int npass = (nruns + NG - 1) / NG;
+            uint32_t ln = (uint32_t)lane;
+            asm volatile("" : "+v"(ln));
+            // Slot order as above.  The last token of every piece puts down its slot: the row's length, the piece's tokens, its
+            // first token; the row's offset.
+            const unsigned long long lasts = ((cuts >> 1) | (1ull << (n - 1))) & in_class, sing = cm & lasts;
+            const uint32_t rank1 = bits_up_to_lane(sing), rank2 = (uint32_t)__builtin_popcountll(sing) + bits_up_to_lane(cm & ~sing);
+            const uint32_t piece_at = tok_at + kWave * 4u - 8u;
+            const uint32_t mine_at = piece_at + (__builtin_amdgcn_inverse_ballot_w64(sing) ? rank1 : rank2) * 8u;
+            const uint32_t jp = jpos & (uint32_t)(G - 1);
+            if (__builtin_amdgcn_inverse_ballot_w64(lasts))
+                *(lds_pair *)mine_at = pair_t{row_bytes | ((jp + 1u) << 16) | ((ln - jp) << 26), row_off};
+            if (__builtin_amdgcn_inverse_ballot_w64((1ull << (2 * NG)) - 1ull))   // spare ones: rows of length 0
+                *(lds_pair *)(piece_at + (uint32_t)(nruns + 1) * 8u + ln * 8u) = pair_t{0u, 0u};
+            wave_lds_fence();
+            constexpr unsigned long long ONES = G == 16 ? 0x0001000100010001ull : 0x0000000100000001ull;   // first lane of every group
+            const uint32_t li16 = (ln & (uint32_t)(G - 1)) << 4;
+            uint32_t slot_at = piece_at + 8u + (ln >> LG) * 8u;   // of the pass that is computed
+            auto issue = [&](const int ahead, uint4 &blk, uint32_t &pk) {
+                const pair_t w = *(lds_pair *)(slot_at + (uint32_t)(ahead * NG) * 8u);
+                pk = w.x;
+                blk = load_rows_at(rows, li16 < (w.x & 0xffffu) ? w.y + li16 : 0xffffffffu);
+            };
+            auto compute = [&](const uint4 &cur, const uint32_t pk) {
+                uint32_t at = tok_at + (pk >> 24);               // place of the token that is served next
+                float u = __uint_as_float(*(lds_word *)at);
+                RowBlock b;
+                block_products<STAGED, PACK, G>(cur, cbits, lds_phi, phi_row, b, ov);
+                const float S = G == 16 ? dpp_f32<0x15f, 0xf>(b.incl) : half_last(b.incl);
+                if (__builtin_amdgcn_inverse_ballot_w64(ONES << (G - 1))) *(lds_word *)slot_at = __float_as_uint(b.incl);
+                slot_at += (uint32_t)NG * 8u;
+                const float base = b.incl - b.a3;
+                const float p0 = base + b.a0, p1 = base + b.a1, p2 = base + b.a2;
+                // the last lane of every group's row: if rounding leaves no lane, the choice falls on it
+                const unsigned long long sent = __builtin_amdgcn_ballot_w64(li16 + 16u == (pk & 0xffffu));
+                unsigned long long act = __builtin_amdgcn_ballot_w64(((pk >> 16) & 0xffu) > 0u);   // groups whose piece has a token left
+                for (uint32_t j = 1;; j++) {
+                    const float x = u * S;
+                    const unsigned long long ge = __builtin_amdgcn_ballot_w64(b.incl >= x) | sent;
+                    const unsigned long long win = ge & ~(ge - ONES) & act;   // first such lane of every group
+                    uint32_t sel = cur.w;
+                    sel = p2 >= x ? cur.z : sel;
+                    sel = p1 >= x ? cur.y : sel;
+                    sel = p0 >= x ? cur.x : sel;
+                    if (__builtin_amdgcn_inverse_ballot_w64(win)) *(lds_word *)at = sel;
+                    act = __builtin_amdgcn_ballot_w64(((pk >> 16) & 0xffu) > j);
+                    if (!act) break;
+                    at += 4u;
+                    u = __uint_as_float(*(lds_word *)at);
+                }
+            };
+            uint4 blk_a, blk_b; uint32_t pk_a, pk_b;
+            issue(0, blk_a, pk_a);
+            for (int ps = 0;; ps += 2) {
+                issue(1, blk_b, pk_b);
+                compute(blk_a, pk_a);
+                if (ps + 1 >= npass) break;
+                issue(1, blk_a, pk_a);
+                compute(blk_b, pk_b);
+                if (ps + 2 >= npass) break;
+            }
+            wave_lds_fence();
+            const float St = __uint_as_float(*(lds_word *)mine_at);
+            my_S = __builtin_amdgcn_inverse_ballot_w64(in_class) ? St : my_S;
+        };
         // ---- longer rows: one run at a time over the whole wavefront ----
         // `cur` holds the run's row (its first block), `last` the number of the row's last piece of 16 bytes; the next run's row
         // is fetched into `nxt` before this run's arithmetic starts.  Rows of several blocks have a loop of their own, so that
@@ -860,8 +943,20 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         fetch(e_c, blk_c, last_c, off_c);
         blk_c2 = fetch_more(last_c, off_c, 1);
 
-        run_class(std::integral_constant<int, 16>{}, cm16, cuts16, __builtin_amdgcn_inverse_ballot_w64(m16));
-        run_class(std::integral_constant<int, 32>{}, cm32, cuts32, __builtin_amdgcn_inverse_ballot_w64(m32));
+        if (SLOTS) {
+            if (m16 | m32) {
+                lds_word *mine = (lds_word *)(tok_at + (uint32_t)lane * 4u);
+                *mine = __float_as_uint(u1);
+                wave_lds_fence();
+                run_class_slots(std::integral_constant<int, 16>{}, m16, cm16, cuts16);
+                run_class_slots(std::integral_constant<int, 32>{}, m32, cm32, cuts32);
+                wave_lds_fence();
+                my_z = *mine;
+            }
+        } else {
+            run_class(std::integral_constant<int, 16>{}, cm16, cuts16, __builtin_amdgcn_inverse_ballot_w64(m16));
+            run_class(std::integral_constant<int, 32>{}, cm32, cuts32, __builtin_amdgcn_inverse_ballot_w64(m32));
+        }
         if (MODE == MODE_SAMPLE && (m16 | m32)) {
             // the coin of the tokens served above, all at once
             sparse_mask = __builtin_amdgcn_ballot_w64(u0 * (my_S + Q) < my_S) & (m16 | m32);
@@ -1431,9 +1526,6 @@ __device__ __forceinline__ void count_segment_wave(const ZT *__restrict__ zs, in
 // z[0] at position z_first of that numbering (a streaming buffer holds one chunk only); its row goes to ent from
 // rec[s].x * 32 on, its length to rec[s].y.
 struct SegGroup { const int32_t *list; const int64_t *ptr; const void *z; int64_t z_first; uint2 *rec; uint32_t *ent; };
-
-// What a wavefront wrote to its own part of LDS is in LDS order before what it reads there next; this keeps the compiler to it.
-__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
 // One segment of len > 0 assignments at zd by the whole workgroup, or (WAVE) by one wavefront of it; lds: bitmap, rank prefixes
 // (nwords words each), lds_entries entries of the row; scan_scratch: a word per wavefront and one more.

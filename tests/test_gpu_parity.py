@@ -215,6 +215,30 @@ def test_short_rows_share_a_wavefront(V):
     o.close()
 
 
+@pytest.mark.parametrize("V", [3, 40, 900])
+@pytest.mark.parametrize("K", [90, 1050, 1100, 4000, 5000])
+def test_short_rows_exchange_through_lds_or_lanes(K, V):
+    """What short rows' runs exchange goes through LDS where a wavefront has room for it (K = 5,000 leaves none), through lane
+    permutations otherwise: batches of up to 64 single-token runs, of a few runs of hundreds of tokens, of both, with some
+    groups of lanes spare, against the plain layout of one run at a time, and that against the oracle."""
+    rng = np.random.default_rng(V + K)
+    lens = np.r_[np.full(70, 1), rng.integers(1, 60, 150), rng.integers(60, 130, 150), rng.integers(130, 700, 25)]
+    doc_ptr = np.r_[0, np.cumsum(lens)].astype(np.int64)
+    word_ids = np.minimum((V * rng.random(int(doc_ptr[-1])) ** 1.5).astype(np.int32), V - 1)
+    pk = saber()
+    p = pk.Saber(doc_ptr, word_ids, V, K, 0.02, 0.01, 5, quarter_row_entries=-1, half_row_entries=-1)
+    o = oracle.Model(doc_ptr, word_ids, V, K, 0.02, 0.01, 5)
+    assert_estep_parity(p, o)
+    assert_estep_parity(p, o)
+    z = p.get_z()
+    for opts in [{}, {"half_row_entries": -1}, {"quarter_row_entries": -1}, {"tile_tokens": 64}, {"block_threads": 320}]:
+        g = pk.Saber(doc_ptr, word_ids, V, K, 0.02, 0.01, 5, **opts)
+        g.iterate(2)
+        assert np.array_equal(g.get_z(), z), opts
+        g.close()
+    p.close(); o.close()
+
+
 def test_large_counts_in_a_row():
     """Few topics and documents of 6,000 to 30,000 tokens: single entries of A with counts of many thousands next
     to ordinary rows (16/16 packing is used up to its limit of 65,535 tokens per document)."""
