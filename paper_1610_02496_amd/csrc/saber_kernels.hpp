@@ -559,6 +559,11 @@ template <typename T> __device__ __forceinline__ ConstMem<T> *const_mem(const T 
 // A light word keeps B sparse: its Bhat row is built in LDS from the base vector and the word's non-zeros (staged rows have
 // 16-bit assignments then), or where LDS cannot hold a row read from memory with marks in LDS (Overlay).  Tiles of both kinds share a launch: a launch of its own for the light words cost a small
 // corpus 10 of its 47 us per iteration (T = 100 K, K = 100), a large one the tail of the other.
+// Tokens of a run from which on their positions in its row are looked for at once (5 to 9; a fifth of the tokens are in runs of 16
+// and more, 28 per cent in runs of 8 and more).  One token after the other takes ten vector and six scalar instructions each, all
+// of a run's at once about 35 and 13 lane permutations.  An iteration at T = 100 M, K = 10,000 7.34 -> 7.21 ms, T = 10 M, K = 1,000
+// 575 -> 562 us; from 6 or 12 tokens on the same within 0.5 %.
+constexpr int kManyTokens = 8;
 // SLOTS (sampling): a wavefront has kSlotBytes of LDS of its own, through which short rows' runs and their tokens exchange what
 // they need, instead of lane permutations.
 constexpr int kSpareSlots = 8;                                             // read ahead by the last passes
@@ -719,6 +724,19 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         unsigned long long m32 = __builtin_amdgcn_ballot_w64(row_bytes <= half) & acts & ~m16;
         const unsigned long long cuts16 = __builtin_amdgcn_ballot_w64((jpos & 15u) == 0u) & acts;   // where pieces begin
         const unsigned long long cuts32 = __builtin_amdgcn_ballot_w64((jpos & 31u) == 0u) & acts;
+        // Runs of many tokens go with the longer rows, whatever their length is: their search is made for all tokens at once there.
+        // (many: where the next kManyTokens - 1 lanes continue the run.  Not in small batches: their 14 scalar instructions were 2 % of an
+        // iteration at T = 15 M, K = 20,011, where a batch has 6 tokens)
+        if (MODE == MODE_SAMPLE && n >= 2 * kManyTokens) {
+            const unsigned long long more = ~starts & ~(~1ull << (n - 1));   // tokens that continue a run
+            unsigned long long next = more >> 1;
+            next &= next >> 1;
+            next &= next >> 2;
+            next &= next >> (kManyTokens - 5);
+            const unsigned long long many = starts & next, inside = more | many;
+            const unsigned long long lanes = (((inside + many) ^ inside) & inside) | many;   // (a carry runs from a start to the run's end)
+            m16 &= ~lanes; m32 &= ~lanes;
+        }
         // a pass serves four (two) runs at the cost of about one: a class that would not fill most of one pass goes
         // with the next wider one
         if (__builtin_popcountll(m16 & cuts16) < 3) { if (half >= quarter) m32 |= m16; m16 = 0ull; }
@@ -994,7 +1012,25 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
                 const float xs = u1 * S;
                 const float base = b.incl - b.a3;
                 const float p0 = base + b.a0, p1 = base + b.a1, p2 = base + b.a2;
-                do {
+                if ((int)__builtin_popcountll(sparse) >= kManyTokens) {
+                    // many tokens: every lane looks for its own.  "First lane whose sum reaches x" is the same over the sums' running
+                    // maximum, which rounding leaves in order, and a search by halves of that finds it.
+                    const int top = wave_incl_scan_max(__float_as_int(b.incl));
+                    // 4 times the lane; the first step tells the halves apart (half of 128 is a constant an instruction can hold)
+                    uint32_t at4 = readlane_f32(__int_as_float(top), 31) < xs ? 64u : 0u;
+                    asm volatile("" : "+v"(at4));
+                    at4 <<= 1;
+#pragma unroll
+                    for (uint32_t half = 16u; half; half >>= 1)
+                        at4 = __int_as_float((int)lane_pull((uint32_t)top, at4 + (half - 1u) * 4u)) < xs ? at4 + half * 4u : at4;
+                    at4 = min(at4, (uint32_t)last * 4u);
+                    uint32_t sel = lane_pull(cur.w, at4);
+                    const uint32_t s2 = lane_pull(cur.z, at4), s1 = lane_pull(cur.y, at4), s0 = lane_pull(cur.x, at4);
+                    sel = lane_pull(p2, at4) >= xs ? s2 : sel;
+                    sel = lane_pull(p1, at4) >= xs ? s1 : sel;
+                    sel = lane_pull(p0, at4) >= xs ? s0 : sel;
+                    my_z = __builtin_amdgcn_inverse_ballot_w64(sparse) ? sel : my_z;
+                } else do {
                     // problem 1: position of x in the prefix sums of P.  If rounding leaves no lane of the row's, the choice falls
                     // on its last one, whose padding repeats the row's last topic
                     const int r = first_bit(sparse);
@@ -1261,7 +1297,9 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
     }
     if (tid < n3) lds_l3[tid] = c;
     for (int i = tid + nt; i < n3; i += nt) lds_l3[i] = l3_row[i];
-    if (tid == 0) reinterpret_cast<int *>(lds_phi)[K4] = nwaves;
+    int first_ticket = nwaves;
+    asm volatile("" : "+s"(first_ticket));   // (not held in a vector register over the tiles)
+    if (tid == 0) reinterpret_cast<int *>(lds_phi)[K4] = first_ticket;
     lds_barrier();
     if (tid < (int)wr.y) lds_phi[e >> cbits] = v;
     for (int j = tid + nt; j < (int)wr.y; j += nt) lds_phi[ent[j] >> cbits] = val[j];
