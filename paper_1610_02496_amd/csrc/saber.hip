@@ -815,6 +815,10 @@ constexpr int64_t kJoinedSegments = 384 * 1024, kJoinedTokens = 16ll << 20;
 // T = 10 M, K = 1,000 649 with T / 48, 653 with T / 32, 686 with T / 20.
 static int64_t joined_share(const saber_ctx *c) { return std::max<int64_t>(std::max<int64_t>(16384, std::min(16 * c->K, 65536)), (c->T / 48 + 4095) & ~4095ll); }
 
+// Rows up to which a row of several ranges of topics has a workgroup for each, and a second launch for the running sums: as many as
+// leave CUs without a row.  An iteration at T = 1.5 M, K = 70,000, 22 rows of 9 ranges 358 -> 318 us, at T = 15 M, K = 20,011, 125
+// rows of 3 ranges 1,591 -> 1,583.
+constexpr int64_t kPhiPartRows = 256;
 static int launch_phi(saber_ctx *c) {
     hipLaunchKernelGGL(denominators_kernel, dim3(grid_for(c->Kpad, 256)), dim3(256), 0, c->stream, c->ck_acc, c->ck, c->denom, c->K,
                        c->Kpad, c->vbeta);
@@ -825,16 +829,23 @@ static int launch_phi(saber_ctx *c) {
     const int range = std::min(c->Kpad, kPhiSteps * 4 * (int)block.x);
     const size_t hist = (size_t)range * sizeof(uint32_t);
     const int64_t rows = (int64_t)c->V_dense + 1;
+    const int parts = (c->Kpad + range - 1) / range;
+    const bool by_parts = parts > 1 && rows <= kPhiPartRows;
     for (int64_t r = 0, n; r < rows; r += n) {
         n = std::min(rows - r, most_blocks((int)block.x));
-        const dim3 grid((unsigned)n);
+        const dim3 grid((unsigned)n, by_parts ? (unsigned)parts : 1u);
         const size_t at = (size_t)r * (size_t)c->Kpad;
-        if (c->z16)
-            hipLaunchKernelGGL((phi_tree_kernel<uint16_t>), grid, block, hist, c->stream, c->phi_rows + r, (const uint16_t *)c->z_wm, c->cwk + at,
-                               c->denom, c->phi + at, c->l3, c->l3_64, c->sumphi, c->Kpad, c->n3, c->n3pad, c->beta, range);
-        else
-            hipLaunchKernelGGL((phi_tree_kernel<int32_t>), grid, block, hist, c->stream, c->phi_rows + r, (const int32_t *)c->z_wm, c->cwk + at,
-                               c->denom, c->phi + at, c->l3, c->l3_64, c->sumphi, c->Kpad, c->n3, c->n3pad, c->beta, range);
+        auto launch = [&](auto kernel, auto *z_wm) {
+            hipLaunchKernelGGL(kernel, grid, block, hist, c->stream, c->phi_rows + r, z_wm, c->cwk + at, c->denom, c->phi + at, c->l3, c->l3_64, c->sumphi,
+                               c->Kpad, c->n3, c->n3pad, c->beta, range);
+        };
+        if (c->z16) launch(by_parts ? phi_tree_kernel<uint16_t, true> : phi_tree_kernel<uint16_t, false>, (const uint16_t *)c->z_wm);
+        else launch(by_parts ? phi_tree_kernel<int32_t, true> : phi_tree_kernel<int32_t, false>, (const int32_t *)c->z_wm);
+        HIP_TRY(hipGetLastError());
+    }
+    if (by_parts) {
+        hipLaunchKernelGGL(phi_sums_kernel, dim3((unsigned)rows), dim3(256), ((size_t)c->n3 + (size_t)(c->n3 + 15) / 16) * sizeof(double), c->stream,
+                           c->phi_rows, c->l3, c->l3_64, c->sumphi, c->n3, c->n3pad);
         HIP_TRY(hipGetLastError());
     }
     c->acc_used = false;

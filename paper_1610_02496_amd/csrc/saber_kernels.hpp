@@ -1678,64 +1678,80 @@ __global__ void denominators_kernel(unsigned long long *acc, unsigned long long 
 // The running sums associate in groups of 1,024 columns whatever the workgroup's size.
 struct PhiRow { int32_t word; int32_t count; int64_t begin; };
 constexpr int kPhiSteps = 2;   // steps of 4 columns per thread that share one histogram and one exchange of running sums
+constexpr int kPhiHeld = 4;    // assignments per thread that are read once and held
+
+// Bhat of the n columns from r0 on of the row whose columns start at rbase, and the lanes' running sums over their wavefront's
+// columns.  held: zr has the row's assignments.
+template <typename ZT>
+__device__ __forceinline__ void phi_range(const PhiRow pr, const ZT *__restrict__ zs, bool held, const uint32_t (&zr)[kPhiHeld], size_t rbase, int r0, int n,
+                                          int32_t *cwk, const float *denom, float *phi, float beta, int4 *phi_hist4, double (&incl)[kPhiSteps]) {
+    uint32_t *phi_hist = reinterpret_cast<uint32_t *>(phi_hist4);
+    const int step = 4 * (int)blockDim.x;
+    const bool own = pr.count >= 0;
+    float4 den[kPhiSteps];             // requested before the counting
+#pragma unroll
+    for (int st = 0; st < kPhiSteps; st++) {
+        const int k = st * step + (int)threadIdx.x * 4;
+        den[st] = k < n ? *reinterpret_cast<const float4 *>(denom + r0 + k) : make_float4(1.f, 1.f, 1.f, 1.f);
+    }
+    if (own) {
+        for (int k = threadIdx.x; k < n / 4; k += blockDim.x) phi_hist4[k] = make_int4(0, 0, 0, 0);
+        lds_barrier();
+        auto count = [&](uint32_t k) { if (k - (uint32_t)r0 < (uint32_t)n) atomicAdd(&phi_hist[k - (uint32_t)r0], 1u); };
+        if (held) {
+#pragma unroll
+            for (int j = 0; j < kPhiHeld; j++) count(zr[j]);
+        } else {
+            block_for_each_z(zs, (int64_t)pr.count, count);
+        }
+        lds_barrier();
+    }
+#pragma unroll
+    for (int st = 0; st < kPhiSteps; st++) {
+        if (st * step >= n) break;     // uniform
+        const int k = st * step + (int)threadIdx.x * 4;
+        float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (k < n) {   // n is a multiple of 64, so k..k+3 are all inside the padded row
+            int4 c;
+            if (own) c = phi_hist4[k / 4];
+            else c = *reinterpret_cast<const int4 *>(cwk + rbase + r0 + k);
+            f.x = ((float)c.x + beta) / den[st].x; f.y = ((float)c.y + beta) / den[st].y;
+            f.z = ((float)c.z + beta) / den[st].z; f.w = ((float)c.w + beta) / den[st].w;
+            *reinterpret_cast<float4 *>(phi + rbase + r0 + k) = f;
+            if (!own) *reinterpret_cast<int4 *>(cwk + rbase + r0 + k) = make_int4(0, 0, 0, 0);
+        }
+        incl[st] = wave_incl_scan((((double)f.x + (double)f.y) + (double)f.z) + (double)f.w);
+    }
+}
+template <typename ZT>
+__device__ __forceinline__ bool phi_hold(const PhiRow pr, const ZT *__restrict__ zs, uint32_t (&zr)[kPhiHeld]) {
+    const bool held = pr.count >= 0 && pr.count <= kPhiHeld * (int)blockDim.x;
+#pragma unroll
+    for (int j = 0; j < kPhiHeld; j++) {
+        const int i = (int)threadIdx.x + j * (int)blockDim.x;
+        zr[j] = held && i < pr.count ? (uint32_t)zs[i] : 0xffffffffu;
+    }
+    return held;
+}
 
 template <typename ZT>
 __device__ __forceinline__ void phi_row(const PhiRow pr, size_t row, const ZT *z_wm, int32_t *cwk, const float *denom, float *phi, float *l3,
                                         double *l3_64, float *sumphi, int Kpad, int n3, int n3pad, float beta, int range, int4 *phi_hist4) {
-    constexpr int kHeld = 4;               // assignments per thread that are read once and held
-    uint32_t *phi_hist = reinterpret_cast<uint32_t *>(phi_hist4);
     __shared__ double wave_tot[kPhiSteps * 16];
     __shared__ float row_total;
     const int v = pr.word, step = 4 * (int)blockDim.x;
     const int lane = lane_id(), wave = threadIdx.x / kWave, nwaves = blockDim.x / kWave;
-    const size_t rbase = row * (size_t)Kpad;
-    const bool own = pr.count >= 0, held = own && pr.count <= kHeld * (int)blockDim.x;
     const ZT *__restrict__ zs = z_wm + pr.begin;
-    uint32_t zr[kHeld];
-#pragma unroll
-    for (int j = 0; j < kHeld; j++) {
-        const int i = (int)threadIdx.x + j * (int)blockDim.x;
-        zr[j] = held && i < pr.count ? (uint32_t)zs[i] : 0xffffffffu;
-    }
+    uint32_t zr[kPhiHeld];
+    const bool held = phi_hold(pr, zs, zr);
     double carry = 0.0;
     for (int r0 = 0; r0 < Kpad; r0 += range) {
         const int n = min(range, Kpad - r0);
-        float4 den[kPhiSteps];             // requested before the counting
-#pragma unroll
-        for (int st = 0; st < kPhiSteps; st++) {
-            const int k = st * step + (int)threadIdx.x * 4;
-            den[st] = k < n ? *reinterpret_cast<const float4 *>(denom + r0 + k) : make_float4(1.f, 1.f, 1.f, 1.f);
-        }
-        if (own) {
-            for (int k = threadIdx.x; k < n / 4; k += blockDim.x) phi_hist4[k] = make_int4(0, 0, 0, 0);
-            lds_barrier();
-            auto count = [&](uint32_t k) { if (k - (uint32_t)r0 < (uint32_t)n) atomicAdd(&phi_hist[k - (uint32_t)r0], 1u); };
-            if (held) {
-#pragma unroll
-                for (int j = 0; j < kHeld; j++) count(zr[j]);
-            } else {
-                block_for_each_z(zs, (int64_t)pr.count, count);
-            }
-            lds_barrier();
-        }
         double incl[kPhiSteps];
+        phi_range(pr, zs, held, zr, row * (size_t)Kpad, r0, n, cwk, denom, phi, beta, phi_hist4, incl);
 #pragma unroll
-        for (int st = 0; st < kPhiSteps; st++) {
-            if (st * step >= n) break;     // uniform
-            const int k = st * step + (int)threadIdx.x * 4;
-            float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (k < n) {   // n is a multiple of 64, so k..k+3 are all inside the padded row
-                int4 c;
-                if (own) c = phi_hist4[k / 4];
-                else c = *reinterpret_cast<const int4 *>(cwk + rbase + r0 + k);
-                f.x = ((float)c.x + beta) / den[st].x; f.y = ((float)c.y + beta) / den[st].y;
-                f.z = ((float)c.z + beta) / den[st].z; f.w = ((float)c.w + beta) / den[st].w;
-                *reinterpret_cast<float4 *>(phi + rbase + r0 + k) = f;
-                if (!own) *reinterpret_cast<int4 *>(cwk + rbase + r0 + k) = make_int4(0, 0, 0, 0);
-            }
-            incl[st] = wave_incl_scan((((double)f.x + (double)f.y) + (double)f.z) + (double)f.w);
-            if (lane == kWave - 1) wave_tot[st * 16 + wave] = incl[st];
-        }
+        for (int st = 0; st < kPhiSteps; st++)
+            if (st * step < n && lane == kWave - 1) wave_tot[st * 16 + wave] = incl[st];
         lds_barrier();
 #pragma unroll
         for (int st = 0; st < kPhiSteps; st++) {
@@ -1768,12 +1784,73 @@ __device__ __forceinline__ void phi_row(const PhiRow pr, size_t row, const ZT *z
     if (threadIdx.x == 0) sumphi[v] = total;
 }
 
+// The same with a workgroup per `range` columns of a row, for few rows of many topics (bound by a row's chain of steps: 22 rows of
+// 70,000 topics on 22 of 256 CUs took 53 us): first Bhat, and in l3_64 the running sums at
+// the block ends inside each wavefront's 256 columns ...
 template <typename ZT>
+__device__ __forceinline__ void phi_part(const PhiRow pr, size_t row, int r0, const ZT *z_wm, int32_t *cwk, const float *denom, float *phi, double *l3_64,
+                                         int Kpad, int n3, float beta, int range, int4 *phi_hist4) {
+    const int n = min(range, Kpad - r0);
+    const ZT *__restrict__ zs = z_wm + pr.begin;
+    uint32_t zr[kPhiHeld];
+    const bool held = phi_hold(pr, zs, zr);
+    double incl[kPhiSteps];
+    phi_range(pr, zs, held, zr, row * (size_t)Kpad, r0, n, cwk, denom, phi, beta, phi_hist4, incl);
+#pragma unroll
+    for (int st = 0; st < kPhiSteps; st++) {
+        const int k = st * 4 * (int)blockDim.x + (int)threadIdx.x * 4;
+        if (k < n && ((k + 3) & (kWave - 1)) == kWave - 1) l3_64[(size_t)pr.word * (size_t)n3 + (size_t)((r0 + k + 3) / kWave)] = incl[st];
+    }
+}
+// ... then a workgroup per row adds what lies before: the same sums in the same order as phi_row's.  LDS: n3 doubles, one per 16 blocks.
+// A group is 1,024 columns, 16 blocks, those of four wavefronts.
+__global__ void __launch_bounds__(256) phi_sums_kernel(const PhiRow *rows, float *l3, double *l3_64, float *sumphi, int n3, int n3pad) {
+    extern __shared__ double ps_lds[];
+    const int ngroups = (n3 + 15) / 16;
+    double *inside = ps_lds, *before = ps_lds + n3;   // sums inside a wavefront's columns; sum of a group, then of all before it
+    const size_t v = (size_t)rows[blockIdx.x].word;
+    for (int i = threadIdx.x; i < n3; i += blockDim.x) inside[i] = l3_64[v * (size_t)n3 + i];
+    __syncthreads();
+    auto wave_total = [&](int g, int w) {             // (the last wavefront with columns may have fewer than four blocks)
+        const int first = 16 * g + 4 * w;
+        return first < n3 ? inside[min(first + 3, n3 - 1)] : 0.0;
+    };
+    for (int g = threadIdx.x; g < ngroups; g += blockDim.x) {
+        double sum = 0.0;
+        for (int w = 0; w < 4; w++) sum += wave_total(g, w);
+        before[g] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double carry = 0.0;
+        for (int g = 0; g < ngroups; g++) { const double sum = before[g]; before[g] = carry; carry += sum; }
+    }
+    __syncthreads();
+    float last = 0.f;
+    for (int i = threadIdx.x; i < n3; i += blockDim.x) {
+        const int g = i / 16, wave = (i % 16) / 4;
+        double woff = 0.0;
+        for (int w = 0; w < wave; w++) woff += wave_total(g, w);
+        const double run = before[g] + woff + inside[i];
+        l3_64[v * (size_t)n3 + i] = run;
+        l3[v * (size_t)n3pad + i] = (float)run;
+        if (i == n3 - 1) { sumphi[v] = (float)run; last = (float)run; }
+    }
+    __shared__ float row_total;
+    if ((int)threadIdx.x == (n3 - 1) % (int)blockDim.x) row_total = last;
+    __syncthreads();
+    for (int i = n3 + (int)threadIdx.x; i < n3pad; i += blockDim.x) l3[v * (size_t)n3pad + i] = row_total;
+}
+
+// PARTS: grid row y takes the y-th range of columns.
+template <typename ZT, bool PARTS>
 __global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, const ZT *z_wm, int32_t *cwk, const float *denom,
                                                         float *phi, float *l3, double *l3_64, float *sumphi, int Kpad,
                                                         int n3, int n3pad, float beta, int range) {
     extern __shared__ int4 phi_lds[];
-    phi_row(rows[blockIdx.x], (size_t)blockIdx.x, z_wm, cwk, denom, phi, l3, l3_64, sumphi, Kpad, n3, n3pad, beta, range, phi_lds);
+    const PhiRow pr = rows[blockIdx.x];
+    if (PARTS) phi_part(pr, (size_t)blockIdx.x, (int)blockIdx.y * range, z_wm, cwk, denom, phi, l3_64, Kpad, n3, beta, range, phi_lds);
+    else phi_row(pr, (size_t)blockIdx.x, z_wm, cwk, denom, phi, l3, l3_64, sumphi, Kpad, n3, n3pad, beta, range, phi_lds);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -321,3 +321,27 @@ def test_rows_of_many_blocks(K):
     assert_estep_parity(g, o)
     g.close()
     o.close()
+
+
+@pytest.mark.parametrize("K", [8256, 9216, 12_000, 20_011, 70_000])
+def test_rows_of_bhat_by_parts(K):
+    """Few rows of many topics have a workgroup per range of topics and their running sums added up afterwards, more rows a
+    workgroup each: the same sums in the same order, so the same bits; rows that are counted where they are normalised, also with
+    more assignments than a workgroup holds, and rows counted before."""
+    counts = np.r_[np.resize([1, 3, 64, 700], 190), 4000, 5000, 20_000, 40_000, np.zeros(106, np.int64)]
+    doc_ptr, words = corpus_of_word_counts(counts, 400, K)
+    pk, V, used = saber(), counts.size, np.arange(194, dtype=np.int32)
+    few = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 4, light_word_tokens=1)      # (a word without tokens keeps no dense row)
+    all_rows = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 4, light_word_tokens=-1)
+    o = oracle.Model(doc_ptr, words, V, K, 0.1, 0.01, 4)
+    for _ in range(2):
+        phi, prefix = few.get_phi(used)
+        ref, ref_prefix = all_rows.get_phi(used)
+        assert np.array_equal(phi, o.phi[:194]) and np.array_equal(phi, ref) and np.array_equal(prefix, ref_prefix)
+        assert np.mean(prefix != o.c32[:194]) < 1e-5 and np.allclose(prefix, o.c32[:194], rtol=1.2e-7, atol=0)
+        few.iterate(1)
+        all_rows.iterate(1)
+        z = few.get_z()
+        assert np.array_equal(z, all_rows.get_z())
+        o.set_z(z, 1)
+    few.close(); all_rows.close(); o.close()
