@@ -205,20 +205,19 @@ struct saber_ctx {
     std::vector<int64_t> doc_len;     // host copy of the document lengths (statistics only)
     // Host streaming (Sec. 3.1.2), n_slots > 0: tok_t lives in pinned host memory; a chunk's part of it is copied
     // into one of n_slots device buffers for the chunk's pass (4 bytes per token and iteration over the host link).
-    // The rest is derived or kept on the device: the chunk's tok_doc follows from one look-up per token in
+    // The rest is derived or kept on the device: the chunk's tok_doc follows, on a third stream, from one look-up per token in
     // doc_blocks (16 bytes per 64 canonical tokens: where documents start); its assignments in document order exist only in the
     // buffer, between the sampling kernel that writes them and the CountByDZ that turns them into rows of A, and
     // are re-created from the word-major copy when asked for; z_wm (2 bytes per token) and the rows of A are
-    // resident.  Copies run on a stream of their own and are ordered against the compute stream with two events
-    // per buffer.
+    // resident.  Copies run on a stream of their own; the three are ordered with three events per buffer.
     int n_slots = 0, next_slot = 0;
     int64_t slot_tokens = 0;
     uint32_t *h_tok_t = nullptr;
     uint4 *doc_blocks = nullptr;      // [ceil(T/64)] see expand_tok_doc_kernel
     int32_t *ne_doc = nullptr;        // [non-empty documents] their numbers; null when no document is empty
     int32_t *slot_tok_doc[kMaxSlots] = {}; uint32_t *slot_tok_t[kMaxSlots] = {}; void *slot_z[kMaxSlots] = {};
-    hipStream_t s_in = nullptr;
-    hipEvent_t ev_loaded[kMaxSlots] = {}, ev_done[kMaxSlots] = {};
+    hipStream_t s_in = nullptr, s_docs = nullptr;   // copies; the expansion of their tok_doc
+    hipEvent_t ev_copied[kMaxSlots] = {}, ev_loaded[kMaxSlots] = {}, ev_done[kMaxSlots] = {};
     bool slot_used[kMaxSlots] = {};
     // ablation variants (saber_options.ablation): document-order sampling needs the words in canonical order and
     // the word -> row map; the sort-based rebuild of A needs key buffers and the sort's work space
@@ -270,9 +269,10 @@ extern "C" void saber_free(saber_ctx *c) {
         release(c->vz_items); release(c->phi_rows);
     }
     if (c->have_events) for (auto &e : c->ev) if (e) (void)hipEventDestroy(e);
-    if (c->s_in) { (void)hipStreamSynchronize(c->s_in); (void)hipStreamDestroy(c->s_in); }
+    for (hipStream_t s : {c->s_in, c->s_docs}) if (s) { (void)hipStreamSynchronize(s); (void)hipStreamDestroy(s); }
     for (int s = 0; s < kMaxSlots; s++) {
         release(c->slot_tok_doc[s]); release(c->slot_tok_t[s]); release(c->slot_z[s]);
+        if (c->ev_copied[s]) (void)hipEventDestroy(c->ev_copied[s]);
         if (c->ev_loaded[s]) (void)hipEventDestroy(c->ev_loaded[s]);
         if (c->ev_done[s]) (void)hipEventDestroy(c->ev_done[s]);
     }
@@ -672,10 +672,9 @@ static int launch_count_dz_chunk(saber_ctx *c, const Chunk &ch, int slot) {
 }
 
 // ---- host streaming ----
-// Takes the next buffer (round robin) for chunk `ch`: once the kernels of the buffer's previous user have run, the
-// chunk's tok_t is copied in and tok_doc derived from it (both on the copy stream), and the compute stream is made to
-// wait for that.
-static int stream_acquire(saber_ctx *c, const Chunk &ch, int *slot) {
+// Takes the next buffer (round robin) for chunk `ch`: once the kernels of the buffer's previous user have run, the chunk's tok_t is
+// copied in, and with `docs` tok_doc derived from it.  stream_wait() makes the compute stream wait for that.
+static int stream_load(saber_ctx *c, const Chunk &ch, bool docs, int *slot) {
     const int s = c->next_slot;
     c->next_slot = (c->next_slot + 1) % c->n_slots;
     if (ch.ntok > c->slot_tokens) return fail(SABER_ESTATE, "chunk of %lld tokens exceeds the streaming buffers", (long long)ch.ntok);
@@ -683,16 +682,26 @@ static int stream_acquire(saber_ctx *c, const Chunk &ch, int *slot) {
     *slot = s;
     if (ch.ntok == 0) return SABER_OK;
     HIP_TRY(hipMemcpyAsync(c->slot_tok_t[s], c->h_tok_t + ch.t0, (size_t)ch.ntok * sizeof(uint32_t), hipMemcpyHostToDevice, c->s_in));
-    // on the copy stream as well: the look-ups of this kernel wait for memory most of the time, and where the copy ends early
-    // enough they run beside the sampling of the chunk before (1.7 ms per 123 M tokens of short documents when it ran in line
-    // with it).  At T = 20 M in four chunks, K = 2,000, where the link is the slower one, 43 % of its 54 us per chunk do; the
-    // rest lies between two sampling passes, and the next chunk's copy waits for all of it.
-    hipLaunchKernelGGL(expand_tok_doc_kernel, dim3(grid_for(ch.ntok, 256)), dim3(256), 0, c->s_in, c->slot_tok_t[s],
+    HIP_TRY(hipEventRecord(docs ? c->ev_copied[s] : c->ev_loaded[s], c->s_in));
+    if (!docs) return SABER_OK;
+    // on a stream of its own: the look-ups of this kernel wait for memory most of the time and run beside the sampling of the
+    // chunk before (1.7 ms per 123 M tokens of short documents when it ran in line with it), and the next chunk's copy, which
+    // has nothing to wait for, goes on (T = 20 M in four chunks, K = 2,000, the link the slower one: 1.63 -> 1.54 ms
+    // per iteration)
+    HIP_TRY(hipStreamWaitEvent(c->s_docs, c->ev_copied[s], 0));
+    hipLaunchKernelGGL(expand_tok_doc_kernel, dim3(grid_for(ch.ntok, 256)), dim3(256), 0, c->s_docs, c->slot_tok_t[s],
                        ch.ntok, ch.t0, c->doc_blocks, c->ne_doc, c->slot_tok_doc[s]);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipEventRecord(c->ev_loaded[s], c->s_in));
-    HIP_TRY(hipStreamWaitEvent(c->stream, c->ev_loaded[s], 0));
+    HIP_TRY(hipEventRecord(c->ev_loaded[s], c->s_docs));
     return SABER_OK;
+}
+static int stream_wait(saber_ctx *c, const Chunk &ch, int s) {
+    if (ch.ntok) HIP_TRY(hipStreamWaitEvent(c->stream, c->ev_loaded[s], 0));
+    return SABER_OK;
+}
+static int stream_acquire(saber_ctx *c, const Chunk &ch, int *slot, bool docs = true) {
+    SABER_TRY(stream_load(c, ch, docs, slot));
+    return stream_wait(c, ch, *slot);
 }
 // After the chunk's kernels have been queued: the buffer may be overwritten once they have run.
 static int stream_release(saber_ctx *c, int s) {
@@ -702,7 +711,7 @@ static int stream_release(saber_ctx *c, int s) {
 }
 static int sync_all(saber_ctx *c) {
     HIP_TRY(hipStreamSynchronize(c->stream));
-    if (c->n_slots) HIP_TRY(hipStreamSynchronize(c->s_in));
+    if (c->n_slots) { HIP_TRY(hipStreamSynchronize(c->s_in)); HIP_TRY(hipStreamSynchronize(c->s_docs)); }
     return SABER_OK;
 }
 
@@ -953,7 +962,7 @@ static int full_mstep(saber_ctx *c, const int32_t *user_z = nullptr) {
         std::vector<uint16_t> stage;
         for (const Chunk &ch : c->chunks) {
             int s;
-            SABER_TRY(stream_acquire(c, ch, &s));
+            SABER_TRY(stream_acquire(c, ch, &s, false));
             if (user_z && ch.ntok) {
                 HIP_TRY(hipStreamSynchronize(c->stream));   // the buffer's earlier kernels are done: plain copy
                 const void *src = user_z + ch.t0;
@@ -1268,10 +1277,12 @@ static int upload(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids,
     const size_t vk = ((size_t)c->V_dense + 1) * (size_t)c->Kpad;
     if (c->n_slots) {
         HIP_TRY(hipStreamCreateWithFlags(&c->s_in, hipStreamNonBlocking));
+        HIP_TRY(hipStreamCreateWithFlags(&c->s_docs, hipStreamNonBlocking));
         for (int s = 0; s < c->n_slots; s++) {
             SABER_TRY(dev_alloc(c->hooks, &c->slot_tok_doc[s], (size_t)c->slot_tokens)); SABER_TRY(dev_alloc(c->hooks, &c->slot_tok_t[s], (size_t)c->slot_tokens));
             if (c->z16) SABER_TRY(dev_alloc(c->hooks, (uint16_t **)&c->slot_z[s], (size_t)c->slot_tokens));
             else SABER_TRY(dev_alloc(c->hooks, (int32_t **)&c->slot_z[s], (size_t)c->slot_tokens));
+            HIP_TRY(hipEventCreateWithFlags(&c->ev_copied[s], hipEventDisableTiming));
             HIP_TRY(hipEventCreateWithFlags(&c->ev_loaded[s], hipEventDisableTiming));
             HIP_TRY(hipEventCreateWithFlags(&c->ev_done[s], hipEventDisableTiming));
         }
@@ -2094,10 +2105,16 @@ extern "C" int saber_get_z(saber_ctx *c, int32_t *z) {
     if (c->T == 0) return SABER_OK;
     try {
         if (c->n_slots) {   // document order is re-created chunk by chunk from the word-major copy
-            for (const Chunk &ch : c->chunks) {
-                if (ch.ntok == 0) continue;
-                int s;
-                SABER_TRY(stream_acquire(c, ch, &s));
+            // (the next chunk's token list comes in while this one's assignments go out, where there are two buffers: T = 20 M in four
+            // chunks 4.4 -> 3.4 ms, with the documents, which nothing here reads, left out)
+            std::vector<const Chunk *> list;
+            for (const Chunk &ch : c->chunks) if (ch.ntok) list.push_back(&ch);
+            const bool ahead = c->n_slots > 1;
+            int s = -1, s_next = -1;
+            for (size_t i = 0; i < list.size(); i++) {
+                const Chunk &ch = *list[i];
+                if (i == 0 || !ahead) SABER_TRY(stream_load(c, ch, false, &s)); else s = s_next;
+                SABER_TRY(stream_wait(c, ch, s));
                 if (c->z16)
                     hipLaunchKernelGGL((scatter_zwm_kernel<uint16_t>), dim3((unsigned)ch.ntiles), dim3(256), 0, c->stream,
                                        c->tiles + ch.tile0, c->slot_tok_t[s], (const uint16_t *)c->z_wm, (uint16_t *)c->slot_z[s]);
@@ -2105,6 +2122,7 @@ extern "C" int saber_get_z(saber_ctx *c, int32_t *z) {
                     hipLaunchKernelGGL((scatter_zwm_kernel<int32_t>), dim3((unsigned)ch.ntiles), dim3(256), 0, c->stream,
                                        c->tiles + ch.tile0, c->slot_tok_t[s], (const int32_t *)c->z_wm, (int32_t *)c->slot_z[s]);
                 HIP_TRY(hipGetLastError());
+                if (ahead && i + 1 < list.size()) SABER_TRY(stream_load(c, *list[i + 1], false, &s_next));
                 SABER_TRY(pull_z(c, c->slot_z[s], ch.ntok, z + ch.t0));
                 SABER_TRY(stream_release(c, s));
             }
