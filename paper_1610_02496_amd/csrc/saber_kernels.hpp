@@ -1459,7 +1459,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *scratc
 
 // ---------------------------------------------------------------------------------------------
 // Segmented count of a short segment by one wavefront, in registers (bound by its vector instructions: 535,000 segments of
-// 90 assignments take 0.20 ms; neither several segments per wavefront nor their loads ahead of time changed that):
+// 90 assignments take 0.21 ms, 0.23 with a compare and a selection per step and 21 steps for every segment; neither several segments per wavefront nor their loads ahead of time changed that):
 // the sort-and-count of Sec. 3.3 taken
 // literally.  Lane i holds assignment i (lanes past the end an all-ones key); a bitonic network of 21
 // compare-exchange steps sorts the 64 keys (partners at lane ^ m: DPP quad permutations and row mirrors for m = 1,
@@ -1470,8 +1470,20 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *scratc
 // 90 vector instructions per segment (200 with two keys per lane) where the bitmap version below spends 390: it
 // clears, scans and enumerates K / 32 bitmap words whatever the segment's length.
 // ---------------------------------------------------------------------------------------------
+// The lane keeps the middle one of its key, its partner's and a bound: 0 in the lower lane of a pair, which makes that the smaller key,
+// all ones in the upper one (one instruction where a compare and a selection are two, and the masks are formed once per wavefront).
+struct SortBounds { uint32_t b[6]; };   // by the bit of the lane number that tells upper from lower
+__device__ __forceinline__ SortBounds sort_bounds(int lane) {
+    SortBounds s;
+#pragma unroll
+    for (int i = 0; i < 6; i++) s.b[i] = (uint32_t)((int)((uint32_t)lane << (31 - i)) >> 31);
+    return s;
+}
+__device__ __forceinline__ uint32_t middle_of(uint32_t a, uint32_t b, uint32_t c) {
+    return max(min(a, b), min(max(a, b), c));   // (v_med3_u32)
+}
 template <int XOR>
-__device__ __forceinline__ uint32_t sort_exchange(uint32_t v, int lane) {
+__device__ __forceinline__ uint32_t sort_exchange(uint32_t v, int lane, const SortBounds &bounds) {
     uint32_t o;
     if (XOR == 1) o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);            // quad_perm [1,0,3,2]
     else if (XOR == 2) o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true);       // quad_perm [2,3,0,1]
@@ -1480,36 +1492,39 @@ __device__ __forceinline__ uint32_t sort_exchange(uint32_t v, int lane) {
     else if (XOR == 15) o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true);     // row_mirror
     else if (XOR < 32) o = (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (XOR << 10) | 0x1f);   // lane ^ XOR inside 32 lanes
     else o = (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ XOR) << 2, (int)v);
-    // lanes that are the upper one of their pair (the highest bit of XOR is set in the lane number)
-    constexpr unsigned long long upper = XOR >= 32 ? 0xffffffff00000000ull : XOR >= 16 ? 0xffff0000ffff0000ull
-                                       : XOR >= 8 ? 0xff00ff00ff00ff00ull : XOR >= 4 ? 0xf0f0f0f0f0f0f0f0ull
-                                       : XOR >= 2 ? 0xccccccccccccccccull : 0xaaaaaaaaaaaaaaaaull;
-    // the lower lane takes the partner's key if its own is larger, the upper lane if its own is not larger
-    const unsigned long long take = __builtin_amdgcn_ballot_w64(v > o) ^ upper;
-    return __builtin_amdgcn_inverse_ballot_w64(take) ? o : v;
+    constexpr int bit = XOR >= 32 ? 5 : XOR >= 16 ? 4 : XOR >= 8 ? 3 : XOR >= 4 ? 2 : XOR >= 2 ? 1 : 0;   // the highest one of XOR
+    return middle_of(v, o, bounds.b[bit]);
 }
 
-// the 64 keys of one register, ascending over the lanes
-__device__ __forceinline__ uint32_t sort64(uint32_t v, int lane) {
-    v = sort_exchange<1>(v, lane);
-    v = sort_exchange<3>(v, lane); v = sort_exchange<1>(v, lane);
-    v = sort_exchange<7>(v, lane); v = sort_exchange<2>(v, lane); v = sort_exchange<1>(v, lane);
-    v = sort_exchange<15>(v, lane); v = sort_exchange<4>(v, lane); v = sort_exchange<2>(v, lane); v = sort_exchange<1>(v, lane);
-    v = sort_exchange<31>(v, lane); v = sort_exchange<8>(v, lane); v = sort_exchange<4>(v, lane); v = sort_exchange<2>(v, lane);
-    v = sort_exchange<1>(v, lane);
-    v = sort_exchange<63>(v, lane); v = sort_exchange<16>(v, lane); v = sort_exchange<8>(v, lane); v = sort_exchange<4>(v, lane);
-    v = sort_exchange<2>(v, lane); v = sort_exchange<1>(v, lane);
+// the 64 keys of one register, ascending over the lanes; len: no more than this many lanes, from the first on, hold anything but the
+// largest key there is (16 keys take 10 of the 21 steps, 32 take 15)
+__device__ __forceinline__ uint32_t sort64(uint32_t v, int lane, int len, const SortBounds &bounds) {
+    auto step = [&](auto x) { v = sort_exchange<decltype(x)::value>(v, lane, bounds); };
+    using std::integral_constant;
+    step(integral_constant<int, 1>{});
+    step(integral_constant<int, 3>{}); step(integral_constant<int, 1>{});
+    step(integral_constant<int, 7>{}); step(integral_constant<int, 2>{}); step(integral_constant<int, 1>{});
+    step(integral_constant<int, 15>{}); step(integral_constant<int, 4>{}); step(integral_constant<int, 2>{}); step(integral_constant<int, 1>{});
+    if (len <= 16) return v;
+    step(integral_constant<int, 31>{}); step(integral_constant<int, 8>{}); step(integral_constant<int, 4>{}); step(integral_constant<int, 2>{});
+    step(integral_constant<int, 1>{});
+    if (len <= 32) return v;
+    step(integral_constant<int, 63>{}); step(integral_constant<int, 16>{}); step(integral_constant<int, 8>{}); step(integral_constant<int, 4>{});
+    step(integral_constant<int, 2>{}); step(integral_constant<int, 1>{});
     return v;
 }
 // two ascending registers of 64 keys -> one ascending sequence of 128 (v0's lanes, then v1's): the last stage of the network
-__device__ __forceinline__ void merge128(uint32_t &v0, uint32_t &v1, int lane) {
+__device__ __forceinline__ void merge128(uint32_t &v0, uint32_t &v1, int lane, const SortBounds &bounds) {
     const uint32_t o1 = (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ 63) << 2, (int)v1);   // key 127 - i for key i
     const uint32_t o0 = (uint32_t)__builtin_amdgcn_ds_bpermute((lane ^ 63) << 2, (int)v0);
     v0 = min(v0, o1); v1 = max(v1, o0);
-    v0 = sort_exchange<32>(v0, lane); v0 = sort_exchange<16>(v0, lane); v0 = sort_exchange<8>(v0, lane);
-    v0 = sort_exchange<4>(v0, lane); v0 = sort_exchange<2>(v0, lane); v0 = sort_exchange<1>(v0, lane);
-    v1 = sort_exchange<32>(v1, lane); v1 = sort_exchange<16>(v1, lane); v1 = sort_exchange<8>(v1, lane);
-    v1 = sort_exchange<4>(v1, lane); v1 = sort_exchange<2>(v1, lane); v1 = sort_exchange<1>(v1, lane);
+    auto step = [&](auto x) {
+        v0 = sort_exchange<decltype(x)::value>(v0, lane, bounds);
+        v1 = sort_exchange<decltype(x)::value>(v1, lane, bounds);
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 32>{}); step(integral_constant<int, 16>{}); step(integral_constant<int, 8>{});
+    step(integral_constant<int, 4>{}); step(integral_constant<int, 2>{}); step(integral_constant<int, 1>{});
 }
 
 // R = 1: segments of at most 64 assignments; R = 2: of at most 128, two keys per lane (lane i holds keys i and 64 + i).
@@ -1520,8 +1535,9 @@ __device__ __forceinline__ void count_segment_wave(const ZT *__restrict__ zs, in
     constexpr uint32_t kNone = 0xffffffffu;
     uint32_t v0 = lane < len ? (uint32_t)zs[lane] : kNone;
     uint32_t v1 = R > 1 && lane + kWave < len ? (uint32_t)zs[lane + kWave] : kNone;
-    v0 = sort64(v0, lane);
-    if (R > 1) { v1 = sort64(v1, lane); merge128(v0, v1, lane); }
+    const SortBounds bounds = sort_bounds(lane);
+    v0 = sort64(v0, lane, R > 1 ? kWave : len, bounds);
+    if (R > 1) { v1 = sort64(v1, lane, len - kWave, bounds); merge128(v0, v1, lane, bounds); }
     // the i-th smallest key now sits at position i (v0's lanes, then v1's); the all-ones keys follow the len real ones.
     // A key that differs from its left neighbour starts a topic: its slot in the row is the number of such keys
     // before it, its count the distance to the next one (or to the end of the segment).

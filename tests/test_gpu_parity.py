@@ -734,3 +734,25 @@ def test_gpu_chain_recovers_planted_topics_and_generalises():
     assert folded[2] > folded[1] > folded[0] and folded[2] > uniform + 0.3
     assert folded[2] < ll[-1] + 0.3
     g.close(); truth.close()
+
+
+@pytest.mark.parametrize("K", [7, 300, 70000])
+def test_segments_that_take_fewer_steps_to_sort(K):
+    """Segments of up to 16 and 32 assignments, and up to 16 and 32 beyond the first 64, stop sorting early: documents and light words
+    of every length around these lines, with distinct, equal and alternating assignments."""
+    lens = np.r_[np.arange(1, 35), np.arange(78, 100)]
+    doc_ptr = np.r_[0, np.cumsum(np.r_[lens, lens])].astype(np.int64)
+    T = int(doc_ptr[-1])
+    word_ids = np.repeat(np.arange(2 * lens.size, dtype=np.int32), np.r_[lens, lens])
+    np.random.default_rng(K).shuffle(word_ids)
+    V = 2 * lens.size
+    pk = saber()
+    g = pk.Saber(doc_ptr, word_ids, V, K, 0.5, 0.01, 3, light_word_tokens=1000)
+    o = oracle.Model(doc_ptr, word_ids, V, K, 0.5, 0.01, 3)
+    assert_counts_equal(g, o)
+    for z in ((np.arange(T) * 7919) % K, (T - np.arange(T)) % K, np.full(T, K - 1), np.arange(T) % 2 * (K - 1)):
+        z = z.astype(np.int32)
+        g.set_z(z, 1); o.set_z(z, 1)
+        assert_counts_equal(g, o)
+        assert_estep_parity(g, o, min_agree=0.99)
+    g.close(); o.close()
