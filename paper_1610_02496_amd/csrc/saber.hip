@@ -720,9 +720,16 @@ static LightParams light_params(const saber_ctx *c) {
     return LightParams{c->light_words, c->wrec, c->lw_ent, c->lw_phi, c->denom, c->phi + (size_t)c->V_dense * (size_t)c->Kpad,
                        c->l3_64 + (size_t)c->V * (size_t)c->n3, c->l3, c->l3_64, c->sumphi, c->n3, c->n3pad, c->count_bits, c->beta};
 }
+// Light words per wavefront: four where rows are short enough that their chain of loads counts (up to 128 blocks of topics) and the
+// chip stays full of wavefronts.  Kernel with one, two and four: T = 10 M, K = 1,000, 98,600 words (dense rows with them) 35, 29 and
+// 28 us; T = 2.3 M, K = 777, 29,500 words 12.5, 11.3 and 11.2; T = 36 M, K = 5,000, 140,000 words 76, 70 and 69; T = 100 M, K = 10,000
+// 119, 118 and 121; T = 15 M, K = 20,011 104, 106 and 123; T = 1.5 M, K = 70,000, 4,000 words 38, 69 and 126; T = 100 K 5.6 all.
+static int words_per_wave(const saber_ctx *c) { return c->n3 <= 128 && c->V_light >= 16384 ? 4 : 1; }
 static int launch_light_words(saber_ctx *c) {
     if (c->V_light == 0) return SABER_OK;
-    hipLaunchKernelGGL(light_tree_kernel, dim3((unsigned)c->V_light), dim3(64), light_lds_bytes(c->n3), c->stream, light_params(c));
+    const int per_wave = words_per_wave(c);
+    hipLaunchKernelGGL((per_wave == 4 ? light_tree_kernel<4> : light_tree_kernel<1>), dim3((unsigned)((c->V_light + per_wave - 1) / per_wave)), dim3(64), light_lds_bytes(c->n3),
+                       c->stream, light_params(c), c->V_light);
     HIP_TRY(hipGetLastError());
     return SABER_OK;
 }
@@ -895,9 +902,10 @@ static int launch_joined_mstep(saber_ctx *c, const unsigned long long *slots, un
     const LightParams lp = light_params(c);
     const StatsParams st = stats_params(c, slots, stats_out);
     const int n_stats = stats_blocks(c, block);
-    const unsigned grid2 = (unsigned)(n_stats + c->V_dense + (c->V_light + nw - 1) / nw);
+    const int per_wave = words_per_wave(c);
+    const unsigned grid2 = (unsigned)(n_stats + c->V_dense + (c->V_light + nw * per_wave - 1) / (nw * per_wave));
     const size_t lds2 = std::max((size_t)range * 4, (size_t)nw * light_lds_bytes(c->n3));
-    hipLaunchKernelGGL(mstep_rows_kernel, dim3(grid2), dim3((unsigned)block), lds2, c->stream, c->phi_rows, c->V_dense,
+    hipLaunchKernelGGL((per_wave == 4 ? mstep_rows_kernel<4> : mstep_rows_kernel<1>), dim3(grid2), dim3((unsigned)block), lds2, c->stream, c->phi_rows, c->V_dense,
                        (const uint16_t *)c->z_wm, c->cwk, c->phi, c->Kpad, range, st, n_stats, lp, c->V_light);
     HIP_TRY(hipGetLastError());
     c->acc_used = false;

@@ -1870,92 +1870,119 @@ __global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, c
 }
 
 // ---------------------------------------------------------------------------------------------
-// Preprocess + BuildTree for the light words (one wavefront per word).  Their Bhat row is the base vector
+// Preprocess + BuildTree for the light words (one wavefront per W words).  Their Bhat row is the base vector
 // except at the word's non-zeros, so only those are evaluated (Eq. 2, same three binary32 operations) and
 // stored next to the entries.  The running sums at the block ends follow from the base vector's running sums
 // plus the cumulative difference (Bhat - base) of the non-zeros up to each block, all in binary64: the same
 // sum of the same binary32 numbers as for a dense row, associated differently.
-// LDS: n3 doubles (cumulative difference at the last non-zero of each block) + n3 flags.
+// LDS: a zero and the cumulative differences at the last non-zero of each block that has one, then a bit per block that has.
 // ---------------------------------------------------------------------------------------------
 struct LightParams {
     const int32_t *light_words; const uint2 *wrec; const uint32_t *lw_ent; float *lw_phi;
     const float *denom, *base; const double *basecum; float *l3; double *l3_64; float *sumphi;
     int n3, n3pad; uint32_t count_bits; float beta;
 };
-__host__ __device__ inline size_t light_lds_bytes(int n3) { return ((size_t)n3 * 12u + 7u) & ~(size_t)7u; }
+__host__ __device__ inline size_t light_lds_bytes(int n3) { return ((size_t)n3 + 1u + (size_t)(n3 + 63) / 64u) * 8u; }
 
-// the light word number li, by one wavefront with light_lds_bytes(n3) of LDS at lds_dcum
-__device__ __forceinline__ void light_word(const LightParams &p, int li, double *lds_dcum) {
-    const int n3 = p.n3, n3pad = p.n3pad;
-    const uint32_t count_bits = p.count_bits;
+// W light words from number `first` on (of n_light), by one wavefront with light_lds_bytes(n3) of LDS at lds_dcum.  Bound by the chain of
+// loads that leads to a word's non-zeros' denominators - its record, its entries, their denominators - where rows are short: the
+// words of a wavefront take each of the three steps together (see words_per_wave() on the host).  A block's running sum needs the
+// difference at the last block with a non-zero up to it, which is found by counting these (15 vector instructions per 64 blocks; by a
+// running maximum over the lanes and differences stored by block 30: T = 36 M, K = 5,000 82 -> 79 us).
+template <int W>
+__device__ __forceinline__ void light_words(const LightParams &p, int first, int n_light, double *lds_dcum) {
+    const int n3 = p.n3, n3pad = p.n3pad, lane = lane_id();
+    const uint32_t count_bits = p.count_bits, cmask = (1u << count_bits) - 1u;
     const float beta = p.beta;
     const float *__restrict__ denom = p.denom, *__restrict__ base = p.base;
     const double *__restrict__ basecum = p.basecum;
     float *l3 = p.l3, *sumphi = p.sumphi;
     double *l3_64 = p.l3_64;
-    int *written = reinterpret_cast<int *>(lds_dcum + n3);
-    const int v = p.light_words[li], lane = lane_id();
-    const uint2 wr = p.wrec[li];
-    const int nnz = (int)wr.y;
-    const uint32_t *__restrict__ ent = p.lw_ent + (size_t)wr.x * 32u;
-    float *__restrict__ val = p.lw_phi + (size_t)wr.x * 32u;
-    const uint32_t cmask = (1u << count_bits) - 1u;
-    // the base vector's running sums of the first steps, requested under the chain of loads that leads to the non-zeros
+    uint32_t *has = reinterpret_cast<uint32_t *>(lds_dcum + n3 + 1);
+    int word[W];
+    uint2 rec[W];
+#pragma unroll
+    for (int w = 0; w < W; w++) {
+        const int li = min(first + w, n_light - 1);
+        word[w] = p.light_words[li]; rec[w] = p.wrec[li];
+    }
+    // the base vector's running sums of the first steps, requested under that chain
     constexpr int kSteps = 4;
     double cum[kSteps];
 #pragma unroll
     for (int st = 0; st < kSteps; st++) cum[st] = basecum[min(st * kWave + lane, n3 - 1)];
-    for (int i = lane; i < n3; i += kWave) written[i] = 0;
-    wave_lds_fence();
-    double carry = 0.0;
-    for (int j0 = 0; j0 < nnz; j0 += kWave) {
-        const int j = j0 + lane;
-        const bool valid = j < nnz;
-        const uint32_t e = valid ? ent[j] : 0u;
-        const uint32_t k = e >> count_bits;
-        double delta = 0.0;
-        if (valid) {
-            const float f = ((float)(e & cmask) + beta) / denom[k];
-            val[j] = f;
-            delta = (double)f - (double)base[k];
-        }
-        const double incl = wave_incl_scan(delta) + carry;
-        const int blk = (int)(k >> 6);
-        const int next_blk = (j + 1 < nnz) ? (int)((ent[j + 1] >> count_bits) >> 6) : -1;
-        if (valid && blk != next_blk) { lds_dcum[blk] = incl; written[blk] = 1; }
-        carry = readlane_f64(incl, 63);
-    }
-    wave_lds_fence();
-    int last = -1;   // last block at or before the current one that holds a non-zero
-    float total = 0.f;
-    for (int i0 = 0; i0 < n3; i0 += kSteps * kWave) {
-        int idx[kSteps];                   // of each step alone, then with what lies before it: the steps wait for one another only there
+    uint32_t e0[W];
+    float den0[W], base0[W];
 #pragma unroll
-        for (int st = 0; st < kSteps; st++) {
-            const int i = i0 + st * kWave + lane;
-            idx[st] = i0 + st * kWave < n3 ? wave_incl_scan_max(i < n3 && written[i] ? i : -1) : -1;
-        }
+    for (int w = 0; w < W; w++) e0[w] = lane < (int)rec[w].y ? p.lw_ent[(size_t)rec[w].x * 32u + (size_t)lane] : 0u;
 #pragma unroll
-        for (int st = 0; st < kSteps; st++) {
-            if (i0 + st * kWave >= n3) break;   // uniform
-            const int i = i0 + st * kWave + lane, at = max(idx[st], last);
-            if (i < n3) {
-                const double run = (i0 ? basecum[i] : cum[st]) + (at >= 0 ? lds_dcum[at] : 0.0);
-                l3_64[(size_t)v * (size_t)n3 + (size_t)i] = run;
-                l3[(size_t)v * (size_t)n3pad + (size_t)i] = (float)run;
-                if (i == n3 - 1) total = (float)run;
+    for (int w = 0; w < W; w++) { den0[w] = denom[e0[w] >> count_bits]; base0[w] = base[e0[w] >> count_bits]; }
+#pragma unroll
+    for (int w = 0; w < W; w++) {
+        if (first + w >= n_light) break;   // uniform
+        const int v = word[w], nnz = (int)rec[w].y;
+        const uint32_t *__restrict__ ent = p.lw_ent + (size_t)rec[w].x * 32u;
+        float *__restrict__ val = p.lw_phi + (size_t)rec[w].x * 32u;
+        for (int i = lane; i < (n3 + 63) / 64 * 2; i += kWave) has[i] = 0u;
+        if (lane == 0) lds_dcum[0] = 0.0;
+        wave_lds_fence();
+        double carry = 0.0;
+        int blocks = 0;                    // with a non-zero so far
+        for (int j0 = 0; j0 < nnz; j0 += kWave) {
+            const int j = j0 + lane;
+            const bool valid = j < nnz;
+            const uint32_t e = j0 == 0 ? e0[w] : valid ? ent[j] : 0u;
+            const uint32_t k = e >> count_bits;
+            double delta = 0.0;
+            if (valid) {
+                const float f = ((float)(e & cmask) + beta) / (j0 == 0 ? den0[w] : denom[k]);
+                val[j] = f;
+                delta = (double)f - (double)(j0 == 0 ? base0[w] : base[k]);
             }
-            last = __builtin_amdgcn_readlane(at, 63);
+            const double incl = wave_incl_scan(delta) + carry;
+            const int blk = (int)(k >> 6);
+            int next_blk = __builtin_amdgcn_update_dpp(-1, blk, 0x130, 0xf, 0xf, false);   // wave_shl:1
+            if (j0 + kWave < nnz && lane == kWave - 1) next_blk = (int)((ent[j + 1] >> count_bits) >> 6);
+            const unsigned long long ends = __builtin_amdgcn_ballot_w64(valid && (j + 1 == nnz || blk != next_blk));
+            if (__builtin_amdgcn_inverse_ballot_w64(ends)) {
+                lds_dcum[blocks + (int)bits_up_to_lane(ends)] = incl;
+                atomicOr(&has[blk >> 5], 1u << (blk & 31));
+            }
+            blocks += (int)__builtin_popcountll(ends);
+            carry = readlane_f64(incl, 63);
         }
+        wave_lds_fence();
+        // A block's difference is that of the last block with a non-zero up to it: the blocks with one are counted.
+        int before = 0;
+        float total = 0.f;
+        for (int i0 = 0; i0 < n3; i0 += kSteps * kWave) {
+#pragma unroll
+            for (int st = 0; st < kSteps; st++) {
+                if (i0 + st * kWave >= n3) break;   // uniform
+                const int i = i0 + st * kWave + lane;
+                const uint2 m = reinterpret_cast<const uint2 *>(has)[i0 / kWave + st];
+                const unsigned long long mask = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)m.y) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)m.x);
+                const double delta = lds_dcum[before + (int)bits_up_to_lane(mask)];
+                before += (int)__builtin_popcountll(mask);
+                if (i < n3) {
+                    const double run = (i0 ? basecum[i] : cum[st]) + delta;
+                    l3_64[(size_t)v * (size_t)n3 + (size_t)i] = run;
+                    l3[(size_t)v * (size_t)n3pad + (size_t)i] = (float)run;
+                    if (i == n3 - 1) total = (float)run;
+                }
+            }
+        }
+        wave_lds_fence();
+        total = readlane_f32(total, (n3 - 1) & (kWave - 1));
+        for (int i = n3 + lane; i < n3pad; i += kWave) l3[(size_t)v * (size_t)n3pad + i] = total;
+        if (lane == 0) sumphi[v] = total;
     }
-    total = readlane_f32(total, (n3 - 1) & (kWave - 1));
-    for (int i = n3 + lane; i < n3pad; i += kWave) l3[(size_t)v * (size_t)n3pad + i] = total;
-    if (lane == 0) sumphi[v] = total;
 }
 
-__global__ void __launch_bounds__(64) light_tree_kernel(LightParams p) {
+template <int W>
+__global__ void __launch_bounds__(64) light_tree_kernel(LightParams p, int n_light) {
     extern __shared__ double lds_dcum[];
-    light_word(p, (int)blockIdx.x, lds_dcum);
+    light_words<W>(p, (int)blockIdx.x * W, n_light, lds_dcum);
 }
 
 // Bhat rows of the words asked for, out[i][k], one workgroup each: a dense row is copied, a light word's is the base vector
@@ -2096,8 +2123,9 @@ __global__ void __launch_bounds__(256, 8) mstep_counts_kernel(MCounts p) {
     else if (lane_id() == 0) g.rec[d].y = 0u;
 }
 
-// Then everything that follows from the counts: dense rows of Bhat, a workgroup each, the statistics, and the light words, a
-// wavefront each.
+// Then everything that follows from the counts: dense rows of Bhat, a workgroup each, the statistics, and the light words, W to a
+// wavefront.
+template <int W>
 __global__ void __launch_bounds__(1024, 8) mstep_rows_kernel(const PhiRow *rows, int n_rows, const uint16_t *z_wm, int32_t *cwk, float *phi, int Kpad,
                                                              int range, StatsParams st, int n_stats, LightParams lp, int n_light) {
     extern __shared__ int4 mr_lds4[];
@@ -2108,8 +2136,8 @@ __global__ void __launch_bounds__(1024, 8) mstep_rows_kernel(const PhiRow *rows,
         phi_row(rows[b], (size_t)b, z_wm, cwk, lp.denom, phi, lp.l3, lp.l3_64, lp.sumphi, Kpad, lp.n3, lp.n3pad, lp.beta, range, mr_lds4);
         return;
     }
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), li = (b - n_rows) * (int)(blockDim.x / kWave) + wave;
-    if (li < n_light) light_word(lp, li, reinterpret_cast<double *>(reinterpret_cast<char *>(mr_lds4) + (size_t)wave * light_lds_bytes(lp.n3)));
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), li = ((b - n_rows) * (int)(blockDim.x / kWave) + wave) * W;
+    if (li < n_light) light_words<W>(lp, li, n_light, reinterpret_cast<double *>(reinterpret_cast<char *>(mr_lds4) + (size_t)wave * light_lds_bytes(lp.n3)));
 }
 
 // ---------------------------------------------------------------------------------------------

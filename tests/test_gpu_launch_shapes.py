@@ -345,3 +345,23 @@ def test_rows_of_bhat_by_parts(K):
         assert np.array_equal(z, all_rows.get_z())
         o.set_z(z, 1)
     few.close(); all_rows.close(); o.close()
+
+
+@pytest.mark.parametrize("K", [60, 1000, 8192, 8200])
+@pytest.mark.parametrize("V", [16_380, 16_500])
+def test_light_words_of_a_wavefront(K, V):
+    """Four light words to a wavefront where rows are short and words many, one otherwise: words without tokens, with one, with one
+    block of topics, with more non-zeros than lanes; a last wavefront with fewer words."""
+    counts = np.r_[np.resize([0, 1, 2, 29], V - 9), 63, 64, 65, 128, 129, 200, 400, 0, 1]
+    doc_ptr, words = corpus_of_word_counts(counts, 300, K)
+    pk = saber()
+    g = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 4, light_word_tokens=1000)
+    o = oracle.Model(doc_ptr, words, V, K, 0.1, 0.01, 4)
+    assert g.get_stats()["light_words_present"] == np.count_nonzero(counts)
+    some = np.r_[0:400, V - 30:V].astype(np.int32)
+    for _ in range(2):
+        phi, prefix = g.get_phi(some)
+        assert np.array_equal(phi, o.phi[some])
+        assert np.mean(prefix != o.c32[some]) < 1e-5 and np.allclose(prefix, o.c32[some], rtol=1.2e-7, atol=0)
+        assert_estep_parity(g, o)
+    g.close(); o.close()
