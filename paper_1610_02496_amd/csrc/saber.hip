@@ -138,7 +138,7 @@ struct saber_ctx {
     uint64_t seed = 0;
     uint32_t iter = 0, topic_bits = 0, count_bits = 0;   // (a packed entry: the topic above the count)
     bool z16 = false, staged = false, b16 = false;
-    int pack = PACK_ANY;              // what the sampling kernel may take for granted of entries
+    int pack = PACK_ANY;              // what a kernel may take for granted of the entries of this context's rows of A
     bool slots = false;               // sampling wavefronts have a part of LDS of their own (estep_kernel, SLOTS)
     bool overlay = false;             // rows do not fit LDS: light words are read from memory with marks in LDS (Overlay)
     bool auto_light_block = false;    // neither workgroup size was given: those of light words' tiles follow the tile
@@ -306,12 +306,12 @@ static void set_rows(EStepParams &p, const saber_ctx *theta, const Chunk &ch) {
     p.quarter_row_bytes = 4u * (uint32_t)theta->opt.quarter_row_entries; p.half_row_bytes = 4u * (uint32_t)theta->opt.half_row_entries;
 }
 
+// everything but the rows of A, which launch_estep() adds
 static EStepParams make_params(saber_ctx *c, const Chunk &ch, int slot = -1) {
     EStepParams p{};
     p.tiles = c->tiles + ch.tile0;
     if (slot < 0) { p.tok_doc = c->tok_doc + ch.t0; p.tok_t = c->tok_t + ch.t0; }
     else { p.tok_doc = c->slot_tok_doc[slot]; p.tok_t = c->slot_tok_t[slot]; }
-    set_rows(p, c, ch);
     p.phi = c->phi; p.l3 = c->l3; p.l3_64 = c->l3_64; p.sumphi = c->sumphi;
     const ZView zv = z_view(c, ch, slot);
     p.z = zv.z; p.z_rel = ch.t0 - zv.first;
@@ -345,11 +345,11 @@ static void launch_with_lds(Kern kern, dim3 grid, dim3 block, size_t lds, hipStr
 }
 
 template <int MODE, bool STAGED, typename ZT>
-static void launch_estep_packed(saber_ctx *c, dim3 grid, dim3 block, size_t lds, const EStepParams &p) {
+static void launch_estep_packed(saber_ctx *c, int pack, dim3 grid, dim3 block, size_t lds, const EStepParams &p) {
     if (MODE == MODE_SAMPLE && STAGED && sizeof(ZT) == 2 && c->slots)
         launch_with_lds(estep_kernel<MODE_SAMPLE, true, uint16_t, PACK_16_14, true>, grid, block, lds, c->stream, p);
-    else if (STAGED && c->pack == PACK_16_14) launch_with_lds(estep_kernel<MODE, STAGED, ZT, STAGED ? PACK_16_14 : PACK_16>, grid, block, lds, c->stream, p);
-    else if (c->pack != PACK_ANY) launch_with_lds(estep_kernel<MODE, STAGED, ZT, PACK_16>, grid, block, lds, c->stream, p);
+    else if (STAGED && pack == PACK_16_14) launch_with_lds(estep_kernel<MODE, STAGED, ZT, STAGED ? PACK_16_14 : PACK_16>, grid, block, lds, c->stream, p);
+    else if (pack != PACK_ANY) launch_with_lds(estep_kernel<MODE, STAGED, ZT, PACK_16>, grid, block, lds, c->stream, p);
     else launch_with_lds(estep_kernel<MODE, STAGED, ZT, PACK_ANY>, grid, block, lds, c->stream, p);
 }
 
@@ -400,8 +400,12 @@ static int32_t walkers_for(const saber_ctx *c, int mode, int64_t n, int block) {
 }
 
 // One E-step launch per tile class (tile_classes() below).  All stage the row in LDS when it fits.
+// `theta`: the context whose rows of A are read, c itself but for the scored part of held-out documents.  What may be taken for
+// granted of their entries is its knowledge: an observed part may be longer than any scored one.
 template <int MODE>
-static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
+static int launch_estep(saber_ctx *c, const saber_ctx *theta, const Chunk &ch, EStepParams &p0) {
+    // (theta's documents are c's documents: same D, same chunks - the held-out contexts have one chunk each)
+    set_rows(p0, theta, theta->chunks[(size_t)(&ch - c->chunks.data())]);
     for (const TileClass &cl : ch.classes) {
         for (int64_t i = 0, n; i < cl.count; i += n) {
             n = std::min(cl.count - i, most_blocks(cl.block));
@@ -414,11 +418,11 @@ static int launch_estep(saber_ctx *c, const Chunk &ch, EStepParams &p0) {
             const dim3 grid((unsigned)(p.first_light + p.walkers)), block((unsigned)cl.block);
             const size_t lds = estep_lds_bytes(c, MODE, cl.block);
             if (c->staged) {
-                if (c->z16) launch_estep_packed<MODE, true, uint16_t>(c, grid, block, lds, p);
-                else launch_estep_packed<MODE, true, int32_t>(c, grid, block, lds, p);
+                if (c->z16) launch_estep_packed<MODE, true, uint16_t>(c, theta->pack, grid, block, lds, p);
+                else launch_estep_packed<MODE, true, int32_t>(c, theta->pack, grid, block, lds, p);
             } else {
-                if (c->z16) launch_estep_packed<MODE, false, uint16_t>(c, grid, block, lds, p);
-                else launch_estep_packed<MODE, false, int32_t>(c, grid, block, lds, p);
+                if (c->z16) launch_estep_packed<MODE, false, uint16_t>(c, theta->pack, grid, block, lds, p);
+                else launch_estep_packed<MODE, false, int32_t>(c, theta->pack, grid, block, lds, p);
             }
             HIP_TRY(hipGetLastError());
         }
@@ -1588,7 +1592,7 @@ extern "C" int saber_iterate(saber_ctx *c, int32_t n) {
                 if (c->n_slots) SABER_TRY(stream_acquire(c, ch, &s));
                 EStepParams p = make_params(c, ch, s);
                 p.n_dense = c->dense_slots + (size_t)kDenseSlots * b;
-                SABER_TRY(launch_estep<MODE_SAMPLE>(c, ch, p));
+                SABER_TRY(launch_estep<MODE_SAMPLE>(c, c, ch, p));
                 if (c->n_slots) {
                     // the chunk's rows of A are rebuilt while its new assignments are in the buffer (the sampling
                     // of later chunks reads other documents' rows only); after that only z_wm keeps them
@@ -1910,10 +1914,8 @@ static int launch_loglik(saber_ctx *c, const saber_ctx *theta, const LlScratch &
         int s = -1;
         if (c->n_slots) SABER_TRY(stream_acquire(c, ch, &s));
         EStepParams p = make_params(c, ch, s);
-        // theta's documents are c's documents (same D, same chunks: the held-out contexts have one chunk each)
-        set_rows(p, theta, theta->chunks[(size_t)(&ch - c->chunks.data())]);
         p.out_ll = ws.tile_part;
-        SABER_TRY(launch_estep<MODE_LOGLIK>(c, ch, p));
+        SABER_TRY(launch_estep<MODE_LOGLIK>(c, theta, ch, p));
         if (c->n_slots) SABER_TRY(stream_release(c, s));
         hipLaunchKernelGGL(reduce_partials_kernel, dim3(kReduceBlocks), dim3(kReduceThreads), 0, c->stream, ws.tile_part,
                            ch.ntiles, ws.block_part);
@@ -1990,7 +1992,7 @@ static int foldin_iterate(saber_ctx *c, int32_t n) {
         for (const Chunk &ch : c->chunks) {
             EStepParams p = make_params(c, ch);
             p.n_dense = c->dense_slots;
-            SABER_TRY(launch_estep<MODE_SAMPLE>(c, ch, p));
+            SABER_TRY(launch_estep<MODE_SAMPLE>(c, c, ch, p));
         }
         SABER_TRY(launch_counts(c));
     }
@@ -2265,7 +2267,7 @@ extern "C" int saber_token_probs(saber_ctx *c, const int64_t *tok, int64_t m, fl
         }
         EStepParams p = make_params(c, ch, s);
         p.marks = marks; p.out_S = dS; p.out_Q = dQ;
-        SABER_TRY(launch_estep<MODE_PROBS>(c, ch, p));
+        SABER_TRY(launch_estep<MODE_PROBS>(c, c, ch, p));
         if (c->n_slots) SABER_TRY(stream_release(c, s));
         SABER_TRY(by_pieces([&](int64_t i, int64_t n, dim3 grid) {
             hipLaunchKernelGGL(gather_probs_kernel, grid, dim3(256), 0, c->stream, dS, dQ, marks, dtok + i, n, ch.t0, ch.ntok,

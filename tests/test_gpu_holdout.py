@@ -141,3 +141,23 @@ def test_held_out_layouts_of_any_size(tile_tokens):
         ll_o, n_o, z_o = o.holdout_loglik(dp, words, (mask != 0).astype(np.uint8), 0, 77)
         assert n == n_o == scored and np.array_equal(z, z_o) and abs(ll - ll_o) <= 1e-6 * abs(ll_o)
     g.close(); o.close()
+
+
+@pytest.mark.parametrize("observed,scored", [(16_383, 4000), (16_384, 4000), (20_000, 4000), (65_535, 1), (4000, 20_000)])
+@pytest.mark.parametrize("K", [40, 900])
+def test_observed_and_scored_parts_on_two_sides_of_the_packing(K, observed, scored):
+    """The scored part reads the observed part's rows of A, whose counts reach the documents' observed lengths: below 2^14 a topic's
+    place in LDS is one shift of an entry, from there on it is not, whichever side the scored parts' lengths are on."""
+    c, g, o = trained_pair(K)
+    rng = np.random.default_rng(observed + K)
+    T = observed + scored
+    dp = np.array([0, T, T + 300], dtype=np.int64)
+    words = rng.integers(0, o.V, T + 300).astype(np.int32)
+    mask = np.zeros(T + 300, np.uint8)
+    mask[rng.permutation(T)[:observed]] = 1
+    mask[T::2] = 1
+    z0 = rng.integers(0, K, int(mask.sum())).astype(np.int32)
+    z0[:observed] = K - 1                                # one entry, its count the part's length
+    got, ref = g.holdout_loglik(dp, words, mask, 0, 5, z0), o.holdout_loglik(dp, words, mask, 0, 5, z0)
+    assert got[1] == ref[1] == scored + 150 and abs(got[0] - ref[0]) <= 1e-6 * abs(ref[0])
+    g.close(); o.close()

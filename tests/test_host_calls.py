@@ -473,3 +473,18 @@ def test_workgroups_that_light_words_are_dealt_to(host, K, opts, cus, walkers):
         g.loglik()
         assert fake.fake_blocks(b"estep_kernel") == g.get_stats()["tiles"] == 20_000
     """ % ((K, opts, cus, walkers),))
+
+
+@pytest.mark.parametrize("observed,scored,pack", [(16_383, 4000, 2), (16_384, 4000, 1), (20_000, 4000, 1), (4000, 20_000, 2), (16_383, 16_384, 2)])
+def test_scored_parts_read_the_observed_parts_rows(host, observed, scored, pack):
+    """The kernel that scores is the one for the counts in the rows of A that it reads, whatever length the scored parts have."""
+    host("""
+        observed, scored, pack = %r
+        words = (np.arange(observed + scored) %% 40).astype(np.int32)
+        g = pk.Saber(np.array([0, 1000]), words[:1000], 40, 300, 0.1, 0.01, 3)
+        fake.fake_clear()
+        mask = np.arange(observed + scored) < observed
+        g.holdout_loglik(np.array([0, words.size]), words, mask, 0, 5)
+        kernel = "estep_kernelILi2ELb1EtLi%%dE"      # log-likelihood, staged rows, 16-bit assignments
+        assert [launches(kernel %% p)[0] for p in (0, 1, 2)] == [int(p == pack) for p in (0, 1, 2)]
+    """ % ((observed, scored, pack),))
