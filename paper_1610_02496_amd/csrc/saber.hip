@@ -376,6 +376,7 @@ static int check_estep_lds_layout() {
 
 // Wavefronts a CU holds of a sampling kernel with `block` threads per workgroup, given its LDS (handed out in 1,280-byte pieces; the
 // choice of a workgroup's size reckons with 512) and the 32 wavefronts a CU can hold.
+constexpr size_t kLdsPiece = 1280;
 static int estep_waves_per_cu(const saber_ctx *c, int block, size_t piece = 512) {
     const size_t need = c->staged || c->overlay ? ((estep_lds_bytes(c, MODE_SAMPLE, block) + (piece == 512 ? 144 : 0) + piece - 1) / piece) * piece : 512;
     const int by_lds = (int)std::min<size_t>(64, (size_t)c->lds_per_cu / need), by_waves = 32 / (block / 64);
@@ -394,7 +395,7 @@ constexpr int64_t kWalkTiles = 8, kWalkRounds = 16;
 constexpr size_t kWalkRow = 16 * 1024;
 static int32_t walkers_for(const saber_ctx *c, int mode, int64_t n, int block) {
     if (!c->staged || !c->z16 || mode != MODE_SAMPLE || n <= 0 || estep_row_bytes(c) < kWalkRow) return (int32_t)n;
-    const int64_t places = c->cus * estep_waves_per_cu(c, block) / (block / 64);
+    const int64_t places = c->cus * estep_waves_per_cu(c, block, kLdsPiece) / (block / 64);   // (at least one workgroup fits: make_ctx() sees to it)
     const int64_t tiles = std::max<int64_t>(1, std::min(kWalkTiles, n / (kWalkRounds * places)));
     return (int32_t)((n + tiles - 1) / tiles);
 }
@@ -1529,9 +1530,9 @@ static int make_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word
     // one) 1,629 -> 1,628.  Not for the sake of it: T = 36 M, K = 5,000 2.36 ms with 32 wavefronts per CU and lane
     // permutations, 2.51 with 24 of the same workgroups, 2.62 with 32 in larger ones; T = 100 M, K = 10,000 7.1 and 7.4.
     if (c->staged && c->z16 && c->pack == PACK_16_14) {
-        const int without = estep_waves_per_cu(c, c->opt.block_threads, 1280), light = estep_waves_per_cu(c, c->opt.light_block_threads, 1280);
+        const int without = estep_waves_per_cu(c, c->opt.block_threads, kLdsPiece), light = estep_waves_per_cu(c, c->opt.light_block_threads, kLdsPiece);
         c->slots = true;
-        c->slots = estep_waves_per_cu(c, c->opt.block_threads, 1280) == without && estep_waves_per_cu(c, c->opt.light_block_threads, 1280) == light;
+        c->slots = estep_waves_per_cu(c, c->opt.block_threads, kLdsPiece) == without && estep_waves_per_cu(c, c->opt.light_block_threads, kLdsPiece) == light;
     }
     if (c->opt.tile_tokens <= 0) c->opt.tile_tokens = auto_tile_tokens(c, per_chunk);
     c->vbeta = (float)V * beta;

@@ -365,3 +365,22 @@ def test_light_words_of_a_wavefront(K, V):
         assert np.mean(prefix != o.c32[some]) < 1e-5 and np.allclose(prefix, o.c32[some], rtol=1.2e-7, atol=0)
         assert_estep_parity(g, o)
     g.close(); o.close()
+
+
+@pytest.mark.parametrize("K", [11_000, 14_000, 20_500, 36_990, 37_013, 37_048, 37_049])
+def test_short_rows_exchange_beside_a_long_row_in_lds(K):
+    """Rows of Bhat that leave some of a CU's LDS to the wavefronts' parts, from K = 37,013 to 37,048 all but 144 bytes of it
+    or fewer; from 37,049 on there is none left for them."""
+    counts = np.r_[np.resize([1, 2, 5, 29, 40], 3000), 500, 3000]
+    doc_ptr, words = corpus_of_word_counts(counts, 900, K)
+    pk, V = saber(), counts.size
+    g = pk.Saber(doc_ptr, words, V, K, 0.01, 0.01, 4)
+    p = pk.Saber(doc_ptr, words, V, K, 0.01, 0.01, 4, quarter_row_entries=-1, half_row_entries=-1)
+    o = oracle.Model(doc_ptr, words, V, K, 0.01, 0.01, 4)
+    assert_estep_parity(g, o)
+    p.iterate(1)
+    assert np.array_equal(g.get_z(), p.get_z())
+    g.iterate(2)
+    p.iterate(2)
+    assert np.array_equal(g.get_z(), p.get_z())
+    g.close(); p.close(); o.close()

@@ -488,3 +488,19 @@ def test_scored_parts_read_the_observed_parts_rows(host, observed, scored, pack)
         kernel = "estep_kernelILi2ELb1EtLi%%dE"      # log-likelihood, staged rows, 16-bit assignments
         assert [launches(kernel %% p)[0] for p in (0, 1, 2)] == [int(p == pack) for p in (0, 1, 2)]
     """ % ((observed, scored, pack),))
+
+
+@pytest.mark.parametrize("K,opts,walkers", [(37_010, {}, 2500), (37_020, {}, 2500), (37_040, {}, 2500), (37_060, {}, 2500), (37_240, {"block_threads": 960}, 2500),
+                                            (37_650, {"block_threads": 832}, 2500), (36_000, {"light_block_threads": 1024, "block_threads": 64}, 2500)])
+def test_workgroups_whose_lds_is_all_a_cu_has(host, K, opts, walkers):
+    """A staged row and the wavefronts' parts of LDS may fill a CU's to the last piece: one workgroup fits, and light words' tiles
+    are dealt to as many as fit the chip."""
+    host("""
+        K, opts, walkers = %r
+        fake.fake_cus(8)
+        words = np.repeat(np.arange(20_000, dtype=np.int32), 5)
+        g = pk.Saber(np.r_[np.arange(0, words.size, 1000), words.size], words, 20_000, K, 0.1, 0.01, 3, **opts)
+        fake.fake_clear()
+        g.iterate(1)
+        assert fake.fake_blocks(b"estep_kernel") == walkers
+    """ % ((K, opts, walkers),))
