@@ -218,7 +218,8 @@ struct saber_ctx {
     int32_t *slot_tok_doc[kMaxSlots] = {}; uint32_t *slot_tok_t[kMaxSlots] = {}; void *slot_z[kMaxSlots] = {};
     hipStream_t s_in = nullptr, s_docs = nullptr;   // copies; the expansion of their tok_doc
     hipEvent_t ev_copied[kMaxSlots] = {}, ev_loaded[kMaxSlots] = {}, ev_done[kMaxSlots] = {};
-    bool slot_used[kMaxSlots] = {};
+    bool slot_used[kMaxSlots] = {};   // ev_done says when its last user's kernels are done
+    bool slot_open[kMaxSlots] = {};   // loaded, and ev_done not recorded since
     // ablation variants (saber_options.ablation): document-order sampling needs the words in canonical order and
     // the word -> row map; the sort-based rebuild of A needs key buffers and the sort's work space
     int32_t *word_ids_d = nullptr, *word_row_d = nullptr;
@@ -677,13 +678,21 @@ static int launch_count_dz_chunk(saber_ctx *c, const Chunk &ch, int slot) {
 }
 
 // ---- host streaming ----
+static int sync_all(saber_ctx *c) {
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    if (c->n_slots) { HIP_TRY(hipStreamSynchronize(c->s_in)); HIP_TRY(hipStreamSynchronize(c->s_docs)); }
+    return SABER_OK;
+}
 // Takes the next buffer (round robin) for chunk `ch`: once the kernels of the buffer's previous user have run, the chunk's tok_t is
 // copied in, and with `docs` tok_doc derived from it.  stream_wait() makes the compute stream wait for that.
 static int stream_load(saber_ctx *c, const Chunk &ch, bool docs, int *slot) {
     const int s = c->next_slot;
     c->next_slot = (c->next_slot + 1) % c->n_slots;
     if (ch.ntok > c->slot_tokens) return fail(SABER_ESTATE, "chunk of %lld tokens exceeds the streaming buffers", (long long)ch.ntok);
-    if (c->slot_used[s]) HIP_TRY(hipStreamWaitEvent(c->s_in, c->ev_done[s], 0));
+    // (a call that broke off between here and stream_release() has left work on any of the three streams that no event tells of)
+    if (c->slot_open[s]) SABER_TRY(sync_all(c));
+    else if (c->slot_used[s]) HIP_TRY(hipStreamWaitEvent(c->s_in, c->ev_done[s], 0));
+    c->slot_open[s] = true;
     *slot = s;
     if (ch.ntok == 0) return SABER_OK;
     HIP_TRY(hipMemcpyAsync(c->slot_tok_t[s], c->h_tok_t + ch.t0, (size_t)ch.ntok * sizeof(uint32_t), hipMemcpyHostToDevice, c->s_in));
@@ -712,11 +721,7 @@ static int stream_acquire(saber_ctx *c, const Chunk &ch, int *slot, bool docs = 
 static int stream_release(saber_ctx *c, int s) {
     HIP_TRY(hipEventRecord(c->ev_done[s], c->stream));
     c->slot_used[s] = true;
-    return SABER_OK;
-}
-static int sync_all(saber_ctx *c) {
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    if (c->n_slots) { HIP_TRY(hipStreamSynchronize(c->s_in)); HIP_TRY(hipStreamSynchronize(c->s_docs)); }
+    c->slot_open[s] = false;
     return SABER_OK;
 }
 

@@ -15,7 +15,7 @@ fake.fake_launches.restype, fake.fake_launches.argtypes = ctypes.c_int64, [ctype
 fake.fake_blocks.restype, fake.fake_blocks.argtypes = ctypes.c_uint64, [ctypes.c_char_p]
 fake.fake_calls.restype, fake.fake_calls.argtypes = ctypes.c_int64, [ctypes.c_char_p]
 fake.fake_new_limit.argtypes = [ctypes.c_int64]
-fake.fake_host_bytes.restype = fake.fake_mallocs_on.restype = ctypes.c_int64
+fake.fake_host_bytes.restype = fake.fake_mallocs_on.restype = fake.fake_races.restype = ctypes.c_int64
 import numpy as np
 import paper_1610_02496_amd as pk
 
@@ -24,6 +24,11 @@ def launches(name):
     most = ctypes.c_uint64()
     n = fake.fake_launches(name.encode(), ctypes.addressof(most))
     return n, fake.fake_blocks(name.encode()), most.value
+
+def races():
+    '''accesses to the buffers of streamed chunks so far that nothing puts in order, and the first one'''
+    first = ctypes.create_string_buffer(200)
+    return fake.fake_races(first, ctypes.c_int64(200)), first.value.decode()
 
 def code_of(call):
     '''status code of a call of the binding'''

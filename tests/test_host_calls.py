@@ -504,3 +504,52 @@ def test_workgroups_whose_lds_is_all_a_cu_has(host, K, opts, walkers):
         g.iterate(1)
         assert fake.fake_blocks(b"estep_kernel") == walkers
     """ % ((K, opts, walkers),))
+
+
+STREAMED = """
+        V, K = 60, %d
+        words = np.arange(30_000, dtype=np.int32) * 7 %% V
+        lens = np.r_[np.resize([0, 40, 900, 3], 60), 1000]
+        lens[-1] = words.size - lens[:-1].sum()
+        doc_ptr = np.r_[0, np.cumsum(lens)]
+        g = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 3, stream_workers=%d, n_chunks=%d)
+        z = np.zeros(words.size, np.int32)
+        uses = {"iterate": lambda: g.iterate(2), "get_z": g.get_z, "loglik": g.loglik, "probs": lambda: g.token_probs([3, 29_000]),
+                "set_z": lambda: g.set_z(z, 0), "counts": lambda: g.counts()}
+"""
+
+
+@pytest.mark.parametrize("workers,chunks", [(1, 5), (2, 5), (3, 5), (3, 2), (2, 1), (4, 3)])
+@pytest.mark.parametrize("K", [100, 70_000])
+def test_buffers_of_streamed_chunks_are_used_in_order(host, K, workers, chunks):
+    """Copies of token lists, the expansion of their documents and the kernels that read them run on three streams, a checkpoint
+    looks a chunk ahead: whatever call follows which, a buffer's uses are in order."""
+    host(STREAMED % (K, workers, chunks) + """
+        for first in uses.values():
+            for second in uses.values():
+                first()
+                second()
+        assert launches("expand_tok_doc")[0] and launches("scatter_zwm")[0] and launches("estep_kernel")[0]
+        assert races() == (0, "")
+    """)
+
+
+@pytest.mark.parametrize("workers,chunks", [(1, 5), (2, 5), (3, 4)])
+def test_buffers_of_streamed_chunks_after_a_call_that_broke_off(host, workers, chunks):
+    """What a failed call has queued for a buffer may still run when the next call takes the buffer."""
+    host(STREAMED % (100, workers, chunks) + """
+        nth_max = 0
+        for name, first in uses.items():
+            for call in ("expand_tok_doc", "estep_kernel", "count_dz", "scatter_zwm", "fill_zwm", "hipEventRecord", "hipMemcpyAsync", "hipMemcpy:", "hipStreamWaitEvent"):
+                for nth in range(1, 60):
+                    fake.fake_fail(call.encode(), nth)
+                    code = code_of(first)
+                    if fake.fake_fail_pending(): break
+                    nth_max = max(nth, nth_max)
+                    fake.fake_fail(b"", 0)
+                    assert code in (0, -2, -3), (name, call, nth, code)
+                    for second in (uses["get_z"], uses["iterate"])[::1 if nth % 2 else -1]: second()
+                    assert races() == (0, ""), (name, call, nth, races())
+                fake.fake_fail(b"", 0)
+        assert nth_max > 4
+    """)
