@@ -165,6 +165,7 @@ struct saber_ctx {
     int32_t *light_words = nullptr;   // [V_light] word of each light row
     int32_t *light_short = nullptr, *light_long = nullptr;   // light rows by token count, for the count launches
     int64_t n_light_short = 0, n_light_long = 0;
+    int32_t n_light_wide = 0;         // light rows of words with more than kWideWord tokens: they come first
     int64_t *light_tok_ptr = nullptr; // [V_light+1] positions of the light words' tokens in z_wm
     uint2 *wrec = nullptr;            // [V_light] {row start / 32, non-zeros}
     uint32_t *lw_ent = nullptr;       // packed rows of B of the light words
@@ -728,18 +729,29 @@ static int stream_release(saber_ctx *c, int s) {
 // Preprocess + BuildTree for the light words (sparse rows of B); needs the base vector, i.e. runs after launch_phi
 static LightParams light_params(const saber_ctx *c) {
     return LightParams{c->light_words, c->wrec, c->lw_ent, c->lw_phi, c->denom, c->phi + (size_t)c->V_dense * (size_t)c->Kpad,
-                       c->l3_64 + (size_t)c->V * (size_t)c->n3, c->l3, c->l3_64, c->sumphi, c->n3, c->n3pad, c->count_bits, c->beta};
+                       c->l3_64 + (size_t)c->V * (size_t)c->n3, c->l3, c->l3_64, c->sumphi, c->n3, c->n3pad, c->V_light, c->n_light_wide, c->count_bits, c->beta};
 }
 // Light words per wavefront: four where rows are short enough that their chain of loads counts (up to 128 blocks of topics) and the
-// chip stays full of wavefronts.  Kernel with one, two and four: T = 10 M, K = 1,000, 98,600 words (dense rows with them) 35, 29 and
-// 28 us; T = 2.3 M, K = 777, 29,500 words 12.5, 11.3 and 11.2; T = 36 M, K = 5,000, 140,000 words 76, 70 and 69; T = 100 M, K = 10,000
-// 119, 118 and 121; T = 15 M, K = 20,011 104, 106 and 123; T = 1.5 M, K = 70,000, 4,000 words 38, 69 and 126; T = 100 K 5.6 all.
-static int words_per_wave(const saber_ctx *c) { return c->n3 <= 128 && c->V_light >= 16384 ? 4 : 1; }
+// chip stays full of wavefronts.  Kernel with one, two and four, late iterations: T = 10 M, K = 1,000, 98,600 words (dense rows with
+// them) 35, 29 and 28 us; T = 2.3 M, K = 777, 29,500 words 12.5, 11.3 and 11.2; T = 36 M, K = 5,000, 140,000 words 76, 70 and 69; T =
+// 100 M, K = 10,000 119, 118 and 121; T = 15 M, K = 20,011 104, 106 and 123; T = 1.5 M, K = 70,000, 4,000 words 38, 69 and 126; T = 100 K
+// 5.6 all.
+//   A word has a step of 64 non-zeros after the other, and those of four words come one after the other: the first iterations, and
+// words that the caller keeps light, have thousands.  So words of more than kWideWord tokens (four steps, as a wavefront of four
+// words has then too) have a wavefront each, before the others.  Phi group with one word, four, and four of those of at most
+// 64, 256 and 512 tokens, iterations 2 to 4 / late: T = 6 M, K = 8,000, 60,000 words 51 / 40, 109 / 54, 51 / 39, 50 / 39, 51 / 38 us; T =
+// 2 M, K = 4,000, 30,000 words 23.6 / 18.5, 58.6 / 25.3, 22.6 / 16.1, 21.8 / 16.5, 25.2 / 17.4; T = 10 M, K = 1,000 40 / 36, 32 / 29, 34 / 30,
+// 33 / 29, 33 / 29; T = 3 M, K = 5,000, all of 20,000 words light 83 / 51, 260 / 129, 83 / 51, 82 / 50, 82 / 50.
+constexpr int64_t kWideWord = 256;
+static int words_per_wave(const saber_ctx *c) { return c->n3 <= 128 && c->V_light - c->n_light_wide >= 16384 ? 4 : 1; }
+static unsigned light_waves(const saber_ctx *c) {
+    const int per_wave = words_per_wave(c);
+    return (unsigned)(c->n_light_wide + (c->V_light - c->n_light_wide + per_wave - 1) / per_wave);
+}
 static int launch_light_words(saber_ctx *c) {
     if (c->V_light == 0) return SABER_OK;
-    const int per_wave = words_per_wave(c);
-    hipLaunchKernelGGL((per_wave == 4 ? light_tree_kernel<4> : light_tree_kernel<1>), dim3((unsigned)((c->V_light + per_wave - 1) / per_wave)), dim3(64), light_lds_bytes(c->n3),
-                       c->stream, light_params(c), c->V_light);
+    hipLaunchKernelGGL((words_per_wave(c) == 4 ? light_tree_kernel<4> : light_tree_kernel<1>), dim3(light_waves(c)), dim3(64), light_lds_bytes(c->n3),
+                       c->stream, light_params(c));
     HIP_TRY(hipGetLastError());
     return SABER_OK;
 }
@@ -912,11 +924,10 @@ static int launch_joined_mstep(saber_ctx *c, const unsigned long long *slots, un
     const LightParams lp = light_params(c);
     const StatsParams st = stats_params(c, slots, stats_out);
     const int n_stats = stats_blocks(c, block);
-    const int per_wave = words_per_wave(c);
-    const unsigned grid2 = (unsigned)(n_stats + c->V_dense + (c->V_light + nw * per_wave - 1) / (nw * per_wave));
+    const unsigned grid2 = (unsigned)(n_stats + c->V_dense) + (light_waves(c) + nw - 1) / nw;
     const size_t lds2 = std::max((size_t)range * 4, (size_t)nw * light_lds_bytes(c->n3));
-    hipLaunchKernelGGL((per_wave == 4 ? mstep_rows_kernel<4> : mstep_rows_kernel<1>), dim3(grid2), dim3((unsigned)block), lds2, c->stream, c->phi_rows, c->V_dense,
-                       (const uint16_t *)c->z_wm, c->cwk, c->phi, c->Kpad, range, st, n_stats, lp, c->V_light);
+    hipLaunchKernelGGL((words_per_wave(c) == 4 ? mstep_rows_kernel<4> : mstep_rows_kernel<1>), dim3(grid2), dim3((unsigned)block), lds2, c->stream, c->phi_rows, c->V_dense,
+                       (const uint16_t *)c->z_wm, c->cwk, c->phi, c->Kpad, range, st, n_stats, lp);
     HIP_TRY(hipGetLastError());
     c->acc_used = false;
     return SABER_OK;
@@ -1095,8 +1106,10 @@ static int lay_out(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids
         for (int64_t t = 0; t < T; t++) n_v[(size_t)word_ids[t]]++;
         c->h_word_row.assign((size_t)V, 0);
         int64_t lunits = 0;
-        for (int32_t v = 0; v < V; v++) {
+        // (light words of many tokens first: see words_per_wave())
+        for (const bool wide : {true, false}) for (int32_t v = 0; v < V; v++) {
             if (light_ok && n_v[(size_t)v] < c->opt.light_word_tokens) {
+                if ((n_v[(size_t)v] > kWideWord) != wide) continue;
                 const int32_t li = (int32_t)h_light_words.size();
                 c->h_word_row[(size_t)v] = -li - 1;
                 h_light_words.push_back(v);
@@ -1105,7 +1118,8 @@ static int lay_out(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids
                 h_wrec.push_back(make_uint2((uint32_t)lunits, 0u));
                 lunits += (std::min<int64_t>(n_v[(size_t)v], K) + 31) / 32;
                 (n_v[(size_t)v] > c->opt.long_doc_tokens ? h_light_long : h_light_short).push_back(li);
-            } else {
+                c->n_light_wide += wide;
+            } else if (wide) {
                 c->h_word_row[(size_t)v] = (int32_t)h_row_word.size();
                 h_row_word.push_back(v);
             }

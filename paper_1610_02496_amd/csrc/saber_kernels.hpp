@@ -1870,7 +1870,7 @@ __global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, c
 }
 
 // ---------------------------------------------------------------------------------------------
-// Preprocess + BuildTree for the light words (one wavefront per W words).  Their Bhat row is the base vector
+// Preprocess + BuildTree for the light words (one wavefront per word, or per W words of few tokens).  Their Bhat row is the base vector
 // except at the word's non-zeros, so only those are evaluated (Eq. 2, same three binary32 operations) and
 // stored next to the entries.  The running sums at the block ends follow from the base vector's running sums
 // plus the cumulative difference (Bhat - base) of the non-zeros up to each block, all in binary64: the same
@@ -1880,17 +1880,18 @@ __global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, c
 struct LightParams {
     const int32_t *light_words; const uint2 *wrec; const uint32_t *lw_ent; float *lw_phi;
     const float *denom, *base; const double *basecum; float *l3; double *l3_64; float *sumphi;
-    int n3, n3pad; uint32_t count_bits; float beta;
+    int n3, n3pad, n_light, n_wide;   // the first n_wide words have many tokens and a wavefront each
+    uint32_t count_bits; float beta;
 };
 __host__ __device__ inline size_t light_lds_bytes(int n3) { return ((size_t)n3 + 1u + (size_t)(n3 + 63) / 64u) * 8u; }
 
-// W light words from number `first` on (of n_light), by one wavefront with light_lds_bytes(n3) of LDS at lds_dcum.  Bound by the chain of
+// Up to W light words, numbers `first` to `end`, by one wavefront with light_lds_bytes(n3) of LDS at lds_dcum.  Bound by the chain of
 // loads that leads to a word's non-zeros' denominators - its record, its entries, their denominators - where rows are short: the
 // words of a wavefront take each of the three steps together (see words_per_wave() on the host).  A block's running sum needs the
 // difference at the last block with a non-zero up to it, which is found by counting these (15 vector instructions per 64 blocks; by a
 // running maximum over the lanes and differences stored by block 30: T = 36 M, K = 5,000 82 -> 79 us).
 template <int W>
-__device__ __forceinline__ void light_words(const LightParams &p, int first, int n_light, double *lds_dcum) {
+__device__ __forceinline__ void light_words(const LightParams &p, int first, int end, double *lds_dcum) {
     const int n3 = p.n3, n3pad = p.n3pad, lane = lane_id();
     const uint32_t count_bits = p.count_bits, cmask = (1u << count_bits) - 1u;
     const float beta = p.beta;
@@ -1903,7 +1904,7 @@ __device__ __forceinline__ void light_words(const LightParams &p, int first, int
     uint2 rec[W];
 #pragma unroll
     for (int w = 0; w < W; w++) {
-        const int li = min(first + w, n_light - 1);
+        const int li = min(first + w, end - 1);
         word[w] = p.light_words[li]; rec[w] = p.wrec[li];
     }
     // the base vector's running sums of the first steps, requested under that chain
@@ -1912,14 +1913,15 @@ __device__ __forceinline__ void light_words(const LightParams &p, int first, int
 #pragma unroll
     for (int st = 0; st < kSteps; st++) cum[st] = basecum[min(st * kWave + lane, n3 - 1)];
     uint32_t e0[W];
+    const int others = end - first > 1 ? kWave : 0;   // (a word that is alone: nothing is loaded in the others' place)
     float den0[W], base0[W];
 #pragma unroll
-    for (int w = 0; w < W; w++) e0[w] = lane < (int)rec[w].y ? p.lw_ent[(size_t)rec[w].x * 32u + (size_t)lane] : 0u;
+    for (int w = 0; w < W; w++) e0[w] = lane < (w ? min((int)rec[w].y, others) : (int)rec[w].y) ? p.lw_ent[(size_t)rec[w].x * 32u + (size_t)lane] : 0u;
 #pragma unroll
     for (int w = 0; w < W; w++) { den0[w] = denom[e0[w] >> count_bits]; base0[w] = base[e0[w] >> count_bits]; }
 #pragma unroll
     for (int w = 0; w < W; w++) {
-        if (first + w >= n_light) break;   // uniform
+        if (first + w >= end) break;   // uniform
         const int v = word[w], nnz = (int)rec[w].y;
         const uint32_t *__restrict__ ent = p.lw_ent + (size_t)rec[w].x * 32u;
         float *__restrict__ val = p.lw_phi + (size_t)rec[w].x * 32u;
@@ -1979,10 +1981,16 @@ __device__ __forceinline__ void light_words(const LightParams &p, int first, int
     }
 }
 
+// The share of wavefront number `wave`: one of the first n_wide words, or W of the others.
 template <int W>
-__global__ void __launch_bounds__(64) light_tree_kernel(LightParams p, int n_light) {
+__device__ __forceinline__ void light_share(const LightParams &p, int wave, double *lds_dcum) {
+    const int first = W == 1 ? wave : min(wave, p.n_wide) + max(wave - p.n_wide, 0) * W;
+    light_words<W>(p, first, W == 1 || wave < p.n_wide ? first + 1 : min(first + W, p.n_light), lds_dcum);
+}
+template <int W>
+__global__ void __launch_bounds__(64) light_tree_kernel(LightParams p) {
     extern __shared__ double lds_dcum[];
-    light_words<W>(p, (int)blockIdx.x * W, n_light, lds_dcum);
+    light_share<W>(p, (int)blockIdx.x, lds_dcum);
 }
 
 // Bhat rows of the words asked for, out[i][k], one workgroup each: a dense row is copied, a light word's is the base vector
@@ -2123,11 +2131,11 @@ __global__ void __launch_bounds__(256, 8) mstep_counts_kernel(MCounts p) {
     else if (lane_id() == 0) g.rec[d].y = 0u;
 }
 
-// Then everything that follows from the counts: dense rows of Bhat, a workgroup each, the statistics, and the light words, W to a
-// wavefront.
+// Then everything that follows from the counts: dense rows of Bhat, a workgroup each, the statistics, and the light words, a wavefront
+// each or W to a wavefront.
 template <int W>
 __global__ void __launch_bounds__(1024, 8) mstep_rows_kernel(const PhiRow *rows, int n_rows, const uint16_t *z_wm, int32_t *cwk, float *phi, int Kpad,
-                                                             int range, StatsParams st, int n_stats, LightParams lp, int n_light) {
+                                                             int range, StatsParams st, int n_stats, LightParams lp) {
     extern __shared__ int4 mr_lds4[];
     int b = (int)blockIdx.x;
     if (b < n_stats) { stats_share(st, b, n_stats); return; }
@@ -2136,8 +2144,9 @@ __global__ void __launch_bounds__(1024, 8) mstep_rows_kernel(const PhiRow *rows,
         phi_row(rows[b], (size_t)b, z_wm, cwk, lp.denom, phi, lp.l3, lp.l3_64, lp.sumphi, Kpad, lp.n3, lp.n3pad, lp.beta, range, mr_lds4);
         return;
     }
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), li = ((b - n_rows) * (int)(blockDim.x / kWave) + wave) * W;
-    if (li < n_light) light_words<W>(lp, li, n_light, reinterpret_cast<double *>(reinterpret_cast<char *>(mr_lds4) + (size_t)wave * light_lds_bytes(lp.n3)));
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), share = (b - n_rows) * (int)(blockDim.x / kWave) + wave;
+    if (share < lp.n_wide + (lp.n_light - lp.n_wide + W - 1) / W)
+        light_share<W>(lp, share, reinterpret_cast<double *>(reinterpret_cast<char *>(mr_lds4) + (size_t)wave * light_lds_bytes(lp.n3)));
 }
 
 // ---------------------------------------------------------------------------------------------

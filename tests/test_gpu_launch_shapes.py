@@ -384,3 +384,27 @@ def test_short_rows_exchange_beside_a_long_row_in_lds(K):
     p.iterate(2)
     assert np.array_equal(g.get_z(), p.get_z())
     g.close(); p.close(); o.close()
+
+
+@pytest.mark.parametrize("K", [1000, 5000, 8200])
+def test_light_words_of_many_tokens_among_others(K):
+    """Words of more than 256 tokens have a wavefront each and come first among the light ones, wherever they are in the vocabulary:
+    words on both sides of that line, of up to 12,000 tokens, between 16,400 of few."""
+    rng = np.random.default_rng(K)
+    counts = rng.permutation(np.r_[np.resize([0, 1, 2, 9], 16_400), 65, 128, 255, 256, 256, 257, 257, 300, 1000, 3000, 12_000])
+    doc_ptr, words = corpus_of_word_counts(counts, 500, K)
+    pk, V = saber(), counts.size
+    g = pk.Saber(doc_ptr, words, V, K, 0.1, 0.01, 4, light_word_tokens=20_000)
+    o = oracle.Model(doc_ptr, words, V, K, 0.1, 0.01, 4)
+    assert g.get_stats()["light_tokens"] == o.T
+    some = np.r_[np.nonzero(counts > 9)[0], 0:200, V - 30:V].astype(np.int32)
+    for _ in range(2):
+        phi, prefix = g.get_phi(some)
+        assert np.array_equal(phi, o.phi[some])
+        assert np.mean(prefix != o.c32[some]) < 1e-5 and np.allclose(prefix, o.c32[some], rtol=1.2e-7, atol=0)
+        assert_estep_parity(g, o)
+    h = np.array([0, 4000], dtype=np.int64)              # a context that borrows the model's rows
+    hw, mask = rng.choice(words, 4000).astype(np.int32), (np.arange(4000) % 2).astype(np.uint8)
+    got, ref = g.holdout_loglik(h, hw, mask, 0, 5), o.holdout_loglik(h, hw, mask, 0, 5)
+    assert got[1] == ref[1] and abs(got[0] - ref[0]) <= 1e-6 * abs(ref[0])
+    g.close(); o.close()

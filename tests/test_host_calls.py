@@ -553,3 +553,21 @@ def test_buffers_of_streamed_chunks_after_a_call_that_broke_off(host, workers, c
                 fake.fake_fail(b"", 0)
         assert nth_max > 4
     """)
+
+
+@pytest.mark.parametrize("K,few,wide,shares", [(5000, 16_384, 40, 40 + 4096), (5000, 16_383, 40, 16_423), (8192, 20_001, 3, 3 + 5001), (8193, 20_001, 3, 20_004),
+                                               (1000, 16_386, 0, 4097), (1000, 16_386, 40, 40 + 4097), (1000, 16_383, 1, 16_384)])
+def test_wavefronts_of_light_words(host, K, few, wide, shares):
+    """Light words are four to a wavefront where rows are short and words many, those of more than 256 tokens alone."""
+    host("""
+        K, few, wide, shares = %r
+        rng = np.random.default_rng(K)
+        counts = np.r_[np.full(wide, 257), 256, np.ones(few - 1, int)]
+        words = np.repeat(rng.permutation(counts.size).astype(np.int32), counts)
+        g = pk.Saber(np.r_[np.arange(0, words.size, 1000), words.size], words, counts.size, K, 0.1, 0.01, 3, light_word_tokens=1000)
+        fake.fake_clear()
+        g.iterate(1)
+        alone, joined = launches("light_tree")[1], launches("mstep_rows")[1]
+        if K > 4096: assert (alone, joined) == (shares, 0)
+        else: assert alone == 0 and joined == -(-shares // 4) + min(256, -(-counts.size // fake.fake_block(b"mstep_rows")))
+    """ % ((K, few, wide, shares),))
