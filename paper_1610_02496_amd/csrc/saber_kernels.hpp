@@ -942,7 +942,9 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             // Requested without any branch around the load: a load inside a branch would make the compiler wait for ALL
             // outstanding loads where the branches meet, i.e. for the row just requested, before the current run's
             // arithmetic.  Without a further run (e < 0) it is lane 63's row, which the batch has read as a rule, or nothing.
+            // (Batches of the other modes may have a token or two of 64, and then it is nothing: see below.)
             last = (int)readlane_u32((uint32_t)row_last, e);
+            if (MODE != MODE_SAMPLE) last = e < 0 ? -1 : last;
             off = readlane_u32(row_off, e);
             asm volatile("" : "+v"(lane16));
             const auto v = __builtin_amdgcn_raw_buffer_load_b128(row_at(last, off), lane16, (int)off, 0);
@@ -958,8 +960,12 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
         uint32_t off_a, off_b, off_c, off_d;
         uint4 blk_a, blk_b, blk_c, blk_c2, blk_d, blk_d2;
         fetch(e_a, blk_a, last_a, off_a);
-        fetch(e_c, blk_c, last_c, off_c);
-        blk_c2 = fetch_more(last_c, off_c, 1);
+        // (Not those of several blocks where nothing is sampled: few batches have any, and with marks the loads are most of what a batch
+        // costs.  S and Q of 3,000 tokens of T = 10 M, K = 12,000 182 -> 177 us, of 200,000 547 -> 542.)
+        if (MODE == MODE_SAMPLE) {
+            fetch(e_c, blk_c, last_c, off_c);
+            blk_c2 = fetch_more(last_c, off_c, 1);
+        }
 
         if (SLOTS) {
             if (m16 | m32) {
@@ -996,6 +1002,8 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             wide_ends = clear_bit(wide_ends, e);
             e_next = first_bit(wide_ends);
             fetch(e_next, nxt, nxt_last, nxt_off);
+            __builtin_amdgcn_sched_barrier(0);      // (left to the compiler the request goes out after the wait for this run's row:
+                                                    // log-likelihood at T = 10 M, K = 12,000 500 -> 472 us, sampling 0 to 0.7 %)
             const unsigned long long in_run = take_run(e, wide);
             // element-wise product A_d (.) Bhat_v, its prefix sums and its sum S (Alg. 2, product loop)
             RowBlock b;
@@ -1051,6 +1059,7 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             e_next = first_bit(large_ends);
             fetch(e_next, nxt, nxt_last, nxt_off);
             nxt2 = fetch_more(nxt_last, nxt_off, 1);
+            __builtin_amdgcn_sched_barrier(0);
             const unsigned long long in_run = take_run(e, large);
             RowBlock b0, b1;
             block_products<STAGED, PACK>(cur, cbits, lds_phi, phi_row, b0, ov);
@@ -1119,6 +1128,10 @@ __global__ void __launch_bounds__(1024, 8) estep_kernel(EStepParams p) {
             }
         }
         if (large) {
+            if (MODE != MODE_SAMPLE) {
+                fetch(e_c, blk_c, last_c, off_c);
+                blk_c2 = fetch_more(last_c, off_c, 1);
+            }
             for (;;) {
                 do_large(e_c, blk_c, blk_c2, last_c, off_c, e_d, blk_d, blk_d2, last_d, off_d);
                 if (!large_ends) break;
