@@ -855,10 +855,10 @@ constexpr int64_t kJoinedSegments = 384 * 1024, kJoinedTokens = 16ll << 20;
 // T = 10 M, K = 1,000 649 with T / 48, 653 with T / 32, 686 with T / 20.
 static int64_t joined_share(const saber_ctx *c) { return std::max<int64_t>(std::max<int64_t>(16384, std::min(16 * c->K, 65536)), (c->T / 48 + 4095) & ~4095ll); }
 
-// Rows up to which a row of several ranges of topics has a workgroup for each, and a second launch for the running sums: as many as
-// leave CUs without a row.  An iteration at T = 1.5 M, K = 70,000, 22 rows of 9 ranges 358 -> 318 us, at T = 15 M, K = 20,011, 125
-// rows of 3 ranges 1,591 -> 1,583.
-constexpr int64_t kPhiPartRows = 256;
+// A row of several ranges of topics has a workgroup for each, and a second launch for the running sums, where one workgroup per row
+// would leave CUs without any.  Phi group without and with, late iterations at T = 1.5 M: K = 8,257 61 rows 28.0 and 25.9 us, 255 25.3 and
+// 24.0; K = 20,011 37.9 and 31.5, 34.9 and 31.2; K = 60,000 71 and 45, 66 and 49.  The gain does not end at that line: 301 and 501 rows
+// 27.8 and 24.5, 28.4 and 26.4 at K = 8,257, 75 and 51, 75 and 61 at K = 60,000; more rows, and larger corpora, were not measured.
 static int launch_phi(saber_ctx *c) {
     hipLaunchKernelGGL(denominators_kernel, dim3(grid_for(c->Kpad, 256)), dim3(256), 0, c->stream, c->ck_acc, c->ck, c->denom, c->K,
                        c->Kpad, c->vbeta);
@@ -870,7 +870,7 @@ static int launch_phi(saber_ctx *c) {
     const size_t hist = (size_t)range * sizeof(uint32_t);
     const int64_t rows = (int64_t)c->V_dense + 1;
     const int parts = (c->Kpad + range - 1) / range;
-    const bool by_parts = parts > 1 && rows <= kPhiPartRows;
+    const bool by_parts = parts > 1 && rows <= c->cus;
     for (int64_t r = 0, n; r < rows; r += n) {
         n = std::min(rows - r, most_blocks((int)block.x));
         const dim3 grid((unsigned)n, by_parts ? (unsigned)parts : 1u);

@@ -571,3 +571,18 @@ def test_wavefronts_of_light_words(host, K, few, wide, shares):
         if K > 4096: assert (alone, joined) == (shares, 0)
         else: assert alone == 0 and joined == -(-shares // 4) + min(256, -(-counts.size // fake.fake_block(b"mstep_rows")))
     """ % ((K, few, wide, shares),))
+
+
+@pytest.mark.parametrize("K,cus,rows,parts", [(8257, 256, 256, 2), (8257, 256, 257, 0), (8192, 256, 10, 0), (20_011, 64, 64, 3), (20_011, 64, 65, 0), (70_000, 256, 2, 9)])
+def test_which_rows_of_bhat_are_worked_on_by_parts(host, K, cus, rows, parts):
+    """Rows of several ranges of topics, where there are no more of them (with the base vector) than CUs."""
+    host("""
+        K, cus, rows, parts = %r
+        fake.fake_cus(cus)
+        words = np.repeat(np.arange(rows - 1 + 5, dtype=np.int32), np.r_[np.full(rows - 1, 20), np.full(5, 3)])
+        g = pk.Saber(np.r_[np.arange(0, words.size, 1000), words.size], words, rows + 4, K, 0.1, 0.01, 3, light_word_tokens=10)
+        fake.fake_clear()
+        g.iterate(1)
+        assert launches("phi_sums")[1] == (rows if parts else 0)
+        assert launches("phi_tree")[1] == rows * max(parts, 1)
+    """ % ((K, cus, rows, parts),))
