@@ -289,7 +289,8 @@ def test_document_longer_than_16_bit_counts():
 def test_counts_next_to_the_topic_of_an_entry(longest, K):
     """Entries of 16 bits each hold the count below the topic.  Below 2^14 tokens in the longest document the sampling kernel forms
     a topic's place in LDS by one shift of the entry, from there on without the count's upper bits: a document whose tokens are
-    nearly all of one topic, the last one, on both sides of the line, and held-out documents on the other side than the model's."""
+    nearly all of one topic, the last one, on both sides of the line, and held-out documents whose two parts are both beyond it (the
+    parts on either side of it: test_gpu_holdout.py)."""
     rng = np.random.default_rng(longest + K)
     lens = np.r_[longest, rng.integers(1, 300, 60)]
     doc_ptr = np.r_[0, np.cumsum(lens)].astype(np.int64)
@@ -756,3 +757,39 @@ def test_segments_that_take_fewer_steps_to_sort(K):
         assert_counts_equal(g, o)
         assert_estep_parity(g, o, min_agree=0.99)
     g.close(); o.close()
+
+
+@pytest.mark.parametrize("K,row", [(40, 30), (900, 50), (900, 110), (1300, 240), (5000, 250), (3000, 600)])
+def test_runs_of_many_tokens_look_for_their_positions_at_once(K, row):
+    """From eight tokens of a document in a batch of sixteen and more on, all of the run's positions are searched for at once: runs
+    of 7, 8 and 9 in batches of 15, 16 and 17 and of 64, at a batch's start, in its middle, at its end and cut by it, among single
+    tokens, of documents whose rows of A have one piece to several blocks."""
+    runs = [[15], [16], [17], [8, 8], [7, 9], [9, 7], [8, 1, 1, 1, 1, 1, 1, 1, 1], [1, 1, 1, 1, 1, 1, 1, 1, 8], [1, 7, 8], [64], [63, 1], [1, 63],
+            [57, 7], [56, 8], [56, 9], [1] * 60 + [9], [8] * 8, [7] * 9 + [1], [9] * 8, [200], [1] * 30 + [8] + [1] * 26, [3] * 30]
+    D = max(len(r) for r in runs)
+    rng = np.random.default_rng(K + row)
+    doc, word = [], []
+    for v, r in enumerate(runs):                       # word v: its runs in ascending documents
+        for d, n in zip(np.sort(rng.permutation(D)[:len(r)]), r):
+            doc += n * [d]
+            word += n * [v]
+    filler = rng.integers(row // 2, row + 1, D)        # other words, so that rows of A have about as many entries
+    doc += list(np.repeat(np.arange(D), filler))
+    word += list(rng.integers(len(runs), len(runs) + 400, int(filler.sum())))
+    order = np.argsort(doc, kind="stable")
+    word_ids = np.array(word, np.int32)[order]
+    doc_ptr = np.r_[0, np.cumsum(np.bincount(doc, minlength=D))].astype(np.int64)
+    V, pk = len(runs) + 400, saber()
+    for alpha in (0.001, 1.0):                         # nearly all tokens on the sparse branch, and few
+        g = pk.Saber(doc_ptr, word_ids, V, K, alpha, 0.01, 5, block_threads=64)
+        o = oracle.Model(doc_ptr, word_ids, V, K, alpha, 0.01, 5)
+        assert_estep_parity(g, o)
+        assert_estep_parity(g, o)
+        z = g.get_z()
+        g.close()
+        for opts in ({"block_threads": 256}, {"tile_tokens": 16}, {"quarter_row_entries": -1, "half_row_entries": -1}):
+            h = pk.Saber(doc_ptr, word_ids, V, K, alpha, 0.01, 5, **opts)
+            h.iterate(2)
+            assert np.array_equal(h.get_z(), z), opts
+            h.close()
+        o.close()
