@@ -377,8 +377,12 @@ static int check_estep_lds_layout() {
     return SABER_OK;
 }
 
-// Wavefronts a CU holds of a sampling kernel with `block` threads per workgroup, given its LDS (handed out in 1,280-byte pieces; the
-// choice of a workgroup's size reckons with 512) and the 32 wavefronts a CU can hold.
+// Wavefronts a CU holds of a sampling kernel with `block` threads per workgroup, given its LDS (handed out in 1,280-byte pieces) and
+// the 32 wavefronts a CU can hold.  The choice of a workgroup's size (estep_auto_block(), tile_classes()) reckons with pieces of 512 bytes
+// and 144 bytes on top instead, and just below its lines a CU then holds fewer wavefronts than it asks for: in chunks of 4 M
+// tokens and more 20 at K = 6,613 to 6,640 and 16 at 13,229 to 13,316 (for 24), in smaller ones 21 at 1,569 to 1,724 (for 22), 20 at
+// 3,461 to 3,612 (for 22) and 16 at 7,873 to 8,024 (for 20).  An iteration at T = 15 M: K = 5,700 1.26 ms, 6,630 1.39, 8,200 1.30; 11,500
+// 1.43, 13,300 1.82, 15,000 1.60.
 constexpr size_t kLdsPiece = 1280;
 static int estep_waves_per_cu(const saber_ctx *c, int block, size_t piece = 512) {
     const size_t need = c->staged || c->overlay ? ((estep_lds_bytes(c, MODE_SAMPLE, block) + (piece == 512 ? 144 : 0) + piece - 1) / piece) * piece : 512;
@@ -1551,8 +1555,13 @@ static int make_ctx(saber_ctx **out, const int64_t *doc_ptr, const int32_t *word
     if (c->opt.light_block_threads <= 0) c->opt.light_block_threads = c->opt.block_threads;
     // A part of LDS per sampling wavefront, where a CU still holds as many of them: an iteration at T = 2.3 M, K = 777 161 -> 149
     // us, T = 10 M, K = 1,000 583 -> 573, T = 100 K, K = 100 32.5 -> 31.5, T = 20 M, K = 2,000 (streamed, the link is the slower
-    // one) 1,629 -> 1,628.  Not for the sake of it: T = 36 M, K = 5,000 2.36 ms with 32 wavefronts per CU and lane
-    // permutations, 2.51 with 24 of the same workgroups, 2.62 with 32 in larger ones; T = 100 M, K = 10,000 7.1 and 7.4.
+    // one) 1,629 -> 1,628; T = 15 M, 370 tokens per document, K = 1,000 913 -> 890, 8,200 1,322 -> 1,304, 13,300 1,850 -> 1,820, 16,800
+    // 1,620 -> 1,592, 30,000 2,382 -> 2,307; 94 tokens, K = 5,700 1,110 -> 1,087, 15,000 1,598 -> 1,551; T = 2 M, K = 300 to 37,030 0.2 to
+    // 7 %.  Not for the sake of it: T = 36 M, K = 5,000 2.36 ms with 32 wavefronts per CU and lane
+    // permutations, 2.51 with 24 of the same workgroups, 2.62 with 32 in larger ones; T = 100 M, K = 10,000 7.1 and 7.4.  Of chunks
+    // of 4 M tokens and more it is in use at K up to 1,048, from 1,221 to 2,104, 2,733 to 4,216, 5,665 to 5,792, 6,613 to 8,440, 10,077 to 11,588,
+    // 13,229 to 16,884 and 20,161 to 37,048.
+    // (The kernel is built for the packing of counts below 2^14 only; what it exchanges would be the same for the others.)
     if (c->staged && c->z16 && c->pack == PACK_16_14) {
         const int without = estep_waves_per_cu(c, c->opt.block_threads, kLdsPiece), light = estep_waves_per_cu(c, c->opt.light_block_threads, kLdsPiece);
         c->slots = true;
