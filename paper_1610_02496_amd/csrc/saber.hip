@@ -165,8 +165,7 @@ struct saber_ctx {
     int32_t *light_words = nullptr;   // [V_light] word of each light row
     int32_t *light_short = nullptr, *light_long = nullptr;   // light rows by token count, for the count launches
     int64_t n_light_short = 0, n_light_long = 0;
-    int32_t *light_order = nullptr;   // light rows in the order in which they are worked on where several share a wavefront: those of
-    int32_t n_light_wide = 0;         // words with more than kWideWord tokens first, so many, then the others
+    int32_t n_light_wide = 0;         // light rows of words with more than kWideWord tokens: they have the first numbers
     int64_t *light_tok_ptr = nullptr; // [V_light+1] positions of the light words' tokens in z_wm
     uint2 *wrec = nullptr;            // [V_light] {row start / 32, non-zeros}
     uint32_t *lw_ent = nullptr;       // packed rows of B of the light words
@@ -268,7 +267,7 @@ extern "C" void saber_free(saber_ctx *c) {
     if (!c->parent) {   // the model's arrays belong to the model
         release(c->cwk); release(c->ck); release(c->ck_acc); release(c->denom); release(c->phi); release(c->l3_64); release(c->l3);
         release(c->sumphi); release(c->row_word); release(c->light_words); release(c->light_short);
-        release(c->light_long); release(c->light_order); release(c->light_tok_ptr); release(c->wrec); release(c->lw_ent); release(c->lw_phi);
+        release(c->light_long); release(c->light_tok_ptr); release(c->wrec); release(c->lw_ent); release(c->lw_phi);
         release(c->vz_items); release(c->phi_rows);
     }
     if (c->have_events) for (auto &e : c->ev) if (e) (void)hipEventDestroy(e);
@@ -733,7 +732,7 @@ static int stream_release(saber_ctx *c, int s) {
 
 // Preprocess + BuildTree for the light words (sparse rows of B); needs the base vector, i.e. runs after launch_phi
 static LightParams light_params(const saber_ctx *c) {
-    return LightParams{c->light_order, c->light_words, c->wrec, c->lw_ent, c->lw_phi, c->denom, c->phi + (size_t)c->V_dense * (size_t)c->Kpad,
+    return LightParams{c->light_words, c->wrec, c->lw_ent, c->lw_phi, c->denom, c->phi + (size_t)c->V_dense * (size_t)c->Kpad,
                        c->l3_64 + (size_t)c->V * (size_t)c->n3, c->l3, c->l3_64, c->sumphi, c->n3, c->n3pad, c->V_light, c->n_light_wide, c->count_bits, c->beta};
 }
 // Light words per wavefront: four where rows are short enough that their chain of loads counts (up to 128 blocks of topics) and the
@@ -746,8 +745,8 @@ static LightParams light_params(const saber_ctx *c) {
 // words has then too) have a wavefront each, before the others.  Phi group with one word, with four, and so, iterations 2 to 4 / late: T =
 // 6 M, K = 8,000, 60,000 words 51 / 40, 109 / 54 and 51 / 39 us; T = 2 M, K = 4,000, 30,000 words 24 / 18, 59 / 25 and 23 / 17; T = 10 M,
 // K = 1,000 40 / 36, 32 / 29 and 34 / 30; T = 3 M, K = 5,000, all of 20,000 words light 83 / 51, 260 / 129 and 81 / 52.  (Lines at 64 and at
-// 512 tokens are 0 to 2 us slower late, and in the first iterations.)  The order is a list, 0.4 to 1.3 us of that: with the words
-// numbered in it an export went over the caller's pages twice, 6.3 -> 10.1 ms for B of 60,000 words at K = 1,000.
+// 512 tokens are 0 to 2 us slower late, and in the first iterations.)  The words of many tokens have the first numbers: a list cost 0.4 to
+// 1.3 us, marks 1 to 4.
 constexpr int64_t kWideWord = 256;
 static int words_per_wave(const saber_ctx *c) { return c->n3 <= 128 && c->V_light - c->n_light_wide >= 16384 ? 4 : 1; }
 static unsigned light_waves(const saber_ctx *c) {
@@ -1047,7 +1046,7 @@ static int full_mstep(saber_ctx *c, const int32_t *user_z = nullptr) {
 // ------------------------------------------------------------------------------------------------
 // What lay_out() makes on the host and upload() takes to the device.
 struct Layout {
-    std::vector<int32_t> row_word, light_words, light_short, light_long, light_order, short_docs, long_docs;
+    std::vector<int32_t> row_word, light_words, light_short, light_long, short_docs, long_docs;
     std::vector<int64_t> light_tok_ptr = std::vector<int64_t>(1, 0);
     std::vector<uint2> wrec, docrec;
     std::vector<VzItem> vz_items;
@@ -1063,7 +1062,7 @@ struct Layout {
 // (For a context on a trained model no call of the runtime is made: another thread may do it.)
 static int lay_out(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids, Layout &lay) {
     const int64_t D = c->D, T = c->T; const int32_t V = c->V, K = c->K;
-    auto &h_row_word = lay.row_word, &h_light_words = lay.light_words, &h_light_short = lay.light_short, &h_light_long = lay.light_long, &h_light_order = lay.light_order;
+    auto &h_row_word = lay.row_word, &h_light_words = lay.light_words, &h_light_short = lay.light_short, &h_light_long = lay.light_long;
     auto &h_light_tok_ptr = lay.light_tok_ptr;
     auto &h_wrec = lay.wrec;
     auto &h_vz_items = lay.vz_items; auto &h_phi_rows = lay.phi_rows;
@@ -1111,29 +1110,32 @@ static int lay_out(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids
         n_v.assign((size_t)V, 0);
         for (int64_t t = 0; t < T; t++) n_v[(size_t)word_ids[t]]++;
         c->h_word_row.assign((size_t)V, 0);
+        // Light rows lie in the order of the vocabulary, as an export writes them (by number it went over the caller's pages twice: 6.3 ->
+        // 10.1 ms for B of 60,000 words at K = 1,000); those of words with many tokens have the first numbers: see words_per_wave().
         int64_t lunits = 0;
-        std::vector<int32_t> narrow;
+        std::vector<std::pair<int32_t, uint32_t>> wide, narrow;   // word, row start
         for (int32_t v = 0; v < V; v++) {
             if (light_ok && n_v[(size_t)v] < c->opt.light_word_tokens) {
-                const int32_t li = (int32_t)h_light_words.size();
-                c->h_word_row[(size_t)v] = -li - 1;
-                h_light_words.push_back(v);
-                h_light_tok_ptr.push_back(h_light_tok_ptr.back() + n_v[(size_t)v]);
                 if (lunits > 0xffffffffll) return fail(SABER_ERANGE, "sparse rows of B exceed 2^32 * 128 bytes");
-                h_wrec.push_back(make_uint2((uint32_t)lunits, 0u));
+                (n_v[(size_t)v] > kWideWord ? wide : narrow).emplace_back(v, (uint32_t)lunits);
                 lunits += (std::min<int64_t>(n_v[(size_t)v], K) + 31) / 32;
-                (n_v[(size_t)v] > c->opt.long_doc_tokens ? h_light_long : h_light_short).push_back(li);
-                (n_v[(size_t)v] > kWideWord ? h_light_order : narrow).push_back(li);
             } else {
                 c->h_word_row[(size_t)v] = (int32_t)h_row_word.size();
                 h_row_word.push_back(v);
             }
         }
+        c->n_light_wide = (int32_t)wide.size();
+        for (const auto *list : {&wide, &narrow}) for (const auto &[v, unit] : *list) {
+            const int32_t li = (int32_t)h_light_words.size();
+            c->h_word_row[(size_t)v] = -li - 1;
+            h_light_words.push_back(v);
+            h_light_tok_ptr.push_back(h_light_tok_ptr.back() + n_v[(size_t)v]);
+            h_wrec.push_back(make_uint2(unit, 0u));
+            (n_v[(size_t)v] > c->opt.long_doc_tokens ? h_light_long : h_light_short).push_back(li);
+        }
         c->V_dense = (int32_t)h_row_word.size(); c->V_light = (int32_t)h_light_words.size();
         h_row_word.push_back(V);   // the all-zero row: its Bhat is the base vector, its tree level the base running sums
         c->T_light = h_light_tok_ptr.back(); c->lw_cap = lunits * 32;
-        c->n_light_wide = (int32_t)h_light_order.size();
-        h_light_order.insert(h_light_order.end(), narrow.begin(), narrow.end());
         c->n_light_short = (int64_t)h_light_short.size(); c->n_light_long = (int64_t)h_light_long.size();
     }
     // ---- resident or streamed?  stream_workers = 0 keeps everything on the device when it fits and falls back to
@@ -1297,7 +1299,7 @@ static int lay_out(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids
 static int upload(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids, const Layout &lay) {
     const int64_t D = c->D, T = c->T; const int32_t V = c->V, K = c->K;
     const saber_ctx *par = c->parent;
-    const auto &h_row_word = lay.row_word, &h_light_words = lay.light_words, &h_light_short = lay.light_short, &h_light_long = lay.light_long, &h_light_order = lay.light_order;
+    const auto &h_row_word = lay.row_word, &h_light_words = lay.light_words, &h_light_short = lay.light_short, &h_light_long = lay.light_long;
     const auto &h_light_tok_ptr = lay.light_tok_ptr;
     const auto &h_wrec = lay.wrec;
     const auto &h_vz_items = lay.vz_items; const auto &h_phi_rows = lay.phi_rows;
@@ -1362,7 +1364,6 @@ static int upload(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids,
     SABER_TRY(dev_alloc(c->hooks, &c->phi, vk)); SABER_TRY(dev_alloc(c->hooks, &c->l3_64, ((size_t)V + 1) * (size_t)c->n3));
     SABER_TRY(dev_alloc(c->hooks, &c->row_word, h_row_word.size())); SABER_TRY(dev_alloc(c->hooks, &c->light_words, h_light_words.size()));
     SABER_TRY(dev_alloc(c->hooks, &c->light_short, h_light_short.size())); SABER_TRY(dev_alloc(c->hooks, &c->light_long, h_light_long.size()));
-    SABER_TRY(dev_alloc(c->hooks, &c->light_order, h_light_order.size()));
     SABER_TRY(dev_alloc(c->hooks, &c->light_tok_ptr, h_light_tok_ptr.size())); SABER_TRY(dev_alloc(c->hooks, &c->wrec, h_wrec.size()));
     SABER_TRY(dev_alloc(c->hooks, &c->lw_ent, (size_t)c->lw_cap)); SABER_TRY(dev_alloc(c->hooks, &c->lw_phi, (size_t)c->lw_cap));
     }
@@ -1381,7 +1382,6 @@ static int upload(saber_ctx *c, const int64_t *doc_ptr, const int32_t *word_ids,
         HIP_TRY(hipMemcpy(c->light_words, h_light_words.data(), sizeof(int32_t) * h_light_words.size(), hipMemcpyHostToDevice));
         HIP_TRY(hipMemcpy(c->wrec, h_wrec.data(), sizeof(uint2) * h_wrec.size(), hipMemcpyHostToDevice));
         if (!h_light_short.empty()) HIP_TRY(hipMemcpy(c->light_short, h_light_short.data(), sizeof(int32_t) * h_light_short.size(), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(c->light_order, h_light_order.data(), sizeof(int32_t) * h_light_order.size(), hipMemcpyHostToDevice));
         if (!h_light_long.empty()) HIP_TRY(hipMemcpy(c->light_long, h_light_long.data(), sizeof(int32_t) * h_light_long.size(), hipMemcpyHostToDevice));
     }
     if (!par) SABER_TRY(dev_alloc(c->hooks, &c->doc_words, (size_t)D));
@@ -1902,10 +1902,14 @@ extern "C" int saber_counts(saber_ctx *c, int64_t *cd_row_ptr, int32_t *cd_topic
             }
             // light words: unpack the sparse rows by pieces of whole words (format conversion only)
             if (c->V_light) {
-                std::vector<uint2> wrec((size_t)c->V_light);
+                std::vector<uint2> by_number((size_t)c->V_light), wrec((size_t)c->V_light);   // by number; as the rows lie, like lwords
                 std::vector<int32_t> lwords((size_t)c->V_light);
-                HIP_TRY(hipMemcpy(wrec.data(), c->wrec, sizeof(uint2) * wrec.size(), hipMemcpyDeviceToHost));
-                HIP_TRY(hipMemcpy(lwords.data(), c->light_words, sizeof(int32_t) * lwords.size(), hipMemcpyDeviceToHost));
+                HIP_TRY(hipMemcpy(by_number.data(), c->wrec, sizeof(uint2) * by_number.size(), hipMemcpyDeviceToHost));
+                size_t n = 0;
+                for (int32_t v = 0; v < c->V; v++) {
+                    const int32_t row = c->h_word_row[(size_t)v];
+                    if (row < 0) { lwords[n] = v; wrec[n++] = by_number[(size_t)(-row - 1)]; }
+                }
                 std::vector<int64_t> cuts(1, 0), piece_word(1, 0);
                 // (a word's row of K counts has to be cleared as well: threads share those out by at most 1 MB per piece)
                 const int64_t out_bytes = 4 * std::max((int64_t)c->V_light * c->K, c->lw_cap);

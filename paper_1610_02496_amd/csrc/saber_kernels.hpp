@@ -1891,14 +1891,14 @@ __global__ void __launch_bounds__(1024, 8) phi_tree_kernel(const PhiRow *rows, c
 // LDS: a zero and the cumulative differences at the last non-zero of each block that has one, then a bit per block that has.
 // ---------------------------------------------------------------------------------------------
 struct LightParams {
-    const int32_t *order, *light_words; const uint2 *wrec; const uint32_t *lw_ent; float *lw_phi;
+    const int32_t *light_words; const uint2 *wrec; const uint32_t *lw_ent; float *lw_phi;
     const float *denom, *base; const double *basecum; float *l3; double *l3_64; float *sumphi;
-    int n3, n3pad, n_light, n_wide;   // the first n_wide words in that order have many tokens and a wavefront each
+    int n3, n3pad, n_light, n_wide;   // the first n_wide words have many tokens and a wavefront each
     uint32_t count_bits; float beta;
 };
 __host__ __device__ inline size_t light_lds_bytes(int n3) { return ((size_t)n3 + 1u + (size_t)(n3 + 63) / 64u) * 8u; }
 
-// Up to W light words, `first` to `end` in the order of p.order (W = 1: by their numbers), by one wavefront with light_lds_bytes(n3) of LDS at lds_dcum.  Bound by the chain of
+// Up to W light words, numbers `first` to `end`, by one wavefront with light_lds_bytes(n3) of LDS at lds_dcum.  Bound by the chain of
 // loads that leads to a word's non-zeros' denominators - its record, its entries, their denominators - where rows are short: the
 // words of a wavefront take each of the three steps together (see words_per_wave() on the host).  A block's running sum needs the
 // difference at the last block with a non-zero up to it, which is found by counting these (15 vector instructions per 64 blocks; by a
@@ -1917,7 +1917,7 @@ __device__ __forceinline__ void light_words(const LightParams &p, int first, int
     uint2 rec[W];
 #pragma unroll
     for (int w = 0; w < W; w++) {
-        const int at = min(first + w, end - 1), li = W > 1 ? p.order[at] : at;
+        const int li = min(first + w, end - 1);
         word[w] = p.light_words[li]; rec[w] = p.wrec[li];
     }
     // the base vector's running sums of the first steps, requested under that chain
